@@ -228,14 +228,17 @@ zi_status zi_engine_destroy(zi_engine* e);   /* NULL is accepted */
 /*
  * AdamW step with p, m, v in PINNED HOST memory (or ordinary host memory if the
  * engine has a pinned ring, see zi_engine_set_option) and g, p_lp in device memory
- * (Section 5.2.2: the state is brought to the faster memory in chunks, one chunk
- * at a time, and written back, with reads, writes and compute overlapped).
- * Tensors larger than a chunk are split on chunk boundaries; consecutive small
- * tensors are packed into one slot.  Results are bit-identical to
- * zi_adamw_step on the same values.
- * The engine's streams first wait for the work already enqueued on hip_stream
- * (where the gradients and d_norm were produced).  If d_norm is given, its flag
- * is read back first; found_inf != 0 returns ZI_SKIPPED_OVERFLOW with no state
+ * (Section 5.2.2: offloaded state is brought to the faster memory and written
+ * back, with reads, writes and compute overlapped).
+ * Page-locked arrays that the device can address as a whole (each inside one
+ * allocation) are read and written over the link by the update's kernel itself, on
+ * hip_stream.  Otherwise, and when ZI_OPT_MAX_INFLIGHT or ZI_OPT_SKIP_KERNEL asks
+ * for it, the state passes through the slots chunk by chunk: tensors larger than a
+ * chunk are split on chunk boundaries, consecutive small tensors are packed into
+ * one slot.  Results are bit-identical to zi_adamw_step on the same values.
+ * The step waits for the work already enqueued on hip_stream
+ * (where the gradients and d_norm were produced).  If d_norm is given and its
+ * found_inf != 0, the call returns ZI_SKIPPED_OVERFLOW with no state
  * moved.  BLOCKING: returns after the last device-to-host copy has completed,
  * so the host arrays are valid on return; p_lp is complete as well.
  * On ZI_ERR_HIP part of the host state may already have been updated.
@@ -334,9 +337,9 @@ typedef struct {
     double seconds;            /* first host-to-device issue .. last device-to-host completion */
     uint64_t bytes_h2d;
     uint64_t bytes_d2h;
-    int64_t n_slot_uses;       /* chunk-slots processed */
-    int64_t n_copies;          /* hipMemcpyAsync calls issued */
-    int64_t n_kernels;         /* kernel launches */
+    int64_t n_slot_uses;       /* chunks of the plan (zi_plan_chunks) that were stepped */
+    int64_t n_copies;          /* hipMemcpyAsync calls issued; 0 where the kernel moves the state itself */
+    int64_t n_kernels;         /* kernel launches that updated state */
     uint64_t bytes_staged_host; /* bytes copied by CPU threads through the pinned ring (both ways) */
 } zi_stream_stats;
 
@@ -347,7 +350,8 @@ zi_status zi_engine_last_stats(const zi_engine* e, zi_stream_stats* out);
  * ZI_OPT_SKIP_KERNEL = 1 runs the identical copy pipeline without launching the
  * update (a measurement aid like the calls of zi_probe.h: the time of the pipeline with the update
  * removed).
- * ZI_OPT_MAX_INFLIGHT selects how the host paces the pipeline.  0 (default, needs n_slots >= 3): a slot
+ * ZI_OPT_MAX_INFLIGHT selects how the host paces the chunk pipeline, and, if it is not 0, that page-locked
+ * state goes through it.  0 (default, needs n_slots >= 3): a slot
  * use is issued when the copy-out of the use two positions back starts (its update is done);
  * the two directions of the link then run side by side one chunk apart and the update of the chunk
  * in between is hidden.  k >= 1: before issuing a slot use the host waits for the use k positions

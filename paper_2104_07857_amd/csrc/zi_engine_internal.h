@@ -31,7 +31,51 @@ struct StateSrc {
     void* p_lp;          // device, or host when lp_host; may be null
     bool g_host;         // gradients live in host memory and are staged chunk by chunk
     bool lp_host;        // the low-precision copy is written back to host memory
+    char* dev[5];        // p, m, v, g, p_lp as the device addresses them, if every host array is mapped (HostRanges)
     int64_t numel;
+};
+
+// Page-locked allocations seen during one call: an array that lies in one of them needs no further query,
+// and its device address follows from the allocation's.
+struct HostRanges {
+    struct Range { uintptr_t lo, hi; ptrdiff_t to_device; };
+    Range known[8] = {};
+    int n_known = 0, next = 0;
+
+    const Range* find(const void* p, size_t bytes) const
+    {
+        const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+        for (int i = 0; i < n_known; ++i)
+            if (lo >= known[i].lo && lo + bytes <= known[i].hi) return &known[i];
+        return nullptr;
+    }
+
+    // Notes the allocation around p if all of [p, p + bytes) lies in it and is mapped for the device.
+    // Arrays that span several registrations stay unknown: only a copy engine may touch those.
+    void note(const void* p, size_t bytes)
+    {
+        hipPointerAttribute_t attr{};
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipPointerGetAttributes(&attr, p) != hipSuccess || attr.type != hipMemoryTypeHost || !attr.devicePointer ||
+            hipMemGetAddressRange(&base, &size, attr.devicePointer) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        const uintptr_t at = reinterpret_cast<uintptr_t>(p), dev = reinterpret_cast<uintptr_t>(attr.devicePointer);
+        const uintptr_t lo = reinterpret_cast<uintptr_t>(base);
+        if (dev < lo || dev + bytes > lo + size) return;
+        known[next] = {at - (dev - lo), at - (dev - lo) + size, (ptrdiff_t)(dev - at)};
+        next = (next + 1) % 8;
+        if (n_known < 8) ++n_known;
+    }
+
+    // Device address of a page-locked array, null if it is not known to be mapped as a whole.
+    char* device_address(const void* p, size_t bytes) const
+    {
+        const Range* r = find(p, bytes);
+        return r ? reinterpret_cast<char*>(reinterpret_cast<uintptr_t>(p) + (uintptr_t)r->to_device) : nullptr;
+    }
 };
 
 }  // namespace host

@@ -207,6 +207,62 @@ struct StepIssuer {
     }
 };
 
+// Issues the step over segments in page-locked host memory (adamw_link_kernel).  Long segments are cut
+// where a launch is full, a multiple of 512 elements into the segment's body.
+struct LinkIssuer {
+    zi::LinkArgs args{};
+    int dt;
+    bool l2;
+    hipStream_t stream;
+    int64_t launches = 0;
+
+    LinkIssuer(const zi::StepConsts& c, const zi_norm_result* d_norm, uint32_t* h_flag, int dt_, bool l2_, hipStream_t s)
+        : dt(dt_), l2(l2_), stream(s)
+    {
+        args.c = c;
+        args.d_norm = d_norm;
+        args.h_flag = d_norm ? h_flag : nullptr;
+    }
+
+    hipError_t flush()
+    {
+        if (args.n_desc == 0) return hipSuccess;
+        ++launches;
+        const hipError_t e = zi::launch_step_link(args, dt, l2, stream);
+        args.n_desc = 0;
+        args.n_tiles = 0;
+        return e;
+    }
+
+    hipError_t add(float* p, float* m, float* v, const uint16_t* g, uint16_t* p_lp, int64_t numel)
+    {
+        while (numel > 0) {
+            if (args.n_desc == zi::kMaxLinkDesc || args.n_tiles >= zi::kLinkTilesPerLaunch) {
+                const hipError_t e = flush();
+                if (e != hipSuccess) return e;
+            }
+            const int h = choose_head(p, m, v, g, p_lp);
+            zi::StepDesc d{};
+            d.head = (int32_t)(h < numel ? h : numel);
+            const int64_t room = (int64_t)(zi::kLinkTilesPerLaunch - args.n_tiles) * zi::kStepTileElems;
+            const int64_t n = numel - d.head <= room ? numel : d.head + room;
+            d.p_body = p + d.head; d.m_body = m + d.head; d.v_body = v + d.head; d.g_body = g + d.head;
+            d.lp_body = p_lp ? p_lp + d.head : nullptr;
+            d.numel = n;
+            d.nquad = (n - d.head) / zi::kQuad;
+            const int64_t nt = (d.nquad + zi::kStepTileQuads - 1) / zi::kStepTileQuads;
+            d.n_tiles = nt < 1 ? 1u : (uint32_t)nt;
+            d.first_tile = args.n_tiles;
+            args.t[args.n_desc++] = d;
+            args.n_tiles += d.n_tiles;
+            p += n; m += n; v += n; g += n;
+            if (p_lp) p_lp += n;
+            numel -= n;
+        }
+        return hipSuccess;
+    }
+};
+
 inline zi_status check_norm_args(const zi_tensor* t, int32_t n_tensors, int dt, float loss_scale, zi_norm_result* d_out,
                           void* d_workspace, size_t workspace_bytes)
 {

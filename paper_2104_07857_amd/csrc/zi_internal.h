@@ -78,6 +78,26 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
+// The step over state in page-locked host memory (adamw_link_kernel): a persistent grid of
+// single-wavefront workgroups that read and write the host arrays over the link themselves.
+// The kernel is bound by the link's two directions, so the grid only has to keep the link's queues full.
+// Measured on 3 x 512 MiB of pinned arrays updated in place, GB/s per direction by workgroups: 32: 47.0,
+// 64: 50.1, 96: 49.4, 128: 48.8, 256: 45.2, 512: 44.4; with four quads a lane instead of two 64 give 48.9;
+// 256-thread workgroups 50.1 at best (32 of them, one quad a lane), 47.1 at 64.
+constexpr int kLinkGroups = 64;
+constexpr int kMaxLinkDesc = 48;                       // segments per launch (the argument block stays below 4 KiB)
+constexpr uint32_t kLinkTilesPerLaunch = 1u << 19;     // 2^28 elements, some 65 ms of link time
+
+struct LinkArgs {
+    StepDesc t[kMaxLinkDesc];       // addresses as the device sees them
+    int32_t n_desc;
+    uint32_t n_tiles;
+    StepConsts c;
+    const zi_norm_result* d_norm;   // device, may be null
+    uint32_t* h_flag;               // page-locked: receives d_norm->found_inf; null without d_norm
+};
+static_assert(sizeof(LinkArgs) < 4096, "kernel arguments");
+
 struct NormDesc {
     const uint16_t* g;
     int64_t numel;
@@ -97,6 +117,7 @@ struct NormArgs {
 
 // Launchers (zi_kernels.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s);
+hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);

@@ -369,6 +369,102 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
     return hipGetLastError();
 }
 
+// ------------------------------------------------- the step over state in page-locked host memory
+
+// Bound: the host link, 12 bytes per element each way (14 with gradients and copy in host memory too), both
+// directions at once.  The wavefronts load the host arrays over the link, update them in registers
+// and store them back, so no element waits for a chunk of its neighbours: copies through staging memory
+// expose one chunk's way in and one chunk's way out per call and pay two stream hand-overs and six copies per
+// chunk and tensor.  Tiles are walked in order by a grid that stays small on purpose (kLinkGroups): the
+// wavefronts drift apart, so at any time some read while others write, and the requests that queue at the
+// link come from few pages.  A ragged tile has all its loads in flight before the first use like a full
+// one, and the elements outside the vector body are loaded with the first tile's: a short tensor costs one
+// round trip of the link, not three.
+template <int DT, bool L2>
+__global__ __launch_bounds__(kStepThreads) void adamw_link_kernel(const LinkArgs a)
+{
+    if (a.h_flag && blockIdx.x == 0 && threadIdx.x == 0) *a.h_flag = a.d_norm->found_inf;
+    float gscale;
+    if (!step_prologue(a.d_norm, a.c, gscale)) return;
+
+    int d = 0;
+    for (uint32_t t = blockIdx.x; t < a.n_tiles; t += gridDim.x) {
+        while (d + 1 < a.n_desc && t >= a.t[d + 1].first_tile) ++d;
+        const StepDesc& T = a.t[d];
+        const uint32_t tile = t - T.first_tile;
+        const int64_t nquad = T.nquad;
+        GlobalF4 __restrict__ p4 = (GlobalF4)(uintptr_t)T.p_body;
+        GlobalF4 __restrict__ m4 = (GlobalF4)(uintptr_t)T.m_body;
+        GlobalF4 __restrict__ v4 = (GlobalF4)(uintptr_t)T.v_body;
+        GlobalConstU2 __restrict__ g2 = (GlobalConstU2)(uintptr_t)T.g_body;
+        GlobalU2 __restrict__ lp2 = (GlobalU2)(uintptr_t)T.lp_body;
+
+        int64_t e = 0;                    // this lane's element outside the body, if any
+        bool end = false;
+        float pe = 0.0f, me = 0.0f, ve = 0.0f, ge = 0.0f;
+        if (tile == 0) {
+            const int64_t lane = threadIdx.x, head = T.head, body = nquad * kQuad, tail = T.numel - head - body;
+            // the head's elements, then the tail's: 66 at most, so the last two may need a second pass
+            if (lane < head) { e = lane - head; end = true; }
+            else if (lane - head < tail) { e = body + (lane - head); end = true; }
+            if (end) {
+                pe = T.p_body[e]; me = T.m_body[e]; ve = T.v_body[e];
+                ge = widen16<DT>(T.g_body[e]);
+            }
+            const int64_t rest = body + (kStepThreads - head) + lane;
+            if (rest < body + tail) step_scalar_at<DT, L2>(T, rest, gscale, a.c);
+        }
+
+        const int64_t q0 = (int64_t)tile * kStepTileQuads + threadIdx.x;
+        f32x4 p[kStepUnroll], m[kStepUnroll], v[kStepUnroll];
+        u32x2 g[kStepUnroll];
+#pragma unroll
+        for (int u = 0; u < kStepUnroll; ++u) {
+            const int64_t i = q0 + (int64_t)u * kStepThreads;
+            p[u] = m[u] = v[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            g[u] = u32x2{0, 0};
+            if (i < nquad) {
+                g[u] = load_stream_any(g2 + i);
+                p[u] = load_stream_any(p4 + i);
+                m[u] = load_stream_any(m4 + i);
+                v[u] = load_stream_any(v4 + i);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kStepUnroll; ++u) {
+            const int64_t i = q0 + (int64_t)u * kStepThreads;
+            const u32x2 lp = step_quad<DT, L2>(p[u], m[u], v[u], g[u], gscale, a.c);
+            if (i < nquad) {
+                store_stream_any(p4 + i, p[u]);
+                store_stream_any(m4 + i, m[u]);
+                store_stream_any(v4 + i, v[u]);
+                if (lp2) store_stream_any(lp2 + i, lp);
+            }
+        }
+        if (end) {
+            adamw_element<L2>(pe, me, ve, ge, gscale, a.c);
+            T.p_body[e] = pe;
+            T.m_body[e] = me;
+            T.v_body[e] = ve;
+            if (T.lp_body) T.lp_body[e] = (uint16_t)narrow16<DT>(pe);
+        }
+    }
+}
+
+hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s)
+{
+    if (a.n_tiles == 0) return hipSuccess;
+    const dim3 grid(a.n_tiles < (uint32_t)kLinkGroups ? a.n_tiles : (uint32_t)kLinkGroups), block(kStepThreads);
+    if (dt == ZI_BF16) {
+        if (l2) hipLaunchKernelGGL((adamw_link_kernel<ZI_BF16, true>), grid, block, 0, s, a);
+        else    hipLaunchKernelGGL((adamw_link_kernel<ZI_BF16, false>), grid, block, 0, s, a);
+    } else {
+        if (l2) hipLaunchKernelGGL((adamw_link_kernel<ZI_FP16, true>), grid, block, 0, s, a);
+        else    hipLaunchKernelGGL((adamw_link_kernel<ZI_FP16, false>), grid, block, 0, s, a);
+    }
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------- gradient sum of squares + overflow flag
 
 // Bit 15 / bit 31 of the result is set iff the exponent field of the low / high half is all ones.

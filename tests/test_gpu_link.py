@@ -1,0 +1,110 @@
+"""The step that reads and writes page-locked state over the link, against the oracle and against the chunk
+pipeline (which a chosen pacing selects), at the places where its tiles, ends and launches change."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2104_07857_amd as zi
+import zi_synth
+from gpu_util import NormBuffers, compare_state, gen_numpy, oracle_cfg, progress, to_dev, to_np, zi_cfg
+
+pytestmark = pytest.mark.gpu
+
+TILE, GROUPS, DESCS = 512, 64, 48
+
+
+def _placed(a, offset, host):
+    """A copy of `a` that starts `offset` elements into a buffer of its own, with guard elements behind."""
+    buf = torch.full((a.size + offset + 8,), 7, dtype=torch.int16 if a.dtype == np.uint16 else torch.float32)
+    src = torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a)
+    buf[offset:offset + a.size] = src
+    if not host:
+        return buf.cuda()
+    pinned = torch.empty(buf.shape, dtype=buf.dtype, pin_memory=True)
+    pinned.copy_(buf)
+    return pinned
+
+
+def _run(host, offsets, dt, cfg, *, g_host, lp_host, lp, pacing, norm=False):
+    """One streamed step; returns status, stats and every buffer (guards included) on the host."""
+    eng = zi.zi_engine_create(0, 64 * 1024, 3)
+    try:
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, pacing)
+        bufs, tl = [], []
+        for (p, m, v, g), o in zip(host, offsets):
+            n = p.size
+            b = [_placed(p, o, True), _placed(m, o, True), _placed(v, o, True), _placed(g, o, g_host)]
+            b.append(_placed(np.zeros(n, np.uint16), o, lp_host) if lp else None)
+            bufs.append(b)
+            tl.append(tuple(None if x is None else x[o:o + n] for x in b) + (n,))
+        nb = None
+        if norm:
+            nb = NormBuffers()
+            zi.zi_grad_norm([(None, None, None, t[3], None, t[5]) for t in tl], dt, cfg.loss_scale, nb.out, nb.ws)
+        status = zi.zi_adamw_step_streamed(eng, tl, dt, cfg, nb.out if nb else None, torch.cuda.current_stream())
+        return status, zi.zi_engine_last_stats(eng), [[None if x is None else to_np(x) for x in b] for b in bufs]
+    finally:
+        zi.zi_engine_destroy(eng)
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        for u, v in zip(x, y):
+            assert (u is None) == (v is None)
+            if u is not None:
+                assert np.array_equal(u.view(np.uint8), v.view(np.uint8))
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 61, 63])
+@pytest.mark.parametrize("n", [1, 3, 64, 67, TILE - 1, TILE + 1, GROUPS * TILE, GROUPS * TILE + 5, 3 * GROUPS * TILE + 259])
+def test_sizes_and_offsets_against_the_oracle(n, offset):
+    """Heads of 0, 63, 62, 3 and 1 elements with every tail: a head of 62 or 63 leaves less than three lanes to it."""
+    w = zi_synth.workload("c2")
+    dt = zi.ZI_BF16 if n % 2 else zi.ZI_FP16
+    host = [gen_numpy(zi_synth.StateSpec(9000 + n, dt), n)]
+    ep, em, ev, g = (a.copy() for a in host[0])
+    elp = np.zeros(n, np.uint16)
+    oracle.step([(ep, em, ev, g, elp)], dt, oracle_cfg(w), False)
+    status, st, got = _run(host, [offset], dt, zi_cfg(w), g_host=False, lp_host=False, lp=True, pacing=0)
+    assert status == zi.ZI_OK and st.n_copies == 0 and st.n_kernels == 1
+    inside = [x[offset:offset + n] for x in got[0]]
+    compare_state((ep, em, ev, elp), (inside[0], inside[1], inside[2], inside[4]), dt, f"n={n} offset={offset} ")
+    for x in got[0]:                                           # nothing around the tensor was touched
+        assert (x[:offset] == 7).all() and (x[offset + n:] == 7).all()
+
+
+@pytest.mark.parametrize("g_host", [False, True])
+@pytest.mark.parametrize("lp", [None, "device", "host"])
+@pytest.mark.parametrize("l2,dt", [(False, zi.ZI_FP16), (True, zi.ZI_BF16)])
+def test_lists_equal_the_chunk_pipeline(g_host, lp, l2, dt):
+    """More tensors than one launch takes, ragged and misaligned, every placement of gradients and copy: the
+    same bits as the chunk pipeline, which a pacing of two uses selects."""
+    rng = np.random.default_rng(5)
+    sizes = [int(x) for x in rng.integers(1, 3000, 2 * DESCS + 3)] + [70_001]
+    offsets = [int(x) for x in rng.integers(0, 64, len(sizes))]
+    scale = 1024.0 if dt == zi.ZI_FP16 else 1.0
+    spec = zi_synth.StateSpec(31, dt, g_std=2e-3 * scale)
+    host = [gen_numpy(spec, n, tensor=i) for i, n in enumerate(sizes)]
+    cfg = zi_cfg(zi_synth.workload("c4"), loss_scale=scale, max_grad_norm=0.7,
+                 mode=zi.ZI_MODE_ADAM_L2 if l2 else zi.ZI_MODE_ADAMW)
+    kw = dict(g_host=g_host, lp_host=lp == "host", lp=lp is not None, norm=not g_host)
+    s1, st1, a = _run(host, offsets, dt, cfg, pacing=0, **kw)
+    s2, st2, b = _run(host, offsets, dt, cfg, pacing=2, **kw)
+    assert s1 == s2 == zi.ZI_OK
+    assert st1.n_copies == 0 and st1.n_kernels == 3 and st2.n_copies > 0
+    assert (st1.bytes_h2d, st1.bytes_d2h, st1.n_slot_uses) == (st2.bytes_h2d, st2.bytes_d2h, st2.n_slot_uses)
+    _same(a, b)
+    progress(f"link step, {len(sizes)} tensors, g_host={g_host}, lp={lp}: equal to the chunk pipeline")
+
+
+def test_overflow_skips_and_touches_nothing():
+    w = zi_synth.workload("c2")
+    host = [gen_numpy(zi_synth.StateSpec(77, zi.ZI_BF16), n) for n in (5000, 70_000)]
+    host[1][3][1234] = 0x7F80
+    status, st, got = _run(host, [0, 3], zi.ZI_BF16, zi_cfg(w), g_host=False, lp_host=True, lp=True, pacing=0, norm=True)
+    assert status == zi.ZI_SKIPPED_OVERFLOW
+    assert st.bytes_h2d == st.bytes_d2h == 0 and st.n_kernels == 0 and st.n_slot_uses == 0
+    for (p, m, v, _), b, o in zip(host, got, (0, 3)):
+        for x, y in zip((p, m, v, np.zeros(p.size, np.uint16)), (b[0], b[1], b[2], b[4])):
+            assert np.array_equal(x.view(np.uint8), y[o:o + x.size].view(np.uint8))
