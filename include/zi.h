@@ -159,10 +159,7 @@ zi_status zi_grad_norm(const zi_tensor* t, int32_t n_tensors, zi_lp_dtype dt, fl
  * library runs on holds until the process ends.  The call itself allocates nothing, on the device or
  * on the host.
  * Limit: at most ZI_NOALLOC_MAX_PARTIALS non-empty tensors per call (ZI_ERR_UNSUPPORTED beyond,
- * nothing launched); within it any sizes are accepted, long tensors simply get fewer workgroups so
- * that all partials of the call fit the array in one pass.  The sum is accumulated in double in a
- * different grouping than zi_grad_norm's when that happens (agreement ~1e-15 relative), and is
- * bit-identical otherwise.
+ * nothing launched); within it any sizes are accepted.  The result is bit-identical to zi_grad_norm's.
  * All calls on one GPU share that GPU's array: two calls that overlap in time on the same GPU (different
  * streams or threads) race on it and give garbage; order them on one stream or with events.  Nothing in
  * the array needs clearing between calls: every partial the final pass reads was written by this call.
@@ -253,9 +250,9 @@ zi_status zi_adamw_step_streamed(zi_engine* e, const zi_tensor* t, int32_t n_ten
  * the low-precision copy travels back with it (14 bytes per element each way instead of 12).
  * This is the gradient-side offload of Section 6.2 (gradients moved to slow memory during the
  * backward pass) seen from the optimizer step.  zi_grad_norm_streamed is the matching reduction:
- * as zi_grad_norm, but gradients in host memory are staged through the engine's slots chunk by
- * chunk (2 bytes per element over the link), overlapped with the reduction kernels; device-resident
- * gradients in the same list are reduced in place.  BLOCKING: returns when the result is in d_out.
+ * as zi_grad_norm, but gradients may be in host memory (2 bytes per element over the link): page-locked ones
+ * are read by the reduction's kernels over the link, others are staged through the engine's slots chunk by
+ * chunk, overlapped with the reduction; device-resident gradients in the same list are reduced in place.  BLOCKING: returns when the result is in d_out.
  */
 zi_status zi_grad_norm_streamed(zi_engine* e, const zi_tensor* t, int32_t n_tensors, zi_lp_dtype dt,
                                 float loss_scale, zi_norm_result* d_out, void* d_workspace,

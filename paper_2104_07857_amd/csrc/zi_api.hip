@@ -113,22 +113,14 @@ extern "C" zi_status zi_grad_norm_noalloc(const zi_tensor* t, int32_t n_tensors,
         if (zi_status st = reach.check(t[i].g, (size_t)t[i].numel * 2, i, "g")) return st;
         non_empty += t[i].numel > 0;
     }
-    // One pass: every partial of the call must fit the fixed array.  Each tensor needs at least one
-    // workgroup, so the list length is the hard limit; below it, long tensors get fewer workgroups.
+    // Every launch leaves at most kNormGroups partials and the sums are folded together when the array is
+    // full, so the array bounds nothing by itself; the list length is held to what the header promises.
     if (non_empty > ZI_NOALLOC_MAX_PARTIALS)
         return fail(ZI_ERR_UNSUPPORTED, "%lld non-empty gradient tensors: the fixed scratch holds one partial for each of "
                     "at most %d (split the list, or use zi_grad_norm with a workspace)", (long long)non_empty,
                     ZI_NOALLOC_MAX_PARTIALS);
-    int64_t cap = NormIssuer::kBlocksPerTensor;
-    for (;; cap /= 2) {
-        int64_t total = 0;
-        for (int32_t i = 0; i < n_tensors; ++i)
-            if (t[i].numel > 0) total += NormIssuer::blocks_for(t[i].numel, cap);
-        if (total <= ZI_NOALLOC_MAX_PARTIALS || cap == 1) break;
-    }
 
     NormIssuer issue(partials, (int)dt, loss_scale, d_out, (hipStream_t)hip_stream);
-    issue.blocks_cap = cap;
     for (int32_t i = 0; i < n_tensors; ++i) ZI_HIP(issue.add((const uint16_t*)t[i].g, t[i].numel));
     ZI_HIP(issue.finish());
     return ZI_OK;

@@ -398,6 +398,14 @@ struct StreamedRun {
     }
 };
 
+zi_status check_stream_device(const zi_engine* e, hipStream_t user)
+{
+    hipDevice_t on = e->device;
+    if (user) ZI_HIP(hipStreamGetDevice(user, &on));
+    if (on != e->device) return fail(ZI_ERR_HIP, "the stream belongs to device %d, the engine to device %d", (int)on, e->device);
+    return ZI_OK;
+}
+
 // The step over page-locked state that the device can address: one kernel reads and writes the host arrays
 // over the link (adamw_link_kernel), on the caller's stream; nothing passes through the slots.  Against the
 // chunk pipeline below it measured (chunks of 64 MiB, norm included, per call): 3.0e5 elements 289 -> 143 us,
@@ -412,10 +420,7 @@ zi_status run_linked(zi_engine* e, zi_lp_dtype dt, const zi_adamw_config* cfg, c
     for (size_t i = 0; i < e->src.size(); ++i) e->plan_numel[i] = e->src[i].numel;
     plan_chunks(e->plan_numel.data(), (int32_t)e->src.size(), e->chunk_elems, e->segs, n_uses);
 
-    hipDevice_t on = e->device;
-    if (user) ZI_HIP(hipStreamGetDevice(user, &on));
-    if (on != e->device) return fail(ZI_ERR_HIP, "the stream belongs to device %d, the engine to device %d", (int)on, e->device);
-
+    if (zi_status bad = check_stream_device(e, user)) return bad;
     const auto t0 = std::chrono::steady_clock::now();
     zi_stream_stats st{};
     st.n_slot_uses = n_uses;
@@ -782,6 +787,47 @@ struct NormRun {
     }
 };
 
+// The reduction over gradients that the device can address wherever they are: the partial-sum kernel reads
+// the page-locked ones over the link, on the caller's stream.  The chunk pipeline makes a launch and a
+// final sum for every chunk and a copy for every tensor of it.
+zi_status run_linked_norm(zi_engine* e, int dt, float loss_scale, zi_norm_result* d_out, zi::NormPartial* partials,
+                          int64_t n_uses, hipStream_t user)
+{
+    if (zi_status bad = check_stream_device(e, user)) return bad;
+    const auto t0 = std::chrono::steady_clock::now();
+    zi_stream_stats st{};
+    st.n_slot_uses = n_uses;
+    auto issue_all = [&]() -> zi_status {
+        ZI_HIP(order_after_offloads(e, user));
+        NormIssuer issue(partials, dt, loss_scale, d_out, user);
+        for (const StateSrc& S : e->src)
+            if (S.numel > 0 && !S.g_host) ZI_HIP(issue.add((const uint16_t*)S.dev[3], S.numel));
+        if (n_uses > 0) {
+            if (issue.solo_tiles > zi::kNormSoloTiles) ZI_HIP(issue.flush_launch());
+            issue.groups = zi::kNormLinkGroups;
+            for (const StateSrc& S : e->src) {
+                if (S.numel == 0 || !S.g_host) continue;
+                ZI_HIP(issue.add((const uint16_t*)S.dev[3], S.numel));
+                st.bytes_h2d += (uint64_t)S.numel * 2;
+            }
+        }
+        ZI_HIP(issue.finish());
+        st.n_kernels = issue.launches;
+        return ZI_OK;
+    };
+    const zi_status status = issue_all();
+    const hipError_t he = hipStreamSynchronize(user);     // also after an error: nothing of ours is in flight on return
+    if (status != ZI_OK) {
+        (void)hipGetLastError();
+        return status;
+    }
+    ZI_HIP(he);
+    e->offload_pending = false;           // the stream waited for every offload issued so far
+    st.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    e->stats = st;
+    return ZI_OK;
+}
+
 }  // namespace
 
 extern "C" zi_status zi_grad_norm_streamed(zi_engine* e, const zi_tensor* t, int32_t n_tensors, zi_lp_dtype dt,
@@ -800,14 +846,21 @@ extern "C" zi_status zi_grad_norm_streamed(zi_engine* e, const zi_tensor* t, int
     // Device-resident gradients are reduced in place; host-resident ones are staged chunk by chunk.
     e->host_idx.clear();
     e->plan_numel.clear();
-    bool pageable = false;
+    bool pageable = false, mapped = true;
     PointerChecker reach;
     HostRanges pinned;
+    e->src.resize((size_t)n_tensors);
     for (int32_t i = 0; i < n_tensors; ++i) {
+        StateSrc& S = e->src[(size_t)i];
+        S.numel = t[i].numel;
+        S.g_host = false;
         if (t[i].numel == 0) continue;
         int k = 0;
         if (zi_status st = classify_array(reach, pinned, t[i].g, (size_t)t[i].numel * 2, i, "g", k)) return st;
+        S.g_host = k != 0;
+        S.dev[3] = k == 0 ? (char*)t[i].g : pinned.device_address(t[i].g, (size_t)t[i].numel * 2);
         if (k == 0) continue;
+        mapped = mapped && S.dev[3];
         if (k == 2) pageable = true;
         e->host_idx.push_back(i);
         e->plan_numel.push_back(t[i].numel);
@@ -820,6 +873,8 @@ extern "C" zi_status zi_grad_norm_streamed(zi_engine* e, const zi_tensor* t, int
     index_uses(e->segs, n_uses, e->use_begin);
     const std::vector<Segment>& segs = e->segs;
     const std::vector<size_t>& use_begin = e->use_begin;
+    if (mapped && !pageable && e->max_inflight == 0)
+        return run_linked_norm(e, (int)dt, loss_scale, d_out, (zi::NormPartial*)d_workspace, n_uses, user);
 
     ZI_HIP(hipEventRecord(e->ev_in, user));
     ZI_HIP(hipStreamWaitEvent(e->s_h2d, e->ev_in, 0));

@@ -278,90 +278,88 @@ inline zi_status check_norm_args(const zi_tensor* t, int32_t n_tensors, int dt, 
     return ZI_OK;
 }
 
-// Issues the gradient reduction over a list of device-resident gradient arrays: partial-sum launches
-// of up to kMaxNormDesc tensors, and a finalize pass whenever the workspace's partial slots run out
-// and at finish().  After the first finalize the later ones add to the result already in d_out.
+// Issues the gradient reduction over a list of gradient arrays that the device can reach: partial-sum
+// launches of up to kMaxNormDesc tensors, and a finalize pass whenever the workspace's partial slots run out
+// and at finish().  After the first finalize the later ones add to the result already in d_out.  A list
+// that one workgroup reduces in kNormSoloTiles passes is one launch and needs no partials.
 struct NormIssuer {
-    // A workgroup covers at least four tile iterations of its tensor; at most kBlocksPerTensor
-    // workgroups walk one tensor, so the partial count stays small whatever the size.
-    static constexpr int64_t kMinElemsPerBlock = 4 * zi::kNormTileElems;
-    static constexpr int64_t kBlocksPerTensor = 4096;
-
     zi::NormArgs a{};
-    int64_t blocks_cap = kBlocksPerTensor;   // workgroups one tensor may get (lowered by callers with a tight budget)
-    uint32_t blocks = 0;       // blocks of the launch being assembled
-    uint32_t used = 0;         // partials written since the last finalize
+    zi::NormPartial* partials;
+    uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
+    uint32_t used = 0;                   // partials written since the last finalize
+    uint32_t solo_tiles = 0;             // tiles of the list so far, counted for the one-workgroup kernel
+    int launches = 0;                    // kernels so far
     int finalized = 0;
     int dt;
     float loss_scale;
     zi_norm_result* d_out;
     hipStream_t s;
 
-    NormIssuer(zi::NormPartial* partials, int dt_, float ls, zi_norm_result* out, hipStream_t st)
-        : dt(dt_), loss_scale(ls), d_out(out), s(st)
+    NormIssuer(zi::NormPartial* partials_, int dt_, float ls, zi_norm_result* out, hipStream_t st)
+        : partials(partials_), dt(dt_), loss_scale(ls), d_out(out), s(st)
     {
-        a.partials = partials;
-        a.partial_base = 0;
-        clear_table();
     }
-    static int64_t blocks_for(int64_t n, int64_t cap)
+    static int64_t tiles_for(const uint16_t* g, int64_t n, int64_t tile_elems)
     {
-        const int64_t nb = (n + kMinElemsPerBlock - 1) / kMinElemsPerBlock;
-        return nb > cap ? cap : nb;
-    }
-    void clear_table()
-    {
-        a.n_desc = 0;
-        for (uint32_t& f : a.first_block) f = 0xFFFFFFFFu;
+        const int64_t lead = (int64_t)(-(reinterpret_cast<uintptr_t>(g) / 2) % zi::kVec);
+        const int64_t body = n > lead ? (n - lead) / zi::kVec * zi::kVec : 0;
+        const int64_t nt = (body + tile_elems - 1) / tile_elems;
+        return nt < 1 ? 1 : nt;              // the first tile also owns the unaligned ends
     }
     hipError_t flush_launch()
     {
+        if (a.n_desc == 0) return hipSuccess;
         hipError_t e = hipSuccess;
-        if (a.n_desc > 0) e = zi::launch_norm_partials(a, blocks, dt, s);
+        const uint32_t blocks = a.n_tiles < groups ? a.n_tiles : groups;
+        if (used + blocks > zi::kMaxPartials && (e = flush_partials()) != hipSuccess) return e;
+        a.partials = partials + used;
+        e = zi::launch_norm_partials(a, blocks, dt, s);
+        ++launches;
         used += blocks;
-        a.partial_base = used;
-        clear_table();
-        blocks = 0;
+        a.n_desc = a.n_tiles = 0;
         return e;
     }
     hipError_t flush_partials()
     {
-        hipError_t e = zi::launch_norm_finalize(a.partials, used, loss_scale, finalized, d_out, s);
+        const hipError_t e = zi::launch_norm_finalize(partials, used, loss_scale, finalized, d_out, s);
+        ++launches;
         finalized = 1;
         used = 0;
-        a.partial_base = 0;
         return e;
     }
     hipError_t add(const uint16_t* g, int64_t n)
     {
-        if (n <= 0) return hipSuccess;
-        int64_t nb = blocks_for(n, blocks_cap);
-        hipError_t e = hipSuccess;
-        if (a.n_desc == zi::kMaxNormDesc && (e = flush_launch()) != hipSuccess) return e;
-        if ((uint64_t)used + blocks + (uint64_t)nb > zi::kMaxPartials) {
-            if ((e = flush_launch()) != hipSuccess) return e;
-            if ((e = flush_partials()) != hipSuccess) return e;
+        for (; n > 0; g += zi::kNormMaxPiece, n -= zi::kNormMaxPiece) {
+            if (a.n_desc == zi::kMaxNormDesc)
+                if (const hipError_t e = flush_launch(); e != hipSuccess) return e;
+            const int64_t m = n < zi::kNormMaxPiece ? n : zi::kNormMaxPiece;
+            a.t[a.n_desc++] = {g, (uint32_t)m, a.n_tiles};
+            a.n_tiles += (uint32_t)tiles_for(g, m, zi::kNormTileElems);
+            if (solo_tiles <= zi::kNormSoloTiles) solo_tiles += (uint32_t)tiles_for(g, m, zi::kNormSoloTileElems);
         }
-        zi::NormDesc d{};
-        d.g = g;
-        d.numel = n;
-        const int h = (int)((8 - (reinterpret_cast<uintptr_t>(g) / 2) % 8) % 8);
-        d.head = (int32_t)(h < n ? h : n);
-        d.first_block = blocks;
-        d.n_blocks = (uint32_t)nb;
-        a.first_block[a.n_desc] = blocks;
-        a.t[a.n_desc++] = d;
-        blocks += (uint32_t)nb;
         return hipSuccess;
     }
     hipError_t finish()
     {
-        hipError_t e = flush_launch();
-        if (e != hipSuccess) return e;
+        hipError_t e = hipSuccess;
+        if (launches == 0 && a.n_desc > 0 && solo_tiles <= zi::kNormSoloTiles) {
+            a.n_tiles = 0;
+            for (uint32_t i = 0; i < a.n_desc; ++i) {
+                a.t[i].first_tile = a.n_tiles;
+                a.n_tiles += (uint32_t)tiles_for(a.t[i].g, a.t[i].numel, zi::kNormSoloTileElems);
+            }
+            a.out = d_out;
+            a.loss_scale = loss_scale;
+            e = zi::launch_norm_solo(a, dt, s);
+            ++launches;
+            finalized = 1;
+            a.n_desc = a.n_tiles = 0;
+            return e;
+        }
+        if ((e = flush_launch()) != hipSuccess) return e;
         return flush_partials();
     }
 };
-
 
 }  // namespace host
 }  // namespace zi

@@ -37,8 +37,24 @@ constexpr unsigned kStepOccupancyLds = ZI_STEP_LDS;
 
 constexpr int kNormUnroll = 8;
 constexpr int kNormTileVecs = kThreads * kNormUnroll;
-constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 elements per block iteration
-constexpr int kMaxNormDesc = 64;     // gradient tensors per partial-sum launch
+constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 elements per workgroup iteration
+// Workgroups of a partial-sum launch (two per compute unit, 64 KiB of loads in flight in each).  Microseconds
+// for partials and final sum together on 2.5e7 / 3.0e8 / 1.3e9 elements and on a list of 288 tensors with 3.0e8:
+// 512: 12.0 / 91 / 372 / 99, 1024: 11.8 / 92 / 379 / 106, 2048: 11.8 / 92 / 376 / 105, 4096: 11.5 / 94 / 379 / 109;
+// a contiguous run of tiles per workgroup 12.2 / 94 / 378 / 101, half the loads in flight 13.0 / 92 / 376 / 100,
+// single-wavefront workgroups 12.7 / 92 / 373 / 105 at best.
+constexpr int kNormGroups = 512;
+// Gradients in host memory are bound by the link, which few requests in flight fill: GB/s by workgroups
+// 32: 55.9, 64: 57.5, 128: 57.4, 256: 56.4, 1024: 55.9.
+constexpr int kNormLinkGroups = 64;
+constexpr int kMaxNormDesc = 224;    // gradient tensors per partial-sum launch (the argument block stays below 4 KiB)
+constexpr int64_t kNormMaxPiece = (int64_t)1 << 31;   // longer tensors take several descriptors
+// Up to this many tiles of kNormSoloThreads threads one workgroup does the whole reduction, final sum
+// included, in one launch.  On one tensor: 3.3e4 elements 4.8 us against 7.6 for partials and final sum, 6.6e4 (three
+// tiles) 6.6 against 7.7, 1.3e5 (four) 7.6 against 7.7, and the host pays for one launch instead of two.
+constexpr int kNormSoloThreads = 512;
+constexpr int64_t kNormSoloTileElems = (int64_t)kNormSoloThreads * kNormUnroll * kVec;
+constexpr uint32_t kNormSoloTiles = 4;
 constexpr uint32_t kMaxPartials = 16384;   // per-block partial results the workspace holds
 
 // One per-block partial of the gradient reduction (device workspace element).
@@ -81,10 +97,11 @@ struct StepArgs {
 // The step over state in page-locked host memory (adamw_link_kernel): a persistent grid of
 // single-wavefront workgroups that read and write the host arrays over the link themselves.
 // The kernel is bound by the link's two directions, so the grid only has to keep the link's queues full.
-// Measured on 3 x 512 MiB of pinned arrays updated in place, GB/s per direction by workgroups: 32: 47.0,
-// 64: 50.1, 96: 49.4, 128: 48.8, 256: 45.2, 512: 44.4; with four quads a lane instead of two 64 give 48.9;
-// 256-thread workgroups 50.1 at best (32 of them, one quad a lane), 47.1 at 64.
-constexpr int kLinkGroups = 64;
+// Measured on three pinned arrays updated in place, GB/s per direction by workgroups, two hosts:
+// 32: 47.0 / 49.2, 64: 50.1 / 46.5, 96: 49.4 / 49.5, 128: 48.8 / 49.6, 256: 45.2, 512: 44.4.  96 is within 2%
+// of the best on both.  Four quads a lane, one quad a lane, larger workgroups and loads of the next tile
+// in front of this one's stores moved it by 1% up or down.
+constexpr int kLinkGroups = 96;
 constexpr int kMaxLinkDesc = 48;                       // segments per launch (the argument block stays below 4 KiB)
 constexpr uint32_t kLinkTilesPerLaunch = 1u << 19;     // 2^28 elements, some 65 ms of link time
 
@@ -100,25 +117,25 @@ static_assert(sizeof(LinkArgs) < 4096, "kernel arguments");
 
 struct NormDesc {
     const uint16_t* g;
-    int64_t numel;
-    int32_t head;          // 0..7 elements before the first 16-byte aligned one
-    uint32_t first_block;
-    uint32_t n_blocks;
-    uint32_t pad;
+    uint32_t numel;
+    uint32_t first_tile;   // index of this tensor's first tile within the launch
 };
 
 struct NormArgs {
     NormDesc t[kMaxNormDesc];
-    uint32_t first_block[kMaxNormDesc];   // packed copy of the descriptors' first_block, 0xFFFFFFFF beyond n_desc
-    int32_t n_desc;
-    uint32_t partial_base;          // index of this launch's first partial
-    NormPartial* partials;
+    uint32_t n_desc, n_tiles;
+    NormPartial* partials;          // of this launch
+    // the one-workgroup launch only:
+    zi_norm_result* out;
+    float loss_scale;
 };
+static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 
 // Launchers (zi_kernels.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, hipStream_t s);
+hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);
 

@@ -537,70 +537,96 @@ __device__ __forceinline__ void block_reduce(double& sum, uint32_t& flag)
     }
 }
 
-// Each workgroup walks its tensor with a stride of n_blocks tiles and leaves one partial.
+// The workgroup's share of a list: tiles blockIdx.x, blockIdx.x + gridDim.x, ... of all tensors in order, each
+// tile THREADS * kNormUnroll 16-byte vectors with all loads in flight before the first use (a vector past the
+// end counts as zeros).  A tensor's first tile also takes the elements in front of its first 16-byte
+// aligned one and behind its last whole vector.  The tiles of a list are shared out evenly, whatever its
+// tensors' lengths: with workgroups of its own for every tensor a list of short ones left most of the chip idle.
 // Squares are accumulated in double: exact products, and a finite gradient whose square would
 // overflow fp32 still gives a finite sum.
+template <int DT, int THREADS>
+__device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint32_t& flag)
+{
+    constexpr uint32_t tile_vecs = THREADS * kNormUnroll;
+    double acc0 = 0.0, acc1 = 0.0;
+    flag = 0;
+    uint32_t d = 0;
+    for (uint32_t t = blockIdx.x; t < a.n_tiles; t += gridDim.x) {
+        while (d + 1 < a.n_desc && t >= a.t[d + 1].first_tile) ++d;
+        const NormDesc& T = a.t[d];
+        const uint32_t tile = t - T.first_tile;
+        const uint32_t lead = (uint32_t)(-(reinterpret_cast<uintptr_t>(T.g) / 2)) % kVec;
+        const uint32_t head = lead < T.numel ? lead : T.numel;
+        const uint32_t nvec = (T.numel - head) / kVec;
+        const u32x4* __restrict__ g4 = reinterpret_cast<const u32x4*>(T.g + head);
+
+        const uint32_t v0 = tile * tile_vecs + threadIdx.x;
+        u32x4 g[kNormUnroll];
+        if ((tile + 1) * tile_vecs <= nvec) {
+#pragma unroll
+            for (int u = 0; u < kNormUnroll; ++u) g[u] = load_stream(g4 + v0 + u * THREADS);
+        } else {
+#pragma unroll
+            for (int u = 0; u < kNormUnroll; ++u) {
+                g[u] = u32x4{0, 0, 0, 0};
+                if (v0 + u * THREADS < nvec) g[u] = load_stream(g4 + v0 + u * THREADS);
+            }
+        }
+        if (tile == 0) {
+            const uint32_t lane = threadIdx.x, body_end = head + nvec * kVec;
+            const bool front = lane < head, back = lane >= kVec && lane - kVec < T.numel - body_end;
+            if (front || back) {
+                const uint32_t h = T.g[front ? lane : body_end + (lane - kVec)];
+                flag |= nonfinite_bits<DT>(h);
+                const double x = (double)widen16<DT>(h);
+                acc0 = __builtin_fma(x, x, acc0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kNormUnroll; ++u) sumsq_vec<DT>(g[u], acc0, acc1, flag);
+    }
+    sum = acc0 + acc1;
+    block_reduce<THREADS / 64>(sum, flag);
+}
+
+// Bound: HBM (or the link), 2 bytes per element read.  Each workgroup leaves one partial.
 template <int DT>
 __global__ __launch_bounds__(kThreads) void sumsq_partial_kernel(const NormArgs a)
 {
-    uint32_t b = blockIdx.x;
-    int d = -1;                               // first_block[0] is 0: the count is at least 1
-#pragma unroll
-    for (int i = 0; i < kMaxNormDesc; ++i) d += b >= a.first_block[i] ? 1 : 0;
-    const NormDesc& T = a.t[d];
-    b -= T.first_block;
-
-    const int64_t head = T.head;
-    const int64_t nvec = (T.numel - head) / kVec;
-    const int64_t body_end = head + nvec * kVec;
-    const u32x4* __restrict__ g4 = reinterpret_cast<const u32x4*>(T.g + head);
-
-    double acc0 = 0.0, acc1 = 0.0;
-    uint32_t flag = 0;
-
-    if (b == 0) {
-        const int64_t t = threadIdx.x;
-        const int64_t tail = T.numel - body_end;
-        int64_t idx = -1;
-        if (t < head) idx = t;
-        else if (t >= 8 && t - 8 < tail) idx = body_end + (t - 8);
-        if (idx >= 0) {
-            const uint32_t h = T.g[idx];
-            flag |= nonfinite_bits<DT>(h);
-            const double x = (double)widen16<DT>(h);
-            acc0 = __builtin_fma(x, x, acc0);
-        }
-    }
-
-    const int64_t stride = (int64_t)T.n_blocks * kNormTileVecs;
-    for (int64_t base = (int64_t)b * kNormTileVecs; base < nvec; base += stride) {
-        const int64_t iv = base + threadIdx.x;
-        if (base + kNormTileVecs <= nvec) {
-            u32x4 g[kNormUnroll];
-#pragma unroll
-            for (int u = 0; u < kNormUnroll; ++u) g[u] = load_stream(g4 + iv + (int64_t)u * kThreads);
-#pragma unroll
-            for (int u = 0; u < kNormUnroll; ++u) sumsq_vec<DT>(g[u], acc0, acc1, flag);
-        } else {
-            for (int u = 0; u < kNormUnroll; ++u) {
-                const int64_t j = iv + (int64_t)u * kThreads;
-                if (j < nvec) sumsq_vec<DT>(load_stream(g4 + j), acc0, acc1, flag);
-            }
-        }
-    }
-
-    double sum = acc0 + acc1;
-    block_reduce<kThreads / 64>(sum, flag);
+    double sum;
+    uint32_t flag;
+    sumsq_tiles<DT, kThreads>(a, sum, flag);
     if (threadIdx.x == 0) {
         NormPartial out;
         out.sumsq = sum;
         out.found_inf = flag ? 1u : 0u;
         out.pad = 0;
-        a.partials[a.partial_base + blockIdx.x] = out;
+        a.partials[blockIdx.x] = out;
     }
 }
 
-constexpr int kFinalThreads = 1024;
+__device__ __forceinline__ zi_norm_result norm_result(double sumsq, uint32_t flag, float loss_scale)
+{
+    zi_norm_result r;
+    r.sumsq = sumsq;
+    r.norm = __builtin_sqrt(sumsq) / (double)loss_scale;
+    r.found_inf = flag ? 1u : 0u;
+    r.scale_bits = __float_as_uint(loss_scale);
+    r.inv_norm = 1.0 / (r.norm + 1e-6);
+    return r;
+}
+
+// Bound: launches.  A short list's whole reduction in one workgroup (kNormSoloTiles).
+template <int DT>
+__global__ __launch_bounds__(kNormSoloThreads) void sumsq_solo_kernel(const NormArgs a)
+{
+    double sum;
+    uint32_t flag;
+    sumsq_tiles<DT, kNormSoloThreads>(a, sum, flag);
+    if (threadIdx.x == 0) *a.out = norm_result(sum, flag, a.loss_scale);
+}
+
+constexpr int kFinalThreads = kNormGroups;   // one partial each where one launch made them all
 
 // One workgroup adds the partials in a fixed order (so the result does not depend on scheduling)
 // and writes the device-resident result.
@@ -620,13 +646,7 @@ __global__ __launch_bounds__(kFinalThreads) void norm_finalize_kernel(const Norm
             sum += out->sumsq;
             flag |= out->found_inf;
         }
-        zi_norm_result r;
-        r.sumsq = sum;
-        r.norm = __builtin_sqrt(sum) / (double)loss_scale;
-        r.found_inf = flag ? 1u : 0u;
-        r.scale_bits = __float_as_uint(loss_scale);
-        r.inv_norm = 1.0 / (r.norm + 1e-6);
-        *out = r;
+        *out = norm_result(sum, flag, loss_scale);
     }
 }
 
@@ -635,10 +655,7 @@ __global__ __launch_bounds__(kFinalThreads) void norm_finalize_kernel(const Norm
 __global__ void norm_refresh_kernel(zi_norm_result* r, float loss_scale)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        r->norm = __builtin_sqrt(r->sumsq) / (double)loss_scale;
-        r->found_inf = r->found_inf ? 1u : 0u;
-        r->scale_bits = __float_as_uint(loss_scale);
-        r->inv_norm = 1.0 / (r->norm + 1e-6);
+        *r = norm_result(r->sumsq, r->found_inf, loss_scale);
     }
 }
 
@@ -654,6 +671,14 @@ hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, hi
     const dim3 grid(n_blocks), block(kThreads);
     if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_partial_kernel<ZI_BF16>), grid, block, 0, s, a);
     else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s)
+{
+    const dim3 grid(1), block(kNormSoloThreads);
+    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_solo_kernel<ZI_BF16>), grid, block, 0, s, a);
+    else               hipLaunchKernelGGL((sumsq_solo_kernel<ZI_FP16>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -11,7 +11,7 @@ from gpu_util import NormBuffers, compare_state, gen_numpy, oracle_cfg, progress
 
 pytestmark = pytest.mark.gpu
 
-TILE, GROUPS, DESCS = 512, 64, 48
+TILE, GROUPS, DESCS = 512, 96, 48
 
 
 def _placed(a, offset, host):
@@ -108,3 +108,44 @@ def test_overflow_skips_and_touches_nothing():
     for (p, m, v, _), b, o in zip(host, got, (0, 3)):
         for x, y in zip((p, m, v, np.zeros(p.size, np.uint16)), (b[0], b[1], b[2], b[4])):
             assert np.array_equal(x.view(np.uint8), y[o:o + x.size].view(np.uint8))
+
+
+SOLO = 32768                          # elements one pass of the one-workgroup reduction covers
+
+
+@pytest.mark.parametrize("offset", [0, 1, 7])
+@pytest.mark.parametrize("sizes", [[SOLO - 1], [SOLO + 9], [4 * SOLO], [4 * SOLO + 7], [4 * SOLO + 16], [5, 3 * SOLO],
+                                   [5, 6, 7, 8], [5, 6, 7, 8, 9], [3] * 224, [3] * 225, [512 * 16384 + 11, 1]])
+def test_norm_of_device_and_page_locked_gradients(sizes, offset):
+    """Around the one-workgroup limit, the tensors a launch takes and the workgroups a launch has: the sum against
+    the oracle for gradients in HBM and in host memory, and the flag from the very last element."""
+    dt = zi.ZI_FP16 if offset else zi.ZI_BF16
+    gs = [gen_numpy(zi_synth.StateSpec(60 + n, dt, g_std=1e-2), n, tensor=i)[3] for i, n in enumerate(sizes)]
+    want, _ = oracle.grad_sumsq(gs, dt)
+    eng = zi.zi_engine_create(0, 64 * 1024, 3)
+    try:
+        for planted in (False, True):
+            if planted:
+                gs[-1][-1] = 0x7C00 if dt == zi.ZI_FP16 else 0x7F80
+            flags, sums = [], []
+            for host in (False, True):
+                bufs = [_placed(g, offset, host) for g in gs]
+                tl = [(None, None, None, b[offset:offset + g.size], None, g.size) for b, g in zip(bufs, gs)]
+                nb = NormBuffers()
+                if host:
+                    zi.zi_grad_norm_streamed(eng, tl, dt, 2.0, nb.out, nb.ws)
+                    st = zi.zi_engine_last_stats(eng)
+                    assert st.n_copies == 0 and st.bytes_h2d == 2 * sum(sizes)
+                else:
+                    zi.zi_grad_norm(tl, dt, 2.0, nb.out, nb.ws)
+                    torch.cuda.synchronize()
+                sumsq, norm, flag = nb.read()
+                flags.append(flag)
+                sums.append((sumsq, norm))
+            assert flags == [int(planted)] * 2
+            if not planted:
+                for sumsq, norm in sums:
+                    assert abs(sumsq - want) <= 1e-12 * want          # double sums of exact squares on both sides
+                    assert abs(norm - np.sqrt(want) / 2.0) <= 1e-12 * norm
+    finally:
+        zi.zi_engine_destroy(eng)
