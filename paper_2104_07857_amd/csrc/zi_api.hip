@@ -159,6 +159,7 @@ extern "C" zi_status zi_adamw_step(const zi_tensor* t, int32_t n_tensors, zi_lp_
 
     const zi::StepConsts k = make_consts(*cfg);
     StepIssuer issue(k, d_norm, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, (hipStream_t)hip_stream);
+    issue.expect(t, n_tensors);
     for (int32_t i = 0; i < n_tensors; ++i)
         ZI_HIP(issue.add((float*)t[i].p, (float*)t[i].m, (float*)t[i].v, (const uint16_t*)t[i].g,
                          (uint16_t*)t[i].p_lp, t[i].numel));
@@ -176,6 +177,7 @@ extern "C" zi_status zi_plan_step(const zi_tensor* t, int32_t n_tensors, zi_step
     try {
         StepIssuer issue(zi::StepConsts{}, nullptr, ZI_BF16, false, nullptr);
         issue.plan = &items;
+        issue.expect(t, n_tensors);
         for (int32_t i = 0; i < n_tensors; ++i) {
             issue.cur_tensor = i;
             (void)issue.add((float*)t[i].p, (float*)t[i].m, (float*)t[i].v, (const uint16_t*)t[i].g,

@@ -94,6 +94,32 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
+// A launch over many short tensors (adamw_list_kernel): each shorter than a launch of its own, so 32 bits hold
+// its length and its tiles.
+constexpr int kListGroup = 8;
+constexpr int kListGroups = 8;
+constexpr int kMaxListDesc = kListGroup * kListGroups;
+
+struct ListDesc {
+    float* p_body;         // p + head
+    float* m_body;
+    float* v_body;
+    const uint16_t* g_body;
+    uint16_t* lp_body;     // p_lp + head, null if there is no copy
+    uint32_t numel;
+    uint16_t head;         // 0..63
+    uint16_t n_tiles;
+};
+
+struct ListArgs {
+    ListDesc t[kMaxListDesc];
+    uint32_t first_tile[kMaxListDesc];      // 0xFFFFFFFF beyond the list
+    uint32_t group_start[kListGroups];      // first_tile of every eighth
+    StepConsts c;
+    const zi_norm_result* d_norm;
+};
+static_assert(sizeof(ListArgs) < 4096, "kernel arguments");
+
 // The step over state in page-locked host memory (adamw_link_kernel): a persistent grid of
 // single-wavefront workgroups that read and write the host arrays over the link themselves.
 // The kernel is bound by the link's two directions, so the grid only has to keep the link's queues full.
@@ -132,7 +158,9 @@ struct NormArgs {
 static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 
 // Launchers (zi_kernels.hip).  Each returns the hipError_t of the launch.
-hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s);
+// any_order: may run beside the launches in front of it on the stream (see StepIssuer for where that is safe).
+hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
+hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, hipStream_t s);
 hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s);

@@ -1,0 +1,64 @@
+"""Lists of more than 64 short tensors: how they share launches (no GPU), and that a list gives every tensor the bits
+that a call of its own gives it, where the lookup of the tensor and the overlap of the launches could go wrong."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2104_07857_amd as zi
+import zi_synth
+
+TILE = 512
+
+
+@pytest.mark.parametrize("n_short,per_launch", [(64, [32, 32]), (65, [64, 1]), (129, [64, 64, 1])])
+def test_long_lists_share_launches_of_64(n_short, per_launch):
+    base, gap = 0x7F00_0000_0000, 1 << 36
+    lens = [100 + 600 * (i % 7) for i in range(n_short)]
+    lens.insert(10, 1 << 22)                                       # and one that is launched alone, in between
+    items, launches = zi.zi_plan_step([tuple(base + (5 * i + k) * gap for k in range(5)) + (n,) for i, n in enumerate(lens)])
+    assert launches == len(per_launch) + 1
+    groups = {}
+    for it in items:
+        groups.setdefault(it.launch, []).append(it)
+    assert sorted(len(g) for g in groups.values()) == sorted(per_launch + [1])
+    for g in groups.values():                                      # tiles of a launch are numbered densely, in order
+        nxt = 0
+        for it in g:
+            assert it.first_tile == nxt and it.n_tiles == max(1, -(-((lens[it.tensor] - it.head) // 4) // (TILE // 4)))
+            nxt += it.n_tiles
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("count,l2,dt", [(64, False, zi.ZI_BF16), (65, True, zi.ZI_FP16), (200, False, zi.ZI_FP16)])
+def test_a_list_equals_its_tensors_one_by_one(count, l2, dt):
+    """Ragged tensors at odd offsets of flat buffers (some a tile or less, one longer than an XCD run of tiles, one
+    launched alone in the middle), stepped twice in a row as a list and tensor by tensor."""
+    rng = np.random.default_rng(count)
+    sizes = [int(x) for x in rng.integers(1, 4000, count)]
+    sizes[3], sizes[7], sizes[20], sizes[count - 1] = 1, TILE, 1030 * TILE + 5, 2 * TILE + 3
+    sizes.insert(30, (1 << 22) + 77)
+    starts = np.cumsum([3] + [n + int(x) for n, x in zip(sizes, rng.integers(0, 9, len(sizes)))])[:-1]
+    total = int(starts[-1]) + sizes[-1] + 4
+    spec = zi_synth.StateSpec(11, dt, g_std=2e-3)
+    host = [np.empty(total, np.float32) for _ in range(3)] + [np.empty(total, np.uint16)]
+    for fill, a in zip((spec.fill_p, spec.fill_m, spec.fill_v, spec.fill_g), host):
+        fill(a, total)
+
+    def state():
+        bufs = [torch.from_numpy(a.copy().view(np.int16) if a.dtype == np.uint16 else a.copy()).cuda() for a in host]
+        bufs.append(torch.full((total,), 7, dtype=torch.int16, device="cuda:0"))
+        return bufs, [tuple(b[s:s + n] for b in bufs) + (n,) for s, n in zip(starts.tolist(), sizes)]
+
+    cfg = zi.make_config(step=10, mode=zi.ZI_MODE_ADAM_L2 if l2 else zi.ZI_MODE_ADAMW)
+    (a, ta), (b, tb) = state(), state()
+    norm = torch.zeros(4, dtype=torch.float64, device="cuda:0")
+    for _ in range(2):
+        zi.zi_grad_norm_noalloc(ta, dt, 1.0, norm)
+        zi.zi_adamw_step(ta, dt, cfg, norm)
+    for _ in range(2):
+        for t in tb:
+            zi.zi_adamw_step([t], dt, cfg, norm)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):                                          # what lies between the tensors included
+        assert torch.equal(x.view(torch.int32 if x.dtype == torch.float32 else torch.int16),
+                           y.view(torch.int32 if y.dtype == torch.float32 else torch.int16))
