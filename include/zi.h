@@ -397,7 +397,8 @@ zi_status zi_plan_chunks(const int64_t* numel, int32_t n_tensors, int64_t chunk_
  * elements handled one by one before the 4-element lane vectors start (0..63, chosen so that as much
  * of the tensor's traffic as possible starts on 128-byte lines), its tiles of 512 elements, and the
  * launch it belongs to.  Tensors of 2^22 elements or more get a launch of their own (`alone`);
- * shorter ones share launches of up to 32 tensors, of up to 64 if the list has more than 64 of them.  Writes at most `cap` items and always the totals.
+ * shorter ones share launches of up to 32 tensors.  Lists of more than 64 tensors share launches of 64,
+ * long tensors too.  Writes at most `cap` items and always the totals.
  */
 typedef struct {
     int32_t tensor;        /* index into t[] */

@@ -119,7 +119,8 @@ inline int choose_head(const void* p, const void* m, const void* v, const void* 
 }
 
 // Tensors of at least this many tiles (2^22 elements, some 20 microseconds of HBM time) are launched
-// alone; shorter ones share launches of up to kMaxStepDesc tensors.
+// alone; shorter ones share launches of up to kMaxStepDesc tensors.  Lists of more than kMaxListDesc tensors
+// go to adamw_list_kernel as they are.
 #ifndef ZI_SOLO_TILES
 #define ZI_SOLO_TILES 8192
 #endif
@@ -138,16 +139,16 @@ struct StepIssuer {
     std::vector<zi_step_plan_item>* plan = nullptr;
     int32_t cur_tensor = -1;
     int32_t tensor_of[zi::kMaxListDesc] = {};
-    // Lists of more than kMaxListDesc short tensors (expect()): the launches take that many, in `list`.
+    // Lists of more than kMaxListDesc tensors (expect()): launches of that many, whatever their length, in `list`.
     bool long_list = false;
     zi::ListArgs list;
 
-    // What the list will be, before the first add(): decides how many short tensors share a launch.
+    // What the list will be, before the first add(): decides how many tensors share a launch.
     void expect(const zi_tensor* t, int32_t n_tensors)
     {
-        int64_t n_short = 0;
-        for (int32_t i = 0; i < n_tensors; ++i) n_short += t[i].numel > 0 && t[i].numel < kSoloTiles * zi::kStepTileElems;
-        if (n_short <= zi::kMaxListDesc) return;
+        int64_t n = 0;
+        for (int32_t i = 0; i < n_tensors; ++i) n += t[i].numel > 0;
+        if (n <= zi::kMaxListDesc) return;
         long_list = true;
         list.c = args.c;
         list.d_norm = args.d_norm;
@@ -264,7 +265,7 @@ struct StepIssuer {
         if (nt > 0x7FFFFFFF) return hipErrorInvalidValue;
         d.nquad = nquad;
         d.n_tiles = (uint32_t)nt;
-        if (nt >= kSoloTiles) {                   // a launch of its own: no tensor lookup in the kernel
+        if (long_list ? nquad > 0xFFFFFFFFll : nt >= kSoloTiles) {      // a launch of its own: no tensor lookup in the kernel
             zi::StepArgs solo{};
             solo.c = args.c;
             solo.d_norm = args.d_norm;
@@ -275,13 +276,13 @@ struct StepIssuer {
             solo.t[0] = d;
             return launch(solo, (uint32_t)nt, &cur_tensor);
         }
-        if (args.n_desc == (long_list ? zi::kMaxListDesc : zi::kMaxStepDesc)) {
+        if (args.n_desc == (long_list ? zi::kMaxListDesc : zi::kMaxStepDesc) || (uint64_t)tiles + (uint64_t)nt > 0x7FFFFFFFull) {
             hipError_t e = close();
             if (e != hipSuccess) return e;
         }
         if (long_list) {
-            list.t[args.n_desc] = {d.p_body, d.m_body, d.v_body, d.g_body, d.lp_body, (uint32_t)numel, (uint16_t)d.head,
-                                   (uint16_t)nt};
+            list.t[args.n_desc] = {d.p_body, d.m_body, d.v_body, d.g_body, d.lp_body, (uint32_t)nquad, (uint16_t)d.head,
+                                   (uint16_t)(numel - d.head - nquad * zi::kQuad)};
             list.first_tile[args.n_desc] = tiles;
             tensor_of[args.n_desc++] = cur_tensor;
             tiles += (uint32_t)nt;

@@ -94,8 +94,7 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
-// A launch over many short tensors (adamw_list_kernel): each shorter than a launch of its own, so 32 bits hold
-// its length and its tiles.
+// A launch over many tensors (adamw_list_kernel).
 constexpr int kListGroup = 8;
 constexpr int kListGroups = 8;
 constexpr int kMaxListDesc = kListGroup * kListGroups;
@@ -106,9 +105,8 @@ struct ListDesc {
     float* v_body;
     const uint16_t* g_body;
     uint16_t* lp_body;     // p_lp + head, null if there is no copy
-    uint32_t numel;
-    uint16_t head;         // 0..63
-    uint16_t n_tiles;
+    uint32_t nquad;
+    uint16_t head, tail;   // elements in front of the quads (0..63) and behind them (0..3)
 };
 
 struct ListArgs {

@@ -113,28 +113,34 @@ __device__ __forceinline__ double dwords_as_double(uint32_t lo, uint32_t hi)
 {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-__device__ __forceinline__ bool step_prologue(const zi_norm_result* d_norm, const StepConsts& c, float& gscale)
+__device__ __forceinline__ u32x8_k load_norm_result(const zi_norm_result* d_norm)
 {
-    gscale = c.host_gscale;
-    if (d_norm) {
-        const u32x8_k raw = *(const __attribute__((address_space(4))) u32x8_k*)(uintptr_t)d_norm;
-        const double sumsq = dwords_as_double(raw[0], raw[1]);
-        const double r_norm = dwords_as_double(raw[2], raw[3]);
-        const uint32_t found_inf = raw[4], scale_bits = raw[5];
-        const double r_inv_norm = dwords_as_double(raw[6], raw[7]);
-        if (found_inf) return false;
-        if (c.max_grad_norm > 0.0f) {
-            const double ls = (double)c.loss_scale;
-            const bool same_scale = scale_bits == __float_as_uint(c.loss_scale);
-            const double norm = same_scale ? r_norm : __builtin_sqrt(sumsq) / ls;
-            const double mx = (double)c.max_grad_norm;
-            if (norm + 1e-6 > mx) {
-                const double clip = same_scale && c.max_norm_is_pow2 ? mx * r_inv_norm : mx / (norm + 1e-6);
-                gscale = (float)(c.scale_is_pow2 ? clip * c.inv_loss_scale : clip / ls);
-            }
+    return *(const __attribute__((address_space(4))) u32x8_k*)(uintptr_t)d_norm;
+}
+// What the step makes of the 32 bytes of the result.
+__device__ __forceinline__ bool judge_norm_result(const u32x8_k raw, const StepConsts& c, float& gscale)
+{
+    const double sumsq = dwords_as_double(raw[0], raw[1]);
+    const double r_norm = dwords_as_double(raw[2], raw[3]);
+    const uint32_t found_inf = raw[4], scale_bits = raw[5];
+    const double r_inv_norm = dwords_as_double(raw[6], raw[7]);
+    if (found_inf) return false;
+    if (c.max_grad_norm > 0.0f) {
+        const double ls = (double)c.loss_scale;
+        const bool same_scale = scale_bits == __float_as_uint(c.loss_scale);
+        const double norm = same_scale ? r_norm : __builtin_sqrt(sumsq) / ls;
+        const double mx = (double)c.max_grad_norm;
+        if (norm + 1e-6 > mx) {
+            const double clip = same_scale && c.max_norm_is_pow2 ? mx * r_inv_norm : mx / (norm + 1e-6);
+            gscale = (float)(c.scale_is_pow2 ? clip * c.inv_loss_scale : clip / ls);
         }
     }
     return true;
+}
+__device__ __forceinline__ bool step_prologue(const zi_norm_result* d_norm, const StepConsts& c, float& gscale)
+{
+    gscale = c.host_gscale;
+    return !d_norm || judge_norm_result(load_norm_result(d_norm), c, gscale);
 }
 
 // One element of the unaligned ends, addressed relative to the body (i may be negative: the head).
@@ -268,13 +274,11 @@ __device__ __forceinline__ uint32_t tile_of_block(uint32_t block, uint32_t first
 
 // Elements before the vector body (at most 63) and after it (at most 3), by the tensor's first tile.
 template <int DT, bool L2, typename Desc>
-__device__ __forceinline__ void step_ends(const Desc& T, int64_t nquad, float gscale, const StepConsts& c)
+__device__ __forceinline__ void step_ends(const Desc& T, int64_t head, int64_t body, int64_t tail, float gscale,
+                                          const StepConsts& c)
 {
     const int64_t t = threadIdx.x;
-    const int64_t head = T.head;
     if (t < head) step_scalar_at<DT, L2>(T, t - head, gscale, c);
-    const int64_t body = nquad * kQuad;
-    const int64_t tail = T.numel - head - body;
     if (t >= 4 && t - 4 < tail) step_scalar_at<DT, L2>(T, body + (t - 4), gscale, c);
 }
 
@@ -361,48 +365,74 @@ void adamw_wide_kernel(const StepArgs a)
     float gscale;
     if (!step_prologue(a.d_norm, a.c, gscale)) return;
 
-    if (tile == 0) step_ends<DT, L2>(T, nquad, gscale, a.c);
+    if (tile == 0) {
+        const int64_t body = nquad * kQuad;
+        step_ends<DT, L2>(T, T.head, body, T.numel - T.head - body, gscale, a.c);
+    }
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, a.c);
 }
 
-// The same for long lists of short tensors: twice as many to a launch in a smaller descriptor, found by
-// counting the starts of groups of eight tensors and then the starts inside one group.  The lookup is as long
-// as the 32-entry table's.  200 tensors of 1..40,000 elements, one step call: 45.6 us with seven launches of
-// adamw_wide_kernel, 36.8 with four of this one.
+// n += block >= start; first = the start, if so.  Three scalar instructions; the compiler goes through a
+// vector register.
+__device__ __forceinline__ void count_start(uint32_t block, uint32_t start, uint32_t& n, uint32_t& first)
+{
+    asm("s_cmp_ge_u32 %2, %3\n\ts_cselect_b32 %1, %3, %1\n\ts_addc_u32 %0, %0, 0"
+        : "+s"(n), "+s"(first)
+        : "s"(block), "s"(start)
+        : "scc");
+}
+
+// The same for long lists: 64 tensors of any length to a launch, found by counting the starts of groups of
+// eight tensors and then the starts inside one group.  A workgroup still lives for a few microseconds, so
+// what is in front of its first load is kept to three round trips to the scalar cache (arguments; group starts
+// and norm result together; descriptor) and arithmetic that hides in them.  Measured, step alone in us, against
+// a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
+// 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1430,
+// 200 of 1..40,000 45.6 -> 35.3; with the norm result fetched after the descriptor 1478 instead of 1366.
 template <int DT, bool L2>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void adamw_list_kernel(const ListArgs a)
 {
     const uint32_t block = blockIdx.x;
-    int group = -1;                       // the first start is 0, so both counts are at least 1
+    const zi_norm_result* d_norm = a.d_norm;
+    StepConsts c = a.c;
+    // (what the judgement below needs arrives with the first batch of arguments, not where it is used)
+    asm volatile("" : "+s"(c.host_gscale), "+s"(c.max_grad_norm), "+s"(c.loss_scale), "+s"(c.scale_is_pow2),
+                 "+s"(c.max_norm_is_pow2), "+s"(c.inv_loss_scale));
+    uint32_t group = 0, first = 0;        // the first start is 0, so both counts are at least 1
 #pragma unroll
-    for (int i = 0; i < kListGroups; ++i) group += block >= a.group_start[i] ? 1 : 0;
-    int d = group * kListGroup - 1;
-    uint32_t first = 0;
+    for (int i = 0; i < kListGroups; ++i) count_start(block, a.group_start[i], group, first);
+    // The norm result travels beside the group's starts: one round trip to the scalar cache for both.
+    u32x8_k raw = {};
+    if (d_norm) raw = load_norm_result(d_norm);
+    uint32_t d = --group * kListGroup;
 #pragma unroll
-    for (int i = 0; i < kListGroup; ++i) {
-        const uint32_t f = a.first_tile[group * kListGroup + i];
-        if (block >= f) {
-            ++d;
-            first = f;
-        }
-    }
-    const ListDesc& T = a.t[d];
-
-    const int64_t nquad = (T.numel - T.head) / (uint32_t)kQuad;
-    const uint32_t tile = tile_of_block(block, first, T.n_tiles);
-
+    for (int i = 0; i < kListGroup; ++i) count_start(block, a.first_tile[group * kListGroup + i], d, first);
+    float gscale = c.host_gscale;
+    const bool clips = d_norm && c.max_grad_norm > 0.0f;
+    const bool quick = c.max_norm_is_pow2 && c.scale_is_pow2;
+    const bool same_scale = raw[5] == __float_as_uint(c.loss_scale);
+    if (clips && !(quick && same_scale)) (void)judge_norm_result(raw, c, gscale);
+    const ListDesc& T = a.t[d - 1];
+    uint32_t nquad = T.nquad;
     GlobalF4 __restrict__ p4 = (GlobalF4)(uintptr_t)T.p_body;
     GlobalF4 __restrict__ m4 = (GlobalF4)(uintptr_t)T.m_body;
     GlobalF4 __restrict__ v4 = (GlobalF4)(uintptr_t)T.v_body;
     GlobalConstU2 __restrict__ g2 = (GlobalConstU2)(uintptr_t)T.g_body;
     GlobalU2 __restrict__ lp2 = (GlobalU2)(uintptr_t)T.lp_body;
-    asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2));
+    // The usual clipping step (judge_norm_result's shortcuts, all of them) without a branch: its few double
+    // operations run while the descriptor is on its way.
+    const double mx = (double)c.max_grad_norm;
+    const float clipped = (float)(mx * dwords_as_double(raw[6], raw[7]) * c.inv_loss_scale);
+    const bool over = dwords_as_double(raw[2], raw[3]) + 1e-6 > mx;
+    gscale = clips && quick && same_scale && over ? clipped : gscale;
+    asm volatile("" : "+v"(gscale));
+    asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
+    if (d_norm && raw[4]) return;
 
-    float gscale;
-    if (!step_prologue(a.d_norm, a.c, gscale)) return;
-    if (tile == 0) step_ends<DT, L2>(T, nquad, gscale, a.c);
-    step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, a.c);
+    const uint32_t tile = tile_of_block(block, first, (nquad + kStepTileQuads - 1) / kStepTileQuads);
+    if (tile == 0) step_ends<DT, L2>(T, T.head, (int64_t)nquad * kQuad, T.tail, gscale, c);
+    step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
 }
 
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
