@@ -52,10 +52,14 @@ extern "C" zi_status zi_grad_norm(const zi_tensor* t, int32_t n_tensors, zi_lp_d
     if (zi_status st = check_kernel_visible(d_out, sizeof(zi_norm_result), -1, "d_out")) return st;
     if (zi_status st = check_kernel_visible(d_workspace, workspace_bytes, -1, "d_workspace")) return st;
     PointerChecker reach;
-    for (int32_t i = 0; i < n_tensors; ++i)
+    int64_t total = 0;
+    for (int32_t i = 0; i < n_tensors; ++i) {
         if (zi_status st = reach.check(t[i].g, (size_t)t[i].numel * 2, i, "g")) return st;
+        total += t[i].numel;
+    }
 
     NormIssuer issue((zi::NormPartial*)d_workspace, (int)dt, loss_scale, d_out, (hipStream_t)hip_stream);
+    issue.keep = total <= zi::kNormKeepElems;
     for (int32_t i = 0; i < n_tensors; ++i) ZI_HIP(issue.add((const uint16_t*)t[i].g, t[i].numel));
     ZI_HIP(issue.finish());   // also writes zeros for an empty list
     return ZI_OK;
@@ -108,10 +112,11 @@ extern "C" zi_status zi_grad_norm_noalloc(const zi_tensor* t, int32_t n_tensors,
         return st;
     if (zi_status st = check_kernel_visible(d_out, sizeof(zi_norm_result), -1, "d_out")) return st;
     PointerChecker reach;
-    int64_t non_empty = 0;
+    int64_t non_empty = 0, total = 0;
     for (int32_t i = 0; i < n_tensors; ++i) {
         if (zi_status st = reach.check(t[i].g, (size_t)t[i].numel * 2, i, "g")) return st;
         non_empty += t[i].numel > 0;
+        total += t[i].numel;
     }
     // Every launch leaves at most kNormGroups partials and the sums are folded together when the array is
     // full, so the array bounds nothing by itself; the list length is held to what the header promises.
@@ -121,6 +126,7 @@ extern "C" zi_status zi_grad_norm_noalloc(const zi_tensor* t, int32_t n_tensors,
                     ZI_NOALLOC_MAX_PARTIALS);
 
     NormIssuer issue(partials, (int)dt, loss_scale, d_out, (hipStream_t)hip_stream);
+    issue.keep = total <= zi::kNormKeepElems;
     for (int32_t i = 0; i < n_tensors; ++i) ZI_HIP(issue.add((const uint16_t*)t[i].g, t[i].numel));
     ZI_HIP(issue.finish());
     return ZI_OK;

@@ -378,6 +378,7 @@ struct NormIssuer {
     uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
     uint32_t used = 0;                   // partials written since the last finalize
     uint32_t solo_tiles = 0;             // tiles of the list so far, counted for the one-workgroup kernel
+    bool keep = false;                   // see kNormKeepElems
     int launches = 0;                    // kernels so far
     int finalized = 0;
     int dt;
@@ -403,7 +404,7 @@ struct NormIssuer {
         const uint32_t blocks = a.n_tiles < groups ? a.n_tiles : groups;
         if (used + blocks > zi::kMaxPartials && (e = flush_partials()) != hipSuccess) return e;
         a.partials = partials + used;
-        e = zi::launch_norm_partials(a, blocks, dt, s);
+        e = zi::launch_norm_partials(a, blocks, dt, keep, s);
         ++launches;
         used += blocks;
         a.n_desc = a.n_tiles = 0;

@@ -44,6 +44,12 @@ constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 ele
 // a contiguous run of tiles per workgroup 12.2 / 94 / 378 / 101, half the loads in flight 13.0 / 92 / 376 / 100,
 // single-wavefront workgroups 12.7 / 92 / 373 / 105 at best.
 constexpr int kNormGroups = 512;
+// Calls of up to this many elements (256 MiB, the size of the memory-side cache) read the gradients with ordinary
+// loads, which leave them there for the step that reads them next; streaming loads pass the cache by.  Norm and
+// step together in us, streaming -> ordinary: 1.7e7 elements 88.8 -> 84.5, 6.7e7 322 -> 309, 1.3e8 647 -> 621.  The
+// reduction itself takes 10% longer so (44 -> 49 us at 1.3e8), which is why larger calls, of which only a part
+// would still be there, stay with streaming loads.
+constexpr int64_t kNormKeepElems = (int64_t)1 << 27;
 // Gradients in host memory are bound by the link, which few requests in flight fill: GB/s by workgroups
 // 32: 55.9, 64: 57.5, 128: 57.4, 256: 56.4, 1024: 55.9.
 constexpr int kNormLinkGroups = 64;
@@ -160,7 +166,8 @@ static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
-hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, hipStream_t s);
+// keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
+hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, hipStream_t s);
 hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);

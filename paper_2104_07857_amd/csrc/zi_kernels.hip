@@ -658,7 +658,8 @@ __device__ __forceinline__ void block_reduce(double& sum, uint32_t& flag)
 // tensors' lengths: with workgroups of its own for every tensor a list of short ones left most of the chip idle.
 // Squares are accumulated in double: exact products, and a finite gradient whose square would
 // overflow fp32 still gives a finite sum.
-template <int DT, int THREADS>
+// KEEP: ordinary loads, which leave the gradients in the memory-side cache (kNormKeepElems).
+template <int DT, int THREADS, bool KEEP>
 __device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint32_t& flag)
 {
     constexpr uint32_t tile_vecs = THREADS * kNormUnroll;
@@ -678,12 +679,12 @@ __device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint
         u32x4 g[kNormUnroll];
         if ((tile + 1) * tile_vecs <= nvec) {
 #pragma unroll
-            for (int u = 0; u < kNormUnroll; ++u) g[u] = load_stream(g4 + v0 + u * THREADS);
+            for (int u = 0; u < kNormUnroll; ++u) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
         } else {
 #pragma unroll
             for (int u = 0; u < kNormUnroll; ++u) {
                 g[u] = u32x4{0, 0, 0, 0};
-                if (v0 + u * THREADS < nvec) g[u] = load_stream(g4 + v0 + u * THREADS);
+                if (v0 + u * THREADS < nvec) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
             }
         }
         if (tile == 0) {
@@ -704,12 +705,12 @@ __device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint
 }
 
 // Bound: HBM (or the link), 2 bytes per element read.  Each workgroup leaves one partial.
-template <int DT>
+template <int DT, bool KEEP>
 __global__ __launch_bounds__(kThreads) void sumsq_partial_kernel(const NormArgs a)
 {
     double sum;
     uint32_t flag;
-    sumsq_tiles<DT, kThreads>(a, sum, flag);
+    sumsq_tiles<DT, kThreads, KEEP>(a, sum, flag);
     if (threadIdx.x == 0) {
         NormPartial out;
         out.sumsq = sum;
@@ -736,7 +737,7 @@ __global__ __launch_bounds__(kNormSoloThreads) void sumsq_solo_kernel(const Norm
 {
     double sum;
     uint32_t flag;
-    sumsq_tiles<DT, kNormSoloThreads>(a, sum, flag);
+    sumsq_tiles<DT, kNormSoloThreads, true>(a, sum, flag);
     if (threadIdx.x == 0) *a.out = norm_result(sum, flag, a.loss_scale);
 }
 
@@ -779,12 +780,14 @@ hipError_t launch_norm_refresh(zi_norm_result* d_result, float loss_scale, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, hipStream_t s)
+hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, hipStream_t s)
 {
     if (n_blocks == 0) return hipSuccess;
     const dim3 grid(n_blocks), block(kThreads);
-    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_partial_kernel<ZI_BF16>), grid, block, 0, s, a);
-    else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16>), grid, block, 0, s, a);
+#define ZI_LAUNCH_NORM(DT, KEEP) hipLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP>), grid, block, 0, s, a)
+    if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
+    else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
+#undef ZI_LAUNCH_NORM
     return hipGetLastError();
 }
 
