@@ -49,9 +49,9 @@ extern "C" zi_status zi_grad_norm(const zi_tensor* t, int32_t n_tensors, zi_lp_d
                                   void* hip_stream)
 {
     if (zi_status st = check_norm_args(t, n_tensors, (int)dt, loss_scale, d_out, d_workspace, workspace_bytes)) return st;
-    if (zi_status st = check_kernel_visible(d_out, sizeof(zi_norm_result), -1, "d_out")) return st;
-    if (zi_status st = check_kernel_visible(d_workspace, workspace_bytes, -1, "d_workspace")) return st;
     PointerChecker reach;
+    if (zi_status st = reach.check(d_out, sizeof(zi_norm_result), -1, "d_out")) return st;
+    if (zi_status st = reach.check(d_workspace, workspace_bytes, -1, "d_workspace")) return st;
     int64_t total = 0;
     for (int32_t i = 0; i < n_tensors; ++i) {
         if (zi_status st = reach.check(t[i].g, (size_t)t[i].numel * 2, i, "g")) return st;
@@ -110,8 +110,8 @@ extern "C" zi_status zi_grad_norm_noalloc(const zi_tensor* t, int32_t n_tensors,
     if (zi_status st = check_norm_args(t, n_tensors, (int)dt, loss_scale, d_out, partials,
                                        sizeof(zi::NormPartial) * ZI_NOALLOC_MAX_PARTIALS))
         return st;
-    if (zi_status st = check_kernel_visible(d_out, sizeof(zi_norm_result), -1, "d_out")) return st;
     PointerChecker reach;
+    if (zi_status st = reach.check(d_out, sizeof(zi_norm_result), -1, "d_out")) return st;
     int64_t non_empty = 0, total = 0;
     for (int32_t i = 0; i < n_tensors; ++i) {
         if (zi_status st = reach.check(t[i].g, (size_t)t[i].numel * 2, i, "g")) return st;
@@ -152,8 +152,8 @@ extern "C" zi_status zi_adamw_step(const zi_tensor* t, int32_t n_tensors, zi_lp_
     if (zi_status st = check_config(cfg)) return st;
     if (zi_status st = check_step_tensors(t, n_tensors)) return st;
     if (d_norm && !aligned(d_norm, 8)) return fail(ZI_ERR_ALIGNMENT, "d_norm must be 8-byte aligned");
-    if (zi_status st = check_kernel_visible(d_norm, sizeof(zi_norm_result), -1, "d_norm")) return st;
     PointerChecker reach;
+    if (zi_status st = reach.check(d_norm, sizeof(zi_norm_result), -1, "d_norm")) return st;
     for (int32_t i = 0; i < n_tensors; ++i) {
         const size_t n = (size_t)t[i].numel;
         if (zi_status st = reach.check(t[i].p, n * 4, i, "p")) return st;

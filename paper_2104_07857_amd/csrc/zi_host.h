@@ -58,25 +58,29 @@ struct PointerChecker {
         const uintptr_t lo = reinterpret_cast<uintptr_t>(p), hi = lo + bytes;
         for (int i = 0; i < n_known; ++i)
             if (lo >= known[i].lo && hi <= known[i].hi) return ZI_OK;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        bool inside = false;
+        if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess && size > 0) {
+            const uintptr_t blo = reinterpret_cast<uintptr_t>(base);
+            inside = lo >= blo && hi <= blo + size;
+        } else {
+            (void)hipGetLastError();
+        }
+        // one allocation is one kind of memory: its first byte speaks for all of it
         const void* ends[2] = {p, static_cast<const char*>(p) + bytes - 1};
-        for (const void* e : ends) {
-            const int k = memory_kind(e);
+        for (int i = 0; i < (inside ? 1 : 2); ++i) {
+            const int k = memory_kind(ends[i]);
             if (k == -2) return fail(ZI_ERR_HIP, "no usable HIP device (pointer query failed)");
             if (k != 0 && k != 1)
                 return fail(ZI_ERR_INVALID_ARG, "tensor %d: %s (%zu bytes) is not device or page-locked host memory",
                             tensor, name, bytes);
         }
-        hipDeviceptr_t base = nullptr;
-        size_t size = 0;
-        if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess && size > 0) {
+        if (inside) {
             const uintptr_t blo = reinterpret_cast<uintptr_t>(base);
-            if (lo >= blo && hi <= blo + size) {
-                known[next] = {blo, blo + size};
-                next = (next + 1) % 8;
-                if (n_known < 8) ++n_known;
-            }
-        } else {
-            (void)hipGetLastError();
+            known[next] = {blo, blo + size};
+            next = (next + 1) % 8;
+            if (n_known < 8) ++n_known;
         }
         return ZI_OK;
     }
@@ -125,6 +129,15 @@ inline int choose_head(const void* p, const void* m, const void* v, const void* 
 #define ZI_SOLO_TILES 8192
 #endif
 constexpr int64_t kSoloTiles = ZI_SOLO_TILES;
+
+// Whether a launch that need not wait for the one in front of it may say so: not while the stream is captured.
+inline hipError_t may_overlap(hipStream_t stream, bool& yes)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(stream, &capture);
+    yes = e == hipSuccess && capture == hipStreamCaptureStatusNone;
+    return e;
+}
 
 // Issues the fused step over a list of device-resident segments.
 struct StepIssuer {
@@ -183,13 +196,9 @@ struct StepIssuer {
     hipError_t issue_held(bool last)
     {
         if (held_tiles == 0) return hipSuccess;
-        bool any_order = !last && launches > 0;
-        if (any_order) {
-            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-            const hipError_t e = hipStreamIsCapturing(stream, &capture);
-            if (e != hipSuccess) return e;
-            any_order = capture == hipStreamCaptureStatusNone;
-        }
+        bool any_order = false;
+        if (!last && launches > 0)
+            if (const hipError_t e = may_overlap(stream, any_order); e != hipSuccess) return e;
         ++launches;
         const uint32_t n = held_tiles;
         held_tiles = 0;
@@ -404,7 +413,11 @@ struct NormIssuer {
         const uint32_t blocks = a.n_tiles < groups ? a.n_tiles : groups;
         if (used + blocks > zi::kMaxPartials && (e = flush_partials()) != hipSuccess) return e;
         a.partials = partials + used;
-        e = zi::launch_norm_partials(a, blocks, dt, keep, s);
+        // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
+        // final sum are ordinary launches (the same order as in StepIssuer).
+        bool any_order = false;
+        if (used > 0 && (e = may_overlap(s, any_order)) != hipSuccess) return e;
+        e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
         ++launches;
         used += blocks;
         a.n_desc = a.n_tiles = 0;

@@ -167,7 +167,7 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
-hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, hipStream_t s);
+hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
 hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);

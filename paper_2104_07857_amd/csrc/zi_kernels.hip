@@ -780,11 +780,13 @@ hipError_t launch_norm_refresh(zi_norm_result* d_result, float loss_scale, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, hipStream_t s)
+hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s)
 {
     if (n_blocks == 0) return hipSuccess;
     const dim3 grid(n_blocks), block(kThreads);
-#define ZI_LAUNCH_NORM(DT, KEEP) hipLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP>), grid, block, 0, s, a)
+    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
+#define ZI_LAUNCH_NORM(DT, KEEP) \
+    hipExtLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP>), grid, block, 0, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
     else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
 #undef ZI_LAUNCH_NORM
