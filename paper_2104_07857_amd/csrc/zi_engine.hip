@@ -43,11 +43,12 @@ void ring_release(zi_engine* e)
     e->pool_in = e->pool_out = nullptr;
     for (int i = 0; i < kMaxHostSlots; ++i) {
         if (e->ev_back[i]) (void)hipEventDestroy(e->ev_back[i]);
-        if (e->ev_fill[i]) (void)hipEventDestroy(e->ev_fill[i]);
-        e->ev_back[i] = e->ev_fill[i] = nullptr;
+        e->ev_back[i] = nullptr;
     }
     if (e->hring) (void)hipHostFree(e->hring);
     e->hring = nullptr;
+    if (e->fill_flags) (void)hipHostFree(e->fill_flags);
+    e->fill_flags = nullptr;
     e->n_hslots = 0;
 }
 
@@ -196,9 +197,19 @@ extern "C" zi_status zi_engine_set_option(zi_engine* e, int32_t option, int64_t 
             return fail(he == hipErrorOutOfMemory ? ZI_ERR_NOMEM : ZI_ERR_HIP, "pinned ring of %lld slots: %s",
                         (long long)value, hipGetErrorString(he));
         }
+        // a slot's blocks: the whole ones of a chunk, and a last one for each segment that shares the slot
+        e->flags_per_slot = (size_t)(e->chunk_elems / zi::kCopyBlockElems) + kPlanMaxSegmentsPerUse + 1;
+        he = hipHostMalloc((void**)&e->fill_flags, (size_t)value * e->flags_per_slot * sizeof(uint32_t), hipHostMallocDefault);
+        if (he != hipSuccess) {
+            e->fill_flags = nullptr;
+            (void)hipGetLastError();
+            ring_release(e);
+            return fail(he == hipErrorOutOfMemory ? ZI_ERR_NOMEM : ZI_ERR_HIP, "flags of the pinned ring: %s", hipGetErrorString(he));
+        }
+        memset(e->fill_flags, 0, (size_t)value * e->flags_per_slot * sizeof(uint32_t));
+        e->fill_serial = 0;
         for (int i = 0; i < (int)value; ++i) {
             he = hipEventCreateWithFlags(&e->ev_back[i], hipEventDisableTiming);
-            if (he == hipSuccess) he = hipEventCreateWithFlags(&e->ev_fill[i], hipEventDisableTiming);
             if (he != hipSuccess) {
                 (void)hipGetLastError();
                 ring_release(e);

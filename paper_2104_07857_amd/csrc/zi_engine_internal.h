@@ -103,7 +103,9 @@ struct zi_engine {
     int n_hslots = 0;
     char* hring = nullptr;
     hipEvent_t ev_back[zi::host::kMaxHostSlots] = {};   // the slot's outbound traffic has left / its inbound copy is done
-    hipEvent_t ev_fill[zi::host::kMaxHostSlots] = {};   // the slot's device-to-host fill has landed
+    uint32_t* fill_flags = nullptr;    // page-locked: per ring slot and block of the host-CPU step, see link_copy_kernel
+    size_t flags_per_slot = 0;
+    uint32_t fill_serial = 0;          // of the last fill; a block's flag equals its fill's serial once it has landed
     int copy_threads = 6;
     zi::host::TaskPool* pool_in = nullptr;
     zi::host::TaskPool* pool_out = nullptr;
@@ -125,6 +127,7 @@ struct zi_engine {
     std::vector<size_t> use_begin;
     std::vector<zi::host::Piece> pieces_in, pieces_out;
     std::vector<int32_t> host_idx;
+    std::vector<uint32_t> cpu_done;    // per block of the host-CPU step: stepped in this use
 
     // options and figures
     int64_t skip_kernel = 0;

@@ -306,6 +306,35 @@ struct StepIssuer {
     }
 };
 
+// Issues copies of 2-byte segments between device and page-locked host memory (link_copy_kernel).
+struct CopyIssuer {
+    zi::CopyArgs args{};
+    hipStream_t stream;
+
+    CopyIssuer(hipStream_t s, uint32_t* flags, uint32_t serial) : stream(s)
+    {
+        args.flags = flags;
+        args.serial = serial;
+    }
+    hipError_t flush()
+    {
+        if (args.n_segs == 0) return hipSuccess;
+        const hipError_t e = zi::launch_link_copy(args, stream);
+        args.n_segs = args.n_blocks = 0;
+        return e;
+    }
+    // `flag`: index of the first block's flag (unused without flags).
+    hipError_t add(const uint16_t* src, uint16_t* dst, int64_t elems, uint32_t flag)
+    {
+        if (elems <= 0) return hipSuccess;
+        if (args.n_segs == (uint32_t)zi::kMaxCopySegs)
+            if (const hipError_t e = flush(); e != hipSuccess) return e;
+        args.t[args.n_segs++] = {src, dst, elems, args.n_blocks, flag};
+        args.n_blocks += (uint32_t)((elems + zi::kCopyBlockElems - 1) / zi::kCopyBlockElems);
+        return hipSuccess;
+    }
+};
+
 // Issues the step over segments in page-locked host memory (adamw_link_kernel).  Long segments are cut
 // where a launch is full, a multiple of 512 elements into the segment's body.
 struct LinkIssuer {

@@ -145,6 +145,27 @@ struct LinkArgs {
 };
 static_assert(sizeof(LinkArgs) < 4096, "kernel arguments");
 
+// Copies of 2-byte arrays between device and page-locked host memory by a kernel (link_copy_kernel): many segments in
+// one launch, in blocks of 2^14 elements, each of which can report to the host when it has arrived.
+constexpr int64_t kCopyBlockElems = (int64_t)1 << 14;
+constexpr int kMaxCopySegs = 32;
+constexpr int kCopyGroups = 96;
+
+struct CopySeg {
+    const uint16_t* src;
+    uint16_t* dst;
+    int64_t elems;
+    uint32_t first_tile;   // index of the segment's first block within the launch
+    uint32_t flag;         // index of its first block's flag
+};
+
+struct CopyArgs {
+    CopySeg t[kMaxCopySegs];
+    uint32_t n_segs, n_blocks;
+    uint32_t* flags;       // page-locked, null: the blocks do not report
+    uint32_t serial;       // what a block's flag becomes once the block is at its destination
+};
+
 struct NormDesc {
     const uint16_t* g;
     uint32_t numel;
@@ -165,6 +186,7 @@ static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 // any_order: may run beside the launches in front of it on the stream (see StepIssuer for where that is safe).
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
+hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);

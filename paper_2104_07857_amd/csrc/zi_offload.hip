@@ -7,6 +7,7 @@
 // See include/zi.h for the contract of every call.
 #include <hip/hip_runtime.h>
 
+#include <cerrno>
 #include <chrono>
 #include <cstring>
 
@@ -71,28 +72,82 @@ struct CpuBlock {
     const uint16_t* g;
     uint16_t* lp;
     int64_t n;
+    const uint32_t* arrived;      // flag of the block's gradients (null: they are in host memory already)
+    uint16_t* lp_device;          // where the block of the copy goes (null: it is in its place)
 };
 
+// Tasks are blocks of link_copy_kernel: 64 KiB of each fp32 array.  A chunk of 2^24 elements is 1024
+// tasks, so the barrier at the end of every chunk finds the threads within one short task of each
+// other (2^18-element tasks measured 4% slower, 2^16 2% slower).
+constexpr int64_t kCpuBlockElems = zi::kCopyBlockElems;
+// Stepped blocks whose copy the calling thread sends up together while the others go on: 2 MiB.
+constexpr size_t kUploadBlocks = 64;
+
+// One slot use.  A thread steps a block as soon as the block's gradients have arrived, and the calling thread,
+// which works on blocks like the others, sends up what is finished from the front between two of its own: within a
+// use the fetch, the step and the upload of different blocks overlap, so a state of one chunk does not wait
+// for its whole fetch nor expose its whole upload.
 struct CpuJob {
+    zi_engine* e;
     const CpuBlock* blocks;
+    size_t n_blocks;
+    uint32_t serial;
     zi::StepConsts c;
     float gscale;
     int dt;
     bool l2;
+    uint32_t* done;               // per block
+    size_t sent = 0;              // blocks whose copy is on its way (or in its place)
+    hipError_t upload_error = hipSuccess;
+
+    // Sends up the copies of blocks [sent, to), neighbours of one segment as one.
+    void upload(size_t to)
+    {
+        CopyIssuer up(e->s_h2d, nullptr, 0);
+        while (sent < to && upload_error == hipSuccess) {
+            const CpuBlock& b = blocks[sent];
+            int64_t n = b.n;
+            size_t next = sent + 1;
+            if (b.lp_device)
+                while (next < to && blocks[next].lp_device == b.lp_device + n && blocks[next].lp == b.lp + n) n += blocks[next++].n;
+            if (b.lp_device) {
+                upload_error = up.add(b.lp, b.lp_device, n, 0);
+                e->stats.bytes_h2d += (uint64_t)n * 2;
+            }
+            sent = next;
+        }
+        if (upload_error == hipSuccess) upload_error = up.flush();
+    }
 };
 
-int run_cpu_block(void* ctx, size_t index, int)
+// Waits until a block's gradients are in the ring.  The kernel that brings them ends whatever happens; if its
+// stream reports an error, or is done without having raised the flag, the wait ends with an error.
+bool wait_arrived(const CpuJob& job, const uint32_t* flag)
 {
-    const CpuJob& job = *static_cast<const CpuJob*>(ctx);
-    const CpuBlock& b = job.blocks[index];
-    host_step_range(job.c, job.gscale, job.dt, job.l2, b.p, b.m, b.v, b.g, b.lp, 0, b.n);
-    return 0;
+    for (uint64_t spins = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != job.serial; ++spins) {
+        __builtin_ia32_pause();
+        if (spins % (1u << 16)) continue;
+        const hipError_t e = hipStreamQuery(job.e->s_d2h);
+        if (e == hipErrorNotReady) continue;
+        return e == hipSuccess && __atomic_load_n(flag, __ATOMIC_ACQUIRE) == job.serial;
+    }
+    return true;
 }
 
-// Elements per task of the thread pool: 64 KiB of each fp32 array.  A chunk of 2^24 elements is 1024
-// tasks, so the barrier at the end of every chunk finds the threads within one short task of each
-// other (2^18-element tasks measured 4% slower, 2^16 2% slower).
-constexpr int64_t kCpuBlockElems = (int64_t)1 << 14;
+int run_cpu_block(void* ctx, size_t index, int who)
+{
+    CpuJob& job = *static_cast<CpuJob*>(ctx);
+    const CpuBlock& b = job.blocks[index];
+    if (b.arrived && !wait_arrived(job, b.arrived)) return EIO;
+    host_step_range(job.c, job.gscale, job.dt, job.l2, b.p, b.m, b.v, b.g, b.lp, 0, b.n);
+    __atomic_store_n(&job.done[index], 1u, __ATOMIC_RELEASE);
+    if (who == 0) {
+        size_t front = job.sent;
+        while (front < job.n_blocks && __atomic_load_n(&job.done[front], __ATOMIC_ACQUIRE)) ++front;
+        if (front >= job.sent + kUploadBlocks) job.upload(front);
+    }
+    return 0;
+}
 
 }  // namespace
 
@@ -186,43 +241,51 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     }
 
     const auto t0 = std::chrono::steady_clock::now();
-    // Ring slot u mod n_h carries slot use u: its gradient half is filled by a device-to-host copy,
-    // the CPUs step the use (reading that half, writing the copy half), a host-to-device copy ships
-    // the copy half.  Fetches run `ahead` uses in front of the CPUs; a slot is fetched into again
+    // Ring slot u mod n_h carries slot use u: its gradient half is filled by a kernel that reports every block
+    // (link_copy_kernel), the CPUs step the use (reading that half, writing the copy half), and the copy half is
+    // sent up by the same kind of kernel.  Fetches run `ahead` uses in front of the CPUs; a slot is fetched into again
     // only after the upload of its previous use has left it, which by then is two steps old.
     const int ahead = n_h >= 3 ? n_h - 2 : 1;
+    const uint32_t first_serial = e->fill_serial + 1;         // of use 0; use u has first_serial + u
+    e->fill_serial += (uint32_t)n_uses;
+    auto blocks_of = [](int64_t count) { return (count + kCpuBlockElems - 1) / kCpuBlockElems; };
     auto fetch = [&](int64_t u) -> zi_status {
         const int h = n_h > 0 ? (int)(u % n_h) : 0;
+        CopyIssuer in(e->s_d2h, n_h > 0 ? e->fill_flags + (size_t)h * e->flags_per_slot : nullptr, first_serial + (uint32_t)u);
         bool any = false;
+        uint32_t flag = 0;
         for (size_t j = use_begin[(size_t)u]; j < use_begin[(size_t)u + 1]; ++j) {
             const Segment& sg = segs[j];
             const StateSrc& S = e->src[(size_t)sg.tensor];
-            if (S.g_host) continue;
-            if (!any && u >= n_h) ZI_HIP(hipEventSynchronize(e->ev_back[h]));
-            any = true;
-            ZI_HIP(hipMemcpyAsync(e->hslot_g(h) + sg.slot_offset, (const uint16_t*)S.g + sg.elem_offset,
-                                  (size_t)sg.count * 2, hipMemcpyDeviceToHost, e->s_d2h));
-            e->stats.bytes_d2h += (size_t)sg.count * 2;
-            e->stats.n_copies += 1;
+            if (!S.g_host) {
+                if (!any && u >= n_h) ZI_HIP(hipEventSynchronize(e->ev_back[h]));
+                any = true;
+                ZI_HIP(in.add((const uint16_t*)S.g + sg.elem_offset, e->hslot_g(h) + sg.slot_offset, sg.count, flag));
+                e->stats.bytes_d2h += (size_t)sg.count * 2;
+            }
+            flag += (uint32_t)blocks_of(sg.count);
         }
-        if (any) ZI_HIP(hipEventRecord(e->ev_fill[h], e->s_d2h));
+        ZI_HIP(in.flush());
         return ZI_OK;
     };
     auto pipeline = [&]() -> zi_status {
         std::vector<CpuBlock> blocks;
         for (int64_t u = 0; u < n_uses && u < ahead; ++u)
             if (zi_status st = fetch(u)) return st;
+        ZI_HIP(hipEventSynchronize(e->ev_in));      // one thread waits for the gradients' producer, not all of them
         for (int64_t u = 0; u < n_uses; ++u) {
             if (u + ahead < n_uses)
                 if (zi_status st = fetch(u + ahead)) return st;
             const int h = n_h > 0 ? (int)(u % n_h) : 0;
+            const uint32_t* flags = n_h > 0 ? e->fill_flags + (size_t)h * e->flags_per_slot : nullptr;
             blocks.clear();
             bool fetched = false, upload = false;
             for (size_t j = use_begin[(size_t)u]; j < use_begin[(size_t)u + 1]; ++j) {
                 const Segment& sg = segs[j];
                 const StateSrc& S = e->src[(size_t)sg.tensor];
+                const bool up = S.p_lp && !S.lp_host;
                 fetched = fetched || !S.g_host;
-                upload = upload || (S.p_lp && !S.lp_host);
+                upload = upload || up;
                 const uint16_t* g = S.g_host ? (const uint16_t*)S.g + sg.elem_offset : e->hslot_g(h) + sg.slot_offset;
                 uint16_t* lp = !S.p_lp ? nullptr
                                : S.lp_host ? (uint16_t*)S.p_lp + sg.elem_offset : e->hslot_lp(h) + sg.slot_offset;
@@ -230,24 +293,20 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
                     const int64_t nb = sg.count - o < kCpuBlockElems ? sg.count - o : kCpuBlockElems;
                     const int64_t at = sg.elem_offset + o;
                     blocks.push_back({(float*)S.ptr[0] + at, (float*)S.ptr[1] + at, (float*)S.ptr[2] + at, g + o,
-                                      lp ? lp + o : nullptr, nb});
+                                      lp ? lp + o : nullptr, nb, S.g_host ? nullptr : flags + blocks.size(),
+                                      up ? (uint16_t*)S.p_lp + at : nullptr});
                 }
             }
             // A ring slot whose upload of `n_h` uses ago is still leaving must not be written yet
             // (uses with host-resident gradients skip the fetch that would have waited for it).
             if (upload && !fetched && u >= n_h) ZI_HIP(hipEventSynchronize(e->ev_back[h]));
-            if (fetched) ZI_HIP(hipEventSynchronize(e->ev_fill[h]));
-            CpuJob job{blocks.data(), k, gscale, (int)dt, cfg->mode == ZI_MODE_ADAM_L2};
-            (void)e->pool_step->run(blocks.size(), run_cpu_block, &job);
-            for (size_t j = use_begin[(size_t)u]; j < use_begin[(size_t)u + 1]; ++j) {
-                const Segment& sg = segs[j];
-                const StateSrc& S = e->src[(size_t)sg.tensor];
-                if (!S.p_lp || S.lp_host) continue;
-                ZI_HIP(hipMemcpyAsync((uint16_t*)S.p_lp + sg.elem_offset, e->hslot_lp(h) + sg.slot_offset,
-                                      (size_t)sg.count * 2, hipMemcpyHostToDevice, e->s_h2d));
-                e->stats.bytes_h2d += (size_t)sg.count * 2;
-                e->stats.n_copies += 1;
-            }
+            e->cpu_done.assign(blocks.size(), 0);
+            CpuJob job{e, blocks.data(), blocks.size(), first_serial + (uint32_t)u, k, gscale, (int)dt,
+                       cfg->mode == ZI_MODE_ADAM_L2, e->cpu_done.data()};
+            if (e->pool_step->run(blocks.size(), run_cpu_block, &job) != 0)
+                return fail(ZI_ERR_HIP, "gradients did not arrive in the pinned ring");
+            job.upload(blocks.size());
+            ZI_HIP(job.upload_error);
             if (upload || fetched) ZI_HIP(hipEventRecord(e->ev_back[h], e->s_h2d));
             ++e->stats.n_slot_uses;
         }

@@ -149,3 +149,41 @@ def test_norm_of_device_and_page_locked_gradients(sizes, offset):
                     assert abs(norm - np.sqrt(want) / 2.0) <= 1e-12 * norm
     finally:
         zi.zi_engine_destroy(eng)
+
+
+BLOCK = 16384                         # elements of one block of the copies of the CPU placement
+
+
+@pytest.mark.parametrize("offset", [0, 1, 6])
+@pytest.mark.parametrize("sizes", [[1], [7, 8, 9], [BLOCK - 1], [BLOCK], [BLOCK + 1], [64 * BLOCK + 3], [5] * 33 + [BLOCK + 5] + [1] * 33,
+                                   [3 * 65536 + 11, 200, 2 * 65536]])
+def test_cpu_placement_at_block_edges(sizes, offset):
+    """Gradients and copy at odd places in HBM, state in host memory: tensors of less than a vector to several slot uses,
+    more segments than a use packs; the same bits as the step that goes over the link, twice in a row on one engine."""
+    dt = zi.ZI_BF16
+    host = [gen_numpy(zi_synth.StateSpec(500 + len(sizes), dt), n, tensor=i) for i, n in enumerate(sizes)]
+    cfg = zi_cfg(zi_synth.workload("c4"))
+    results = []
+    eng = zi.zi_engine_create(0, 256 * 1024, 3)              # 65,536-element chunks: four blocks to a use
+    try:
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_HOST_RING_SLOTS, 3)
+        for cpu in (True, False):
+            bufs, tl = [], []
+            for i, (p, m, v, g) in enumerate(host):
+                b = [_placed(p, 0, True), _placed(m, 0, True), _placed(v, 0, True), _placed(g, offset, False),
+                     _placed(np.zeros(p.size, np.uint16), offset, False) if i % 3 != 2 else None]
+                bufs.append(b)
+                tl.append((b[0][:p.size], b[1][:p.size], b[2][:p.size], b[3][offset:offset + p.size],
+                           None if b[4] is None else b[4][offset:offset + p.size], p.size))
+            for _ in range(2):
+                if cpu:
+                    assert zi.zi_adamw_step_cpu(eng, tl, dt, cfg, None, 3) == zi.ZI_OK
+                    st = zi.zi_engine_last_stats(eng)
+                    assert st.bytes_d2h == 2 * sum(sizes)
+                    assert st.bytes_h2d == 2 * sum(n for i, n in enumerate(sizes) if i % 3 != 2)
+                else:
+                    assert zi.zi_adamw_step_streamed(eng, tl, dt, cfg) == zi.ZI_OK
+            results.append([[None if x is None else to_np(x) for x in b] for b in bufs])
+    finally:
+        zi.zi_engine_destroy(eng)
+    _same(*results)
