@@ -342,7 +342,9 @@ struct CopyIssuer {
 // Issues the step over segments in page-locked host memory (adamw_link_kernel).  Long segments are cut
 // where a launch is full, a multiple of 512 elements into the segment's body.
 struct LinkIssuer {
-    zi::LinkArgs args{};
+    zi::LinkArgs args[2];          // the launch being assembled and the one held back
+    int now = 0;
+    bool held = false;
     int dt;
     bool l2;
     hipStream_t stream;
@@ -351,32 +353,57 @@ struct LinkIssuer {
     LinkIssuer(const zi::StepConsts& c, const zi_norm_result* d_norm, uint32_t* h_flag, int dt_, bool l2_, hipStream_t s)
         : dt(dt_), l2(l2_), stream(s)
     {
-        args.c = c;
-        args.d_norm = d_norm;
-        args.h_flag = d_norm ? h_flag : nullptr;
+        for (zi::LinkArgs& a : args) {
+            a.n_desc = 0;
+            a.n_tiles = 0;
+            a.c = c;
+            a.d_norm = d_norm;
+            a.h_flag = d_norm ? h_flag : nullptr;
+        }
     }
 
-    hipError_t flush()
+    // As in StepIssuer, launches are held back by one and those between the first and the last may overlap: the
+    // link stays busy while one launch's last tiles return and the next one's first requests are on their way.
+    hipError_t issue_held(bool last)
     {
-        if (args.n_desc == 0) return hipSuccess;
+        if (!held) return hipSuccess;
+        bool any_order = false;
+        if (!last && launches > 0)
+            if (const hipError_t e = may_overlap(stream, any_order); e != hipSuccess) return e;
         ++launches;
-        const hipError_t e = zi::launch_step_link(args, dt, l2, stream);
-        args.n_desc = 0;
-        args.n_tiles = 0;
+        held = false;
+        return zi::launch_step_link(args[now ^ 1], dt, l2, any_order, stream);
+    }
+
+    hipError_t close()       // the launch being assembled is complete
+    {
+        if (args[now].n_desc == 0) return hipSuccess;
+        const hipError_t e = issue_held(false);
+        now ^= 1;
+        held = true;
+        args[now].n_desc = 0;
+        args[now].n_tiles = 0;
         return e;
+    }
+
+    hipError_t flush()       // end of the call
+    {
+        const hipError_t e = close();
+        return e != hipSuccess ? e : issue_held(true);
     }
 
     hipError_t add(float* p, float* m, float* v, const uint16_t* g, uint16_t* p_lp, int64_t numel)
     {
         while (numel > 0) {
-            if (args.n_desc == zi::kMaxLinkDesc || args.n_tiles >= zi::kLinkTilesPerLaunch) {
-                const hipError_t e = flush();
+            if (args[now].n_desc == zi::kMaxLinkDesc || args[now].n_tiles >= zi::kLinkTilesPerLaunch) {
+                const hipError_t e = close();
                 if (e != hipSuccess) return e;
             }
+            zi::LinkArgs& a = args[now];
             const int h = choose_head(p, m, v, g, p_lp);
             zi::StepDesc d{};
             d.head = (int32_t)(h < numel ? h : numel);
-            const int64_t room = (int64_t)(zi::kLinkTilesPerLaunch - args.n_tiles) * zi::kStepTileElems;
+            const int64_t room = (int64_t)(zi::kLinkTilesPerLaunch - a.n_tiles) * zi::kStepTileElems;
             const int64_t n = numel - d.head <= room ? numel : d.head + room;
             d.p_body = p + d.head; d.m_body = m + d.head; d.v_body = v + d.head; d.g_body = g + d.head;
             d.lp_body = p_lp ? p_lp + d.head : nullptr;
@@ -384,9 +411,9 @@ struct LinkIssuer {
             d.nquad = (n - d.head) / zi::kQuad;
             const int64_t nt = (d.nquad + zi::kStepTileQuads - 1) / zi::kStepTileQuads;
             d.n_tiles = nt < 1 ? 1u : (uint32_t)nt;
-            d.first_tile = args.n_tiles;
-            args.t[args.n_desc++] = d;
-            args.n_tiles += d.n_tiles;
+            d.first_tile = a.n_tiles;
+            a.t[a.n_desc++] = d;
+            a.n_tiles += d.n_tiles;
             p += n; m += n; v += n; g += n;
             if (p_lp) p_lp += n;
             numel -= n;

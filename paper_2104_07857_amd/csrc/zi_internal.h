@@ -187,7 +187,7 @@ static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
-hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s);
+hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
 hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s);

@@ -618,17 +618,15 @@ hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, hipStream_t s)
+hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (a.n_tiles == 0) return hipSuccess;
     const dim3 grid(a.n_tiles < (uint32_t)kLinkGroups ? a.n_tiles : (uint32_t)kLinkGroups), block(kStepThreads);
-    if (dt == ZI_BF16) {
-        if (l2) hipLaunchKernelGGL((adamw_link_kernel<ZI_BF16, true>), grid, block, 0, s, a);
-        else    hipLaunchKernelGGL((adamw_link_kernel<ZI_BF16, false>), grid, block, 0, s, a);
-    } else {
-        if (l2) hipLaunchKernelGGL((adamw_link_kernel<ZI_FP16, true>), grid, block, 0, s, a);
-        else    hipLaunchKernelGGL((adamw_link_kernel<ZI_FP16, false>), grid, block, 0, s, a);
-    }
+    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
+#define ZI_LAUNCH_LINK(DT, L2) hipExtLaunchKernelGGL((adamw_link_kernel<DT, L2>), grid, block, 0, s, nullptr, nullptr, flags, a)
+    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LINK(ZI_BF16, true); else ZI_LAUNCH_LINK(ZI_BF16, false); }
+    else               { if (l2) ZI_LAUNCH_LINK(ZI_FP16, true); else ZI_LAUNCH_LINK(ZI_FP16, false); }
+#undef ZI_LAUNCH_LINK
     return hipGetLastError();
 }
 
