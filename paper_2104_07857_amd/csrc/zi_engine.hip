@@ -489,7 +489,7 @@ zi_status run_streamed(zi_engine* e, bool staged, zi_lp_dtype dt, const zi_adamw
     ZI_HIP(hipStreamWaitEvent(e->s_h2d, e->ev_in, 0));
     ZI_HIP(hipStreamWaitEvent(e->s_k, e->ev_in, 0));
     ZI_HIP(order_after_offloads(e, e->s_h2d));
-    if (staged && e->offload_pending) ZI_HIP(hipEventSynchronize(e->ev_offload_done));   // CPU threads read host memory
+    if (staged) ZI_HIP(wait_for_offloads(e));   // CPU threads read host memory
 
     const zi::StepConsts k = make_consts(*cfg);
     const bool l2 = cfg->mode == ZI_MODE_ADAM_L2;
@@ -891,7 +891,7 @@ extern "C" zi_status zi_grad_norm_streamed(zi_engine* e, const zi_tensor* t, int
     ZI_HIP(hipStreamWaitEvent(e->s_h2d, e->ev_in, 0));
     ZI_HIP(hipStreamWaitEvent(e->s_k, e->ev_in, 0));
     ZI_HIP(order_after_offloads(e, e->s_h2d));
-    if (pageable && e->offload_pending) ZI_HIP(hipEventSynchronize(e->ev_offload_done));
+    if (pageable) ZI_HIP(wait_for_offloads(e));
 
     const int n_h = e->n_hslots;
     NormRun run;

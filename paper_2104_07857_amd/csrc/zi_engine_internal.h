@@ -115,7 +115,7 @@ struct zi_engine {
 
     // Gradient offload: copies in flight on the device-to-host stream, ordered after their producers.
     hipEvent_t ev_offload[zi::host::kOffloadEvents] = {};
-    hipEvent_t ev_offload_done = nullptr;               // recorded after the last offload copy issued
+    hipEvent_t ev_offload_done = nullptr;               // recorded behind the offloads when somebody waits for them
     uint64_t n_offloads = 0;
     bool offload_pending = false;
 
@@ -184,10 +184,19 @@ inline void index_uses(const std::vector<Segment>& segs, int64_t n_uses, std::ve
 
 // Work already enqueued on the device-to-host stream by zi_grad_offload happens before anything a
 // streamed call reads from host memory: its copy-in stream waits for the last offload.
+// (The event behind the offloads is recorded when somebody waits for them, not with each of them.)
+inline hipError_t mark_offloads(zi_engine* e) { return hipEventRecord(e->ev_offload_done, e->s_d2h); }
 inline hipError_t order_after_offloads(zi_engine* e, hipStream_t consumer)
 {
     if (!e->offload_pending) return hipSuccess;
-    return hipStreamWaitEvent(consumer, e->ev_offload_done, 0);
+    const hipError_t he = mark_offloads(e);
+    return he != hipSuccess ? he : hipStreamWaitEvent(consumer, e->ev_offload_done, 0);
+}
+inline hipError_t wait_for_offloads(zi_engine* e)       // blocks the host
+{
+    if (!e->offload_pending) return hipSuccess;
+    const hipError_t he = mark_offloads(e);
+    return he != hipSuccess ? he : hipEventSynchronize(e->ev_offload_done);
 }
 
 // Maps a C++ exception that reached an entry point to a status (nothing may cross the C ABI).

@@ -334,7 +334,8 @@ struct CopyIssuer {
         if (args.n_segs == (uint32_t)zi::kMaxCopySegs)
             if (const hipError_t e = flush(); e != hipSuccess) return e;
         args.t[args.n_segs++] = {src, dst, elems, args.n_blocks, flag};
-        args.n_blocks += (uint32_t)((elems + zi::kCopyBlockElems - 1) / zi::kCopyBlockElems);
+        const int64_t block = args.flags ? zi::kCopyBlockElems : zi::kCopyPieceElems;
+        args.n_blocks += (uint32_t)((elems + block - 1) / block);
         return hipSuccess;
     }
 };

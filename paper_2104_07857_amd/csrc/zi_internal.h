@@ -146,8 +146,10 @@ struct LinkArgs {
 static_assert(sizeof(LinkArgs) < 4096, "kernel arguments");
 
 // Copies of 2-byte arrays between device and page-locked host memory by a kernel (link_copy_kernel): many segments in
-// one launch, in blocks of 2^14 elements, each of which can report to the host when it has arrived.
+// one launch, in blocks of 2^14 elements that report to the host when they have arrived, or in pieces of 2^12 (one
+// round of loads for a wavefront) where nobody waits for a part.
 constexpr int64_t kCopyBlockElems = (int64_t)1 << 14;
+constexpr int64_t kCopyPieceElems = (int64_t)1 << 12;
 constexpr int kMaxCopySegs = 32;
 constexpr int kCopyGroups = 96;
 

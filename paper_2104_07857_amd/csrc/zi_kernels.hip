@@ -569,22 +569,24 @@ typedef u32x4 u32x4_mem __attribute__((aligned(2)));
 typedef ZI_GLOBAL u32x4_mem* GlobalU4;
 typedef const ZI_GLOBAL u32x4_mem* GlobalConstU4;
 
-// Bound: the host link, one direction.  A wavefront copies a block of 2^14 elements, eight 16-byte vectors per lane
-// in flight; either side may start at any element.  With flags, the block's flag is written after its data is
+// Bound: the host link, one direction.  A wavefront copies a block at a time, eight 16-byte vectors per lane
+// in flight; either side may start at any element.  REPORT: the block's flag is written after its data is
 // visible to the host: CPU threads that wait for a block start as soon as it is there, and no call into the runtime is
 // made per block, segment or chunk.  (One copy per segment costs 2.5 us of host time and 8 us of the link's for short
 // ones: 64 KiB 10.2 us, against 3.0 for a launch of this kernel; 1 MiB 27.6 against 20.2; 32 MiB 599 against 608.)
+template <bool REPORT>
 __global__ __launch_bounds__(64) void link_copy_kernel(const CopyArgs a)
 {
     constexpr int kUnroll = 8;
-    constexpr uint32_t kVecs = kCopyBlockElems / 8;
+    constexpr int64_t kElems = REPORT ? kCopyBlockElems : kCopyPieceElems;
+    constexpr uint32_t kVecs = kElems / 8;
     uint32_t d = 0;
     for (uint32_t b = blockIdx.x; b < a.n_blocks; b += gridDim.x) {
         d = find_desc(a.t, d, a.n_segs, b);
         const CopySeg& T = a.t[d];
         const uint32_t k = b - T.first_tile;
-        const int64_t at = (int64_t)k * kCopyBlockElems;
-        const uint32_t n = (uint32_t)(T.elems - at < kCopyBlockElems ? T.elems - at : kCopyBlockElems);
+        const int64_t at = (int64_t)k * kElems;
+        const uint32_t n = (uint32_t)(T.elems - at < kElems ? T.elems - at : kElems);
         const uint32_t nvec = n / 8;
         GlobalConstU4 src = (GlobalConstU4)(uintptr_t)(T.src + at);
         GlobalU4 dst = (GlobalU4)(uintptr_t)(T.dst + at);
@@ -601,7 +603,7 @@ __global__ __launch_bounds__(64) void link_copy_kernel(const CopyArgs a)
         }
         const uint32_t rest = nvec * 8 + threadIdx.x;
         if (rest < n) T.dst[at + rest] = T.src[at + rest];
-        if (a.flags) {
+        if constexpr (REPORT) {
             __threadfence_system();               // every lane's part of the block is at the host ...
             __syncthreads();
             if (threadIdx.x == 0)                 // ... before the flag is
@@ -614,7 +616,8 @@ hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s)
 {
     if (a.n_blocks == 0) return hipSuccess;
     const dim3 grid(a.n_blocks < (uint32_t)kCopyGroups ? a.n_blocks : (uint32_t)kCopyGroups), block(64);
-    hipLaunchKernelGGL(link_copy_kernel, grid, block, 0, s, a);
+    if (a.flags) hipLaunchKernelGGL(link_copy_kernel<true>, grid, block, 0, s, a);
+    else         hipLaunchKernelGGL(link_copy_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -187,3 +187,27 @@ def test_cpu_placement_at_block_edges(sizes, offset):
     finally:
         zi.zi_engine_destroy(eng)
     _same(*results)
+
+
+@pytest.mark.parametrize("nbytes", [1, 2, 6, 16, 8190, 8192, 8194, 100_001, (4 << 20) - 2, 4 << 20, (4 << 20) + 2])
+@pytest.mark.parametrize("offset", [0, 2, 3, 14])
+def test_offloaded_bytes_arrive(nbytes, offset):
+    """Around the pieces of the copying kernel, its limit and what it does not take (odd counts and addresses): the bytes
+    arrive, nothing around them changes, and a stream that is ordered behind the offload reads them."""
+    src = torch.randint(0, 256, (nbytes + 64,), dtype=torch.uint8, device="cuda:0")
+    dst = torch.full((nbytes + 64,), 7, dtype=torch.uint8).pin_memory()
+    back = torch.zeros(nbytes + 64, dtype=torch.uint8, device="cuda:0")
+    eng = zi.zi_engine_create(0, 64 * 1024, 3)
+    try:
+        zi.zi_grad_offload(eng, src.data_ptr() + offset, dst.data_ptr() + 2 * offset, nbytes, torch.cuda.current_stream())
+        side = torch.cuda.Stream()
+        zi.zi_grad_offload_order(eng, side)
+        with torch.cuda.stream(side):
+            back.copy_(dst, non_blocking=True)
+        side.synchronize()
+        zi.zi_grad_offload_wait(eng)
+    finally:
+        zi.zi_engine_destroy(eng)
+    want = torch.full((nbytes + 64,), 7, dtype=torch.uint8)
+    want[2 * offset:2 * offset + nbytes] = src.cpu()[offset:offset + nbytes]
+    assert torch.equal(dst, want) and torch.equal(back.cpu(), want)
