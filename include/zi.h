@@ -15,12 +15,13 @@
  *                           precision; Section 2, "Adam Optimizer and Mixed
  *                           Precision Training": updates are done in fp32);
  *   zi_adamw_step_streamed  the same step when the fp32 states live in pinned
- *                           host memory and move through HBM in fixed-size
- *                           chunks, with reads, compute and writes overlapped
- *                           through a small ring of reused staging buffers
- *                           (Section 5.2.2: chunked step, overlap of reads,
- *                           writes and compute; Section 6.3: reused pinned
- *                           buffers).
+ *                           host memory: read, updated and written back over
+ *                           the link by one kernel, or moved through HBM in
+ *                           fixed-size chunks over a small ring of reused
+ *                           staging buffers, with reads, compute and writes
+ *                           overlapped (Section 5.2.2: offloaded step, overlap
+ *                           of reads, writes and compute; Section 6.3: reused
+ *                           pinned buffers).
  *
  * The step reads every state once and writes it once (Section 4.1, "AIT w.r.t.
  * Optimizer States"): 28 bytes per element here (read p, m, v 4 B each and g
@@ -281,9 +282,9 @@ zi_status zi_grad_offload_order(zi_engine* e, void* consumer_stream);
  * optimizer states in CPU memory the step runs on the CPUs; gradients come down, updated
  * low-precision parameters go up: 2 + 2 bytes per element over the link instead of 12 + 12).
  * p, m, v: host memory of any kind, updated in place by n_threads CPU threads (AVX2 / FMA / F16C,
- * the arithmetic of zi_host_adamw_step).  g, p_lp: DEVICE memory — each chunk of gradients is
- * fetched into the engine's pinned ring, stepped, and the chunk of the copy is shipped back, the
- * fetch of later chunks and the upload of earlier ones overlapping the CPUs' work — or host memory,
+ * the arithmetic of zi_host_adamw_step).  g, p_lp: DEVICE memory — the gradients are brought
+ * into the engine's pinned ring, stepped, and the copy is sent back, the
+ * fetch of later blocks and the upload of earlier ones overlapping the CPUs' work — or host memory,
  * used in place.  Device-resident g / p_lp need ZI_OPT_HOST_RING_SLOTS >= 3.
  * d_norm: device result of zi_grad_norm or NULL; read back first; found_inf != 0 returns
  * ZI_SKIPPED_OVERFLOW with nothing touched.  The engine's streams first wait for hip_stream.

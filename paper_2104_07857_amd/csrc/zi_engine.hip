@@ -419,8 +419,8 @@ zi_status check_stream_device(const zi_engine* e, hipStream_t user)
 
 // The step over page-locked state that the device can address: one kernel reads and writes the host arrays
 // over the link (adamw_link_kernel), on the caller's stream; nothing passes through the slots.  Against the
-// chunk pipeline below it measured (chunks of 64 MiB, norm included, per call): 3.0e5 elements 289 -> 143 us,
-// 2.5e7 elements 9.4 -> 6.2 ms (one chunk's way in and out is not exposed any more), and with gradients and
+// chunk pipeline below it measured (chunks of 64 MiB, norm included, per call): 3.0e5 elements 288 -> 123 us,
+// 2.5e7 elements 9.4 -> 6.1 ms (one chunk's way in and out is not exposed any more), and with gradients and
 // copy in host memory too 2.0e8 elements 76.2 -> 71.8 ms (offload and reduction included).
 // The skip flag is read by the kernel and comes back with it instead of a copy and a wait in front.
 zi_status run_linked(zi_engine* e, zi_lp_dtype dt, const zi_adamw_config* cfg, const zi_norm_result* d_norm,

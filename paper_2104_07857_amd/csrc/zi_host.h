@@ -52,12 +52,19 @@ struct PointerChecker {
     Range known[8] = {};
     int n_known = 0, next = 0;
 
-    zi_status check(const void* p, size_t bytes, int tensor, const char* name)
+    // Whether the array lies in an allocation that has been looked up.
+    bool covers(const void* p, size_t bytes) const
     {
-        if (!p || bytes == 0) return ZI_OK;
         const uintptr_t lo = reinterpret_cast<uintptr_t>(p), hi = lo + bytes;
         for (int i = 0; i < n_known; ++i)
-            if (lo >= known[i].lo && hi <= known[i].hi) return ZI_OK;
+            if (lo >= known[i].lo && hi <= known[i].hi) return true;
+        return false;
+    }
+
+    zi_status check(const void* p, size_t bytes, int tensor, const char* name)
+    {
+        if (!p || bytes == 0 || covers(p, bytes)) return ZI_OK;
+        const uintptr_t lo = reinterpret_cast<uintptr_t>(p), hi = lo + bytes;
         hipDeviceptr_t base = nullptr;
         size_t size = 0;
         bool inside = false;

@@ -1,10 +1,11 @@
-// gfx950 kernels of the optimizer hot path: gradient sum of squares + overflow flag,
-// and the fused AdamW read-modify-write pass.
+// gfx950 kernels of the optimizer hot path: gradient sum of squares + overflow flag, the fused AdamW
+// read-modify-write pass over state in HBM (one tensor or few, long lists) and in page-locked host memory, and
+// copies of the 2-byte arrays over the host link.
 //
-// Both are pure HBM streams (Section 4.1, "AIT w.r.t. Optimizer States": the step reads every
+// All are pure streams (Section 4.1, "AIT w.r.t. Optimizer States": the step reads every
 // state once and writes it once), so the design is about bytes, not flops: each wavefront-wide
 // access is one contiguous run of 16-byte (fp32 arrays) or 8-byte (2-byte arrays) lanes, marked
-// non-temporal because nothing is reused, a thread has all loads of a tile in flight before the
+// non-temporal where nothing is reused, a thread has all loads of a tile in flight before the
 // first use, nothing goes through LDS except the block reduction of the norm, and no matrix core
 // is involved because there is no contraction.
 //
@@ -387,7 +388,7 @@ __device__ __forceinline__ void count_start(uint32_t block, uint32_t start, uint
 // what is in front of its first load is kept to three round trips to the scalar cache (arguments; group starts
 // and norm result together; descriptor) and arithmetic that hides in them.  Measured, step alone in us, against
 // a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
-// 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1430,
+// 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,
 // 200 of 1..40,000 45.6 -> 35.3; with the norm result fetched after the descriptor 1478 instead of 1366.
 template <int DT, bool L2>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))

@@ -44,7 +44,7 @@ extern "C" zi_status zi_grad_offload(zi_engine* e, const void* d_src, void* h_ds
     ZI_HIP(hipEventRecord(e->ev_offload[idx], (hipStream_t)producer_stream));
     ZI_HIP(hipStreamWaitEvent(e->s_d2h, e->ev_offload[idx], 0));
     uint16_t* dst = nullptr;
-    if (bytes <= kOffloadByKernel && bytes % 2 == 0 && aligned(d_src, 2) && aligned(h_dst, 2)) {
+    if (bytes <= kOffloadByKernel && bytes % 2 == 0 && aligned(d_src, 2) && aligned(h_dst, 2) && reach.covers(d_src, bytes)) {
         HostRanges pinned;
         pinned.note(h_dst, bytes);
         dst = (uint16_t*)pinned.device_address(h_dst, bytes);
