@@ -399,7 +399,8 @@ zi_status zi_plan_chunks(const int64_t* numel, int32_t n_tensors, int64_t chunk_
  * of the tensor's traffic as possible starts on 128-byte lines), its tiles of 512 elements, and the
  * launch it belongs to.  Tensors of 2^22 elements or more get a launch of their own (`alone`);
  * shorter ones share launches of up to 32 tensors.  Lists of more than 64 tensors share launches of 64,
- * long tensors too.  Writes at most `cap` items and always the totals.
+ * long tensors too, or of 256 if they are short (327,680 elements on average at most) and all tensors are at the
+ * same places of five flat buffers (one for each of p, m, v, g and p_lp).  Writes at most `cap` items and always the totals.
  */
 typedef struct {
     int32_t tensor;        /* index into t[] */

@@ -158,21 +158,55 @@ struct StepIssuer {
     // launch is recorded instead.  `cur_tensor` is the caller's index of the tensor being added.
     std::vector<zi_step_plan_item>* plan = nullptr;
     int32_t cur_tensor = -1;
-    int32_t tensor_of[zi::kMaxListDesc] = {};
-    // Lists of more than kMaxListDesc tensors (expect()): launches of that many, whatever their length, in `list`.
-    bool long_list = false;
+    int32_t tensor_of[zi::FlatArgs::kMax] = {};
+    // Lists of more than kMaxListDesc tensors (expect()): launches of many, whatever their length, in `list`, or in
+    // `flat` if the tensors are short and all at the same places of five flat buffers.  Four times as many to a launch
+    // save 3 us each time, and twice as many entries in the lookup cost every workgroup some 4%.  Step alone, us, list /
+    // flat: 200 tensors of 2e4 elements 35.3 / 25.3, 1000 of 1e5 512 / 480, 288 of 2.6e5 361 / 352, 288 of 1.0e6
+    // 1368 / 1427, 72 of 4.2e6 1363 / 1420: the line is drawn at an average of 5 * 2^16.
+    static constexpr int64_t kFlatAverage = 5 << 16;
+    enum Kind { kFew, kList, kFlat };
+    Kind kind = kFew;
     zi::ListArgs list;
+    zi::FlatArgs flat;
 
     // What the list will be, before the first add(): decides how many tensors share a launch.
     void expect(const zi_tensor* t, int32_t n_tensors)
     {
-        int64_t n = 0;
-        for (int32_t i = 0; i < n_tensors; ++i) n += t[i].numel > 0;
+        int64_t n = 0, total = 0;
+        for (int32_t i = 0; i < n_tensors; ++i) {
+            n += t[i].numel > 0;
+            total += t[i].numel;
+        }
         if (n <= zi::kMaxListDesc) return;
-        long_list = true;
-        list.c = args.c;
-        list.d_norm = args.d_norm;
+        kind = total / n <= kFlatAverage && is_flat(t, n_tensors) ? kFlat : kList;
+        list.c = flat.c = args.c;
+        list.d_norm = flat.d_norm = args.d_norm;
     }
+
+    // Every tensor's five arrays begin the same number of elements (less than 2^32, its end included) behind the
+    // first tensor's, and all have a copy or none.  Sets the first tensor's addresses.
+    bool is_flat(const zi_tensor* t, int32_t n_tensors)
+    {
+        const zi_tensor* f = nullptr;
+        for (int32_t i = 0; i < n_tensors; ++i) {
+            if (t[i].numel <= 0) continue;
+            if (!f) f = &t[i];
+            const auto bytes = [](const void* x, const void* from) { return reinterpret_cast<uintptr_t>(x) - reinterpret_cast<uintptr_t>(from); };
+            const uintptr_t at = bytes(t[i].p, f->p);
+            if (at % 4 || at / 4 + (uintptr_t)t[i].numel > 0xFFFFFFFFull) return false;
+            if (bytes(t[i].m, f->m) != at || bytes(t[i].v, f->v) != at || bytes(t[i].g, f->g) != at / 2) return false;
+            if (!t[i].p_lp != !f->p_lp || (f->p_lp && bytes(t[i].p_lp, f->p_lp) != at / 2)) return false;
+        }
+        flat.p = (float*)f->p;
+        flat.m = (float*)f->m;
+        flat.v = (float*)f->v;
+        flat.g = (const uint16_t*)f->g;
+        flat.lp = (uint16_t*)f->p_lp;
+        return true;
+    }
+
+    int32_t max_desc() const { return kind == kFlat ? zi::FlatArgs::kMax : kind == kList ? zi::kMaxListDesc : zi::kMaxStepDesc; }
 
     StepIssuer(const zi::StepConsts& c, const zi_norm_result* d_norm, int dt_, bool l2_, hipStream_t s)
         : dt(dt_), l2(l2_), stream(s)
@@ -201,8 +235,9 @@ struct StepIssuer {
     uint32_t last_tiles = 0;          // of the launch issued last
     zi::StepArgs held;
     zi::ListArgs held_list;
+    zi::FlatArgs held_flat;
     uint32_t held_tiles = 0;
-    bool held_is_list = false;
+    Kind held_kind = kFew;
 
     hipError_t issue_held(bool last)
     {
@@ -213,8 +248,9 @@ struct StepIssuer {
         ++launches;
         const uint32_t n = last_tiles = held_tiles;
         held_tiles = 0;
-        return held_is_list ? zi::launch_step_list(held_list, n, dt, l2, any_order, stream)
-                            : zi::launch_step_wide(held, n, dt, l2, any_order, stream);
+        return held_kind == kFlat   ? zi::launch_step_flat(held_flat, n, dt, l2, any_order, stream)
+               : held_kind == kList ? zi::launch_step_list(held_list, n, dt, l2, any_order, stream)
+                                    : zi::launch_step_wide(held, n, dt, l2, any_order, stream);
     }
 
     void planned(int32_t tensor, int32_t head, int64_t first, int64_t end, bool alone)
@@ -234,32 +270,37 @@ struct StepIssuer {
         const hipError_t e = issue_held(false);
         held = a;
         held_tiles = n_tiles;
-        held_is_list = false;
+        held_kind = kFew;
         return e;
     }
 
-    hipError_t launch_list()
+    template <typename Args>
+    hipError_t launch_list(Args& a, Args& into)
     {
         const int32_t n = args.n_desc;
         if (plan) {
             for (int32_t i = 0; i < n; ++i)
-                planned(tensor_of[i], list.t[i].head, list.first_tile[i], i + 1 < n ? list.first_tile[i + 1] : tiles, n == 1);
+                planned(tensor_of[i], kind == kFlat ? flat.head[i] : list.t[i].head, a.first_tile[i],
+                        i + 1 < n ? a.first_tile[i + 1] : tiles, n == 1);
             ++launches;
             return hipSuccess;
         }
         const hipError_t e = issue_held(false);
-        for (int32_t i = n; i < zi::kMaxListDesc; ++i) list.first_tile[i] = 0xFFFFFFFFu;
-        for (int i = 0; i < zi::kListGroups; ++i) list.group_start[i] = list.first_tile[i * zi::kListGroup];
-        held_list = list;
+        for (int32_t i = n; i < Args::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
+        for (int i = 0; i < Args::kGroups; ++i) a.group_start[i] = a.first_tile[i * Args::kGroup];
+        into = a;
         held_tiles = tiles;
-        held_is_list = true;
+        held_kind = kind;
         return e;
     }
 
     hipError_t close()       // the launch being assembled is complete
     {
         hipError_t e = hipSuccess;
-        if (args.n_desc > 0) e = long_list ? launch_list() : launch(args, tiles, tensor_of);
+        if (args.n_desc > 0)
+            e = kind == kFlat   ? launch_list(flat, held_flat)
+                : kind == kList ? launch_list(list, held_list)
+                                : launch(args, tiles, tensor_of);
         reset();
         return e;
     }
@@ -285,7 +326,7 @@ struct StepIssuer {
         if (nt > 0x7FFFFFFF) return hipErrorInvalidValue;
         d.nquad = nquad;
         d.n_tiles = (uint32_t)nt;
-        if (long_list ? nquad > 0xFFFFFFFFll : nt >= kSoloTiles) {      // a launch of its own: no tensor lookup in the kernel
+        if (kind != kFew ? nquad > 0xFFFFFFFFll : nt >= kSoloTiles) {      // a launch of its own: no tensor lookup in the kernel
             zi::StepArgs solo{};
             solo.c = args.c;
             solo.d_norm = args.d_norm;
@@ -296,15 +337,23 @@ struct StepIssuer {
             solo.t[0] = d;
             return launch(solo, (uint32_t)nt, &cur_tensor);
         }
-        if (args.n_desc == (long_list ? zi::kMaxListDesc : zi::kMaxStepDesc) || (uint64_t)tiles + (uint64_t)nt > 0x7FFFFFFFull) {
+        if (args.n_desc == max_desc() || (uint64_t)tiles + (uint64_t)nt > 0x7FFFFFFFull) {
             hipError_t e = close();
             if (e != hipSuccess) return e;
         }
-        if (long_list) {
-            list.t[args.n_desc] = {d.p_body, d.m_body, d.v_body, d.g_body, d.lp_body, (uint32_t)nquad, (uint16_t)d.head,
-                                   (uint16_t)(numel - d.head - nquad * zi::kQuad)};
-            list.first_tile[args.n_desc] = tiles;
-            tensor_of[args.n_desc++] = cur_tensor;
+        if (kind != kFew) {
+            const int32_t n = args.n_desc++;
+            const int64_t tail = numel - d.head - nquad * zi::kQuad;
+            if (kind == kFlat) {
+                flat.t[n] = {(uint32_t)(d.p_body - flat.p), (uint32_t)nquad};
+                flat.head[n] = (uint8_t)d.head;
+                flat.tail[n] = (uint8_t)tail;
+                flat.first_tile[n] = tiles;
+            } else {
+                list.t[n] = {d.p_body, d.m_body, d.v_body, d.g_body, d.lp_body, (uint32_t)nquad, (uint16_t)d.head, (uint16_t)tail};
+                list.first_tile[n] = tiles;
+            }
+            tensor_of[n] = cur_tensor;
             tiles += (uint32_t)nt;
             return hipSuccess;
         }

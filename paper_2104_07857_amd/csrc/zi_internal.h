@@ -100,11 +100,9 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
-// A launch over many tensors (adamw_list_kernel).
-constexpr int kListGroup = 8;
-constexpr int kListGroups = 8;
-constexpr int kMaxListDesc = kListGroup * kListGroups;
-
+// Launches over many tensors (adamw_list_kernel), which a workgroup looks up in groups.  A list whose tensors are
+// views at the same places of five flat buffers, as the partitions of a sharded optimizer are, needs one place per
+// tensor (FlatArgs); any other list five addresses (ListArgs).
 struct ListDesc {
     float* p_body;         // p + head
     float* m_body;
@@ -116,13 +114,34 @@ struct ListDesc {
 };
 
 struct ListArgs {
-    ListDesc t[kMaxListDesc];
-    uint32_t first_tile[kMaxListDesc];      // 0xFFFFFFFF beyond the list
-    uint32_t group_start[kListGroups];      // first_tile of every eighth
+    static constexpr int kGroup = 8, kGroups = 8, kMax = kGroup * kGroups;
+    ListDesc t[kMax];
+    uint32_t first_tile[kMax];              // 0xFFFFFFFF beyond the list
+    uint32_t group_start[kGroups];          // first_tile of every group's first
     StepConsts c;
     const zi_norm_result* d_norm;
 };
 static_assert(sizeof(ListArgs) < 4096, "kernel arguments");
+constexpr int kMaxListDesc = ListArgs::kMax;
+
+struct FlatDesc {
+    uint32_t body;         // elements from the list's first tensor to this one's body
+    uint32_t nquad;
+};
+
+struct FlatArgs {
+    static constexpr int kGroup = 16, kGroups = 16, kMax = kGroup * kGroups;
+    FlatDesc t[kMax];
+    uint32_t first_tile[kMax];
+    uint32_t group_start[kGroups];
+    float *p, *m, *v;      // the list's first tensor
+    const uint16_t* g;
+    uint16_t* lp;          // null if there are no copies
+    StepConsts c;
+    const zi_norm_result* d_norm;
+    uint8_t head[kMax], tail[kMax];
+};
+static_assert(sizeof(FlatArgs) < 4096, "kernel arguments");
 
 // The step over state in page-locked host memory (adamw_link_kernel): a persistent grid of
 // single-wavefront workgroups that read and write the host arrays over the link themselves.
@@ -188,6 +207,7 @@ static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 // any_order: may run beside the launches in front of it on the stream (see StepIssuer for where that is safe).
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
+hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).

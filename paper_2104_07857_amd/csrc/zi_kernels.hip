@@ -383,16 +383,37 @@ __device__ __forceinline__ void count_start(uint32_t block, uint32_t start, uint
         : "scc");
 }
 
-// The same for long lists: 64 tensors of any length to a launch, found by counting the starts of groups of
-// eight tensors and then the starts inside one group.  A workgroup still lives for a few microseconds, so
+// Where the vector bodies of a list's tensor d are, and the elements around them.
+struct Bodies {
+    float *p_body, *m_body, *v_body;
+    const uint16_t* g_body;
+    uint16_t* lp_body;
+};
+__device__ __forceinline__ Bodies bodies_of(const ListArgs& a, uint32_t d)
+{
+    const ListDesc& T = a.t[d];
+    return {T.p_body, T.m_body, T.v_body, T.g_body, T.lp_body};
+}
+__device__ __forceinline__ int64_t head_of(const ListArgs& a, uint32_t d) { return a.t[d].head; }
+__device__ __forceinline__ int64_t tail_of(const ListArgs& a, uint32_t d) { return a.t[d].tail; }
+__device__ __forceinline__ Bodies bodies_of(const FlatArgs& a, uint32_t d)
+{
+    const uint64_t at = a.t[d].body;
+    return {a.p + at, a.m + at, a.v + at, a.g + at, a.lp ? a.lp + at : nullptr};
+}
+__device__ __forceinline__ int64_t head_of(const FlatArgs& a, uint32_t d) { return a.head[d]; }
+__device__ __forceinline__ int64_t tail_of(const FlatArgs& a, uint32_t d) { return a.tail[d]; }
+
+// The same for long lists: 64 tensors of any length to a launch (ListArgs), or 256 short ones of flat buffers
+// (FlatArgs), found by counting the starts of groups of tensors and then the starts inside one group.  A workgroup still lives for a few microseconds, so
 // what is in front of its first load is kept to three round trips to the scalar cache (arguments; group starts
 // and norm result together; descriptor) and arithmetic that hides in them.  Measured, step alone in us, against
 // a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
 // 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,
-// 200 of 1..40,000 45.6 -> 35.3; with the norm result fetched after the descriptor 1478 instead of 1366.
-template <int DT, bool L2>
+// 200 of 1..40,000 45.6 -> 35.3, as FlatArgs 25.3; with the norm result fetched after the descriptor 1478 instead of 1366.
+template <int DT, bool L2, typename Args>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void adamw_list_kernel(const ListArgs a)
+void adamw_list_kernel(const Args a)
 {
     const uint32_t block = blockIdx.x;
     const zi_norm_result* d_norm = a.d_norm;
@@ -402,20 +423,21 @@ void adamw_list_kernel(const ListArgs a)
                  "+s"(c.max_norm_is_pow2), "+s"(c.inv_loss_scale));
     uint32_t group = 0, first = 0;        // the first start is 0, so both counts are at least 1
 #pragma unroll
-    for (int i = 0; i < kListGroups; ++i) count_start(block, a.group_start[i], group, first);
+    for (int i = 0; i < Args::kGroups; ++i) count_start(block, a.group_start[i], group, first);
     // The norm result travels beside the group's starts: one round trip to the scalar cache for both.
     u32x8_k raw = {};
     if (d_norm) raw = load_norm_result(d_norm);
-    uint32_t d = --group * kListGroup;
+    uint32_t d = --group * Args::kGroup;
 #pragma unroll
-    for (int i = 0; i < kListGroup; ++i) count_start(block, a.first_tile[group * kListGroup + i], d, first);
+    for (int i = 0; i < Args::kGroup; ++i) count_start(block, a.first_tile[group * Args::kGroup + i], d, first);
     float gscale = c.host_gscale;
     const bool clips = d_norm && c.max_grad_norm > 0.0f;
     const bool quick = c.max_norm_is_pow2 && c.scale_is_pow2;
     const bool same_scale = raw[5] == __float_as_uint(c.loss_scale);
     if (clips && !(quick && same_scale)) (void)judge_norm_result(raw, c, gscale);
-    const ListDesc& T = a.t[d - 1];
-    uint32_t nquad = T.nquad;
+    --d;
+    uint32_t nquad = a.t[d].nquad;
+    const Bodies T = bodies_of(a, d);
     GlobalF4 __restrict__ p4 = (GlobalF4)(uintptr_t)T.p_body;
     GlobalF4 __restrict__ m4 = (GlobalF4)(uintptr_t)T.m_body;
     GlobalF4 __restrict__ v4 = (GlobalF4)(uintptr_t)T.v_body;
@@ -432,7 +454,7 @@ void adamw_list_kernel(const ListArgs a)
     if (d_norm && raw[4]) return;
 
     const uint32_t tile = tile_of_block(block, first, (nquad + kStepTileQuads - 1) / kStepTileQuads);
-    if (tile == 0) step_ends<DT, L2>(T, T.head, (int64_t)nquad * kQuad, T.tail, gscale, c);
+    if (tile == 0) step_ends<DT, L2>(T, head_of(a, d), (int64_t)nquad * kQuad, tail_of(a, d), gscale, c);
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
 }
 
@@ -455,17 +477,26 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
     return hipGetLastError();
 }
 
-hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
+template <typename Args>
+static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
     const dim3 grid(n_tiles), block(kStepThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
 #define ZI_LAUNCH_LIST(DT, L2) \
-    hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2>), grid, block, kStepOccupancyLds, s, nullptr, nullptr, flags, a)
+    hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, kStepOccupancyLds, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LIST(ZI_BF16, true); else ZI_LAUNCH_LIST(ZI_BF16, false); }
     else               { if (l2) ZI_LAUNCH_LIST(ZI_FP16, true); else ZI_LAUNCH_LIST(ZI_FP16, false); }
 #undef ZI_LAUNCH_LIST
     return hipGetLastError();
+}
+hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
+{
+    return launch_list_of(a, n_tiles, dt, l2, any_order, s);
+}
+hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
+{
+    return launch_list_of(a, n_tiles, dt, l2, any_order, s);
 }
 
 // The descriptor that holds tile t of a launch, at or after entry d, by halving: a walk from entry to entry

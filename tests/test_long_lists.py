@@ -38,13 +38,31 @@ def test_long_lists_share_launches_of_64(count, per_launch):
             nxt += it.n_tiles
 
 
+def test_flat_lists_share_launches_of_256():
+    """Tensors at the same places of five buffers; one array out of step, or a copy missing, and it is 64 again."""
+    base, gap, n = 0x7F00_0000_0000, 1 << 36, 300
+
+    def plan(shift=0, missing=-1):
+        t = [[base + k * gap + 1001 * i * (4 if k < 3 else 2) for k in range(5)] + [1000] for i in range(n)]
+        t[n - 1][3] += 2 * shift
+        if missing >= 0:
+            t[missing][4] = None
+        items, launches = zi.zi_plan_step([tuple(x) for x in t])
+        assert len(items) == n and [it.tensor for it in items] == list(range(n))
+        return launches
+
+    assert plan() == 2 and plan(shift=1) == 5 and plan(missing=7) == 5
+
+
 @pytest.mark.gpu
+@pytest.mark.parametrize("flat", [True, False])
 @pytest.mark.parametrize("clip,scale,norm_scale", [(0.0, 1.0, 1.0), (0.5, 2.0, 2.0), (0.7, 2.0, 2.0), (0.5, 3.0, 3.0), (0.5, 2.0, 4.0),
                                                    (1e9, 1.0, 1.0)])
-@pytest.mark.parametrize("count,l2,dt", [(63, False, zi.ZI_BF16), (64, True, zi.ZI_FP16), (200, False, zi.ZI_FP16)])
-def test_a_list_equals_its_tensors_one_by_one(count, l2, dt, clip, scale, norm_scale):
+@pytest.mark.parametrize("count,l2,dt", [(63, False, zi.ZI_BF16), (64, True, zi.ZI_FP16), (270, False, zi.ZI_FP16)])
+def test_a_list_equals_its_tensors_one_by_one(count, l2, dt, clip, scale, norm_scale, flat):
     """Ragged tensors at odd offsets of flat buffers (some a tile or less, one longer than an XCD run of tiles, one
-    of 2^22 elements in the middle), with a norm that clips or not, stepped twice in a row as a list and tensor by tensor."""
+    of 2^22 elements in the middle), with a norm that clips or not, stepped twice in a row as a list and tensor by tensor; the copies at the
+    same places as the other arrays or at others."""
     rng = np.random.default_rng(count)
     sizes = [int(x) for x in rng.integers(1, 4000, count)]
     sizes[3], sizes[7], sizes[20], sizes[count - 1] = 1, TILE, 1030 * TILE + 5, 2 * TILE + 3
@@ -58,8 +76,10 @@ def test_a_list_equals_its_tensors_one_by_one(count, l2, dt, clip, scale, norm_s
 
     def state():
         bufs = [torch.from_numpy(a.copy().view(np.int16) if a.dtype == np.uint16 else a.copy()).cuda() for a in host]
-        bufs.append(torch.full((total,), 7, dtype=torch.int16, device="cuda:0"))
-        return bufs, [tuple(b[s:s + n] for b in bufs) + (n,) for s, n in zip(starts.tolist(), sizes)]
+        skew = 0 if flat else 3
+        bufs.append(torch.full((total + skew * len(sizes),), 7, dtype=torch.int16, device="cuda:0"))
+        return bufs, [tuple(b[s:s + n] for b in bufs[:4]) + (bufs[4][s + skew * i:s + skew * i + n], n)
+                      for i, (s, n) in enumerate(zip(starts.tolist(), sizes))]
 
     cfg = zi.make_config(step=10, loss_scale=scale, max_grad_norm=clip, mode=zi.ZI_MODE_ADAM_L2 if l2 else zi.ZI_MODE_ADAMW)
     (a, ta), (b, tb) = state(), state()
