@@ -43,7 +43,8 @@ void ring_release(zi_engine* e)
     e->pool_in = e->pool_out = nullptr;
     for (int i = 0; i < kMaxHostSlots; ++i) {
         if (e->ev_back[i]) (void)hipEventDestroy(e->ev_back[i]);
-        e->ev_back[i] = nullptr;
+        if (e->ev_fill[i]) (void)hipEventDestroy(e->ev_fill[i]);
+        e->ev_back[i] = e->ev_fill[i] = nullptr;
     }
     if (e->hring) (void)hipHostFree(e->hring);
     e->hring = nullptr;
@@ -210,6 +211,7 @@ extern "C" zi_status zi_engine_set_option(zi_engine* e, int32_t option, int64_t 
         e->fill_serial = 0;
         for (int i = 0; i < (int)value; ++i) {
             he = hipEventCreateWithFlags(&e->ev_back[i], hipEventDisableTiming);
+            if (he == hipSuccess) he = hipEventCreateWithFlags(&e->ev_fill[i], hipEventDisableTiming);
             if (he != hipSuccess) {
                 (void)hipGetLastError();
                 ring_release(e);

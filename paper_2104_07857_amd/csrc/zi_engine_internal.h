@@ -31,6 +31,7 @@ struct StateSrc {
     void* p_lp;          // device, or host when lp_host; may be null
     bool g_host;         // gradients live in host memory and are staged chunk by chunk
     bool lp_host;        // the low-precision copy is written back to host memory
+    bool g_peer, lp_peer;   // device memory, but not the engine's device's: no kernel of this one may touch it
     char* dev[5];        // p, m, v, g, p_lp as the device addresses them, if every host array is mapped (HostRanges)
     int64_t numel;
 };
@@ -103,6 +104,7 @@ struct zi_engine {
     int n_hslots = 0;
     char* hring = nullptr;
     hipEvent_t ev_back[zi::host::kMaxHostSlots] = {};   // the slot's outbound traffic has left / its inbound copy is done
+    hipEvent_t ev_fill[zi::host::kMaxHostSlots] = {};   // gradients of another device have landed in the slot
     uint32_t* fill_flags = nullptr;    // page-locked: per ring slot and block of the host-CPU step, see link_copy_kernel
     size_t flags_per_slot = 0;
     uint32_t fill_serial = 0;          // of the last fill; a block's flag equals its fill's serial once it has landed

@@ -27,9 +27,9 @@ namespace host {
         }                                                                                             \
     } while (0)
 
-// What kind of memory an address is: 0 device, 1 page-locked host, 2 ordinary host, -1 anything else,
-// -2 if the HIP runtime cannot answer (no usable device).
-inline int memory_kind(const void* p)
+// What kind of memory an address is: 0 device (whose, in *device), 1 page-locked host, 2 ordinary host, -1 anything
+// else, -2 if the HIP runtime cannot answer (no usable device).
+inline int memory_kind(const void* p, int* device = nullptr)
 {
     hipPointerAttribute_t attr{};
     const hipError_t pe = hipPointerGetAttributes(&attr, p);
@@ -37,6 +37,7 @@ inline int memory_kind(const void* p)
         (void)hipGetLastError();
         return pe == hipErrorInvalidValue ? 2 : -2;      // older runtimes report unregistered memory this way
     }
+    if (device) *device = attr.device;
     if (attr.type == hipMemoryTypeDevice) return 0;
     if (attr.type == hipMemoryTypeHost) return 1;
     if (attr.type == hipMemoryTypeUnregistered) return 2;

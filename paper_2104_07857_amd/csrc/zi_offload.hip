@@ -30,7 +30,8 @@ extern "C" zi_status zi_grad_offload(zi_engine* e, const void* d_src, void* h_ds
     if (bytes == 0) return ZI_OK;
     if (!d_src || !h_dst) return fail(ZI_ERR_INVALID_ARG, "d_src and h_dst must not be NULL");
     PointerChecker reach;
-    if (memory_kind(d_src) != 0) return fail(ZI_ERR_INVALID_ARG, "d_src must be device memory");
+    int owner = -1;
+    if (memory_kind(d_src, &owner) != 0) return fail(ZI_ERR_INVALID_ARG, "d_src must be device memory");
     if (zi_status st = reach.check(d_src, bytes, -1, "d_src")) return st;
     if (memory_kind(h_dst) != 1 || memory_kind(static_cast<const char*>(h_dst) + bytes - 1) != 1)
         return fail(ZI_ERR_INVALID_ARG, "h_dst (%zu bytes) must be page-locked host memory", bytes);
@@ -44,7 +45,9 @@ extern "C" zi_status zi_grad_offload(zi_engine* e, const void* d_src, void* h_ds
     ZI_HIP(hipEventRecord(e->ev_offload[idx], (hipStream_t)producer_stream));
     ZI_HIP(hipStreamWaitEvent(e->s_d2h, e->ev_offload[idx], 0));
     uint16_t* dst = nullptr;
-    if (bytes <= kOffloadByKernel && bytes % 2 == 0 && aligned(d_src, 2) && aligned(h_dst, 2) && reach.covers(d_src, bytes)) {
+    // (memory of another device is for the runtime's copy: a kernel of this one cannot be expected to reach it)
+    if (owner == e->device && bytes <= kOffloadByKernel && bytes % 2 == 0 && aligned(d_src, 2) && aligned(h_dst, 2) &&
+        reach.covers(d_src, bytes)) {
         HostRanges pinned;
         pinned.note(h_dst, bytes);
         dst = (uint16_t*)pinned.device_address(h_dst, bytes);
@@ -91,6 +94,7 @@ struct CpuBlock {
     int64_t n;
     const uint32_t* arrived;      // flag of the block's gradients (null: they are in host memory already)
     uint16_t* lp_device;          // where the block of the copy goes (null: it is in its place)
+    bool lp_peer;                 // ... in the memory of another device than the engine's
 };
 
 // Tasks are blocks of link_copy_kernel: 64 KiB of each fp32 array.  A chunk of 2^24 elements is 1024
@@ -117,7 +121,8 @@ struct CpuJob {
     size_t sent = 0;              // blocks whose copy is on its way (or in its place)
     hipError_t upload_error = hipSuccess;
 
-    // Sends up the copies of blocks [sent, to), neighbours of one segment as one.
+    // Sends up the copies of blocks [sent, to), neighbours of one segment as one, by a kernel or, to another
+    // device's memory, by the runtime's copy.
     void upload(size_t to)
     {
         CopyIssuer up(e->s_h2d, nullptr, 0);
@@ -126,9 +131,13 @@ struct CpuJob {
             int64_t n = b.n;
             size_t next = sent + 1;
             if (b.lp_device)
-                while (next < to && blocks[next].lp_device == b.lp_device + n && blocks[next].lp == b.lp + n) n += blocks[next++].n;
+                while (next < to && blocks[next].lp_device == b.lp_device + n && blocks[next].lp == b.lp + n &&
+                       blocks[next].lp_peer == b.lp_peer)
+                    n += blocks[next++].n;
             if (b.lp_device) {
-                upload_error = up.add(b.lp, b.lp_device, n, 0);
+                upload_error = b.lp_peer ? hipMemcpyAsync(b.lp_device, b.lp, (size_t)n * 2, hipMemcpyHostToDevice, e->s_h2d)
+                                         : up.add(b.lp, b.lp_device, n, 0);
+                e->stats.n_copies += b.lp_peer;
                 e->stats.bytes_h2d += (uint64_t)n * 2;
             }
             sent = next;
@@ -204,19 +213,22 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
             if ((k0 != 1 && k0 != 2) || k1 != k0)
                 return fail(ZI_ERR_INVALID_ARG, "tensor %d: p, m, v must be host memory", i);
         }
-        const int gk = memory_kind(S.g);
+        int owner = e->device;
+        const int gk = memory_kind(S.g, &owner);
         if (gk < 0) return fail(ZI_ERR_INVALID_ARG, "tensor %d: g is neither device nor host memory", i);
         if (gk == 0) {
             if (zi_status st = reach.check(S.g, n * 2, i, "g")) return st;
             S.g_host = false;
+            S.g_peer = owner != e->device;
             any_device = true;
         }
         if (S.p_lp) {
-            const int lk = memory_kind(S.p_lp);
+            const int lk = memory_kind(S.p_lp, &owner);
             if (lk < 0) return fail(ZI_ERR_INVALID_ARG, "tensor %d: p_lp is neither device nor host memory", i);
             if (lk == 0) {
                 if (zi_status st = reach.check(S.p_lp, n * 2, i, "p_lp")) return st;
                 S.lp_host = false;
+                S.lp_peer = owner != e->device;
                 any_device = true;
             }
         }
@@ -267,7 +279,7 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     auto fetch = [&](int64_t u) -> zi_status {
         const int h = n_h > 0 ? (int)(u % n_h) : 0;
         CopyIssuer in(e->s_d2h, n_h > 0 ? e->fill_flags + (size_t)h * e->flags_per_slot : nullptr, first_serial + (uint32_t)u);
-        bool any = false;
+        bool any = false, peer = false;
         uint32_t flag = 0;
         for (size_t j = use_begin[(size_t)u]; j < use_begin[(size_t)u + 1]; ++j) {
             const Segment& sg = segs[j];
@@ -275,12 +287,21 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
             if (!S.g_host) {
                 if (!any && u >= n_h) ZI_HIP(hipEventSynchronize(e->ev_back[h]));
                 any = true;
-                ZI_HIP(in.add((const uint16_t*)S.g + sg.elem_offset, e->hslot_g(h) + sg.slot_offset, sg.count, flag));
+                const uint16_t* from = (const uint16_t*)S.g + sg.elem_offset;
+                uint16_t* to = e->hslot_g(h) + sg.slot_offset;
+                if (S.g_peer) {
+                    ZI_HIP(hipMemcpyAsync(to, from, (size_t)sg.count * 2, hipMemcpyDeviceToHost, e->s_d2h));
+                    ++e->stats.n_copies;
+                    peer = true;
+                } else {
+                    ZI_HIP(in.add(from, to, sg.count, flag));
+                }
                 e->stats.bytes_d2h += (size_t)sg.count * 2;
             }
             flag += (uint32_t)blocks_of(sg.count);
         }
         ZI_HIP(in.flush());
+        if (peer) ZI_HIP(hipEventRecord(e->ev_fill[h], e->s_d2h));
         return ZI_OK;
     };
     auto pipeline = [&]() -> zi_status {
@@ -294,12 +315,13 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
             const int h = n_h > 0 ? (int)(u % n_h) : 0;
             const uint32_t* flags = n_h > 0 ? e->fill_flags + (size_t)h * e->flags_per_slot : nullptr;
             blocks.clear();
-            bool fetched = false, upload = false;
+            bool fetched = false, peer = false, upload = false;
             for (size_t j = use_begin[(size_t)u]; j < use_begin[(size_t)u + 1]; ++j) {
                 const Segment& sg = segs[j];
                 const StateSrc& S = e->src[(size_t)sg.tensor];
                 const bool up = S.p_lp && !S.lp_host;
                 fetched = fetched || !S.g_host;
+                peer = peer || S.g_peer;
                 upload = upload || up;
                 const uint16_t* g = S.g_host ? (const uint16_t*)S.g + sg.elem_offset : e->hslot_g(h) + sg.slot_offset;
                 uint16_t* lp = !S.p_lp ? nullptr
@@ -308,13 +330,14 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
                     const int64_t nb = sg.count - o < kCpuBlockElems ? sg.count - o : kCpuBlockElems;
                     const int64_t at = sg.elem_offset + o;
                     blocks.push_back({(float*)S.ptr[0] + at, (float*)S.ptr[1] + at, (float*)S.ptr[2] + at, g + o,
-                                      lp ? lp + o : nullptr, nb, S.g_host ? nullptr : flags + blocks.size(),
-                                      up ? (uint16_t*)S.p_lp + at : nullptr});
+                                      lp ? lp + o : nullptr, nb, S.g_host || S.g_peer ? nullptr : flags + blocks.size(),
+                                      up ? (uint16_t*)S.p_lp + at : nullptr, S.lp_peer});
                 }
             }
             // A ring slot whose upload of `n_h` uses ago is still leaving must not be written yet
             // (uses with host-resident gradients skip the fetch that would have waited for it).
             if (upload && !fetched && u >= n_h) ZI_HIP(hipEventSynchronize(e->ev_back[h]));
+            if (peer) ZI_HIP(hipEventSynchronize(e->ev_fill[h]));      // the runtime's copies raise no flags
             e->cpu_done.assign(blocks.size(), 0);
             CpuJob job{e, blocks.data(), blocks.size(), first_serial + (uint32_t)u, k, gscale, (int)dt,
                        cfg->mode == ZI_MODE_ADAM_L2, e->cpu_done.data()};

@@ -1,0 +1,246 @@
+// The library's host code against a stand-in for the HIP runtime, for what one GPU cannot show: memory of two
+// devices, runtime calls that report an error, sizes at the end of the 64-bit range.  The executable defines the
+// runtime's functions itself and is linked against the built library, whose calls bind to these definitions.
+//
+// Every stand-in operation runs at once.  "Device" memory is ordinary memory with an owner; a kernel may touch its own
+// device's and page-locked memory only, and anything else is counted as a fault.  link_copy_kernel is carried out;
+// of the other kernels only the launch is seen.
+#define __HIP_PLATFORM_AMD__ 1
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "zi.h"
+#include "zi_internal.h"
+
+namespace {
+
+struct Alloc { char* base; size_t size; int device; };          // device -1: page-locked host memory
+struct Launch { const void* func; };
+Alloc allocs[256];
+int n_allocs = 0;
+const void* kernels[256];                                       // filled while the library is being loaded
+const char* kernel_names[256];
+int n_kernels = 0;
+int current_device = 0;
+int n_launches = 0, n_copies = 0, n_faults = 0;
+hipError_t capture_query = hipSuccess;
+char streams[64];
+int stream_device[64], n_streams = 1;                           // 0 is the null stream
+char events[1024];
+int n_events = 0;
+
+const Alloc* find(const void* p)
+{
+    for (int i = 0; i < n_allocs; ++i)
+        if ((const char*)p >= allocs[i].base && (const char*)p < allocs[i].base + allocs[i].size) return &allocs[i];
+    return nullptr;
+}
+hipError_t allocate(void** out, size_t bytes, int device)
+{
+    *out = aligned_alloc(4096, (bytes + 4095) / 4096 * 4096);
+    allocs[n_allocs++] = {(char*)*out, bytes, device};
+    return hipSuccess;
+}
+hipError_t release(void* p)
+{
+    for (int i = 0; i < n_allocs; ++i)
+        if (allocs[i].base == p) allocs[i] = allocs[--n_allocs];
+    free(p);
+    return hipSuccess;
+}
+int device_of(hipStream_t s) { return s ? stream_device[(char*)s - streams] : current_device; }
+
+// What a kernel on `device` may touch.
+bool reachable(const void* p, size_t bytes, int device)
+{
+    const Alloc* a = find(p);
+    return a && (a->device == -1 || a->device == device) && bytes <= (size_t)(a->base + a->size - (const char*)p);
+}
+void run_link_copy(const zi::CopyArgs& a, int device, bool report)
+{
+    const int64_t block = report ? zi::kCopyBlockElems : zi::kCopyPieceElems;
+    for (uint32_t i = 0; i < a.n_segs; ++i) {
+        const zi::CopySeg& s = a.t[i];
+        if (!reachable(s.src, (size_t)s.elems * 2, device) || !reachable(s.dst, (size_t)s.elems * 2, device)) ++n_faults;
+        memcpy(s.dst, s.src, (size_t)s.elems * 2);
+        for (int64_t k = 0; report && k * block < s.elems; ++k) __atomic_store_n(a.flags + s.flag + k, a.serial, __ATOMIC_RELEASE);
+    }
+}
+
+thread_local struct { dim3 grid, block; size_t shared; hipStream_t stream; } configured;
+
+}  // namespace
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*)
+{
+    kernels[n_kernels] = host;
+    kernel_names[n_kernels++] = name;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t stream)
+{
+    configured = {grid, block, shared, stream};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hipStream_t* stream)
+{
+    *grid = configured.grid; *block = configured.block; *shared = configured.shared; *stream = configured.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s)
+{
+    ++n_launches;
+    for (int i = 0; i < n_kernels; ++i)
+        if (kernels[i] == f && strstr(kernel_names[i], "link_copy_kernel"))
+            run_link_copy(*(const zi::CopyArgs*)args[0], device_of(s), strstr(kernel_names[i], "ILb1E") != nullptr);
+    return hipSuccess;
+}
+hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sh, hipStream_t s, hipEvent_t, hipEvent_t, int)
+{
+    return hipLaunchKernel(f, g, b, args, sh, s);
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error of the stand-in"; }
+hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = current_device; return hipSuccess; }
+hipError_t hipSetDevice(int d) { current_device = d; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { return allocate(p, n, current_device); }
+hipError_t hipFree(void* p) { return release(p); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return allocate(p, n, -1); }
+hipError_t hipHostFree(void* p) { return release(p); }
+hipError_t hipGetSymbolAddress(void** p, const void*)
+{
+    static void* scratch = nullptr;
+    if (!scratch) (void)allocate(&scratch, sizeof(zi::NormPartial) * ZI_NOALLOC_MAX_PARTIALS, 0);
+    *p = scratch;
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p)
+{
+    memset(at, 0, sizeof *at);
+    const Alloc* a = find(p);
+    at->type = !a ? hipMemoryTypeUnregistered : a->device < 0 ? hipMemoryTypeHost : hipMemoryTypeDevice;
+    at->device = a && a->device >= 0 ? a->device : 0;
+    at->devicePointer = a ? const_cast<void*>(p) : nullptr;
+    return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p)
+{
+    const Alloc* a = find(p);
+    if (!a) return hipErrorNotFound;
+    *base = a->base;
+    *size = a->size;
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t)
+{
+    ++n_copies;
+    memcpy(dst, src, n);
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned)
+{
+    stream_device[n_streams] = current_device;
+    *s = (hipStream_t)(streams + n_streams++);
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = device_of(s); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st)
+{
+    *st = hipStreamCaptureStatusNone;
+    return capture_query;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)(events + n_events++); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+}
+
+#define CHECK(cond)                                                                                     \
+    do {                                                                                                \
+        if (!(cond)) {                                                                                  \
+            fprintf(stderr, "CHECK failed: %s (line %d; %s)\n", #cond, __LINE__, zi_last_error());      \
+            return 1;                                                                                   \
+        }                                                                                               \
+    } while (0)
+
+static void* on_device(size_t bytes, int device) { void* p; (void)allocate(&p, bytes, device); memset(p, 0, bytes); return p; }
+static zi_adamw_config config()
+{
+    zi_adamw_config c{};
+    c.lr = 1e-3f; c.beta1 = 0.9f; c.beta2 = 0.999f; c.eps = 1e-8f; c.weight_decay = 0.01f; c.step = 10; c.loss_scale = 1.0f;
+    return c;
+}
+
+// Gradients and copies on another device than the engine's: the copies are the runtime's, no kernel touches them.
+static int peer()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    CHECK(zi_engine_set_option(e, ZI_OPT_HOST_RING_SLOTS, 3) == ZI_OK);
+    for (int owner = 0; owner < 2; ++owner) {
+        const size_t bytes = 40000;
+        uint16_t* src = (uint16_t*)on_device(bytes, owner);
+        for (size_t i = 0; i < bytes / 2; ++i) src[i] = (uint16_t)(i * 7 + 1);
+        uint16_t* dst = (uint16_t*)on_device(bytes, -1);
+        CHECK(zi_grad_offload(e, src, dst, bytes, nullptr) == ZI_OK);
+        CHECK(zi_grad_offload_wait(e) == ZI_OK);
+        CHECK(n_faults == 0 && memcmp(src, dst, bytes) == 0);
+    }
+    const int64_t sizes[] = {70001, 5, 16384, 40003};
+    std::vector<std::vector<float>> state[2];
+    std::vector<std::vector<uint16_t>> copies[2];
+    for (int mixed = 0; mixed < 2; ++mixed) {                  // all on the engine's device, then every other tensor elsewhere
+        std::vector<zi_tensor> list;
+        for (int i = 0; i < 4; ++i) {
+            const size_t n = (size_t)sizes[i];
+            zi_tensor t{};
+            float* a[3];
+            for (int w = 0; w < 3; ++w) {
+                state[mixed].emplace_back(n);
+                a[w] = state[mixed].back().data();
+                for (size_t k = 0; k < n; ++k) a[w][k] = (float)((k * 13 + 5 * (size_t)w) % 997) * 1e-4f;
+            }
+            uint16_t* g = (uint16_t*)on_device(n * 2, mixed && i % 2 == 0 ? 1 : 0);
+            for (size_t k = 0; k < n; ++k) g[k] = (uint16_t)(0x3A00 + k % 200);
+            t.p = a[0]; t.m = a[1]; t.v = a[2]; t.g = g;
+            t.p_lp = i == 1 ? nullptr : on_device(n * 2, mixed && i >= 2 ? 1 : 0);
+            t.numel = sizes[i];
+            list.push_back(t);
+        }
+        const zi_adamw_config c = config();
+        for (int twice = 0; twice < 2; ++twice)
+            CHECK(zi_adamw_step_cpu(e, list.data(), 4, ZI_BF16, &c, nullptr, 3, nullptr) == ZI_OK);
+        CHECK(n_faults == 0);
+        zi_stream_stats st{};
+        CHECK(zi_engine_last_stats(e, &st) == ZI_OK);
+        CHECK(st.bytes_d2h == 2 * (70001 + 5 + 16384 + 40003) && st.bytes_h2d == 2 * (70001 + 16384 + 40003));
+        for (int i = 0; i < 4; ++i)
+            if (list[(size_t)i].p_lp)
+                copies[mixed].emplace_back((uint16_t*)list[(size_t)i].p_lp, (uint16_t*)list[(size_t)i].p_lp + sizes[i]);
+    }
+    CHECK(state[0] == state[1] && copies[0] == copies[1]);
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}};
+    for (const auto& t : all)
+        if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
+    fprintf(stderr, "which check?\n");
+    return 2;
+}
