@@ -27,6 +27,15 @@ namespace host {
 zi_status fail(zi_status st, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 const char* last_error();
 
+// A caller's size may be anything: whether [p, p + bytes) would pass the end of the address space, and whether it lies
+// in [lo, hi), without a sum that wraps around.
+inline bool wraps_around(const void* p, size_t bytes) { return bytes > UINTPTR_MAX - reinterpret_cast<uintptr_t>(p); }
+inline bool lies_within(const void* p, size_t bytes, uintptr_t lo, uintptr_t hi)
+{
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p);
+    return at >= lo && at <= hi && bytes <= hi - at;
+}
+
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 inline zi_status check_dtype(int dt)

@@ -248,7 +248,7 @@ zi_status classify_array(PointerChecker& reach, HostRanges& pinned, const void* 
     if (kind == -2) return fail(ZI_ERR_HIP, "no usable HIP device (pointer query failed)");
     if (kind < 0) return fail(ZI_ERR_INVALID_ARG, "tensor %d: %s is neither device nor host memory", tensor, name);
     if (kind == 0) return reach.check(p, bytes, tensor, name);
-    const int last = memory_kind(static_cast<const char*>(p) + bytes - 1);
+    const int last = wraps_around(p, bytes) ? -1 : memory_kind(static_cast<const char*>(p) + bytes - 1);
     if (last != kind)
         return fail(ZI_ERR_INVALID_ARG, "tensor %d: %s (%zu bytes) does not lie in one kind of host memory", tensor,
                     name, bytes);

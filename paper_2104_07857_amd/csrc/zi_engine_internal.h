@@ -45,9 +45,8 @@ struct HostRanges {
 
     const Range* find(const void* p, size_t bytes) const
     {
-        const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
         for (int i = 0; i < n_known; ++i)
-            if (lo >= known[i].lo && lo + bytes <= known[i].hi) return &known[i];
+            if (lies_within(p, bytes, known[i].lo, known[i].hi)) return &known[i];
         return nullptr;
     }
 
@@ -65,7 +64,7 @@ struct HostRanges {
         }
         const uintptr_t at = reinterpret_cast<uintptr_t>(p), dev = reinterpret_cast<uintptr_t>(attr.devicePointer);
         const uintptr_t lo = reinterpret_cast<uintptr_t>(base);
-        if (dev < lo || dev + bytes > lo + size) return;
+        if (!lies_within(attr.devicePointer, bytes, lo, lo + size)) return;
         known[next] = {at - (dev - lo), at - (dev - lo) + size, (ptrdiff_t)(dev - at)};
         next = (next + 1) % 8;
         if (n_known < 8) ++n_known;

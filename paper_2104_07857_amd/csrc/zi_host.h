@@ -56,25 +56,24 @@ struct PointerChecker {
     // Whether the array lies in an allocation that has been looked up.
     bool covers(const void* p, size_t bytes) const
     {
-        const uintptr_t lo = reinterpret_cast<uintptr_t>(p), hi = lo + bytes;
         for (int i = 0; i < n_known; ++i)
-            if (lo >= known[i].lo && hi <= known[i].hi) return true;
+            if (lies_within(p, bytes, known[i].lo, known[i].hi)) return true;
         return false;
     }
 
     zi_status check(const void* p, size_t bytes, int tensor, const char* name)
     {
         if (!p || bytes == 0 || covers(p, bytes)) return ZI_OK;
-        const uintptr_t lo = reinterpret_cast<uintptr_t>(p), hi = lo + bytes;
         hipDeviceptr_t base = nullptr;
         size_t size = 0;
         bool inside = false;
         if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess && size > 0) {
             const uintptr_t blo = reinterpret_cast<uintptr_t>(base);
-            inside = lo >= blo && hi <= blo + size;
+            inside = lies_within(p, bytes, blo, blo + size);
         } else {
             (void)hipGetLastError();
         }
+        if (wraps_around(p, bytes)) return fail(ZI_ERR_INVALID_ARG, "tensor %d: %s (%zu bytes) is no array", tensor, name, bytes);
         // one allocation is one kind of memory: its first byte speaks for all of it
         const void* ends[2] = {p, static_cast<const char*>(p) + bytes - 1};
         for (int i = 0; i < (inside ? 1 : 2); ++i) {

@@ -236,9 +236,55 @@ static int peer()
     return 0;
 }
 
+// Element counts whose byte counts, or addresses of whose ends, pass the end of the 64-bit range: refused, with nothing
+// launched, also behind a tensor that has made the allocations known.
+static int sizes()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    CHECK(zi_engine_set_option(e, ZI_OPT_HOST_RING_SLOTS, 3) == ZI_OK);
+    const int64_t n = 5000, huge[] = {INT64_MAX, INT64_MAX - 1000, INT64_MAX / 2 + 1, INT64_MAX / 2 + 3, INT64_MAX / 4 + 1};
+    const zi_adamw_config c = config();
+    char* out = (char*)on_device(64 * 1024 * 8, 0);                // the norm's workspace, and room for its result
+    zi_norm_result* norm = (zi_norm_result*)(out + zi_norm_workspace_bytes(0, 0));
+    for (int host = 0; host < 2; ++host) {                         // p, m, v; the gradients follow them in the streamed calls
+        char* a[4];
+        for (char*& x : a) x = (char*)on_device(8 * n, host ? -1 : 0);
+        char* g_device = (char*)on_device(8 * n, 0);
+        for (int known = 0; known < 2; ++known)
+            for (const int64_t bad : huge) {
+                zi_tensor t[2]{};
+                for (int i = 0; i < 2; ++i) {
+                    t[i].p = a[0] + 4 * n * i; t[i].m = a[1] + 4 * n * i; t[i].v = a[2] + 4 * n * i;
+                    t[i].g = a[3] + 4 * n * i;
+                    t[i].numel = n;
+                }
+                t[1].numel = bad;
+                const zi_tensor* list = known ? t : t + 1;
+                const int32_t count = known ? 2 : 1;
+                n_launches = n_copies = 0;
+                CHECK(zi_grad_norm(list, count, ZI_BF16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), nullptr) < 0);
+                CHECK(zi_grad_norm_noalloc(list, count, ZI_BF16, 1.0f, norm, nullptr) < 0);
+                CHECK(zi_grad_norm_streamed(e, list, count, ZI_BF16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), nullptr) < 0);
+                CHECK(zi_adamw_step(list, count, ZI_BF16, &c, nullptr, nullptr) < 0);
+                if (host) {
+                    CHECK(zi_adamw_step_streamed(e, list, count, ZI_BF16, &c, nullptr, nullptr) < 0);
+                    t[0].g = g_device;
+                    t[1].g = g_device + 4 * n;
+                    CHECK(zi_adamw_step_streamed(e, list, count, ZI_BF16, &c, nullptr, nullptr) < 0);
+                    CHECK(zi_adamw_step_cpu(e, list, count, ZI_BF16, &c, nullptr, 2, nullptr) < 0);
+                    CHECK(zi_grad_offload(e, g_device, a[3], (size_t)bad * 2, nullptr) < 0);
+                }
+                CHECK(n_launches == 0 && n_copies == 0);
+            }
+    }
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");
