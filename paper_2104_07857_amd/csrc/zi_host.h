@@ -137,13 +137,14 @@ inline int choose_head(const void* p, const void* m, const void* v, const void* 
 #endif
 constexpr int64_t kSoloTiles = ZI_SOLO_TILES;
 
-// Whether a launch that need not wait for the one in front of it may say so: not while the stream is captured.
-inline hipError_t may_overlap(hipStream_t stream, bool& yes)
+// Whether a launch that need not wait for the one in front of it may say so: not while the stream is captured, nor
+// where that cannot be told (the query fails for the null stream while another stream is captured; launches do not).
+inline bool may_overlap(hipStream_t stream)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(stream, &capture);
-    yes = e == hipSuccess && capture == hipStreamCaptureStatusNone;
-    return e;
+    if (hipStreamIsCapturing(stream, &capture) == hipSuccess) return capture == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Issues the fused step over a list of device-resident segments.
@@ -242,9 +243,7 @@ struct StepIssuer {
     hipError_t issue_held(bool last)
     {
         if (held_tiles == 0) return hipSuccess;
-        bool any_order = false;
-        if (!last && launches > 0 && held_tiles <= kOverlapTiles && last_tiles <= kOverlapTiles)
-            if (const hipError_t e = may_overlap(stream, any_order); e != hipSuccess) return e;
+        const bool any_order = !last && launches > 0 && held_tiles <= kOverlapTiles && last_tiles <= kOverlapTiles && may_overlap(stream);
         ++launches;
         const uint32_t n = last_tiles = held_tiles;
         held_tiles = 0;
@@ -424,9 +423,7 @@ struct LinkIssuer {
     hipError_t issue_held(bool last)
     {
         if (!held) return hipSuccess;
-        bool any_order = false;
-        if (!last && launches > 0)
-            if (const hipError_t e = may_overlap(stream, any_order); e != hipSuccess) return e;
+        const bool any_order = !last && launches > 0 && may_overlap(stream);
         ++launches;
         held = false;
         return zi::launch_step_link(args[now ^ 1], dt, l2, any_order, stream);
@@ -532,8 +529,7 @@ struct NormIssuer {
         a.partials = partials + used;
         // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
         // final sum are ordinary launches (the same order as in StepIssuer).
-        bool any_order = false;
-        if (used > 0 && (e = may_overlap(s, any_order)) != hipSuccess) return e;
+        const bool any_order = used > 0 && may_overlap(s);
         e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
         ++launches;
         used += blocks;

@@ -282,9 +282,51 @@ static int sizes()
     return 0;
 }
 
+// The query whether a stream is being captured fails for the null stream while another stream is: calls of several
+// launches go on as before.
+static int capture()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    const zi_adamw_config c = config();
+    constexpr int kMost = 700;                                     // three launches each of the step's kernels and the reduction
+    const int64_t n = 600;
+    char* device = (char*)on_device((size_t)kMost * n * 16, 0);
+    char* pinned = (char*)on_device((size_t)kMost * n * 16, -1);
+    char* out = (char*)on_device(64 * 1024 * 8, 0);
+    zi_norm_result* norm = (zi_norm_result*)(out + zi_norm_workspace_bytes(0, 0));
+    for (int32_t count : {60, 200, kMost})
+        for (int flat = 0; flat < 2; ++flat)
+            for (int host = 0; host < 2; ++host) {
+                std::vector<zi_tensor> list((size_t)count);
+                for (int32_t i = 0; i < count; ++i) {
+                    char* a = host ? pinned : device;
+                    const int64_t at = flat ? (int64_t)i * n : (int64_t)((i * 7) % count) * n;
+                    zi_tensor& t = list[(size_t)i];
+                    t.p = a + 4 * at; t.m = a + 4 * (kMost * n + at); t.v = a + 4 * (2 * kMost * n + at);
+                    t.g = device + 2 * (6 * kMost * n + at); t.p_lp = device + 2 * (7 * kMost * n + at);
+                    t.numel = n;
+                }
+                int launches[2][3] = {};
+                for (int fails = 0; fails < 2; ++fails) {
+                    capture_query = fails ? hipErrorStreamCaptureImplicit : hipSuccess;
+                    auto counted = [&](zi_status st, int which) { launches[fails][which] = st == ZI_OK ? n_launches : -1; n_launches = 0; };
+                    n_launches = 0;
+                    counted(zi_grad_norm(list.data(), count, ZI_BF16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), nullptr), 0);
+                    if (host) counted(zi_adamw_step_streamed(e, list.data(), count, ZI_BF16, &c, nullptr, nullptr), 1);
+                    else      counted(zi_adamw_step(list.data(), count, ZI_BF16, &c, nullptr, nullptr), 2);
+                }
+                capture_query = hipSuccess;
+                CHECK(launches[0][0] > 0 && launches[0][host ? 1 : 2] > 0);
+                CHECK(!memcmp(launches[0], launches[1], sizeof launches[0]));
+            }
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");

@@ -56,3 +56,40 @@ def test_norm_and_step_replay_from_a_captured_graph():
             for x, y in zip(a, b):
                 assert torch.equal(x, y), f"replay {replay}, tensor {i}"
     assert not torch.equal(eager[0][0], to_dev(host[0][0]))      # the steps did change the state
+
+
+@pytest.mark.parametrize("count", [60, 140, 700])
+def test_a_call_on_the_null_stream_while_another_stream_is_captured(count):
+    """A call of several launches on the legacy null stream is carried out although a blocking stream is being captured
+    (the runtime then refuses to say whether the null stream is); the same bits as without the capture."""
+    import ctypes
+    hip = zi.lib()                       # symbols of the runtime that the library is linked with
+    dt, rng = zi.ZI_BF16, np.random.default_rng(count)
+    sizes = [int(x) for x in rng.integers(1, 3000, count)]
+    starts = np.cumsum([0] + sizes)
+    p, m, v, g = gen_numpy(zi_synth.StateSpec(4, dt), int(starts[-1]))
+    cfg = zi_cfg(zi_synth.workload("c4"))
+    capturing = ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(capturing)) == 0
+    results = []
+    for captured in (False, True):
+        bufs = [to_dev(a.copy()) for a in (p, m, v, g)] + [torch.zeros(g.size, dtype=torch.int16, device="cuda:0")]
+        tl = zi.make_tensors([tuple(b[s:s + n] for b in bufs) + (n,) for s, n in zip(starts.tolist(), sizes)])
+        nb = NormBuffers()
+        torch.cuda.synchronize()
+        if captured:
+            assert hip.hipStreamBeginCapture(capturing, 2) == 0            # relaxed
+        try:
+            zi.zi_grad_norm(tl, dt, 1.0, nb.out, nb.ws, stream=0)
+            zi.zi_adamw_step(tl, dt, cfg, nb.out, 0)
+        finally:
+            if captured:
+                graph = ctypes.c_void_p()
+                assert hip.hipStreamEndCapture(capturing, ctypes.byref(graph)) == 0
+                if graph.value:
+                    hip.hipGraphDestroy(graph)
+        torch.cuda.synchronize()
+        results.append(bufs + [nb.out])
+    hip.hipStreamDestroy(capturing)
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
