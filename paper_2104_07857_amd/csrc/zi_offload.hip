@@ -94,7 +94,7 @@ struct CpuBlock {
     int64_t n;
     const uint32_t* arrived;      // flag of the block's gradients (null: they are in host memory already)
     uint16_t* lp_device;          // where the block of the copy goes (null: it is in its place)
-    bool lp_peer;                 // ... in the memory of another device than the engine's
+    bool lp_by_copy;              // ... by the runtime's copy, not by a kernel
 };
 
 // Tasks are blocks of link_copy_kernel: 64 KiB of each fp32 array.  A chunk of 2^24 elements is 1024
@@ -102,6 +102,11 @@ struct CpuBlock {
 // other (2^18-element tasks measured 4% slower, 2^16 2% slower).
 constexpr int64_t kCpuBlockElems = zi::kCopyBlockElems;
 // Stepped blocks whose copy the calling thread sends up together while the others go on: 2 MiB.
+// A use of one segment that is no longer than that goes up when it is stepped, beside the next use, and then the copy
+// engine is the cheaper way: per call with 16 threads, us, kernel / copy (three runs each), 8.4e6 elements in chunks of
+// 1 MiB 1914..1942 / 1728..1846, 1.7e7 in chunks of 2 MiB 3087..3095 / 2830..2956, in chunks of 4 MiB 2466..2608 /
+// 2360..2632; 3.4e7 in chunks of 8 MiB 4442..5478 / 5287..5483.  For the last use, whose upload everybody waits for, the
+// kernel is: 3.0e4 elements 83..93 / 89..96.
 constexpr size_t kUploadBlocks = 64;
 
 // One slot use.  A thread steps a block as soon as the block's gradients have arrived, and the calling thread,
@@ -121,8 +126,7 @@ struct CpuJob {
     size_t sent = 0;              // blocks whose copy is on its way (or in its place)
     hipError_t upload_error = hipSuccess;
 
-    // Sends up the copies of blocks [sent, to), neighbours of one segment as one, by a kernel or, to another
-    // device's memory, by the runtime's copy.
+    // Sends up the copies of blocks [sent, to), neighbours of one segment as one.
     void upload(size_t to)
     {
         CopyIssuer up(e->s_h2d, nullptr, 0);
@@ -132,12 +136,12 @@ struct CpuJob {
             size_t next = sent + 1;
             if (b.lp_device)
                 while (next < to && blocks[next].lp_device == b.lp_device + n && blocks[next].lp == b.lp + n &&
-                       blocks[next].lp_peer == b.lp_peer)
+                       blocks[next].lp_by_copy == b.lp_by_copy)
                     n += blocks[next++].n;
             if (b.lp_device) {
-                upload_error = b.lp_peer ? hipMemcpyAsync(b.lp_device, b.lp, (size_t)n * 2, hipMemcpyHostToDevice, e->s_h2d)
-                                         : up.add(b.lp, b.lp_device, n, 0);
-                e->stats.n_copies += b.lp_peer;
+                upload_error = b.lp_by_copy ? hipMemcpyAsync(b.lp_device, b.lp, (size_t)n * 2, hipMemcpyHostToDevice, e->s_h2d)
+                                            : up.add(b.lp, b.lp_device, n, 0);
+                e->stats.n_copies += b.lp_by_copy;
                 e->stats.bytes_h2d += (uint64_t)n * 2;
             }
             sent = next;
@@ -270,8 +274,9 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     const auto t0 = std::chrono::steady_clock::now();
     // Ring slot u mod n_h carries slot use u: its gradient half is filled by a kernel that reports every block
     // (link_copy_kernel), the CPUs step the use (reading that half, writing the copy half), and the copy half is
-    // sent up by the same kind of kernel.  Fetches run `ahead` uses in front of the CPUs; a slot is fetched into again
-    // only after the upload of its previous use has left it, which by then is two steps old.
+    // sent up by the same kind of kernel or by the runtime's copy (kUploadBlocks; arrays of another device).
+    // Fetches run `ahead` uses in front of the CPUs; a slot is fetched into again only after the upload of its
+    // previous use has left it, which by then is two steps old.
     const int ahead = n_h >= 3 ? n_h - 2 : 1;
     const uint32_t first_serial = e->fill_serial + 1;         // of use 0; use u has first_serial + u
     e->fill_serial += (uint32_t)n_uses;
@@ -316,6 +321,8 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
             const uint32_t* flags = n_h > 0 ? e->fill_flags + (size_t)h * e->flags_per_slot : nullptr;
             blocks.clear();
             bool fetched = false, peer = false, upload = false;
+            const bool in_one = use_begin[(size_t)u + 1] - use_begin[(size_t)u] == 1 && u + 1 < n_uses &&
+                                blocks_of(segs[use_begin[(size_t)u]].count) <= (int64_t)kUploadBlocks;
             for (size_t j = use_begin[(size_t)u]; j < use_begin[(size_t)u + 1]; ++j) {
                 const Segment& sg = segs[j];
                 const StateSrc& S = e->src[(size_t)sg.tensor];
@@ -331,7 +338,7 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
                     const int64_t at = sg.elem_offset + o;
                     blocks.push_back({(float*)S.ptr[0] + at, (float*)S.ptr[1] + at, (float*)S.ptr[2] + at, g + o,
                                       lp ? lp + o : nullptr, nb, S.g_host || S.g_peer ? nullptr : flags + blocks.size(),
-                                      up ? (uint16_t*)S.p_lp + at : nullptr, S.lp_peer});
+                                      up ? (uint16_t*)S.p_lp + at : nullptr, S.lp_peer || in_one});
                 }
             }
             // A ring slot whose upload of `n_h` uses ago is still leaving must not be written yet

@@ -324,9 +324,44 @@ static int capture()
     return 0;
 }
 
+// How the copies of the CPU placement go up: what one slot use takes, by kernels, except that of a use of one segment of
+// at most 64 blocks with more uses behind it.
+static int uploads()
+{
+    const struct { size_t chunk; int64_t numel; int32_t tensors; int copies; } cases[] = {
+        {64 << 10, 16384, 1, 0}, {64 << 10, 5 * 16384, 1, 4}, {64 << 10, 5 * 16384 + 1, 1, 5}, {1 << 20, 4 * 262144, 1, 3},
+        {64 << 10, 1000, 40, 0}, {4 << 20, 3 << 20, 1, 2}, {8 << 20, 3 << 21, 1, 0}};
+    for (const auto& k : cases) {
+        zi_engine* e = nullptr;
+        CHECK(zi_engine_create(&e, 0, k.chunk, 3) == ZI_OK);
+        CHECK(zi_engine_set_option(e, ZI_OPT_HOST_RING_SLOTS, 4) == ZI_OK);
+        const size_t all = (size_t)k.numel * (size_t)k.tensors;
+        std::vector<float> state(3 * all);
+        uint16_t* g = (uint16_t*)on_device(2 * all, 0);
+        uint16_t* lp = (uint16_t*)on_device(2 * all, 0);
+        for (size_t i = 0; i < all; ++i) state[i] = (float)(i % 1000);
+        std::vector<zi_tensor> list((size_t)k.tensors);
+        for (size_t i = 0; i < list.size(); ++i) {
+            const size_t at = i * (size_t)k.numel;
+            list[i] = {state.data() + at, state.data() + all + at, state.data() + 2 * all + at, g + at, lp + at, k.numel};
+        }
+        zi_adamw_config c = config();
+        c.weight_decay = 0.0f;                     // with zero gradients and moments p stays, and the copy is p
+        CHECK(zi_adamw_step_cpu(e, list.data(), k.tensors, ZI_BF16, &c, nullptr, 3, nullptr) == ZI_OK);
+        zi_stream_stats st{};
+        CHECK(zi_engine_last_stats(e, &st) == ZI_OK);
+        CHECK(st.n_copies == k.copies && st.bytes_h2d == 2 * all && n_faults == 0);
+        for (size_t i = 0; i < all; i += 4096) CHECK(lp[i] == (uint16_t)(__builtin_bit_cast(uint32_t, (float)(i % 1000)) >> 16) || i % 1000 > 255);
+        CHECK(zi_engine_destroy(e) == ZI_OK);
+        release(g);
+        release(lp);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");
