@@ -44,12 +44,17 @@ constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 ele
 // a contiguous run of tiles per workgroup 12.2 / 94 / 378 / 101, half the loads in flight 13.0 / 92 / 376 / 100,
 // single-wavefront workgroups 12.7 / 92 / 373 / 105 at best.
 constexpr int kNormGroups = 512;
-// Calls of up to this many elements (256 MiB, the size of the memory-side cache) read the gradients with ordinary
-// loads, which leave them there for the step that reads them next; streaming loads pass the cache by.  Norm and
-// step together in us, streaming -> ordinary: 1.7e7 elements 88.8 -> 84.5, 6.7e7 322 -> 309, 1.3e8 647 -> 621.  The
-// reduction itself takes 10% longer so (44 -> 49 us at 1.3e8), which is why larger calls, of which only a part
-// would still be there, stay with streaming loads.
-constexpr int64_t kNormKeepElems = (int64_t)1 << 27;
+// Calls of up to this many elements (176 of the 256 MiB of the memory-side cache) read the gradients with ordinary
+// loads, which leave them there for the step that reads them next; streaming loads pass the cache by.  In us, streaming /
+// ordinary loads / the reduction with workgroups of its own for every tensor that was here before:
+//   elements           3.4e7               6.7e7               9.2e7               1.0e8               1.3e8
+//   norm and step      172 / 165 / 172     326 / 313 / 328     444 / 428 / 447     488 / 469 / 489     653 / 627 / 657
+//   norm alone, cold   15.2 / 15.8 / 16.9  25.5 / 27.1 / 27.5  33.1 / 35.4 / 36.0  35.6 / 38.4 / 37.7  45.9 / 49.9 / 48.9
+//   norm of gradients a kernel has just written
+//                      15.5 / 14.4 / 17.1  24.9 / 25.0 / 26.6  26.9 / 27.8 / 34.1  33 / 34 / 38        39 / 57 / 44
+// A caller that only wants the norm pays up to 7% here for what a caller that steps gains 3 to 5% of a ten times longer
+// time.  The line is drawn where the reduction alone would become slower than it was before.
+constexpr int64_t kNormKeepElems = (int64_t)11 << 23;
 // Gradients in host memory are bound by the link, which few requests in flight fill: GB/s by workgroups
 // 32: 55.9, 64: 57.5, 128: 57.4, 256: 56.4, 1024: 55.9.
 constexpr int kNormLinkGroups = 64;

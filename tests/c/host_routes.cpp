@@ -28,6 +28,7 @@ const char* kernel_names[256];
 int n_kernels = 0;
 int current_device = 0;
 int n_launches = 0, n_copies = 0, n_faults = 0;
+const char* last_partial_sum = "";                             // name of the partial-sum kernel launched last
 hipError_t capture_query = hipSuccess;
 char streams[64];
 int stream_device[64], n_streams = 1;                           // 0 is the null stream
@@ -98,9 +99,12 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s)
 {
     ++n_launches;
-    for (int i = 0; i < n_kernels; ++i)
-        if (kernels[i] == f && strstr(kernel_names[i], "link_copy_kernel"))
+    for (int i = 0; i < n_kernels; ++i) {
+        if (kernels[i] != f) continue;
+        if (strstr(kernel_names[i], "sumsq_partial_kernel")) last_partial_sum = kernel_names[i];
+        if (strstr(kernel_names[i], "link_copy_kernel"))
             run_link_copy(*(const zi::CopyArgs*)args[0], device_of(s), strstr(kernel_names[i], "ILb1E") != nullptr);
+    }
     return hipSuccess;
 }
 hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sh, hipStream_t s, hipEvent_t, hipEvent_t, int)
@@ -359,9 +363,33 @@ static int uploads()
     return 0;
 }
 
+// Reductions of up to 176 MiB of gradients in HBM, in one tensor or several, read with ordinary loads; longer ones and
+// those over the link with streaming loads.
+static int loads()
+{
+    const int64_t most = (int64_t)11 << 23;
+    char* out = (char*)on_device(64 * 1024 * 8, 0);
+    zi_norm_result* norm = (zi_norm_result*)(out + zi_norm_workspace_bytes(0, 0));
+    void* g;
+    (void)allocate(&g, 2 * (size_t)most + 64, 0);
+    for (int64_t n : {most, most + 1})
+        for (int parts = 1; parts <= 3; parts += 2)
+            for (int noalloc = 0; noalloc < 2; ++noalloc) {
+                zi_tensor t[3]{};
+                for (int i = 0; i < parts; ++i) {
+                    t[i].numel = i + 1 < parts ? n / parts : n - (parts - 1) * (n / parts);
+                    t[i].g = (uint16_t*)g + i * (n / parts);
+                }
+                CHECK((noalloc ? zi_grad_norm_noalloc(t, parts, ZI_FP16, 1.0f, norm, nullptr)
+                               : zi_grad_norm(t, parts, ZI_FP16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), nullptr)) == ZI_OK);
+                CHECK(strstr(last_partial_sum, n <= most ? "ILi1ELb1E" : "ILi1ELb0E"));
+            }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}, {"loads", loads}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");
