@@ -153,7 +153,8 @@ def _host_array(a, where):
 def test_seeded_random_streamed_lists(seed):
     """The streamed step on drawn lists: 1-120 tensors from empty to several chunks long, chunk size and
     slot count drawn too, state pinned or ordinary (ring), gradients / copy on the device or in host
-    memory, with or without a norm result.  Compared with the oracle element by element."""
+    memory, with or without a norm result, every third draw at the default pacing (over the link, if page-locked) and the
+    others at a chosen one (chunk by chunk).  Compared with the oracle element by element."""
     rng = np.random.default_rng(0x5EA0 + seed)
     dt = int(rng.choice([zi.ZI_BF16, zi.ZI_FP16]))
     chunk_elems = int(rng.choice([1024, 4096, 16384]))
@@ -180,6 +181,7 @@ def test_seeded_random_streamed_lists(seed):
     needs_ring = "page" in (state_where, g_where, lp_where)
     eng = zi.zi_engine_create(0, 4 * chunk_elems, n_slots)
     try:
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, seed % 3)
         if needs_ring:
             zi.zi_engine_set_option(eng, zi.ZI_OPT_HOST_COPY_THREADS, int(rng.integers(1, 5)))
             zi.zi_engine_set_option(eng, zi.ZI_OPT_HOST_RING_SLOTS, int(rng.integers(2, 6)))
@@ -205,6 +207,7 @@ def test_seeded_random_streamed_lists(seed):
         stats = zi.zi_engine_last_stats(eng)
         per_elem = 12 + (2 if g_where != "dev" else 0)
         assert stats.n_slot_uses == uses and stats.bytes_h2d == per_elem * sum(sizes)
+        assert (stats.n_copies == 0) == (seed % 3 == 0 and not needs_ring or sum(sizes) == 0)
         rep = ""
         for i, (e, (hs, hg, hl)) in enumerate(zip(exp, holders)):
             got_lp = None

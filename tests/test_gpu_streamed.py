@@ -1,4 +1,6 @@
-"""The streamed step (state in pinned host memory, chunked through HBM) against the oracle and the resident step."""
+"""The streamed step (state in pinned host memory) against the oracle and the resident step, by both of its routes: over
+the link by the step's kernel, which the default pacing takes for page-locked state, and chunk by chunk through HBM, which
+a chosen pacing takes."""
 import os
 import tempfile
 
@@ -40,16 +42,29 @@ def _stream_list(engine, host, dt, ocfg, zcfg, use_norm, g_offset=0):
     tl = [(pp, pm, pv, g, lp, g.numel()) for (pp, pm, pv), g, lp in zip(pinned, dg, dlp)]
     st = zi.zi_adamw_step_streamed(engine, tl, dt, zcfg, None if nb is None else nb.out,
                                    torch.cuda.current_stream())
+    if st == zi.ZI_OK:
+        _check_route(engine, _pacing[id(engine)])
     got = [(pp.numpy().copy(), pm.numpy().copy(), pv.numpy().copy(), to_np(lp))
            for (pp, pm, pv), lp in zip(pinned, dlp)]
     return exp, got, dict(status=st, oracle=info, norm=nb.read() if nb else None)
 
 
-@pytest.fixture(scope="module")
-def engine():
+_pacing = {}                                          # of the engines that the fixture makes
+
+
+@pytest.fixture(scope="module", params=[0, 2], ids=["link", "chunks"])
+def engine(request):
     e = zi.zi_engine_create(0, 64 * 1024, 3)          # 16384-element chunks: many slot uses at small sizes
+    zi.zi_engine_set_option(e, zi.ZI_OPT_MAX_INFLIGHT, request.param)
+    _pacing[id(e)] = request.param
     yield e
+    del _pacing[id(e)]
     zi.zi_engine_destroy(e)
+
+
+def _check_route(engine, pacing):
+    """The last call moved page-locked state by the route that the pacing selects."""
+    assert (zi.zi_engine_last_stats(engine).n_copies == 0) == (pacing == 0)
 
 
 @pytest.mark.parametrize("n", [1, 100, 16384 - 8, 16384, 16384 + 1, 5 * 16384 + 777, 40 * 16384])
@@ -103,10 +118,11 @@ def test_ragged_list_with_packing_and_global_clip(engine, g_offset):
     progress(f"streamed ragged (g offset {g_offset}): {uses} slot uses, {st.n_kernels} launches; last {rep}")
 
 
+@pytest.mark.parametrize("pacing", [0, 1, 2])
 @pytest.mark.parametrize("chunk_bytes,slots", [(4096, 2), (4096, 8), (1 << 20, 3), (1 << 22, 4)])
-def test_chunk_size_and_slot_count_do_not_change_a_bit(chunk_bytes, slots):
+def test_chunk_size_and_slot_count_do_not_change_a_bit(chunk_bytes, slots, pacing):
     """Chunked processing equals unchunked processing for any chunk size, including chunks larger than
-    the whole state, and any number of slots."""
+    the whole state, and any number of slots; and so does the kernel over the link."""
     n = 300_007
     w = zi_synth.workload("c2")
     p, m, v, g = gen_numpy(zi_synth.StateSpec(55, zi.ZI_BF16), n)
@@ -117,7 +133,9 @@ def test_chunk_size_and_slot_count_do_not_change_a_bit(chunk_bytes, slots):
     lp = torch.zeros(n, dtype=torch.int16, device="cuda:0")
     eng = zi.zi_engine_create(0, chunk_bytes, slots)
     try:
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, pacing)
         assert zi.zi_adamw_step_streamed(eng, [(pp, pm, pv, dg, lp, n)], zi.ZI_BF16, zi_cfg(w)) == zi.ZI_OK
+        _check_route(eng, pacing)
         assert zi.zi_engine_last_stats(eng).n_slot_uses == -(-n // (chunk_bytes // 4))
     finally:
         zi.zi_engine_destroy(eng)
@@ -135,6 +153,7 @@ def test_streamed_without_low_precision_copy(engine):
     oracle.adamw(pe, me, ve, g, None, zi.ZI_BF16, oracle_cfg(w))
     pp, pm, pv = _pinned(p), _pinned(m), _pinned(v)
     assert zi.zi_adamw_step_streamed(engine, [(pp, pm, pv, to_dev(g), None, n)], zi.ZI_BF16, zi_cfg(w)) == zi.ZI_OK
+    _check_route(engine, _pacing[id(engine)])
     compare_state((pe, me, ve, None), (pp.numpy(), pm.numpy(), pv.numpy(), None), zi.ZI_BF16)
 
 
@@ -224,8 +243,9 @@ def _pinned16(a: np.ndarray) -> torch.Tensor:
     return t
 
 
+@pytest.mark.parametrize("pacing", [0, 2])
 @pytest.mark.parametrize("placement", ["g_pinned", "lp_pinned", "both_pinned", "all_pageable", "g_pageable_state_pinned"])
-def test_gradients_and_copy_in_host_memory(placement):
+def test_gradients_and_copy_in_host_memory(placement, pacing):
     """Gradient-side offload: gradients and / or the low-precision copy live in host memory and travel with
     their chunk of state; the norm is reduced from host-resident gradients too.  Same bits as resident."""
     w = zi_synth.workload("c4")
@@ -233,6 +253,7 @@ def test_gradients_and_copy_in_host_memory(placement):
     eng = zi.zi_engine_create(0, 64 * 1024, 3)
     try:
         zi.zi_engine_set_option(eng, zi.ZI_OPT_HOST_RING_SLOTS, 4)
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, pacing)
         h = 128
         for numel in ([7 * 16384 + 4322], [n for _ in range(2) for (_, n) in zi_synth.transformer_layer_shapes(h)]):
             spec = zi_synth.StateSpec(99 + len(numel), dt, g_std=2e-3)
@@ -259,10 +280,14 @@ def test_gradients_and_copy_in_host_memory(placement):
                 tl.append((sp, sm, sv, sg, slp, g.size))
             nb = NormBuffers()
             zi.zi_grad_norm_streamed(eng, tl, dt, ocfg.loss_scale, nb.out, nb.ws, stream=torch.cuda.current_stream())
+            if placement in ("g_pinned", "both_pinned"):
+                _check_route(eng, pacing)
             sumsq, norm, flag = nb.read()
             assert flag == 0 and abs(sumsq - info["sumsq"]) <= 1e-12 * info["sumsq"]
             st = zi.zi_adamw_step_streamed(eng, tl, dt, zcfg, nb.out, torch.cuda.current_stream())
             assert st == zi.ZI_OK
+            if placement in ("g_pinned", "lp_pinned", "both_pinned"):
+                _check_route(eng, pacing)
             stats = zi.zi_engine_last_stats(eng)
             g_host = placement != "lp_pinned"
             lp_host = placement in ("lp_pinned", "both_pinned", "all_pageable")
@@ -312,6 +337,34 @@ def test_streamed_norm_flags_and_mixed_residency():
         zi.zi_engine_set_option(eng, zi.ZI_OPT_HOST_RING_SLOTS, 0)
         with pytest.raises(zi.ZiError):
             zi.zi_grad_norm_streamed(eng, tl, dt, 8.0, nb.out, nb.ws)
+    finally:
+        zi.zi_engine_destroy(eng)
+
+
+@pytest.mark.parametrize("pacing", [0, 1, 3])
+@pytest.mark.parametrize("sizes", [[1], [32768 + 5], [5, 70_001, 0, 32768], [200_000, 3, 9] + [700] * 60])
+def test_norm_of_page_locked_gradients_by_both_routes(sizes, pacing):
+    """Gradients in page-locked memory with some in HBM between them: read over the link, or brought into the slots chunk by
+    chunk, short enough for one workgroup or not; sum, norm and the flag of the last element."""
+    dt = zi.ZI_BF16
+    gs = [gen_numpy(zi_synth.StateSpec(600 + len(sizes), dt, g_std=1e-2), n, tensor=i)[3] for i, n in enumerate(sizes)]
+    want, _ = oracle.grad_sumsq(gs, dt)
+    eng = zi.zi_engine_create(0, 64 * 1024, 3)
+    try:
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, pacing)
+        for planted in (False, True):
+            if planted:
+                gs[-1][-1] = 0x7F80
+            placed = [to_dev(g) if i % 4 == 3 else _pinned16(g) for i, g in enumerate(gs)]
+            tl = [(None, None, None, x, None, g.size) for x, g in zip(placed, gs)]
+            nb = NormBuffers()
+            zi.zi_grad_norm_streamed(eng, tl, dt, 4.0, nb.out, nb.ws)
+            _check_route(eng, pacing)
+            assert zi.zi_engine_last_stats(eng).bytes_h2d == 2 * sum(g.size for i, g in enumerate(gs) if i % 4 != 3)
+            sumsq, norm, flag = nb.read()
+            assert flag == int(planted)
+            if not planted:                           # double sums of exact squares on both sides
+                assert abs(sumsq - want) <= 1e-12 * want and abs(norm - np.sqrt(want) / 4.0) <= 1e-12 * norm
     finally:
         zi.zi_engine_destroy(eng)
 
@@ -542,7 +595,8 @@ def test_gradient_partitions_drain_while_the_producer_keeps_running():
         zi.zi_engine_destroy(eng)
 
 
-def test_offloaded_gradients_feed_the_streamed_norm_and_step_without_a_host_wait():
+@pytest.mark.parametrize("pacing", [0, 2])
+def test_offloaded_gradients_feed_the_streamed_norm_and_step_without_a_host_wait(pacing):
     """Gradients offloaded with zi_grad_offload are consumed from host memory by zi_grad_norm_streamed and
     zi_adamw_step_streamed on the same engine with no wait in between: the engine orders itself after the
     offload.  Results equal the oracle's."""
@@ -556,12 +610,14 @@ def test_offloaded_gradients_feed_the_streamed_norm_and_step_without_a_host_wait
     hlp = torch.zeros(n, dtype=torch.int16, pin_memory=True)
     eng = zi.zi_engine_create(0, 64 * 1024, 3)
     try:
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, pacing)
         nb = NormBuffers()
         zi.zi_grad_offload(eng, d_g, hg, 2 * n, torch.cuda.current_stream())
         tl = [(pp, pm, pv, hg, hlp, n)]
         zi.zi_grad_norm_streamed(eng, tl, dt, w["loss_scale"], nb.out, nb.ws)
         st = zi.zi_adamw_step_streamed(eng, tl, dt, zi_cfg(w), nb.out)
         assert st == zi.ZI_OK
+        _check_route(eng, pacing)
     finally:
         zi.zi_engine_destroy(eng)
     assert np.array_equal(hg.numpy().view(np.uint16), g)

@@ -6,7 +6,9 @@ assembly hipcc emits for the library's own source (no GPU needed):
     wavefront's streaming loads (a vector load issued under a saturated stream queues behind it), and
     the result's fields are not fetched one dependent round trip at a time;
   * a full tile issues its eight non-temporal loads back to back, before the first wait on any of them;
-  * every streaming access of the full-tile path is non-temporal.
+  * every streaming access of the full-tile path is non-temporal;
+
+and the same for the kernel of long lists, whose norm result also has to travel beside the table of starts.
 """
 import os
 import re
@@ -18,10 +20,12 @@ import pytest
 from paper_2104_07857_amd import build as zb
 
 KERNEL = re.compile(r"^(_ZN2zi17adamw_wide_kernelILi([01])ELb([01])ELb([01])EEEvNS_8StepArgsE):", re.M)
+LIST_KERNEL = re.compile(r"^(_ZN2zi17adamw_list_kernelILi([01])ELb([01])ENS_8(List|Flat)ArgsEEEvT1_):", re.M)
+LINK_KERNEL = re.compile(r"^(_ZN2zi17adamw_link_kernelILi([01])ELb([01])EEEvNS_8LinkArgsE):", re.M)
 
 
 @pytest.fixture(scope="module")
-def step_kernels(tmp_path_factory):
+def assembly(tmp_path_factory):
     if shutil.which(zb.hipcc()) is None and not os.path.exists(zb.hipcc()):
         pytest.skip("no hipcc here")
     out = tmp_path_factory.mktemp("isa") / "zi_kernels.s"
@@ -30,12 +34,24 @@ def step_kernels(tmp_path_factory):
            "-o", str(out), os.path.join(zb.CSRC, "zi_kernels.hip")]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    text = out.read_text()
-    kernels = {}
-    for mt in KERNEL.finditer(text):
-        end = text.index(".end_amdhsa_kernel", mt.end())
-        kernels[(int(mt.group(2)), int(mt.group(3)), int(mt.group(4)))] = text[mt.end():end]
+    return out.read_text()
+
+
+def _kernels(text, pattern):
+    return {mt.groups()[1:]: text[mt.end():text.index(".end_amdhsa_kernel", mt.end())] for mt in pattern.finditer(text)}
+
+
+@pytest.fixture(scope="module")
+def step_kernels(assembly):
+    kernels = {tuple(int(x) for x in key): body for key, body in _kernels(assembly, KERNEL).items()}
     assert len(kernels) == 8, sorted(kernels)      # {bf16, fp16} x {AdamW, Adam+L2} x {one tensor, list}
+    return kernels
+
+
+@pytest.fixture(scope="module")
+def list_kernels(assembly):
+    kernels = _kernels(assembly, LIST_KERNEL)
+    assert len(kernels) == 8, sorted(kernels)      # {bf16, fp16} x {AdamW, Adam+L2} x {any list, flat buffers}
     return kernels
 
 
@@ -54,8 +70,10 @@ def directive(body, name):
     return int(m.group(1))
 
 
-def test_no_scratch_and_two_wavefronts_per_simd_fit(step_kernels):
-    for key, body in step_kernels.items():
+def test_no_scratch_and_two_wavefronts_per_simd_fit(step_kernels, list_kernels, assembly):
+    link = _kernels(assembly, LINK_KERNEL)
+    assert len(link) == 4, sorted(link)
+    for key, body in [*step_kernels.items(), *list_kernels.items(), *link.items()]:
         assert directive(body, "private_segment_fixed_size") == 0, key
         assert directive(body, "next_free_vgpr") <= 256, key
         assert "scratch_" not in body and "buffer_" not in body, key
@@ -77,8 +95,22 @@ def test_norm_result_is_read_with_one_scalar_load(step_kernels):
         assert re.match(r"s_load_dwordx8 s\[\d+:\d+\], s\[\d+:\d+\], 0x0$", other[-1]), (key, other)
 
 
-def test_full_tile_issues_all_loads_before_the_first_wait(step_kernels):
-    for key, body in step_kernels.items():
+def test_long_lists_fetch_the_norm_result_beside_their_starts(list_kernels):
+    """Nothing but scalar loads in front of a wavefront's first streaming load; the norm result is one 32-byte load, and no
+    wait separates it from the load of the group's starts (fetched behind the descriptor it cost 8%)."""
+    for key, body in list_kernels.items():
+        ins = instructions(body)
+        head = ins[:next(i for i, x in enumerate(ins) if x.startswith("global_"))]
+        assert not [x for x in head if x.startswith(("flat_", "buffer_", "scratch_"))], key
+        result = [i for i, x in enumerate(head) if re.match(r"s_load_dwordx8 s\[\d+:\d+\], s\[(?!0:1\])\d+:\d+\], 0x0$", x)]
+        assert result, key
+        wait = next(i for i in range(result[0], len(head)) if head[i].startswith("s_waitcnt"))
+        starts = [x for x in head[result[0] + 1:wait] if re.match(r"s_load_dwordx(8|16) .*, 0x[1-9a-f]", x)]
+        assert starts, (key, head[result[0]:wait + 1])
+
+
+def test_full_tile_issues_all_loads_before_the_first_wait(step_kernels, list_kernels):
+    for key, body in [*step_kernels.items(), *list_kernels.items()]:
         ins = instructions(body)
         # the full-tile block is the only place with non-temporal 16-byte loads at an immediate offset of one
         # wavefront row (the second quad of a lane)

@@ -58,7 +58,7 @@ def test_flat_lists_share_launches_of_256():
 @pytest.mark.parametrize("flat", [True, False])
 @pytest.mark.parametrize("clip,scale,norm_scale", [(0.0, 1.0, 1.0), (0.5, 2.0, 2.0), (0.7, 2.0, 2.0), (0.5, 3.0, 3.0), (0.5, 2.0, 4.0),
                                                    (1e9, 1.0, 1.0)])
-@pytest.mark.parametrize("count,l2,dt", [(63, False, zi.ZI_BF16), (64, True, zi.ZI_FP16), (270, False, zi.ZI_FP16)])
+@pytest.mark.parametrize("count,l2,dt", [(63, False, zi.ZI_BF16), (64, True, zi.ZI_FP16), (270, False, zi.ZI_FP16), (700, False, zi.ZI_BF16)])
 def test_a_list_equals_its_tensors_one_by_one(count, l2, dt, clip, scale, norm_scale, flat):
     """Ragged tensors at odd offsets of flat buffers (some a tile or less, one longer than an XCD run of tiles, one
     of 2^22 elements in the middle), with a norm that clips or not, stepped twice in a row as a list and tensor by tensor; the copies at the
