@@ -17,12 +17,13 @@ using namespace zi::host;
 
 // ============================================================================ gradient offload
 
-// Partitions of up to this many bytes leave by link_copy_kernel, longer ones by the runtime's copy.  Per call of a
-// row of offloads, us, copy / kernel: 64 KiB 21.4 / 21.5 (the ordering behind the producer costs 13 of them either way),
-// 256 KiB 69 / 22, 1 MiB 70 / 26, 4 MiB 264 / 85; at 16 MiB and beyond both run at the link's rate (a single copy of
-// 32 MiB 599, by the kernel 608).
-constexpr size_t kOffloadByKernel = (size_t)4 << 20;
-
+// The copy is the runtime's, by a copy engine: a kernel that copies is faster for partitions of 1 to 4 MiB while the GPU is
+// idle, but these calls are made beside the backward pass, and there it has to find compute units among the producer's.
+// Per call of a row of offloads on an idle GPU, us, copy / kernel: 64 KiB 15 / 22, 256 KiB 23 / 22, 1 MiB 69 / 25, 4 MiB
+// 206 / 82, 16 MiB 306 / 307.  40 partitions, each behind a matrix product of 110 us, us until the producer is done
+// (4380 without offloads) / until the last partition has arrived, copy and kernel:
+// 256 KiB 4313 / 4377 and 4374 / 4412, 1 MiB 4427 / 4573 and 4915 / 4966, 4 MiB 4764 / 8284 and 6928 / 7037; each behind a
+// kernel of 347 us that streams 2 GiB (13,860 without): 4 MiB 14,020 / 14,134 and 14,903 / 15,011.
 extern "C" zi_status zi_grad_offload(zi_engine* e, const void* d_src, void* h_dst, size_t bytes,
                                      void* producer_stream)
 {
@@ -30,8 +31,7 @@ extern "C" zi_status zi_grad_offload(zi_engine* e, const void* d_src, void* h_ds
     if (bytes == 0) return ZI_OK;
     if (!d_src || !h_dst) return fail(ZI_ERR_INVALID_ARG, "d_src and h_dst must not be NULL");
     PointerChecker reach;
-    int owner = -1;
-    if (memory_kind(d_src, &owner) != 0) return fail(ZI_ERR_INVALID_ARG, "d_src must be device memory");
+    if (memory_kind(d_src) != 0) return fail(ZI_ERR_INVALID_ARG, "d_src must be device memory");
     if (zi_status st = reach.check(d_src, bytes, -1, "d_src")) return st;
     if (memory_kind(h_dst) != 1 || memory_kind(static_cast<const char*>(h_dst) + bytes - 1) != 1)
         return fail(ZI_ERR_INVALID_ARG, "h_dst (%zu bytes) must be page-locked host memory", bytes);
@@ -44,21 +44,7 @@ extern "C" zi_status zi_grad_offload(zi_engine* e, const void* d_src, void* h_ds
     if (e->n_offloads >= (uint64_t)kOffloadEvents) ZI_HIP(hipEventSynchronize(e->ev_offload[idx]));
     ZI_HIP(hipEventRecord(e->ev_offload[idx], (hipStream_t)producer_stream));
     ZI_HIP(hipStreamWaitEvent(e->s_d2h, e->ev_offload[idx], 0));
-    uint16_t* dst = nullptr;
-    // (memory of another device is for the runtime's copy: a kernel of this one cannot be expected to reach it)
-    if (owner == e->device && bytes <= kOffloadByKernel && bytes % 2 == 0 && aligned(d_src, 2) && aligned(h_dst, 2) &&
-        reach.covers(d_src, bytes)) {
-        HostRanges pinned;
-        pinned.note(h_dst, bytes);
-        dst = (uint16_t*)pinned.device_address(h_dst, bytes);
-    }
-    if (dst) {
-        CopyIssuer out(e->s_d2h, nullptr, 0);
-        ZI_HIP(out.add((const uint16_t*)d_src, dst, (int64_t)(bytes / 2), 0));
-        ZI_HIP(out.flush());
-    } else {
-        ZI_HIP(hipMemcpyAsync(h_dst, d_src, bytes, hipMemcpyDeviceToHost, e->s_d2h));
-    }
+    ZI_HIP(hipMemcpyAsync(h_dst, d_src, bytes, hipMemcpyDeviceToHost, e->s_d2h));
     ++e->n_offloads;
     e->offload_pending = true;
     return ZI_OK;

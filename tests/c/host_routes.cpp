@@ -387,9 +387,27 @@ static int loads()
     return 0;
 }
 
+// Gradients leave without a kernel of the library's, which would take compute units from their producer.
+static int offload()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    const size_t most = (size_t)8 << 20;
+    char* src = (char*)on_device(most, 0);
+    char* dst = (char*)on_device(most, -1);
+    for (size_t i = 0; i < most; ++i) src[i] = (char)(i * 31 >> 4);
+    for (size_t bytes : {(size_t)2, (size_t)4096, (size_t)100001, (size_t)1 << 20, (size_t)4 << 20, most}) {
+        memset(dst, 0, most);
+        CHECK(zi_grad_offload(e, src, dst, bytes, nullptr) == ZI_OK && zi_grad_offload_wait(e) == ZI_OK);
+        CHECK(n_launches == 0 && !memcmp(src, dst, bytes));
+    }
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}, {"loads", loads}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");

@@ -192,8 +192,8 @@ def test_cpu_placement_at_block_edges(sizes, offset):
 @pytest.mark.parametrize("nbytes", [1, 2, 6, 16, 8190, 8192, 8194, 100_001, (4 << 20) - 2, 4 << 20, (4 << 20) + 2])
 @pytest.mark.parametrize("offset", [0, 2, 3, 14])
 def test_offloaded_bytes_arrive(nbytes, offset):
-    """Around the pieces of the copying kernel, its limit and what it does not take (odd counts and addresses): the bytes
-    arrive, nothing around them changes, and a stream that is ordered behind the offload reads them."""
+    """Short and long partitions, odd counts and addresses among them: the bytes arrive, nothing around them changes, and a
+    stream that is ordered behind the offload reads them."""
     src = torch.randint(0, 256, (nbytes + 64,), dtype=torch.uint8, device="cuda:0")
     dst = torch.full((nbytes + 64,), 7, dtype=torch.uint8).pin_memory()
     back = torch.zeros(nbytes + 64, dtype=torch.uint8, device="cuda:0")
