@@ -513,7 +513,8 @@ def streamed(args, torch, zi, zs):
             peaks, table = link_peaks(zi, eng, hp, scratch, 2 << 30)
         finally:
             zi.zi_pinned_free(scratch)
-        # With and without the kernel, interleaved (the link's rate drifts by several percent between runs).
+        # The step (a kernel that reads and writes the host state over the link) and, in turn with it, the chunk
+        # pipeline's copies alone (the link's rate drifts by several percent between runs).
         times, copy_only = [], []
         zi.zi_adamw_step_streamed(eng, tl, w["lp_dtype"], cfg)      # warm-up
         for _ in range(3):
@@ -541,8 +542,8 @@ def streamed(args, torch, zi, zs):
             frac_of_one_way_peak=round(per_dir / min(peaks["h2d"], peaks["d2h"]), 4),
             target="streamed step >= 0.85 of the measured pinned-copy peak: quoted against the best two-way rate "
                    "of the sweep (both directions busy, as in the step); the one-way figure is beside it",
-            hidden_ratio=round(median(times) / median(copy_only), 4), copy_only_seconds=median(copy_only),
-            median_seconds=median(times), slot_uses=int(st.n_slot_uses))
+            step_over_copies_alone=round(median(times) / median(copy_only), 4), copy_only_seconds=median(copy_only),
+            median_seconds=median(times))
 
         # Everything below runs on a 2^30-element slice of the same state.
         ns = min(n, 1 << 30)
@@ -552,6 +553,21 @@ def streamed(args, torch, zi, zs):
         for _ in range(3):
             zi.zi_adamw_step_streamed(eng, tls, w["lp_dtype"], cfg)
             gpu_slice.append(zi.zi_engine_last_stats(eng).seconds)
+
+        # The chunk pipeline itself, which a chosen pacing takes: the same copies with the update and without it.
+        pipe, pipe_copies = [], []
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, 2)
+        for skip in (0, 1, 0, 1, 0, 1):
+            zi.zi_engine_set_option(eng, zi.ZI_OPT_SKIP_KERNEL, skip)
+            zi.zi_adamw_step_streamed(eng, tls, w["lp_dtype"], cfg)
+            (pipe_copies if skip else pipe).append(zi.zi_engine_last_stats(eng).seconds)
+        st = zi.zi_engine_last_stats(eng)
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_SKIP_KERNEL, 0)
+        zi.zi_engine_set_option(eng, zi.ZI_OPT_MAX_INFLIGHT, 0)
+        out["chunk_pipeline"] = dict(
+            what=f"{ns} elements of the same state chunk by chunk, paced by the end of the use two back: with and without "
+                 "the update", GBps_per_direction=round(12 * ns / min(pipe) / 1e9, 2), slot_uses=int(st.n_slot_uses),
+            copies=int(st.n_copies), hidden_ratio=round(median(pipe) / median(pipe_copies), 4))
 
         # Gradient-side offload: gradients and the low-precision copy in pinned host memory as well
         # (14 B/element each way), with the norm reduced from the host-resident gradients; and the
