@@ -250,8 +250,8 @@ zi_status zi_adamw_step_streamed(zi_engine* e, const zi_tensor* t, int32_t n_ten
 /*
  * Gradients and the low-precision copy need not be on the device for the streamed step: if
  * t[i].g (and / or t[i].p_lp) of zi_adamw_step_streamed is host memory (pinned, or ordinary with a
- * pinned ring), each chunk of gradients travels to HBM with its chunk of state, and the chunk of
- * the low-precision copy travels back with it (14 bytes per element each way instead of 12).
+ * pinned ring), the gradients come over the link with the state and the low-precision copy goes back
+ * with it, element by element or chunk by chunk (14 bytes per element each way instead of 12).
  * This is the gradient-side offload of Section 6.2 (gradients moved to slow memory during the
  * backward pass) seen from the optimizer step.  zi_grad_norm_streamed is the matching reduction:
  * as zi_grad_norm, but gradients may be in host memory (2 bytes per element over the link): page-locked ones
@@ -338,9 +338,10 @@ typedef struct {
     double seconds;            /* first host-to-device issue .. last device-to-host completion */
     uint64_t bytes_h2d;
     uint64_t bytes_d2h;
-    int64_t n_slot_uses;       /* chunks of the plan (zi_plan_chunks) that were stepped */
-    int64_t n_copies;          /* hipMemcpyAsync calls issued; 0 where the kernel moves the state itself */
-    int64_t n_kernels;         /* kernel launches that updated state */
+    int64_t n_slot_uses;       /* chunks of the plan (zi_plan_chunks) whose elements were stepped or reduced, also where a
+                                  kernel works on the host arrays and no slot is used */
+    int64_t n_copies;          /* hipMemcpyAsync calls that moved state, gradients or copies; 0 where kernels do that */
+    int64_t n_kernels;         /* kernel launches that updated state or reduced gradients */
     uint64_t bytes_staged_host; /* bytes copied by CPU threads through the pinned ring (both ways) */
 } zi_stream_stats;
 
@@ -348,9 +349,9 @@ zi_status zi_engine_last_stats(const zi_engine* e, zi_stream_stats* out);
 
 /*
  * Engine options.
- * ZI_OPT_SKIP_KERNEL = 1 runs the identical copy pipeline without launching the
- * update (a measurement aid like the calls of zi_probe.h: the time of the pipeline with the update
- * removed).
+ * ZI_OPT_SKIP_KERNEL = 1 runs the chunk pipeline's copies without launching the update (a measurement aid
+ * like the calls of zi_probe.h), also for page-locked state that a step would update over the link; what the
+ * update adds to the pipeline shows beside a step at the same ZI_OPT_MAX_INFLIGHT other than 0.
  * ZI_OPT_MAX_INFLIGHT selects how the host paces the chunk pipeline, and, if it is not 0, that page-locked
  * state goes through it.  0 (default, needs n_slots >= 3): a slot
  * use is issued when the copy-out of the use two positions back starts (its update is done);

@@ -17,8 +17,8 @@ using namespace zi::host;
 
 // ============================================================================ gradient offload
 
-// The copy is the runtime's, by a copy engine: a kernel that copies is faster for partitions of 1 to 4 MiB while the GPU is
-// idle, but these calls are made beside the backward pass, and there it has to find compute units among the producer's.
+// The copy is the runtime's: link_copy_kernel is faster for partitions of 1 to 4 MiB while the GPU is idle, but these
+// calls are made beside the backward pass, and there its workgroups keep the producer's waiting.
 // Per call of a row of offloads on an idle GPU, us, copy / kernel: 64 KiB 15 / 22, 256 KiB 23 / 22, 1 MiB 69 / 25, 4 MiB
 // 206 / 82, 16 MiB 306 / 307.  40 partitions, each behind a matrix product of 110 us, us until the producer is done
 // (4380 without offloads) / until the last partition has arrived, copy and kernel:
@@ -88,8 +88,8 @@ struct CpuBlock {
 // other (2^18-element tasks measured 4% slower, 2^16 2% slower).
 constexpr int64_t kCpuBlockElems = zi::kCopyBlockElems;
 // Stepped blocks whose copy the calling thread sends up together while the others go on: 2 MiB.
-// A use of one segment that is no longer than that goes up when it is stepped, beside the next use, and then the copy
-// engine is the cheaper way: per call with 16 threads, us, kernel / copy (three runs each), 8.4e6 elements in chunks of
+// A use of one segment that is no longer than that goes up when it is stepped, beside the next use, and then the runtime's
+// copy is the cheaper way: per call with 16 threads, us, kernel / copy (three runs each), 8.4e6 elements in chunks of
 // 1 MiB 1914..1942 / 1728..1846, 1.7e7 in chunks of 2 MiB 3087..3095 / 2830..2956, in chunks of 4 MiB 2466..2608 /
 // 2360..2632; 3.4e7 in chunks of 8 MiB 4442..5478 / 5287..5483.  For the last use, whose upload everybody waits for, the
 // kernel is: 3.0e4 elements 83..93 / 89..96.
