@@ -28,6 +28,7 @@ const char* kernel_names[256];
 int n_kernels = 0;
 int current_device = 0;
 int n_launches = 0, n_copies = 0, n_faults = 0;
+int n_link_steps = 0;                                           // launches of the step over the link
 const char* last_partial_sum = "";                             // name of the partial-sum kernel launched last
 hipError_t capture_query = hipSuccess;
 char streams[64];
@@ -102,6 +103,7 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
     for (int i = 0; i < n_kernels; ++i) {
         if (kernels[i] != f) continue;
         if (strstr(kernel_names[i], "sumsq_partial_kernel")) last_partial_sum = kernel_names[i];
+        if (strstr(kernel_names[i], "adamw_link_kernel")) ++n_link_steps;
         if (strstr(kernel_names[i], "link_copy_kernel"))
             run_link_copy(*(const zi::CopyArgs*)args[0], device_of(s), strstr(kernel_names[i], "ILb1E") != nullptr);
     }
@@ -405,9 +407,48 @@ static int offload()
     return 0;
 }
 
+// Page-locked arrays that span two registrations are for copies only: the chunk pipeline takes them, at the default pacing
+// too, and (no kernel being carried out here) brings back what it took.
+static int spanning()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    const zi_adamw_config c = config();
+    const int64_t n = 100'000;
+    char* out = (char*)on_device(64 * 1024 * 8, 0);
+    zi_norm_result* norm = (zi_norm_result*)(out + zi_norm_workspace_bytes(0, 0));
+    for (int split = 0; split <= 4; ++split) {                     // 0: none, else this array of p, m, v, g
+        zi_tensor t{};
+        char* a[4];
+        for (int w = 0; w < 4; ++w) {
+            a[w] = (char*)on_device(4 * n, -1);
+            for (int64_t i = 0; i < 4 * n; ++i) a[w][i] = (char)(i * 7 + w);
+            if (split != w + 1) continue;
+            allocs[n_allocs - 1].size = 40960;
+            allocs[n_allocs++] = {a[w] + 40960, 4 * (size_t)n - 40960, -1};
+        }
+        t.p = a[0]; t.m = a[1]; t.v = a[2]; t.g = a[3];
+        t.p_lp = on_device(2 * n, 0);
+        t.numel = n;
+        n_copies = n_link_steps = 0;
+        CHECK(zi_adamw_step_streamed(e, &t, 1, ZI_BF16, &c, nullptr, nullptr) == ZI_OK);
+        zi_stream_stats st{};
+        CHECK(zi_engine_last_stats(e, &st) == ZI_OK && st.n_copies == n_copies && st.n_slot_uses == 7);
+        CHECK(st.bytes_h2d == 14 * (uint64_t)n && st.bytes_d2h == 12 * (uint64_t)n);
+        CHECK(split ? n_copies == 7 * 7 && n_link_steps == 0 : n_copies == 0 && n_link_steps == 1);
+        n_copies = 0;
+        CHECK(zi_grad_norm_streamed(e, &t, 1, ZI_BF16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), nullptr) == ZI_OK);
+        CHECK(n_copies == (split == 4 ? 7 : 0));
+        for (int w = 0; w < 4; ++w)
+            for (int64_t i = 0; i < 4 * n; ++i) CHECK(a[w][i] == (char)(i * 7 + w));
+    }
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");
