@@ -816,7 +816,7 @@ zi_status run_linked_norm(zi_engine* e, int dt, float loss_scale, zi_norm_result
         for (const StateSrc& S : e->src)
             if (S.numel > 0 && !S.g_host) ZI_HIP(issue.add((const uint16_t*)S.dev[3], S.numel));
         if (n_uses > 0) {
-            if (issue.solo_tiles > zi::kNormSoloTiles) ZI_HIP(issue.flush_launch());
+            if (issue.a.n_tiles > (uint32_t)zi::kNormLinkGroups) ZI_HIP(issue.flush_launch());
             issue.groups = zi::kNormLinkGroups;
             for (const StateSrc& S : e->src) {
                 if (S.numel == 0 || !S.g_host) continue;
@@ -942,7 +942,7 @@ extern "C" zi_status zi_grad_norm_streamed(zi_engine* e, const zi_tensor* t, int
             for (size_t j = use_begin[(size_t)use]; j < use_begin[(size_t)use + 1]; ++j)
                 ZI_HIP(issue.add(e->slot_g(slot) + segs[j].slot_offset, segs[j].count));
             ZI_HIP(issue.finish());      // the staged chunk is consumed before its slot is reused
-            e->stats.n_kernels += 2;
+            e->stats.n_kernels = issue.launches;
             ZI_HIP(hipEventRecord(e->ev_k[slot], e->s_k));
             ++e->stats.n_slot_uses;
         }

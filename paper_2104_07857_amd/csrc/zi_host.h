@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <initializer_list>
 #include <cstdint>
@@ -493,16 +495,23 @@ inline zi_status check_norm_args(const zi_tensor* t, int32_t n_tensors, int dt, 
     return ZI_OK;
 }
 
+// What tells the partials of one launch from anything else that the workspace may hold: a number of 62 bits that the
+// process has not used before, from a start that other processes do not share.
+inline uint64_t next_norm_number()
+{
+    static std::atomic<uint64_t> next{(uint64_t)std::chrono::system_clock::now().time_since_epoch().count()};
+    return next.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;      // an odd factor: one to one
+}
+
 // Issues the gradient reduction over a list of gradient arrays that the device can reach: partial-sum
-// launches of up to kMaxNormDesc tensors, and a finalize pass whenever the workspace's partial slots run out
-// and at finish().  After the first finalize the later ones add to the result already in d_out.  A list
-// that one workgroup reduces in kNormSoloTiles passes is one launch and needs no partials.
+// launches of up to kMaxNormDesc tensors.  Where one launch takes what is left, it also makes the final sum; otherwise, and
+// whenever the workspace's partial slots run out, a finalize pass does.  After the first final sum the later ones
+// add to the result already in d_out.
 struct NormIssuer {
     zi::NormArgs a{};
     zi::NormPartial* partials;
     uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
     uint32_t used = 0;                   // partials written since the last finalize
-    uint32_t solo_tiles = 0;             // tiles of the list so far, counted for the one-workgroup kernel
     bool keep = false;                   // see kNormKeepElems
     int launches = 0;                    // kernels so far
     int finalized = 0;
@@ -515,26 +524,35 @@ struct NormIssuer {
         : partials(partials_), dt(dt_), loss_scale(ls), d_out(out), s(st)
     {
     }
-    static int64_t tiles_for(const uint16_t* g, int64_t n, int64_t tile_elems)
+    static int64_t tiles_for(const uint16_t* g, int64_t n)
     {
         const int64_t lead = (int64_t)(-(reinterpret_cast<uintptr_t>(g) / 2) % zi::kVec);
         const int64_t body = n > lead ? (n - lead) / zi::kVec * zi::kVec : 0;
-        const int64_t nt = (body + tile_elems - 1) / tile_elems;
+        const int64_t nt = (body + zi::kNormTileElems - 1) / zi::kNormTileElems;
         return nt < 1 ? 1 : nt;              // the first tile also owns the unaligned ends
     }
-    hipError_t flush_launch()
+    // final: the launch also makes the final sum (no partials of other launches are waiting for one).
+    hipError_t flush_launch(bool final = false)
     {
         if (a.n_desc == 0) return hipSuccess;
         hipError_t e = hipSuccess;
         const uint32_t blocks = a.n_tiles < groups ? a.n_tiles : groups;
         if (used + blocks > zi::kMaxPartials && (e = flush_partials()) != hipSuccess) return e;
         a.partials = partials + used;
+        const uint64_t number = next_norm_number();
+        a.mark_low = (uint32_t)number << 1 | 1u;
+        a.mark_high = (uint32_t)(number >> 31) << 1 | 1u;
+        a.patience = zi::kNormPatience;
+        a.out = final ? d_out : nullptr;
+        a.loss_scale = loss_scale;
+        a.accumulate = finalized;
         // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
         // final sum are ordinary launches (the same order as in StepIssuer).
         const bool any_order = used > 0 && may_overlap(s);
         e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
         ++launches;
-        used += blocks;
+        if (final) finalized = 1;
+        else used += blocks;
         a.n_desc = a.n_tiles = 0;
         return e;
     }
@@ -553,29 +571,14 @@ struct NormIssuer {
                 if (const hipError_t e = flush_launch(); e != hipSuccess) return e;
             const int64_t m = n < zi::kNormMaxPiece ? n : zi::kNormMaxPiece;
             a.t[a.n_desc++] = {g, (uint32_t)m, a.n_tiles};
-            a.n_tiles += (uint32_t)tiles_for(g, m, zi::kNormTileElems);
-            if (solo_tiles <= zi::kNormSoloTiles) solo_tiles += (uint32_t)tiles_for(g, m, zi::kNormSoloTileElems);
+            a.n_tiles += (uint32_t)tiles_for(g, m);
         }
         return hipSuccess;
     }
     hipError_t finish()
     {
-        hipError_t e = hipSuccess;
-        if (launches == 0 && a.n_desc > 0 && solo_tiles <= zi::kNormSoloTiles) {
-            a.n_tiles = 0;
-            for (uint32_t i = 0; i < a.n_desc; ++i) {
-                a.t[i].first_tile = a.n_tiles;
-                a.n_tiles += (uint32_t)tiles_for(a.t[i].g, a.t[i].numel, zi::kNormSoloTileElems);
-            }
-            a.out = d_out;
-            a.loss_scale = loss_scale;
-            e = zi::launch_norm_solo(a, dt, s);
-            ++launches;
-            finalized = 1;
-            a.n_desc = a.n_tiles = 0;
-            return e;
-        }
-        if ((e = flush_launch()) != hipSuccess) return e;
+        if (used == 0 && a.n_desc > 0) return flush_launch(true);
+        if (const hipError_t e = flush_launch(); e != hipSuccess) return e;
         return flush_partials();
     }
 };

@@ -9,7 +9,6 @@
 
 namespace zi {
 
-constexpr int kThreads = 256;        // 4 wavefronts of 64 lanes per workgroup
 constexpr int kVec = 8;              // elements per 16-byte vector of a 2-byte array (norm pass)
 // Fused step: a lane owns quads of 4 consecutive elements = one 16-byte vector of each fp32 array and
 // one 8-byte vector of each 2-byte array, so every wavefront-wide access is one contiguous run.
@@ -35,8 +34,11 @@ constexpr int kXcds = 8;
 constexpr int64_t kStepXcdRun = ZI_STEP_XCD_RUN;
 constexpr unsigned kStepOccupancyLds = ZI_STEP_LDS;
 
-constexpr int kNormUnroll = 8;
-constexpr int kNormTileVecs = kThreads * kNormUnroll;
+// A tile of the reduction is 16,384 elements, one round of loads for a workgroup.  Gradients that are to stay in the
+// memory-side cache (kNormKeepElems) are read by 512 threads with four vectors each, longer lists by 256 with eight: in
+// us, 512 / 256 threads, 6.6e4 elements 2.95 / 3.19, 1.0e6 3.47 / 3.68, 4.2e6 3.48 / 3.68, 3.1e8 91.9 / 91.4, 1.3e9 374 / 370.
+constexpr int kNormTileVecs = 2048;
+constexpr int kNormKeepThreads = 512, kNormStreamThreads = 256;
 constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 elements per workgroup iteration
 // Workgroups of a partial-sum launch (two per compute unit, 64 KiB of loads in flight in each).  Microseconds
 // for partials and final sum together on 2.5e7 / 3.0e8 / 1.3e9 elements and on a list of 288 tensors with 3.0e8:
@@ -60,20 +62,18 @@ constexpr int64_t kNormKeepElems = (int64_t)11 << 23;
 constexpr int kNormLinkGroups = 64;
 constexpr int kMaxNormDesc = 224;    // gradient tensors per partial-sum launch (the argument block stays below 4 KiB)
 constexpr int64_t kNormMaxPiece = (int64_t)1 << 31;   // longer tensors take several descriptors
-// Up to this many tiles of kNormSoloThreads threads one workgroup does the whole reduction, final sum
-// included, in one launch.  On one tensor: 3.3e4 elements 4.8 us against 7.6 for partials and final sum, 6.6e4 (three
-// tiles) 6.6 against 7.7, 1.3e5 (four) 7.6 against 7.7, and the host pays for one launch instead of two.
-constexpr int kNormSoloThreads = 512;
-constexpr int64_t kNormSoloTileElems = (int64_t)kNormSoloThreads * kNormUnroll * kVec;
-constexpr uint32_t kNormSoloTiles = 4;
 constexpr uint32_t kMaxPartials = 16384;   // per-block partial results the workspace holds
 
-// One per-block partial of the gradient reduction (device workspace element).
+// One workgroup's partial sum (device workspace element): the two halves of a double, each in the upper half of a word
+// whose lower half is the launch's mark (NormArgs).  A word is written and read as one, so a mark that is there says that
+// its half of the sum is too.
 struct NormPartial {
-    double sumsq;
-    uint32_t found_inf;
-    uint32_t pad;
+    uint64_t low, high;
 };
+
+// How often the last workgroup of a reduction looks for the other workgroups' partials before it does their work itself
+// (every look is a round trip to memory: about a second).
+constexpr uint32_t kNormPatience = 1u << 20;
 
 // One tensor (or one segment of one) as the fused step sees it.  All pointers are device memory.
 // The first `head` elements are handled one by one; the 4-element lane vectors (the body) start
@@ -202,9 +202,12 @@ struct NormArgs {
     NormDesc t[kMaxNormDesc];
     uint32_t n_desc, n_tiles;
     NormPartial* partials;          // of this launch
-    // the one-workgroup launch only:
+    uint32_t mark_low, mark_high;   // neither is zero; no other launch of the process has the same two
+    uint32_t patience;              // kNormPatience
+    // A launch that leaves all partials of a reduction (null: norm_finalize_kernel sums them up):
     zi_norm_result* out;
     float loss_scale;
+    int32_t accumulate;             // adds to what is there
 };
 static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 
@@ -217,7 +220,6 @@ hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
-hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);
 

@@ -667,19 +667,9 @@ hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, 
 
 // ------------------------------------------------------- gradient sum of squares + overflow flag
 
-// Bit 15 / bit 31 of the result is set iff the exponent field of the low / high half is all ones.
 template <int DT>
-__device__ __forceinline__ uint32_t nonfinite_bits(uint32_t w)
+__device__ __forceinline__ void sumsq_word(uint32_t w, double& acc0, double& acc1)
 {
-    constexpr uint32_t mask = DT == ZI_BF16 ? 0x7F807F80u : 0x7C007C00u;
-    constexpr uint32_t one = DT == ZI_BF16 ? 0x00800080u : 0x04000400u;
-    return ((w & mask) + one) & 0x80008000u;
-}
-
-template <int DT>
-__device__ __forceinline__ void sumsq_word(uint32_t w, double& acc0, double& acc1, uint32_t& flag)
-{
-    flag |= nonfinite_bits<DT>(w);
     float lo, hi;
     widen_pair<DT>(w, lo, hi);
     const double dlo = (double)lo, dhi = (double)hi;
@@ -688,12 +678,12 @@ __device__ __forceinline__ void sumsq_word(uint32_t w, double& acc0, double& acc
 }
 
 template <int DT>
-__device__ __forceinline__ void sumsq_vec(const u32x4 g, double& acc0, double& acc1, uint32_t& flag)
+__device__ __forceinline__ void sumsq_vec(const u32x4 g, double& acc0, double& acc1)
 {
-    sumsq_word<DT>(g.x, acc0, acc1, flag);
-    sumsq_word<DT>(g.y, acc0, acc1, flag);
-    sumsq_word<DT>(g.z, acc0, acc1, flag);
-    sumsq_word<DT>(g.w, acc0, acc1, flag);
+    sumsq_word<DT>(g.x, acc0, acc1);
+    sumsq_word<DT>(g.y, acc0, acc1);
+    sumsq_word<DT>(g.z, acc0, acc1);
+    sumsq_word<DT>(g.w, acc0, acc1);
 }
 
 __device__ __forceinline__ double wave_sum(double x)
@@ -703,56 +693,32 @@ __device__ __forceinline__ double wave_sum(double x)
     return x;
 }
 
-__device__ __forceinline__ uint32_t wave_or(uint32_t x)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, 64);
-    return x;
-}
-
-// Two-level reduction: wavefront shuffles, then one LDS slot per wavefront.  Result valid in thread 0.
+// The sum of NWAVES wavefronts' sums, in their order.  Result valid in thread 0.
 template <int NWAVES>
-__device__ __forceinline__ void block_reduce(double& sum, uint32_t& flag)
+__device__ __forceinline__ double sum_of_waves(const double (&s)[NWAVES])
 {
-    __shared__ double s_sum[NWAVES];
-    __shared__ uint32_t s_flag[NWAVES];
-    sum = wave_sum(sum);
-    flag = wave_or(flag);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) {
-        s_sum[wave] = sum;
-        s_flag[wave] = flag;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        uint32_t f = 0;
+    double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < NWAVES; ++w) {
-            t += s_sum[w];
-            f |= s_flag[w];
-        }
-        sum = t;
-        flag = f;
-    }
+    for (int w = 0; w < NWAVES; ++w) t += s[w];
+    return t;
 }
 
-// The workgroup's share of a list: tiles blockIdx.x, blockIdx.x + gridDim.x, ... of all tensors in order, each
-// tile THREADS * kNormUnroll 16-byte vectors with all loads in flight before the first use (a vector past the
-// end counts as zeros).  A tensor's first tile also takes the elements in front of its first 16-byte
-// aligned one and behind its last whole vector.  The tiles of a list are shared out evenly, whatever its
-// tensors' lengths: with workgroups of its own for every tensor a list of short ones left most of the chip idle.
-// Squares are accumulated in double: exact products, and a finite gradient whose square would
-// overflow fp32 still gives a finite sum.
+// Tiles first, first + step, ... of all tensors of a list in order, each tile THREADS * UNROLL 16-byte vectors with all
+// loads in flight before the first use (a vector past the end counts as zeros).  A tensor's first tile also takes the
+// elements in front of its first 16-byte aligned one and behind its last whole vector.  The tiles of a list are shared
+// out evenly, whatever its tensors' lengths: with workgroups of its own for every tensor a list of short ones left most
+// of the chip idle.
+// Squares are accumulated in double: exact products, and a finite gradient whose square would overflow fp32 still gives a
+// finite sum.  Infinities and NaN make the sum infinite or NaN and nothing else does (2^63 of the largest squares are
+// 1e96), so the sum itself says whether there was one.
 // KEEP: ordinary loads, which leave the gradients in the memory-side cache (kNormKeepElems).
 template <int DT, int THREADS, bool KEEP>
-__device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint32_t& flag)
+__device__ __forceinline__ double sumsq_tiles(const NormArgs& a, uint32_t first, uint32_t step)
 {
-    constexpr uint32_t tile_vecs = THREADS * kNormUnroll;
+    constexpr int UNROLL = kNormTileVecs / THREADS;
     double acc0 = 0.0, acc1 = 0.0;
-    flag = 0;
     uint32_t d = 0;
-    for (uint32_t t = blockIdx.x; t < a.n_tiles; t += gridDim.x) {
+    for (uint32_t t = first; t < a.n_tiles; t += step) {
         d = find_desc(a.t, d, a.n_desc, t);
         const NormDesc& T = a.t[d];
         const uint32_t tile = t - T.first_tile;
@@ -761,14 +727,14 @@ __device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint
         const uint32_t nvec = (T.numel - head) / kVec;
         const u32x4* __restrict__ g4 = reinterpret_cast<const u32x4*>(T.g + head);
 
-        const uint32_t v0 = tile * tile_vecs + threadIdx.x;
-        u32x4 g[kNormUnroll];
-        if ((tile + 1) * tile_vecs <= nvec) {
+        const uint32_t v0 = tile * kNormTileVecs + threadIdx.x;
+        u32x4 g[UNROLL];
+        if ((tile + 1) * kNormTileVecs <= nvec) {
 #pragma unroll
-            for (int u = 0; u < kNormUnroll; ++u) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
+            for (int u = 0; u < UNROLL; ++u) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
         } else {
 #pragma unroll
-            for (int u = 0; u < kNormUnroll; ++u) {
+            for (int u = 0; u < UNROLL; ++u) {
                 g[u] = u32x4{0, 0, 0, 0};
                 if (v0 + u * THREADS < nvec) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
             }
@@ -777,33 +743,27 @@ __device__ __forceinline__ void sumsq_tiles(const NormArgs& a, double& sum, uint
             const uint32_t lane = threadIdx.x, body_end = head + nvec * kVec;
             const bool front = lane < head, back = lane >= kVec && lane - kVec < T.numel - body_end;
             if (front || back) {
-                const uint32_t h = T.g[front ? lane : body_end + (lane - kVec)];
-                flag |= nonfinite_bits<DT>(h);
-                const double x = (double)widen16<DT>(h);
+                const double x = (double)widen16<DT>(T.g[front ? lane : body_end + (lane - kVec)]);
                 acc0 = __builtin_fma(x, x, acc0);
             }
         }
 #pragma unroll
-        for (int u = 0; u < kNormUnroll; ++u) sumsq_vec<DT>(g[u], acc0, acc1, flag);
+        for (int u = 0; u < UNROLL; ++u) sumsq_vec<DT>(g[u], acc0, acc1);
     }
-    sum = acc0 + acc1;
-    block_reduce<THREADS / 64>(sum, flag);
+    return acc0 + acc1;
 }
 
-// Bound: HBM (or the link), 2 bytes per element read.  Each workgroup leaves one partial.
-template <int DT, bool KEEP>
-__global__ __launch_bounds__(kThreads) void sumsq_partial_kernel(const NormArgs a)
+// Partials go straight to memory and come straight from it (stores and loads of agent scope, each word complete in itself), so neither
+// side needs a fence: one in every workgroup, which writes back a cache that all of an XCD's work shares, cost 25 us.
+__device__ __forceinline__ void put_partial(NormPartial* at, double sum, uint32_t mark_low, uint32_t mark_high)
 {
-    double sum;
-    uint32_t flag;
-    sumsq_tiles<DT, kThreads, KEEP>(a, sum, flag);
-    if (threadIdx.x == 0) {
-        NormPartial out;
-        out.sumsq = sum;
-        out.found_inf = flag ? 1u : 0u;
-        out.pad = 0;
-        a.partials[blockIdx.x] = out;
-    }
+    const uint64_t bits = __builtin_bit_cast(uint64_t, sum);
+    __hip_atomic_store(&at->low, (bits << 32) | mark_low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&at->high, (bits >> 32 << 32) | mark_high, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double partial_sum(uint64_t low, uint64_t high)
+{
+    return __builtin_bit_cast(double, (low >> 32) | (high >> 32 << 32));
 }
 
 __device__ __forceinline__ zi_norm_result norm_result(double sumsq, uint32_t flag, float loss_scale)
@@ -816,39 +776,93 @@ __device__ __forceinline__ zi_norm_result norm_result(double sumsq, uint32_t fla
     r.inv_norm = 1.0 / (r.norm + 1e-6);
     return r;
 }
-
-// Bound: launches.  A short list's whole reduction in one workgroup (kNormSoloTiles).
-template <int DT>
-__global__ __launch_bounds__(kNormSoloThreads) void sumsq_solo_kernel(const NormArgs a)
+__device__ __forceinline__ void put_norm_result(double sumsq, float loss_scale, int accumulate, zi_norm_result* out)
 {
-    double sum;
-    uint32_t flag;
-    sumsq_tiles<DT, kNormSoloThreads, true>(a, sum, flag);
-    if (threadIdx.x == 0) *a.out = norm_result(sum, flag, a.loss_scale);
+    if (accumulate) sumsq += out->sumsq;
+    *out = norm_result(sumsq, !__builtin_isfinite(sumsq), loss_scale);
+}
+
+// Bound: HBM (or the link), 2 bytes per element read; short lists: the launch.  Each workgroup leaves one partial.  Where
+// all partials of a reduction come from one launch, its last workgroup waits for them, adds them up and
+// writes the result: a second kernel for that costs 1.5 to 3 us, as long as the reduction of a short list itself.  In us,
+// two kernels / one: 6.6e4 elements 5.2 / 3.0 (one workgroup for everything: 5.8), 1.0e6 5.1 / 3.5, 4.2e6 5.1 / 3.5,
+// 3.1e8 92.5 / 91.4.
+// The wait is short: the tiles are shared out evenly, and workgroups start in order, so the others are on their way when
+// the last one runs.  None of them waits for anything.  Should partials still be missing after `patience` looks (the device
+// is busy with other work, or a call that was not ordered behind this one overwrote them), the last workgroup goes over all
+// tiles itself.
+// Marks tell this launch's partials from whatever the workspace held; they are taken away again behind the sum, since
+// a captured launch is replayed with the same ones.
+// The partials are added in the order of norm_finalize_kernel: the same bits, and independent of scheduling.
+template <int DT, bool KEEP>
+__global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const NormArgs a)
+{
+    constexpr int THREADS = KEEP ? kNormKeepThreads : kNormStreamThreads;
+    constexpr int kWaves = THREADS / 64, kRounds = kNormGroups / THREADS;
+    __shared__ double s_sum[kWaves];
+    __shared__ double s_partial[kNormGroups / 64];
+    __shared__ uint32_t s_missing;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool last = a.out && blockIdx.x == gridDim.x - 1;
+    uint32_t first = blockIdx.x, step = gridDim.x;
+    for (;;) {
+        const double sum = wave_sum(sumsq_tiles<DT, THREADS, KEEP>(a, first, step));
+        if (lane == 0) s_sum[wave] = sum;
+        if (threadIdx.x == 0) s_missing = 0;
+        __syncthreads();
+        if (last && step == 1) {          // the whole list is in this workgroup
+            if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_sum), a.loss_scale, a.accumulate, a.out);
+            return;
+        }
+        if (threadIdx.x == 0) put_partial(a.partials + blockIdx.x, sum_of_waves(s_sum), a.mark_low, a.mark_high);
+        if (!last) return;
+
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const uint32_t i = threadIdx.x + r * THREADS;
+            double x = 0.0;
+            if (i < gridDim.x) {
+                NormPartial* const at = a.partials + i;
+                uint64_t low = 0, high = 0;
+                bool there = false;
+                for (uint32_t looks = 0; !there && looks < a.patience; ++looks) {
+                    low = __hip_atomic_load(&at->low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    high = __hip_atomic_load(&at->high, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    there = (uint32_t)low == a.mark_low && (uint32_t)high == a.mark_high;
+                }
+                if (!there) s_missing = 1;
+                x = partial_sum(low, high);
+                __hip_atomic_store(&at->low, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&at->high, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            x = wave_sum(x);
+            if (lane == 0) s_partial[r * kWaves + wave] = x;
+        }
+        __syncthreads();
+        if (!s_missing) {
+            if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_partial), a.loss_scale, a.accumulate, a.out);
+            return;
+        }
+        __syncthreads();
+        first = 0;
+        step = 1;
+    }
 }
 
 constexpr int kFinalThreads = kNormGroups;   // one partial each where one launch made them all
 
-// One workgroup adds the partials in a fixed order (so the result does not depend on scheduling)
-// and writes the device-resident result.
+// One workgroup adds the partials of several launches in a fixed order and writes the result.
 __global__ __launch_bounds__(kFinalThreads) void norm_finalize_kernel(const NormPartial* __restrict__ partials,
                                                                       uint32_t count, float loss_scale,
                                                                       int accumulate, zi_norm_result* out)
 {
+    __shared__ double s_sum[kFinalThreads / 64];
     double sum = 0.0;
-    uint32_t flag = 0;
-    for (uint32_t i = threadIdx.x; i < count; i += kFinalThreads) {
-        sum += partials[i].sumsq;
-        flag |= partials[i].found_inf;
-    }
-    block_reduce<kFinalThreads / 64>(sum, flag);
-    if (threadIdx.x == 0) {
-        if (accumulate) {
-            sum += out->sumsq;
-            flag |= out->found_inf;
-        }
-        *out = norm_result(sum, flag, loss_scale);
-    }
+    for (uint32_t i = threadIdx.x; i < count; i += kFinalThreads) sum += partial_sum(partials[i].low, partials[i].high);
+    sum = wave_sum(sum);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_sum), loss_scale, accumulate, out);
 }
 
 // After the sum of squares and the flag have been combined across ranks (sum and max), the norm
@@ -869,21 +883,13 @@ hipError_t launch_norm_refresh(zi_norm_result* d_result, float loss_scale, hipSt
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s)
 {
     if (n_blocks == 0) return hipSuccess;
-    const dim3 grid(n_blocks), block(kThreads);
+    const dim3 grid(n_blocks), block(keep ? kNormKeepThreads : kNormStreamThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
 #define ZI_LAUNCH_NORM(DT, KEEP) \
     hipExtLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP>), grid, block, 0, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
     else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
 #undef ZI_LAUNCH_NORM
-    return hipGetLastError();
-}
-
-hipError_t launch_norm_solo(const NormArgs& a, int dt, hipStream_t s)
-{
-    const dim3 grid(1), block(kNormSoloThreads);
-    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_solo_kernel<ZI_BF16>), grid, block, 0, s, a);
-    else               hipLaunchKernelGGL((sumsq_solo_kernel<ZI_FP16>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,114 @@
+"""The reduction in one launch: its last workgroup waits for the others' partials and makes the final sum."""
+import ctypes
+import math
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2104_07857_amd as zi
+import zi_synth
+from gpu_util import NormBuffers, progress, to_dev
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TILE, GROUPS = 16384, 512
+KEEP = 11 << 23                       # elements up to which the gradients are read with ordinary loads
+
+
+def _grads(n, dt, seed):
+    g = np.empty(n, np.uint16)
+    zi_synth.fill_normal_lp(g, n, seed, zi_synth.STREAM_G, dt, std=1e-3 if dt == zi.ZI_BF16 else 65.536)
+    return g
+
+
+def _norm(views, dt, nb):
+    zi.zi_grad_norm([(None, None, None, v, None, v.numel()) for v in views], dt, 2.0, nb.out, nb.ws)
+    torch.cuda.synchronize()
+    return nb.read()
+
+
+@pytest.mark.parametrize("dt", [zi.ZI_BF16, zi.ZI_FP16])
+@pytest.mark.parametrize("n", [TILE + 1, 2 * TILE, 63 * TILE + 9, 64 * TILE + 1, (GROUPS - 1) * TILE + 5, GROUPS * TILE,
+                               (GROUPS + 1) * TILE + 3])
+def test_every_number_of_workgroups(n, dt):
+    """From two workgroups to more tiles than workgroups, whatever the workspace held before."""
+    g = _grads(n + 3, dt, 40 + n)
+    d = to_dev(g)[3:]
+    want, _ = oracle.grad_sumsq([g[3:].copy()], dt)
+    nb = NormBuffers()
+    seen = set()
+    for before in (0x00, 0xFF, 0x5A, None, None):                  # None: what the call before left
+        if before is not None:
+            nb.ws.fill_(before)
+        got = _norm([d], dt, nb)
+        # squares and their sums in double: n additions of 1.1e-16 each, most of them in another order
+        assert got[2] == 0 and abs(got[0] - want) <= 1e-12 * want and abs(got[1] - math.sqrt(want) / 2) <= 1e-12 * got[1]
+        seen.add(got)
+    assert len(seen) == 1
+
+
+@pytest.mark.parametrize("n", [KEEP, KEEP + 1])
+def test_both_ways_of_reading(n):
+    g = to_dev(np.tile(_grads(1 << 16, zi.ZI_BF16, 3), n // (1 << 16) + 1))[:n]
+    one, _ = oracle.grad_sumsq([g[:1 << 16].cpu().numpy().view(np.uint16)], zi.ZI_BF16)
+    rest, _ = oracle.grad_sumsq([g[:n % (1 << 16)].cpu().numpy().view(np.uint16)], zi.ZI_BF16)
+    want = one * (n // (1 << 16)) + rest
+    got = _norm([g], zi.ZI_BF16, NormBuffers())
+    assert got[2] == 0 and abs(got[0] - want) <= 1e-12 * want
+
+
+def test_replays_of_a_captured_call_see_new_gradients():
+    """A replay has the marks of the replay before it: its partials must not be taken for the new ones."""
+    dt, n = zi.ZI_BF16, 40 * TILE + 77
+    d = to_dev(_grads(n, dt, 5))
+    nb, nb_e = NormBuffers(), NormBuffers()
+    tl = zi.make_tensors([(None, None, None, d, None, n)])
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        zi.zi_grad_norm(tl, dt, 1.0, nb.out, nb.ws, stream=side)
+        graph.capture_end()
+    for replay in range(6):
+        d.copy_(to_dev(_grads(n, dt, 100 + replay)))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        zi.zi_grad_norm(tl, dt, 1.0, nb_e.out, nb_e.ws)
+        torch.cuda.synchronize()
+        want, _ = oracle.grad_sumsq([d.cpu().numpy().view(np.uint16)], dt)
+        assert nb.read() == nb_e.read(), replay
+        assert abs(nb.read()[0] - want) <= 1e-12 * want
+
+
+@pytest.mark.parametrize("keep", [0, 1])
+@pytest.mark.parametrize("n", [TILE * 2 + 1, TILE * 600 + 11])
+def test_a_last_workgroup_that_does_not_wait_does_all_the_work(n, keep, tmp_path):
+    """With no patience at all the partials count as missing and the last workgroup goes over the whole list."""
+    rocm = "/opt/rocm/include"
+    if shutil.which("g++") is None or not os.path.isdir(rocm):
+        pytest.skip("no host compiler or no HIP headers")
+    so, libdir = str(tmp_path / "norm_launch.so"), os.path.dirname(zi.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-isystem", rocm, "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(libdir, "csrc"), os.path.join(ROOT, "tests", "c", "norm_launch.cpp"), "-o", so,
+                    "-L", libdir, "-lzi", "-Wl,-rpath," + libdir, "-Wl,--allow-shlib-undefined"], check=True)
+    zi.lib()
+    launch = ctypes.CDLL(so).norm_launch
+    launch.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p]
+    dt = zi.ZI_FP16
+    g = _grads(n, dt, 8)
+    want, _ = oracle.grad_sumsq([g], dt)
+    d, nb = to_dev(g), NormBuffers()
+    for patience in (0, 1 << 20, 0):
+        progress(f"reduction of {n} elements, keep {keep}, patience {patience}")
+        nb.out.fill_(-1.0)
+        torch.cuda.synchronize()
+        assert launch(d.data_ptr(), n, dt, keep, patience, nb.ws.data_ptr(), nb.out.data_ptr()) == 0
+        torch.cuda.synchronize()
+        got = nb.read()
+        assert got[2] == 0 and abs(got[0] - want) <= 1e-12 * want and abs(got[1] - math.sqrt(want) / 2) <= 1e-12 * got[1]
