@@ -18,12 +18,35 @@ constexpr int kStepUnroll = 2;       // quads per thread per tile
 constexpr int kStepTileQuads = kStepThreads * kStepUnroll;
 constexpr int64_t kStepTileElems = (int64_t)kStepTileQuads * kQuad;   // 512 elements per tile
 constexpr int kMaxStepDesc = 32;     // tensors (or segments) per fused-step launch
-// Dynamic LDS requested (never touched) by the fused step: caps residency at six single-wavefront
-// workgroups per compute unit.  On this 1:1 read/write stream few, short-lived wavefronts measured
-// 4-8% faster than full occupancy (sweeps over workgroup size, unroll and residency).
-#ifndef ZI_STEP_LDS
-#define ZI_STEP_LDS (26 * 1024)
-#endif
+// Dynamic LDS requested (never touched) by the fused step caps its residency: single-wavefront workgroups per compute
+// unit.  On this 1:1 read/write stream few, short-lived wavefronts measured 4-8% faster than full occupancy, but how
+// few depends on the launch.  Up to kStepShortTiles or kListShortTiles tiles what counts is how few rounds of resident workgroups it takes; in
+// launches of more than kStepLongTiles bunching begins to cost, above all in adamw_list_kernel, whose wavefronts arrive at their
+// loads later.
+// Step alone in us, averages over six placements of the arrays (short ones: of a captured row of calls),
+// workgroups per compute unit:
+//                                             16      8      7      6
+//   one tensor       1.0e6                    4.4    4.8           6.1
+//                    2.1e6                   10.1   10.6          11.6
+//                    4.2e6                   20.3   20.6          21.6
+//                    8.4e6                   40.8   39.6          40.8
+//                    2.5e7                   113    112    112    113
+//                    3.0e8                          1313   1313   1331
+//                    1.3e9                          5847   5853   5905
+//                    (allocated one after another   5855   5800   5787)
+//   flat list        200 of 1..40,000        20.0   20.6          21.9
+//                    300 of 1.0e5                   145    147    154
+//                    1000 of 3.0e5                  1361   1363   1397
+//   other list       64 of 6e5 a launch             268    269    275
+//                    64 of 1.3e6                    587    583    591
+//                    64 of 2e6                      923    919    928
+//                    64 of 4.2e6                    1418   1400   1388
+//                    64 of 2e7                      6495   6415   6389
+//                    (without a copy, 16 against 8: 4.0e6 17.96 / 17.73, 6.2e6 26.7 / 26.2)
+constexpr uint32_t kStepShortTiles = 3u << 11;     // 3.1e6 elements, of one tensor
+constexpr uint32_t kListShortTiles = 3u << 12;     // 6.3e6 elements, of several
+constexpr uint32_t kStepLongTiles = 1u << 18;      // 1.3e8 elements
+constexpr unsigned kStepLds16 = 10 * 1024, kStepLds8 = 20 * 1024, kStepLds7 = 22 * 1024 + 512, kStepLds6 = 26 * 1024;
 // Workgroup ids are dealt round-robin to the 8 XCDs.  Tiles are renumbered so that, inside every run
 // of 8 * kStepXcdRun tiles, each XCD owns kStepXcdRun consecutive tiles (256 KiB of each fp32 array)
 // instead of every eighth one: measured +4% on top of the residency cap.
@@ -32,7 +55,6 @@ constexpr int kXcds = 8;
 #define ZI_STEP_XCD_RUN 128
 #endif
 constexpr int64_t kStepXcdRun = ZI_STEP_XCD_RUN;
-constexpr unsigned kStepOccupancyLds = ZI_STEP_LDS;
 
 // A tile of the reduction is 16,384 elements, one round of loads for a workgroup.  Gradients that are to stay in the
 // memory-side cache (kNormKeepElems) are read by 512 threads with four vectors each, longer lists by 256 with eight: in

@@ -333,8 +333,11 @@ __device__ __forceinline__ void step_tile(GlobalF4 __restrict__ p4, GlobalF4 __r
 // SINGLE: the launch covers one tensor (every long tensor gets such a launch: a workgroup lives for a few
 // microseconds, so even a short search for its tensor costs bandwidth).  Otherwise the workgroup counts
 // the table entries <= its id: a few wide scalar loads and no dependent chain.
+// (waves_per_eu: with the default target the scheduler saves registers by moving loads behind the first quad's arithmetic.
+// The upper bound is also what a SIMD may hold, and two a SIMD, with six a compute unit, leave a freed slot unusable while
+// its neighbours have none: lists of 72 tensors of 3.0e8 elements 1371 us with two, 1341 with three or four.)
 template <int DT, bool L2, bool SINGLE>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
 void adamw_wide_kernel(const StepArgs a)
 {
     const uint32_t block = blockIdx.x;
@@ -412,7 +415,7 @@ __device__ __forceinline__ int64_t tail_of(const FlatArgs& a, uint32_t d) { retu
 // 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,
 // 200 of 1..40,000 45.6 -> 35.3, as FlatArgs 25.3; with the norm result fetched after the descriptor 1478 instead of 1366.
 template <int DT, bool L2, typename Args>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
 void adamw_list_kernel(const Args a)
 {
     const uint32_t block = blockIdx.x;
@@ -458,14 +461,20 @@ void adamw_list_kernel(const Args a)
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
 }
 
+static unsigned step_lds(uint32_t n_tiles, uint32_t short_tiles, unsigned middling, unsigned longer)
+{
+    return n_tiles <= short_tiles ? kStepLds16 : n_tiles <= kStepLongTiles ? middling : longer;
+}
+
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
     const dim3 grid(n_tiles), block(kStepThreads);
     const bool single = a.n_desc == 1;
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
+    const unsigned lds = step_lds(n_tiles, single ? kStepShortTiles : kListShortTiles, kStepLds8, kStepLds7);
 #define ZI_LAUNCH_STEP(DT, L2, SINGLE) \
-    hipExtLaunchKernelGGL((adamw_wide_kernel<DT, L2, SINGLE>), grid, block, kStepOccupancyLds, s, nullptr, nullptr, flags, a)
+    hipExtLaunchKernelGGL((adamw_wide_kernel<DT, L2, SINGLE>), grid, block, lds, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) {
         if (l2) { if (single) ZI_LAUNCH_STEP(ZI_BF16, true, true); else ZI_LAUNCH_STEP(ZI_BF16, true, false); }
         else    { if (single) ZI_LAUNCH_STEP(ZI_BF16, false, true); else ZI_LAUNCH_STEP(ZI_BF16, false, false); }
@@ -478,13 +487,13 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
 }
 
 template <typename Args>
-static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
+static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, unsigned lds, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
     const dim3 grid(n_tiles), block(kStepThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
 #define ZI_LAUNCH_LIST(DT, L2) \
-    hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, kStepOccupancyLds, s, nullptr, nullptr, flags, a)
+    hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LIST(ZI_BF16, true); else ZI_LAUNCH_LIST(ZI_BF16, false); }
     else               { if (l2) ZI_LAUNCH_LIST(ZI_FP16, true); else ZI_LAUNCH_LIST(ZI_FP16, false); }
 #undef ZI_LAUNCH_LIST
@@ -492,11 +501,11 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
 }
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
-    return launch_list_of(a, n_tiles, dt, l2, any_order, s);
+    return launch_list_of(a, n_tiles, step_lds(n_tiles, kListShortTiles, kStepLds7, kStepLds6), dt, l2, any_order, s);
 }
 hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
-    return launch_list_of(a, n_tiles, dt, l2, any_order, s);
+    return launch_list_of(a, n_tiles, step_lds(n_tiles, kListShortTiles, kStepLds8, kStepLds8), dt, l2, any_order, s);
 }
 
 // The descriptor that holds tile t of a launch, at or after entry d, by halving: a walk from entry to entry
@@ -909,6 +918,7 @@ hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, flo
 // residency capped at six wavefronts per compute unit by unused dynamic LDS, and the same XCD-aware
 // tile renumbering as the fused step.  These are the ceilings the fused step is compared with.
 constexpr int kProbeUnroll = 4;
+constexpr unsigned kProbeLds = 26 * 1024;
 constexpr int kProbeTileVecs = 64 * kProbeUnroll;
 
 template <int MODE>
@@ -958,7 +968,7 @@ hipError_t launch_hbm_probe(void* a, void* b, int64_t n4, int mode, float* sink,
 {
     if (n4 <= 0) return hipSuccess;
     const dim3 grid((uint32_t)((n4 + kProbeTileVecs - 1) / kProbeTileVecs)), block(64);
-    const unsigned lds = kStepOccupancyLds;
+    const unsigned lds = kProbeLds;
     if (mode == 0) hipLaunchKernelGGL(hbm_probe_kernel<0>, grid, block, lds, s, (f32x4*)a, (f32x4*)b, n4, sink);
     else if (mode == 1) hipLaunchKernelGGL(hbm_probe_kernel<1>, grid, block, lds, s, (f32x4*)a, (f32x4*)b, n4, sink);
     else hipLaunchKernelGGL(hbm_probe_kernel<2>, grid, block, lds, s, (f32x4*)a, (f32x4*)b, n4, sink);

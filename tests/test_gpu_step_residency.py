@@ -1,0 +1,49 @@
+"""Step launches on both sides of the sizes where the number of resident workgroups changes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2104_07857_amd as zi
+import zi_synth
+from gpu_util import compare_state, gen_numpy, to_dev, to_np, zi_cfg
+
+pytestmark = pytest.mark.gpu
+TILE, SHORT, SHORT_LIST, LONG = 512, 3 << 11, 3 << 12, 1 << 18
+
+
+@pytest.mark.parametrize("dt", [zi.ZI_BF16, zi.ZI_FP16])
+@pytest.mark.parametrize("n", [SHORT * TILE, SHORT * TILE + 4])
+def test_one_tensor_around_the_short_limit(n, dt):
+    hp, hm, hv, hg = gen_numpy(zi_synth.StateSpec(n + dt, dt), n)
+    dev = [to_dev(a.copy()) for a in (hp, hm, hv, hg)] + [torch.zeros(n, dtype=torch.int16, device="cuda:0")]
+    zi.zi_adamw_step([tuple(dev) + (n,)], dt, zi_cfg(zi_synth.workload("c1")))
+    torch.cuda.synchronize()
+    lp = np.zeros(n, np.uint16)
+    oracle.adamw(hp, hm, hv, hg, lp, dt, oracle.config(step=10), 0.0, 0)
+    compare_state((hp, hm, hv, lp), [to_np(dev[i]) for i in (0, 1, 2, 4)], dt)
+
+
+@pytest.mark.parametrize("count,each,shuffled", [(65, LONG // 64 * TILE, True), (65, LONG // 64 * TILE + 512, True),
+                                                 (256, SHORT_LIST // 256 * TILE, False), (256, SHORT_LIST // 256 * TILE + 512, False)])
+def test_lists_around_the_limits_equal_one_tensor(count, each, shuffled):
+    """Lists whose launch is just short or just long, or just past either, give the bits of one flat tensor.  Shuffled
+    copies keep a list from being views at the same places of five buffers."""
+    dt, n = zi.ZI_BF16, count * each
+    gen = torch.Generator(device="cuda:0").manual_seed(each)
+    rand = lambda std: torch.empty(n, device="cuda:0").normal_(0.0, std, generator=gen)      # noqa: E731
+    state = [rand(0.02), rand(1e-4), rand(1e-6).abs_(), rand(1e-3).bfloat16().view(torch.int16),
+             torch.zeros(n, dtype=torch.int16, device="cuda:0")]
+    whole = [x.clone() for x in state]
+    if shuffled:                                     # the copy's pieces stand in reverse order
+        place = lambda w, i: (count - 1 - i if w == 4 else i) * each                         # noqa: E731
+    else:
+        place = lambda w, i: i * each                                                        # noqa: E731
+    cfg = zi_cfg(zi_synth.workload("c1"))
+    zi.zi_adamw_step([tuple(x[place(w, i):place(w, i) + each] for w, x in enumerate(state)) + (each,) for i in range(count)], dt, cfg)
+    zi.zi_adamw_step([tuple(whole) + (n,)], dt, cfg)
+    torch.cuda.synchronize()
+    for w, (a, b) in enumerate(zip(state, whole)):
+        if shuffled and w == 4:
+            a = a.view(count, each).flip(0).reshape(-1)
+        assert torch.equal(a, b), "p m v g lp".split()[w]
