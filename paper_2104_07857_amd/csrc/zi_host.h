@@ -151,6 +151,37 @@ inline bool may_overlap(hipStream_t stream)
     return false;
 }
 
+// A call on one tensor of up to kStepShortTiles tiles, as adamw_short_kernel takes it: false if it is another call.
+inline bool one_short_tensor(const zi_tensor* t, int32_t n_tensors, const zi::StepConsts& c, bool l2,
+                             const zi_norm_result* d_norm, zi::StepOne& a)
+{
+    const zi_tensor* one = nullptr;
+    for (int32_t i = 0; i < n_tensors; ++i) {
+        if (t[i].numel <= 0) continue;
+        if (one) return false;
+        one = &t[i];
+    }
+    if (!one || one->numel > zi::kStepShortTiles * zi::kStepTileElems) return false;
+    const int64_t h = choose_head(one->p, one->m, one->v, one->g, one->p_lp), head = h < one->numel ? h : one->numel;
+    a.p_body = (float*)one->p + head;
+    a.m_body = (float*)one->m + head;
+    a.v_body = (float*)one->v + head;
+    a.g_body = (const uint16_t*)one->g + head;
+    a.lp_body = one->p_lp ? (uint16_t*)one->p_lp + head : nullptr;
+    a.d_norm = d_norm;
+    a.inv_loss_scale = c.inv_loss_scale;
+    a.nquad = (uint32_t)((one->numel - head) / zi::kQuad);
+    a.head = (uint8_t)head;
+    a.tail = (uint8_t)(one->numel - head - (int64_t)a.nquad * zi::kQuad);
+    a.scale_is_pow2 = (uint8_t)c.scale_is_pow2;
+    a.max_norm_is_pow2 = (uint8_t)c.max_norm_is_pow2;
+    a.beta1 = c.beta1; a.beta2 = c.beta2; a.omb1 = c.omb1; a.omb2 = c.omb2;
+    a.eps = c.eps; a.step_size = c.step_size; a.inv_sqrt_bc2 = c.inv_sqrt_bc2;
+    a.decay = l2 ? c.weight_decay : c.decay;
+    a.loss_scale = c.loss_scale; a.max_grad_norm = c.max_grad_norm; a.host_gscale = c.host_gscale;
+    return true;
+}
+
 // Issues the fused step over a list of device-resident segments.
 struct StepIssuer {
     zi::StepArgs args{};
@@ -546,10 +577,16 @@ struct NormIssuer {
         a.out = final ? d_out : nullptr;
         a.loss_scale = loss_scale;
         a.accumulate = finalized;
+        a.n_groups = blocks;
         // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
         // final sum are ordinary launches (the same order as in StepIssuer).
-        const bool any_order = used > 0 && may_overlap(s);
-        e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
+        if (final && keep && a.n_desc == 1) {
+            e = zi::launch_norm_one({{a.t[0]}, a.n_tiles, blocks, a.partials, a.mark_low, a.mark_high, a.patience, loss_scale,
+                                     a.out, a.accumulate}, dt, s);
+        } else {
+            const bool any_order = used > 0 && may_overlap(s);
+            e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
+        }
         ++launches;
         if (final) finalized = 1;
         else used += blocks;

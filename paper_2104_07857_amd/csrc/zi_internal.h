@@ -127,6 +127,25 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
+// One short tensor (adamw_short_kernel), in few bytes: a call on it takes the host longer than the GPU, and what the runtime takes
+// for a launch depends on the size of its arguments.  Issue of an empty kernel in us (the runtime runs in one of two modes for
+// the life of a process): up to 112 bytes 2.4 or 2.85, 120 and more 2.5 or 3.55, StepArgs' 3.3 KB 2.65 or 4.1.
+struct StepOne {
+    float* p_body;         // p + head
+    float* m_body;
+    float* v_body;
+    const uint16_t* g_body;
+    uint16_t* lp_body;     // p_lp + head, null if there is no copy
+    const zi_norm_result* d_norm;
+    double inv_loss_scale;
+    uint32_t nquad;
+    uint8_t head, tail, scale_is_pow2, max_norm_is_pow2;
+    float beta1, beta2, omb1, omb2, eps, step_size, inv_sqrt_bc2;
+    float decay;           // of AdamW, or the weight decay of Adam with L2
+    float loss_scale, max_grad_norm, host_gscale;
+};
+static_assert(sizeof(StepOne) <= 112, "kernel arguments");
+
 // Launches over many tensors (adamw_list_kernel), which a workgroup looks up in groups.  A list whose tensors are
 // views at the same places of five flat buffers, as the partitions of a sharded optimizer are, needs one place per
 // tensor (FlatArgs); any other list five addresses (ListArgs).
@@ -223,6 +242,7 @@ struct NormDesc {
 struct NormArgs {
     NormDesc t[kMaxNormDesc];
     uint32_t n_desc, n_tiles;
+    uint32_t n_groups;              // workgroups of the launch
     NormPartial* partials;          // of this launch
     uint32_t mark_low, mark_high;   // neither is zero; no other launch of the process has the same two
     uint32_t patience;              // kNormPatience
@@ -233,15 +253,30 @@ struct NormArgs {
 };
 static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
 
+// The same for one tensor, small as StepOne is.
+struct NormOne {
+    static constexpr uint32_t n_desc = 1;
+    NormDesc t[1];
+    uint32_t n_tiles, n_groups;
+    NormPartial* partials;
+    uint32_t mark_low, mark_high, patience;
+    float loss_scale;
+    zi_norm_result* out;
+    int32_t accumulate;
+};
+static_assert(sizeof(NormOne) <= 112, "kernel arguments");
+
 // Launchers (zi_kernels.hip).  Each returns the hipError_t of the launch.
 // any_order: may run beside the launches in front of it on the stream (see StepIssuer for where that is safe).
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
+hipError_t launch_step_short(const StepOne& a, int dt, bool l2, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
+hipError_t launch_norm_one(const NormOne& a, int dt, hipStream_t s);      // ordinary loads
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);
 

@@ -376,6 +376,28 @@ void adamw_wide_kernel(const StepArgs a)
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, a.c);
 }
 
+// Up to kStepShortTiles tiles of one tensor: the same from arguments that are quickly written (StepOne).
+template <int DT, bool L2>
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
+void adamw_short_kernel(const StepOne a)
+{
+    const StepConsts c = {a.beta1, a.beta2, a.omb1, a.omb2, a.eps, a.step_size, a.inv_sqrt_bc2, L2 ? 0.0f : a.decay,
+                          a.decay, a.loss_scale, a.max_grad_norm, a.host_gscale, a.scale_is_pow2, a.max_norm_is_pow2,
+                          a.inv_loss_scale};
+    GlobalF4 __restrict__ p4 = (GlobalF4)(uintptr_t)a.p_body;
+    GlobalF4 __restrict__ m4 = (GlobalF4)(uintptr_t)a.m_body;
+    GlobalF4 __restrict__ v4 = (GlobalF4)(uintptr_t)a.v_body;
+    GlobalConstU2 __restrict__ g2 = (GlobalConstU2)(uintptr_t)a.g_body;
+    GlobalU2 __restrict__ lp2 = (GlobalU2)(uintptr_t)a.lp_body;
+    uint32_t nquad = a.nquad;
+    asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
+    float gscale;
+    if (!step_prologue(a.d_norm, c, gscale)) return;
+    const uint32_t tile = tile_of_block(blockIdx.x, 0, (nquad + kStepTileQuads - 1) / kStepTileQuads);
+    if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
+    step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
+}
+
 // n += block >= start; first = the start, if so.  Three scalar instructions; the compiler goes through a
 // vector register.
 __device__ __forceinline__ void count_start(uint32_t block, uint32_t start, uint32_t& n, uint32_t& first)
@@ -483,6 +505,17 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
         else    { if (single) ZI_LAUNCH_STEP(ZI_FP16, false, true); else ZI_LAUNCH_STEP(ZI_FP16, false, false); }
     }
 #undef ZI_LAUNCH_STEP
+    return hipGetLastError();
+}
+
+hipError_t launch_step_short(const StepOne& a, int dt, bool l2, hipStream_t s)
+{
+    const uint32_t n_tiles = (a.nquad + kStepTileQuads - 1) / kStepTileQuads;
+    const dim3 grid(n_tiles < 1 ? 1 : n_tiles), block(kStepThreads);
+#define ZI_LAUNCH_SHORT(DT, L2) hipLaunchKernelGGL((adamw_short_kernel<DT, L2>), grid, block, kStepLds16, s, a)
+    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_SHORT(ZI_BF16, true); else ZI_LAUNCH_SHORT(ZI_BF16, false); }
+    else               { if (l2) ZI_LAUNCH_SHORT(ZI_FP16, true); else ZI_LAUNCH_SHORT(ZI_FP16, false); }
+#undef ZI_LAUNCH_SHORT
     return hipGetLastError();
 }
 
@@ -721,8 +754,8 @@ __device__ __forceinline__ double sum_of_waves(const double (&s)[NWAVES])
 // finite sum.  Infinities and NaN make the sum infinite or NaN and nothing else does (2^63 of the largest squares are
 // 1e96), so the sum itself says whether there was one.
 // KEEP: ordinary loads, which leave the gradients in the memory-side cache (kNormKeepElems).
-template <int DT, int THREADS, bool KEEP>
-__device__ __forceinline__ double sumsq_tiles(const NormArgs& a, uint32_t first, uint32_t step)
+template <int DT, int THREADS, bool KEEP, typename Args>
+__device__ __forceinline__ double sumsq_tiles(const Args& a, uint32_t first, uint32_t step)
 {
     constexpr int UNROLL = kNormTileVecs / THREADS;
     double acc0 = 0.0, acc1 = 0.0;
@@ -803,8 +836,8 @@ __device__ __forceinline__ void put_norm_result(double sumsq, float loss_scale, 
 // Marks tell this launch's partials from whatever the workspace held; they are taken away again behind the sum, since
 // a captured launch is replayed with the same ones.
 // The partials are added in the order of norm_finalize_kernel: the same bits, and independent of scheduling.
-template <int DT, bool KEEP>
-__global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const NormArgs a)
+template <int DT, bool KEEP, typename Args>
+__global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const Args a)
 {
     constexpr int THREADS = KEEP ? kNormKeepThreads : kNormStreamThreads;
     constexpr int kWaves = THREADS / 64, kRounds = kNormGroups / THREADS;
@@ -812,10 +845,10 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
     __shared__ double s_partial[kNormGroups / 64];
     __shared__ uint32_t s_missing;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool last = a.out && blockIdx.x == gridDim.x - 1;
-    uint32_t first = blockIdx.x, step = gridDim.x;
+    const bool last = a.out && blockIdx.x == a.n_groups - 1;
+    uint32_t first = blockIdx.x, step = a.n_groups;
     for (;;) {
-        const double sum = wave_sum(sumsq_tiles<DT, THREADS, KEEP>(a, first, step));
+        const double sum = wave_sum(sumsq_tiles<DT, THREADS, KEEP, Args>(a, first, step));
         if (lane == 0) s_sum[wave] = sum;
         if (threadIdx.x == 0) s_missing = 0;
         __syncthreads();
@@ -830,7 +863,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
         for (int r = 0; r < kRounds; ++r) {
             const uint32_t i = threadIdx.x + r * THREADS;
             double x = 0.0;
-            if (i < gridDim.x) {
+            if (i < a.n_groups) {
                 NormPartial* const at = a.partials + i;
                 uint64_t low = 0, high = 0;
                 bool there = false;
@@ -895,10 +928,18 @@ hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bo
     const dim3 grid(n_blocks), block(keep ? kNormKeepThreads : kNormStreamThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
 #define ZI_LAUNCH_NORM(DT, KEEP) \
-    hipExtLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP>), grid, block, 0, s, nullptr, nullptr, flags, a)
+    hipExtLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP, NormArgs>), grid, block, 0, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
     else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
 #undef ZI_LAUNCH_NORM
+    return hipGetLastError();
+}
+
+hipError_t launch_norm_one(const NormOne& a, int dt, hipStream_t s)
+{
+    const dim3 grid(a.n_groups), block(kNormKeepThreads);
+    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_partial_kernel<ZI_BF16, true, NormOne>), grid, block, 0, s, a);
+    else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16, true, NormOne>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

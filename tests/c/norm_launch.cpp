@@ -15,5 +15,6 @@ extern "C" int norm_launch(const void* g, int64_t numel, int dt, int keep, uint3
     a.out = (zi_norm_result*)out;
     a.loss_scale = 2.0f;
     const uint32_t blocks = a.n_tiles < (uint32_t)zi::kNormGroups ? a.n_tiles : (uint32_t)zi::kNormGroups;
+    a.n_groups = blocks;
     return (int)zi::launch_norm_partials(a, blocks, dt, keep != 0, false, nullptr);
 }
