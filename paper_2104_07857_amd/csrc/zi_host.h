@@ -133,7 +133,7 @@ inline int choose_head(const void* p, const void* m, const void* v, const void* 
 
 // Tensors of at least this many tiles (2^22 elements, some 20 microseconds of HBM time) are launched
 // alone; shorter ones share launches of up to kMaxStepDesc tensors.  Lists of more than kMaxListDesc tensors
-// go to adamw_list_kernel as they are.  That line is what an argument block holds, not a crossover: by length, shorter
+// (StepIssuer::expect says which others) go to adamw_list_kernel as they are.  That line is what an argument block holds, not a crossover: by length, shorter
 // lists of middling tensors would gain too (65 of 4.2e6 elements 1421 -> 1211 us, of 3.4e7 10.0 -> 9.6 ms, of 1.0e8 28.8 ->
 // 28.9), and 48 tensors of 6.7e7 on average lost 1.4%.
 #ifndef ZI_SOLO_TILES
@@ -196,7 +196,9 @@ struct StepIssuer {
     int32_t cur_tensor = -1;
     int32_t tensor_of[zi::FlatArgs::kMax] = {};
     // Lists of more than kMaxListDesc tensors (expect()): launches of many, whatever their length, in `list`, or in
-    // `flat` if the tensors are short and all at the same places of five flat buffers.  Four times as many to a launch
+    // `flat` if the tensors are short and all at the same places of five flat buffers; those also from kMaxStepDesc
+    // tensors on, which are one launch then instead of two or more (step alone, us: 40 tensors of 1000 elements 6.3 ->
+    // 3.5, 60 of 3.0e4 13.1 -> 10.2, 48 of 2.6e5 69.4 -> 66.6; one launch either way, 24 of 1.0e5 13.0 / 13.4).  Four times as many to a launch
     // save 3 us each time, and twice as many entries in the lookup cost every workgroup some 4%.  Step alone, us, list /
     // flat: 200 tensors of 2e4 elements 35.3 / 25.3, 1000 of 1e5 512 / 480, 288 of 2.6e5 361 / 352, 288 of 1.0e6
     // 1368 / 1427, 72 of 4.2e6 1363 / 1420: the line is drawn at an average of 5 * 2^16.
@@ -214,8 +216,10 @@ struct StepIssuer {
             n += t[i].numel > 0;
             total += t[i].numel;
         }
-        if (n <= zi::kMaxListDesc) return;
-        kind = total / n <= kFlatAverage && is_flat(t, n_tensors) ? kFlat : kList;
+        if (n <= zi::kMaxStepDesc) return;
+        const bool short_and_flat = total / n <= kFlatAverage && is_flat(t, n_tensors);
+        if (!short_and_flat && n <= zi::kMaxListDesc) return;
+        kind = short_and_flat ? kFlat : kList;
         list.c = flat.c = args.c;
         list.d_norm = flat.d_norm = args.d_norm;
     }
