@@ -539,11 +539,13 @@ inline uint64_t next_norm_number()
 }
 
 // Issues the gradient reduction over a list of gradient arrays that the device can reach: partial-sum
-// launches of up to kMaxNormDesc tensors.  Where one launch takes what is left, it also makes the final sum; otherwise, and
-// whenever the workspace's partial slots run out, a finalize pass does.  After the first final sum the later ones
-// add to the result already in d_out.
+// launches of up to NormArgs::kMax tensors, the last of which also makes the final sum.  Whenever the workspace's partial slots
+// run out, a finalize pass folds them; after the first final sum the later ones add to the result already in d_out.
 struct NormIssuer {
-    zi::NormArgs a{};
+    zi::NormArgs a;
+    int32_t n_desc = 0;
+    const uint16_t* g0 = nullptr;        // the first of them
+    uint32_t n0 = 0;
     zi::NormPartial* partials;
     uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
     uint32_t used = 0;                   // partials written since the last finalize
@@ -558,6 +560,7 @@ struct NormIssuer {
     NormIssuer(zi::NormPartial* partials_, int dt_, float ls, zi_norm_result* out, hipStream_t st)
         : partials(partials_), dt(dt_), loss_scale(ls), d_out(out), s(st)
     {
+        a.n_tiles = 0;
     }
     static int64_t tiles_for(const uint16_t* g, int64_t n)
     {
@@ -566,10 +569,10 @@ struct NormIssuer {
         const int64_t nt = (body + zi::kNormTileElems - 1) / zi::kNormTileElems;
         return nt < 1 ? 1 : nt;              // the first tile also owns the unaligned ends
     }
-    // final: the launch also makes the final sum (no partials of other launches are waiting for one).
+    // final: the launch also makes the final sum.
     hipError_t flush_launch(bool final = false)
     {
-        if (a.n_desc == 0) return hipSuccess;
+        if (n_desc == 0) return hipSuccess;
         hipError_t e = hipSuccess;
         const uint32_t blocks = a.n_tiles < groups ? a.n_tiles : groups;
         if (used + blocks > zi::kMaxPartials && (e = flush_partials()) != hipSuccess) return e;
@@ -582,19 +585,27 @@ struct NormIssuer {
         a.loss_scale = loss_scale;
         a.accumulate = finalized;
         a.n_groups = blocks;
-        // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
-        // final sum are ordinary launches (the same order as in StepIssuer).
-        if (final && keep && a.n_desc == 1) {
-            e = zi::launch_norm_one({{a.t[0]}, a.n_tiles, blocks, a.partials, a.mark_low, a.mark_high, a.patience, loss_scale,
-                                     a.out, a.accumulate}, dt, s);
+        a.n_before = final ? used : 0;
+        if (final && n_desc == 1 && used == 0) {
+            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, blocks, a.mark_low, a.mark_high, a.patience, loss_scale,
+                                     a.accumulate}, dt, keep, s);
         } else {
-            const bool any_order = used > 0 && may_overlap(s);
+            a.first_tile[n_desc] = a.n_tiles;
+            for (int32_t i = n_desc + 1; i <= zi::NormArgs::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
+            for (int32_t i = 0; i < zi::NormArgs::kGroups; ++i) {
+                const int32_t d = i * zi::NormArgs::kGroup;
+                a.group_start[i] = d < n_desc ? a.first_tile[d] : 0xFFFFFFFFu;
+            }
+            // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
+            // one with the final sum are ordinary launches (the same order as in StepIssuer).
+            const bool any_order = used > 0 && !final && may_overlap(s);
             e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
         }
         ++launches;
+        used = final ? 0 : used + blocks;
         if (final) finalized = 1;
-        else used += blocks;
-        a.n_desc = a.n_tiles = 0;
+        n_desc = 0;
+        a.n_tiles = 0;
         return e;
     }
     hipError_t flush_partials()
@@ -608,19 +619,24 @@ struct NormIssuer {
     hipError_t add(const uint16_t* g, int64_t n)
     {
         for (; n > 0; g += zi::kNormMaxPiece, n -= zi::kNormMaxPiece) {
-            if (a.n_desc == zi::kMaxNormDesc)
+            if (n_desc == zi::NormArgs::kMax)
                 if (const hipError_t e = flush_launch(); e != hipSuccess) return e;
-            const int64_t m = n < zi::kNormMaxPiece ? n : zi::kNormMaxPiece;
-            a.t[a.n_desc++] = {g, (uint32_t)m, a.n_tiles};
-            a.n_tiles += (uint32_t)tiles_for(g, m);
+            const int64_t m = n < zi::kNormMaxPiece ? n : zi::kNormMaxPiece, tiles = tiles_for(g, m);
+            const uint64_t address = reinterpret_cast<uintptr_t>(g);
+            if (address >> 48) return hipErrorInvalidValue;
+            if (n_desc == 0) {
+                g0 = g;
+                n0 = (uint32_t)m;
+            }
+            a.where[n_desc] = address | (uint64_t)(tiles * zi::kNormTileElems + zi::kNormTileSlack - m) << 48;
+            a.first_tile[n_desc++] = a.n_tiles;
+            a.n_tiles += (uint32_t)tiles;
         }
         return hipSuccess;
     }
     hipError_t finish()
     {
-        if (used == 0 && a.n_desc > 0) return flush_launch(true);
-        if (const hipError_t e = flush_launch(); e != hipSuccess) return e;
-        return flush_partials();
+        return n_desc > 0 ? flush_launch(true) : flush_partials();
     }
 };
 

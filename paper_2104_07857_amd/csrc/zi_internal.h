@@ -82,7 +82,6 @@ constexpr int64_t kNormKeepElems = (int64_t)11 << 23;
 // Gradients in host memory are bound by the link, which few requests in flight fill: GB/s by workgroups
 // 32: 55.9, 64: 57.5, 128: 57.4, 256: 56.4, 1024: 55.9.
 constexpr int kNormLinkGroups = 64;
-constexpr int kMaxNormDesc = 224;    // gradient tensors per partial-sum launch (the argument block stays below 4 KiB)
 constexpr int64_t kNormMaxPiece = (int64_t)1 << 31;   // longer tensors take several descriptors
 constexpr uint32_t kMaxPartials = 16384;   // per-block partial results the workspace holds
 
@@ -233,36 +232,42 @@ struct CopyArgs {
     uint32_t serial;       // what a block's flag becomes once the block is at its destination
 };
 
-struct NormDesc {
-    const uint16_t* g;
-    uint32_t numel;
-    uint32_t first_tile;   // index of this tensor's first tile within the launch
-};
-
+// The reduction over a list: 12 bytes a tensor, so that a launch takes 320 (with address, length and first tile in 16 bytes
+// it took 224), which a workgroup looks up in groups as adamw_list_kernel does, in two round trips to the scalar cache where
+// halving takes eight.  Reduction alone, us: 288 tensors with 3.0e8 elements 94 -> 90, 300 of 1..20,000 8.7 -> 5.1 (two launches and
+// a final sum before), 1000 of 1..100,000 43 -> 29, 200 of 1..40,000 5.1 / 5.2.
 struct NormArgs {
-    NormDesc t[kMaxNormDesc];
-    uint32_t n_desc, n_tiles;
+    static constexpr int kGroup = 16, kGroups = 20, kMax = kGroup * kGroups;
+    // Address of the tensor in the lower 48 bits (the GPU has no others); above, how many elements its length is
+    // short of its tiles * kNormTileElems + kNormTileSlack.
+    uint64_t where[kMax];
+    uint32_t first_tile[kMax + 1];  // behind the list: n_tiles, then 0xFFFFFFFF
+    uint32_t group_start[kGroups];  // first_tile of every group's first
+    uint32_t n_tiles;
     uint32_t n_groups;              // workgroups of the launch
-    NormPartial* partials;          // of this launch
     uint32_t mark_low, mark_high;   // neither is zero; no other launch of the process has the same two
     uint32_t patience;              // kNormPatience
-    // A launch that leaves all partials of a reduction (null: norm_finalize_kernel sums them up):
-    zi_norm_result* out;
     float loss_scale;
-    int32_t accumulate;             // adds to what is there
+    NormPartial* partials;          // of this launch
+    // The last launch of a reduction makes the final sum (null: not this one), over its own partials and the n_before in
+    // front of them that launches before it left.
+    zi_norm_result* out;
+    uint32_t n_before;
+    int32_t accumulate;             // adds to what is in *out
 };
 static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
+// Elements that a tensor's first tile takes beside its vectors: at most 7 in front of them and 7 behind.
+constexpr uint32_t kNormTileSlack = 2 * (kVec - 1);
 
 // The same for one tensor, small as StepOne is.
 struct NormOne {
-    static constexpr uint32_t n_desc = 1;
-    NormDesc t[1];
-    uint32_t n_tiles, n_groups;
+    const uint16_t* g;
     NormPartial* partials;
-    uint32_t mark_low, mark_high, patience;
-    float loss_scale;
     zi_norm_result* out;
+    uint32_t numel, n_tiles, n_groups, mark_low, mark_high, patience;
+    float loss_scale;
     int32_t accumulate;
+    static constexpr uint32_t n_before = 0;
 };
 static_assert(sizeof(NormOne) <= 112, "kernel arguments");
 
@@ -276,7 +281,7 @@ hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
-hipError_t launch_norm_one(const NormOne& a, int dt, hipStream_t s);      // ordinary loads
+hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);
 

@@ -754,33 +754,69 @@ __device__ __forceinline__ double sum_of_waves(const double (&s)[NWAVES])
 // finite sum.  Infinities and NaN make the sum infinite or NaN and nothing else does (2^63 of the largest squares are
 // 1e96), so the sum itself says whether there was one.
 // KEEP: ordinary loads, which leave the gradients in the memory-side cache (kNormKeepElems).
+struct NormTensor {
+    const ZI_GLOBAL uint16_t* g;
+    uint32_t numel, first_tile, next_tile;
+};
+__device__ __forceinline__ NormTensor tensor_of_tile(const NormArgs& a, uint32_t tile)
+{
+    uint32_t group = 0, first = 0;        // the first start is 0, so both counts are at least 1
+#pragma unroll
+    for (int i = 0; i < NormArgs::kGroups; ++i) count_start(tile, a.group_start[i], group, first);
+    uint32_t d = --group * NormArgs::kGroup;
+#pragma unroll
+    for (int i = 0; i < NormArgs::kGroup; ++i) count_start(tile, a.first_tile[group * NormArgs::kGroup + i], d, first);
+    --d;
+    const uint64_t where = a.where[d];
+    const uint32_t next = a.first_tile[d + 1];
+    return {(const ZI_GLOBAL uint16_t*)(uintptr_t)(where << 16 >> 16),
+            (next - first) * (uint32_t)kNormTileElems + kNormTileSlack - (uint32_t)(where >> 48), first, next};
+}
+__device__ __forceinline__ NormTensor tensor_of_tile(const NormOne& a, uint32_t) 
+{
+    return {(const ZI_GLOBAL uint16_t*)(uintptr_t)a.g, a.numel, 0, 0xFFFFFFFFu};
+}
+
+// A buffer of raw data.  All lanes have the same one; readfirstlane says so to the compiler, which would otherwise
+// loop over the lanes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(uintptr_t start, uint32_t bytes)
+{
+    const uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)start), high = __builtin_amdgcn_readfirstlane((uint32_t)(start >> 32));
+    constexpr int kRawData = 0x00020000;
+    return __builtin_amdgcn_make_buffer_rsrc((ZI_GLOBAL void*)((uintptr_t)high << 32 | low), 0,
+                                             __builtin_amdgcn_readfirstlane(bytes), kRawData);
+}
+
+// Vector `byte / 16` of a tile of which `bytes` are there: zeros behind them.  The bound is checked by the memory unit, so a
+// ragged tile has all its loads in flight like a whole one; behind branches they were waited for in three groups.
+template <bool KEEP>
+__device__ __forceinline__ u32x4 load_in_tile(__amdgpu_buffer_rsrc_t tile, uint32_t byte, uint32_t first)
+{
+    constexpr int kStream = 2;            // the streaming (nt) policy of a buffer access
+    return __builtin_amdgcn_raw_buffer_load_b128(tile, (int)byte, (int)first, KEEP ? 0 : kStream);
+}
+
 template <int DT, int THREADS, bool KEEP, typename Args>
 __device__ __forceinline__ double sumsq_tiles(const Args& a, uint32_t first, uint32_t step)
 {
     constexpr int UNROLL = kNormTileVecs / THREADS;
     double acc0 = 0.0, acc1 = 0.0;
-    uint32_t d = 0;
+    NormTensor T = {nullptr, 0, 0, 0};
     for (uint32_t t = first; t < a.n_tiles; t += step) {
-        d = find_desc(a.t, d, a.n_desc, t);
-        const NormDesc& T = a.t[d];
+        if (t >= T.next_tile) T = tensor_of_tile(a, t);
         const uint32_t tile = t - T.first_tile;
-        const uint32_t lead = (uint32_t)(-(reinterpret_cast<uintptr_t>(T.g) / 2)) % kVec;
+        const uint32_t lead = (uint32_t)(-((uintptr_t)T.g / 2)) % kVec;
         const uint32_t head = lead < T.numel ? lead : T.numel;
         const uint32_t nvec = (T.numel - head) / kVec;
-        const u32x4* __restrict__ g4 = reinterpret_cast<const u32x4*>(T.g + head);
+        const ZI_GLOBAL u32x4* __restrict__ g4 = (const ZI_GLOBAL u32x4*)(T.g + head);
 
-        const uint32_t v0 = tile * kNormTileVecs + threadIdx.x;
+        const uint32_t at = tile * kNormTileVecs, left = at < nvec ? nvec - at : 0;
+        const uint32_t bytes = (left < (uint32_t)kNormTileVecs ? left : (uint32_t)kNormTileVecs) * 16;
+        const uintptr_t start = (uintptr_t)(g4 + at);
+        const __amdgpu_buffer_rsrc_t here = raw_buffer(start, bytes);
         u32x4 g[UNROLL];
-        if ((tile + 1) * kNormTileVecs <= nvec) {
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
-        } else {
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                g[u] = u32x4{0, 0, 0, 0};
-                if (v0 + u * THREADS < nvec) g[u] = KEEP ? g4[v0 + u * THREADS] : load_stream(g4 + v0 + u * THREADS);
-            }
-        }
+        for (int u = 0; u < UNROLL; ++u) g[u] = load_in_tile<KEEP>(here, threadIdx.x * 16, (uint32_t)u * THREADS * 16);
         if (tile == 0) {
             const uint32_t lane = threadIdx.x, body_end = head + nvec * kVec;
             const bool front = lane < head, back = lane >= kVec && lane - kVec < T.numel - body_end;
@@ -824,18 +860,18 @@ __device__ __forceinline__ void put_norm_result(double sumsq, float loss_scale, 
     *out = norm_result(sumsq, !__builtin_isfinite(sumsq), loss_scale);
 }
 
-// Bound: HBM (or the link), 2 bytes per element read; short lists: the launch.  Each workgroup leaves one partial.  Where
-// all partials of a reduction come from one launch, its last workgroup waits for them, adds them up and
-// writes the result: a second kernel for that costs 1.5 to 3 us, as long as the reduction of a short list itself.  In us,
+// Bound: HBM (or the link), 2 bytes per element read; short lists: the launch.  Each workgroup leaves one partial.  The last
+// workgroup of a reduction's last launch waits for those of its own launch (the others are older on the stream), adds all up and
+// writes the result: a kernel for that costs 1.5 to 3 us, as long as the reduction of a short list itself.  In us,
 // two kernels / one: 6.6e4 elements 5.2 / 3.0 (one workgroup for everything: 5.8), 1.0e6 5.1 / 3.5, 4.2e6 5.1 / 3.5,
 // 3.1e8 92.5 / 91.4.
 // The wait is short: the tiles are shared out evenly, and workgroups start in order, so the others are on their way when
 // the last one runs.  None of them waits for anything.  Should partials still be missing after `patience` looks (the device
-// is busy with other work, or a call that was not ordered behind this one overwrote them), the last workgroup goes over all
-// tiles itself.
+// is busy with other work, or a call that was not ordered behind this one overwrote them), the last workgroup goes over the
+// launch's tiles itself.
 // Marks tell this launch's partials from whatever the workspace held; they are taken away again behind the sum, since
 // a captured launch is replayed with the same ones.
-// The partials are added in the order of norm_finalize_kernel: the same bits, and independent of scheduling.
+// The order of the sum does not depend on scheduling.
 template <int DT, bool KEEP, typename Args>
 __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const Args a)
 {
@@ -847,12 +883,20 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool last = a.out && blockIdx.x == a.n_groups - 1;
     uint32_t first = blockIdx.x, step = a.n_groups;
+    double before = 0.0;
+    if (last)
+        for (uint32_t i = threadIdx.x; i < a.n_before; i += THREADS) {
+            const NormPartial& p = (a.partials - a.n_before)[i];
+            before += partial_sum(p.low, p.high);
+        }
     for (;;) {
-        const double sum = wave_sum(sumsq_tiles<DT, THREADS, KEEP, Args>(a, first, step));
+        double sum = sumsq_tiles<DT, THREADS, KEEP, Args>(a, first, step);
+        if (last && step == 1) sum += before;
+        sum = wave_sum(sum);
         if (lane == 0) s_sum[wave] = sum;
         if (threadIdx.x == 0) s_missing = 0;
         __syncthreads();
-        if (last && step == 1) {          // the whole list is in this workgroup
+        if (last && step == 1) {          // the launch's whole list is in this workgroup
             if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_sum), a.loss_scale, a.accumulate, a.out);
             return;
         }
@@ -862,7 +906,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
             const uint32_t i = threadIdx.x + r * THREADS;
-            double x = 0.0;
+            double x = r == 0 ? before : 0.0;
             if (i < a.n_groups) {
                 NormPartial* const at = a.partials + i;
                 uint64_t low = 0, high = 0;
@@ -873,7 +917,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
                     there = (uint32_t)low == a.mark_low && (uint32_t)high == a.mark_high;
                 }
                 if (!there) s_missing = 1;
-                x = partial_sum(low, high);
+                x += partial_sum(low, high);
                 __hip_atomic_store(&at->low, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&at->high, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -893,7 +937,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
 
 constexpr int kFinalThreads = kNormGroups;   // one partial each where one launch made them all
 
-// One workgroup adds the partials of several launches in a fixed order and writes the result.
+// One workgroup adds partials in a fixed order and writes the result: where the workspace is full, and for empty lists.
 __global__ __launch_bounds__(kFinalThreads) void norm_finalize_kernel(const NormPartial* __restrict__ partials,
                                                                       uint32_t count, float loss_scale,
                                                                       int accumulate, zi_norm_result* out)
@@ -935,11 +979,13 @@ hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bo
     return hipGetLastError();
 }
 
-hipError_t launch_norm_one(const NormOne& a, int dt, hipStream_t s)
+hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s)
 {
-    const dim3 grid(a.n_groups), block(kNormKeepThreads);
-    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_partial_kernel<ZI_BF16, true, NormOne>), grid, block, 0, s, a);
-    else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16, true, NormOne>), grid, block, 0, s, a);
+    const dim3 grid(a.n_groups), block(keep ? kNormKeepThreads : kNormStreamThreads);
+#define ZI_LAUNCH_NORM(DT, KEEP) hipLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP, NormOne>), grid, block, 0, s, a)
+    if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
+    else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
+#undef ZI_LAUNCH_NORM
     return hipGetLastError();
 }
 

@@ -5,9 +5,13 @@
 extern "C" int norm_launch(const void* g, int64_t numel, int dt, int keep, uint32_t patience, void* partials, void* out)
 {
     zi::NormArgs a{};
-    a.t[0] = {(const uint16_t*)g, (uint32_t)numel, 0};
-    a.n_desc = 1;
-    a.n_tiles = (uint32_t)zi::host::NormIssuer::tiles_for((const uint16_t*)g, numel);
+    const int64_t tiles = zi::host::NormIssuer::tiles_for((const uint16_t*)g, numel);
+    a.where[0] = (uint64_t)g | (uint64_t)(tiles * zi::kNormTileElems + zi::kNormTileSlack - numel) << 48;
+    a.n_tiles = (uint32_t)tiles;
+    for (uint32_t& x : a.first_tile) x = 0xFFFFFFFFu;
+    for (uint32_t& x : a.group_start) x = 0xFFFFFFFFu;
+    a.first_tile[0] = a.group_start[0] = 0;
+    a.first_tile[1] = a.n_tiles;
     a.partials = (zi::NormPartial*)partials;
     a.mark_low = 0x12345679u;
     a.mark_high = 0x9ABCDEF1u;

@@ -52,6 +52,30 @@ def test_every_number_of_workgroups(n, dt):
     assert len(seen) == 1
 
 
+@pytest.mark.parametrize("dt", [zi.ZI_BF16, zi.ZI_FP16])
+@pytest.mark.parametrize("count", [2, 15, 16, 17, 319, 320, 321, 641])
+def test_lists_around_the_lookup_s_limits(count, dt):
+    """Groups of 16 tensors, 320 to a launch, one launch or several; tensors shorter than a vector and ends around a tile's at
+    every distance from a 16-byte boundary."""
+    rng = np.random.default_rng(count)
+    lengths = [int(x) for x in rng.integers(1, 40, count)]
+    for i in range(0, count, 3):
+        lengths[i] = TILE * int(rng.integers(1, 4)) + int(rng.integers(-9, 16))
+    starts = np.cumsum([1] + [n + int(x) for n, x in zip(lengths, rng.integers(0, 9, count))])[:-1].tolist()
+    g = _grads(starts[-1] + lengths[-1] + 1, dt, count)
+    want, _ = oracle.grad_sumsq([g[s:s + n].copy() for s, n in zip(starts, lengths)], dt)
+    d, nb = to_dev(g), NormBuffers()
+    views = [d[s:s + n] for s, n in zip(starts, lengths)]
+    got = _norm(views, dt, nb)
+    assert got[2] == 0 and abs(got[0] - want) <= 1e-12 * want and got == _norm(views, dt, nb)
+    # an overflow in the last element of the last tensor is seen, one behind it is not
+    for at, flag in ((starts[-1] + lengths[-1] - 1, 1), (starts[-1] + lengths[-1], 0)):
+        h = g.copy()
+        h[at] = 0x7F80 if dt == zi.ZI_BF16 else 0x7C00
+        e = to_dev(h)
+        assert _norm([e[s:s + n] for s, n in zip(starts, lengths)], dt, nb)[2] == flag
+
+
 @pytest.mark.parametrize("n", [KEEP, KEEP + 1])
 def test_both_ways_of_reading(n):
     g = to_dev(np.tile(_grads(1 << 16, zi.ZI_BF16, 3), n // (1 << 16) + 1))[:n]
