@@ -88,6 +88,26 @@ class zi_step_plan_item(ctypes.Structure):
 _lib = None
 
 
+def _not_taken(*args):
+    return None
+
+
+# The calls made once per step, for arguments in their usual form (csrc/zi_python.c): a status, or None for other forms.
+_call_norm = _call_norm_noalloc = _call_step = _not_taken
+
+
+def _bind_calls(L):
+    global _call_norm, _call_norm_noalloc, _call_step
+    try:
+        from . import _zi_call as c
+    except ImportError:                # not built: everything goes through ctypes
+        return
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value                             # noqa: E731
+    if c.bind(address(L.zi_grad_norm), address(L.zi_grad_norm_noalloc), address(L.zi_adamw_step), zi_tensor(),
+              zi_adamw_config()):
+        _call_norm, _call_norm_noalloc, _call_step = c.grad_norm, c.grad_norm_noalloc, c.adamw_step
+
+
 def lib() -> ctypes.CDLL:
     """The loaded library.  Raises if it has not been built."""
     global _lib
@@ -160,6 +180,7 @@ def lib() -> ctypes.CDLL:
         L.zi_pinned_free.restype = ctypes.c_int
         L.zi_pinned_free.argtypes = [vp]
         _lib = L
+        _bind_calls(L)
     return _lib
 
 
@@ -231,6 +252,9 @@ def zi_norm_workspace_bytes(total_numel: int = 0, n_tensors: int = 0) -> int:
 
 def zi_grad_norm(tensors, dt: int, loss_scale: float, d_out, d_workspace, workspace_bytes: Optional[int] = None,
                  stream=None) -> int:
+    status = _call_norm(tensors, dt, loss_scale, d_out, d_workspace, workspace_bytes, stream)
+    if status is not None:
+        return status if status >= 0 else _check(status)
     arr, n = _as_tensor_array(tensors)
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size()
@@ -239,11 +263,17 @@ def zi_grad_norm(tensors, dt: int, loss_scale: float, d_out, d_workspace, worksp
 
 
 def zi_grad_norm_noalloc(tensors, dt: int, loss_scale: float, d_out, stream=None) -> int:
+    status = _call_norm_noalloc(tensors, dt, loss_scale, d_out, stream)
+    if status is not None:
+        return status if status >= 0 else _check(status)
     arr, n = _as_tensor_array(tensors)
     return _check(lib().zi_grad_norm_noalloc(arr, n, int(dt), float(loss_scale), _addr(d_out), _stream(stream)))
 
 
 def zi_adamw_step(tensors, dt: int, cfg: zi_adamw_config, d_norm=None, stream=None) -> int:
+    status = _call_step(tensors, dt, cfg, d_norm, stream)
+    if status is not None:
+        return status if status >= 0 else _check(status)
     arr, n = _as_tensor_array(tensors)
     return _check(lib().zi_adamw_step(arr, n, int(dt), ctypes.byref(cfg) if cfg is not None else None,
                                       _addr(d_norm), _stream(stream)))

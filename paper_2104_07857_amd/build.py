@@ -1,14 +1,16 @@
-"""Builds libzi.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libzi.so (HIP kernels + C ABI) for gfx950 with hipcc and _zi_call.so (argument marshalling) with gcc, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libzi.so")
+CALL_PATH = os.path.join(HERE, "_zi_call.so")
 SOURCES = ["zi_kernels.hip", "zi_api.hip", "zi_plan.hip", "zi_engine.hip", "zi_offload.hip", "zi_probe.hip"]
 
 # -ffp-contract=off: the only fused multiply-adds are the ones the kernels write as fma.
@@ -30,9 +32,9 @@ def hipcc() -> str:
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(CALL_PATH):
         return True
-    t = os.path.getmtime(LIB_PATH)
+    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(CALL_PATH))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + \
            [os.path.join(ROOT, "include", f) for f in ("zi.h", "zi_probe.h")]
     return any(os.path.getmtime(d) > t for d in deps)
@@ -44,10 +46,20 @@ HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-mavx2", "-mfma", "-mf16c", "-ffp-c
               "-Wall", "-Wextra", "-pthread"]
 
 
+def build_call() -> str:
+    """The Python side of the calls made once per step (csrc/zi_python.c)."""
+    subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter",
+                    "-Wno-missing-field-initializers", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+                    os.path.join(CSRC, "zi_python.c"), "-o", CALL_PATH], check=True)
+    return CALL_PATH
+
+
 def build(force: bool = True, extra_flags=(), out: str | None = None) -> str:
     out = out or LIB_PATH
     if not force and out == LIB_PATH and not needs_build():
         return out
+    if out == LIB_PATH:
+        build_call()
     objs = []
     for src in HOST_SOURCES:
         obj = os.path.join(HERE, "_" + os.path.splitext(src)[0] + ".o")
