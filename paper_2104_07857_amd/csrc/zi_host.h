@@ -549,7 +549,8 @@ struct NormIssuer {
     zi::NormPartial* partials;
     uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
     uint32_t used = 0;                   // partials written since the last finalize
-    bool keep = false;                   // see kNormKeepElems
+    bool keep = false;                   // see kNormKeepElems: all gradients, or the first tiles (of the launches to come)
+    uint32_t keep_left = 0;
     int launches = 0;                    // kernels so far
     int finalized = 0;
     int dt;
@@ -561,6 +562,11 @@ struct NormIssuer {
         : partials(partials_), dt(dt_), loss_scale(ls), d_out(out), s(st)
     {
         a.n_tiles = 0;
+    }
+    void keep_for_step(int64_t elems_of_call)
+    {
+        keep = elems_of_call <= zi::kNormKeepElems;
+        keep_left = keep || elems_of_call > zi::kNormKeepUpTo ? 0 : (uint32_t)(zi::kNormKeepElems / zi::kNormTileElems);
     }
     static int64_t tiles_for(const uint16_t* g, int64_t n)
     {
@@ -585,9 +591,11 @@ struct NormIssuer {
         a.loss_scale = loss_scale;
         a.accumulate = finalized;
         a.n_groups = blocks;
+        a.keep_tiles = keep_left < a.n_tiles ? keep_left : a.n_tiles;
+        keep_left -= a.keep_tiles;
         a.n_before = final ? used : 0;
         if (final && n_desc == 1 && used == 0) {
-            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, blocks, a.mark_low, a.mark_high, a.patience, loss_scale,
+            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, a.keep_tiles, blocks, a.mark_low, a.mark_high, a.patience, loss_scale,
                                      a.accumulate}, dt, keep, s);
         } else {
             a.first_tile[n_desc] = a.n_tiles;

@@ -68,16 +68,19 @@ constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 ele
 // a contiguous run of tiles per workgroup 12.2 / 94 / 378 / 101, half the loads in flight 13.0 / 92 / 376 / 100,
 // single-wavefront workgroups 12.7 / 92 / 373 / 105 at best.
 constexpr int kNormGroups = 512;
-// Calls of up to this many elements (176 of the 256 MiB of the memory-side cache) read the gradients with ordinary
-// loads, which leave them there for the step that reads them next; streaming loads pass the cache by.  In us, streaming /
-// ordinary loads / the reduction with workgroups of its own for every tensor that was here before:
-//   elements           3.4e7               6.7e7               9.2e7               1.0e8               1.3e8
-//   norm and step      172 / 165 / 172     326 / 313 / 328     444 / 428 / 447     488 / 469 / 489     653 / 627 / 657
-//   norm alone, cold   15.2 / 15.8 / 16.9  25.5 / 27.1 / 27.5  33.1 / 35.4 / 36.0  35.6 / 38.4 / 37.7  45.9 / 49.9 / 48.9
-//   norm of gradients a kernel has just written
-//                      15.5 / 14.4 / 17.1  24.9 / 25.0 / 26.6  26.9 / 27.8 / 34.1  33 / 34 / 38        39 / 57 / 44
-// A caller that only wants the norm pays up to 7% here for what a caller that steps gains 3 to 5% of a ten times longer
-// time.  The line is drawn where the reduction alone would become slower than it was before.
+// So many elements (176 of the 256 MiB of the memory-side cache), all of a call or the first of one of up to kNormKeepUpTo,
+// are read with ordinary loads, which leave them in the cache for the step that begins with them; streaming loads pass it by.
+// Norm and step in us, all streaming / this:
+//   elements                         3.4e7      6.7e7      9.2e7      1.3e8      2.0e8      2.6e8        3.0e8        1.3e9
+//   one call after the other         172 / 165  326 / 313  444 / 428  611 / 588  941 / 919  1228 / 1203  1420 / 1401  6148 / 6116
+//   a kernel has just written the gradients                447 / 431  612 / 597  948 / 924               1440 / 1419  6168 / 6128
+//   the cache is full of what a kernel has written elsewhere
+//                                                          449 / 457  614 / 623  946 / 955               1428 / 1440  6150 / 6170
+// What such a kernel wrote leaves the cache during the reduction then, at 35 us for all of it, which the step does not
+// quite give back.  The reduction alone, cold but clean, takes 2 to 3 us longer (9.2e7 elements 33.1 / 35.4, 288 tensors with 3.0e8
+// 91 / 94), on gradients just written it does not: beyond 2^28 elements that is more of its time than what the step gains of
+// its own.  7168 tiles instead of 5632 gain another 5 us and lose another 5.
+constexpr int64_t kNormKeepUpTo = (int64_t)1 << 28;
 constexpr int64_t kNormKeepElems = (int64_t)11 << 23;
 // Gradients in host memory are bound by the link, which few requests in flight fill: GB/s by workgroups
 // 32: 55.9, 64: 57.5, 128: 57.4, 256: 56.4, 1024: 55.9.
@@ -243,7 +246,7 @@ struct NormArgs {
     uint64_t where[kMax];
     uint32_t first_tile[kMax + 1];  // behind the list: n_tiles, then 0xFFFFFFFF
     uint32_t group_start[kGroups];  // first_tile of every group's first
-    uint32_t n_tiles;
+    uint32_t n_tiles, keep_tiles;
     uint32_t n_groups;              // workgroups of the launch
     uint32_t mark_low, mark_high;   // neither is zero; no other launch of the process has the same two
     uint32_t patience;              // kNormPatience
@@ -264,7 +267,7 @@ struct NormOne {
     const uint16_t* g;
     NormPartial* partials;
     zi_norm_result* out;
-    uint32_t numel, n_tiles, n_groups, mark_low, mark_high, patience;
+    uint32_t numel, n_tiles, keep_tiles, n_groups, mark_low, mark_high, patience;
     float loss_scale;
     int32_t accumulate;
     static constexpr uint32_t n_before = 0;
