@@ -132,10 +132,8 @@ inline int choose_head(const void* p, const void* m, const void* v, const void* 
 }
 
 // Tensors of at least this many tiles (2^22 elements, some 20 microseconds of HBM time) are launched
-// alone; shorter ones share launches of up to kMaxStepDesc tensors.  Lists of more than kMaxListDesc tensors
-// (StepIssuer::expect says which others) go to adamw_list_kernel as they are.  That line is what an argument block holds, not a crossover: by length, shorter
-// lists of middling tensors would gain too (65 of 4.2e6 elements 1421 -> 1211 us, of 3.4e7 10.0 -> 9.6 ms, of 1.0e8 28.8 ->
-// 28.9), and 48 tensors of 6.7e7 on average lost 1.4%.
+// alone; shorter ones share launches of up to kMaxStepDesc tensors.  StepIssuer::expect says which lists go to
+// adamw_list_kernel instead: those of more than kMaxListDesc tensors as they are, and shorter ones by what they consist of.
 #ifndef ZI_SOLO_TILES
 #define ZI_SOLO_TILES 8192
 #endif
@@ -203,6 +201,12 @@ struct StepIssuer {
     // flat: 200 tensors of 2e4 elements 35.3 / 25.3, 1000 of 1e5 512 / 480, 288 of 2.6e5 361 / 352, 288 of 1.0e6
     // 1368 / 1427, 72 of 4.2e6 1363 / 1420: the line is drawn at an average of 5 * 2^16.
     static constexpr int64_t kFlatAverage = 5 << 16;
+    // Shorter lists with several long tensors among few short ones, as a few layers of a decoder are, take `list` too: a launch
+    // of its own for every long tensor pays a start and an end each time, which shows up to 2^25 elements on average, and beyond
+    // that the longer lookup does.  Step alone, us, own launches / list: 2 tensors of 5e6 50.4 / 47.6, 8 of 5e6 198 / 180, 30 of 1e7
+    // 1369 / 1323, 8 of 3e7 1074 / 1056, 30 of 3e7 4000 / 4003, 24 of 5e7 5235 / 5250, 48 of 6.7e7 14120 / 14385; a decoder's tensors at
+    // hidden size 1024, 4 layers 246 / 225, 2048, 1 layer 238 / 225, 4096, 1 layer 918 / 904, 8192, 1 layer 3490 / 3517.
+    static constexpr int64_t kListAverage = (int64_t)1 << 25;
     enum Kind { kFew, kList, kFlat };
     Kind kind = kFew;
     zi::ListArgs list;
@@ -211,14 +215,16 @@ struct StepIssuer {
     // What the list will be, before the first add(): decides how many tensors share a launch.
     void expect(const zi_tensor* t, int32_t n_tensors)
     {
-        int64_t n = 0, total = 0;
+        int64_t n = 0, n_long = 0, total = 0;
         for (int32_t i = 0; i < n_tensors; ++i) {
             n += t[i].numel > 0;
+            n_long += t[i].numel >= kSoloTiles * zi::kStepTileElems;
             total += t[i].numel;
         }
-        if (n <= zi::kMaxStepDesc) return;
-        const bool short_and_flat = total / n <= kFlatAverage && is_flat(t, n_tensors);
-        if (!short_and_flat && n <= zi::kMaxListDesc) return;
+        if (n < 2) return;
+        const bool short_and_flat = n > zi::kMaxStepDesc && total / n <= kFlatAverage && is_flat(t, n_tensors);
+        const bool middling = n_long >= 2 && n_long >= n / 8 && total / n <= kListAverage;
+        if (!short_and_flat && !middling && n <= zi::kMaxListDesc) return;
         kind = short_and_flat ? kFlat : kList;
         list.c = flat.c = args.c;
         list.d_norm = flat.d_norm = args.d_norm;
