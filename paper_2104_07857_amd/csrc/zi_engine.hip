@@ -440,6 +440,9 @@ zi_status run_linked(zi_engine* e, zi_lp_dtype dt, const zi_adamw_config* cfg, c
     auto issue_all = [&]() -> zi_status {
         ZI_HIP(order_after_offloads(e, user));
         LinkIssuer issue(make_consts(*cfg), d_norm, &e->h_norm->found_inf, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, user);
+        e->device_list.clear();
+        for (const StateSrc& S : e->src) e->device_list.push_back({S.dev[0], S.dev[1], S.dev[2], S.dev[3], S.dev[4], S.numel});
+        issue.expect(e->device_list.data(), (int32_t)e->device_list.size());
         for (const StateSrc& S : e->src) {
             if (S.numel == 0) continue;
             ZI_HIP(issue.add((float*)S.dev[0], (float*)S.dev[1], (float*)S.dev[2], (const uint16_t*)S.dev[3],

@@ -122,6 +122,7 @@ struct zi_engine {
 
     // Per-call plans.  The vectors keep their capacity between calls, so once a list of a given size
     // has been seen, later calls allocate no host memory either.
+    std::vector<zi_tensor> device_list;   // src with addresses as the device sees them
     std::vector<zi::host::StateSrc> src;
     std::vector<int64_t> plan_numel;
     std::vector<zi::host::Segment> segs;

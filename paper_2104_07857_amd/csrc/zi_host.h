@@ -180,6 +180,36 @@ inline bool one_short_tensor(const zi_tensor* t, int32_t n_tensors, const zi::St
     return true;
 }
 
+// Every tensor's five arrays begin the same number of elements (less than 2^32, its end included) behind the
+// first tensor's, and all have a copy or none.  Sets the first tensor's addresses.
+inline bool is_flat(const zi_tensor* t, int32_t n_tensors, zi::FlatArgs& flat)
+{
+    const zi_tensor* f = nullptr;
+    for (int32_t i = 0; i < n_tensors; ++i) {
+        if (t[i].numel <= 0) continue;
+        if (!f) f = &t[i];
+        const auto bytes = [](const void* x, const void* from) { return reinterpret_cast<uintptr_t>(x) - reinterpret_cast<uintptr_t>(from); };
+        const uintptr_t at = bytes(t[i].p, f->p);
+        if (at % 4 || at / 4 + (uintptr_t)t[i].numel > 0xFFFFFFFFull) return false;
+        if (bytes(t[i].m, f->m) != at || bytes(t[i].v, f->v) != at || bytes(t[i].g, f->g) != at / 2) return false;
+        if (!t[i].p_lp != !f->p_lp || (f->p_lp && bytes(t[i].p_lp, f->p_lp) != at / 2)) return false;
+    }
+    flat.p = (float*)f->p;
+    flat.m = (float*)f->m;
+    flat.v = (float*)f->v;
+    flat.g = (const uint16_t*)f->g;
+    flat.lp = (uint16_t*)f->p_lp;
+    return true;
+}
+
+// What a launch over n tensors looks its tensors up in, once they are in.
+template <typename Args>
+inline void finish_starts(Args& a, int32_t n)
+{
+    for (int32_t i = n; i < Args::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
+    for (int i = 0; i < Args::kGroups; ++i) a.group_start[i] = a.first_tile[i * Args::kGroup];
+}
+
 // Issues the fused step over a list of device-resident segments.
 struct StepIssuer {
     zi::StepArgs args{};
@@ -222,34 +252,12 @@ struct StepIssuer {
             total += t[i].numel;
         }
         if (n < 2) return;
-        const bool short_and_flat = n > zi::kMaxStepDesc && total / n <= kFlatAverage && is_flat(t, n_tensors);
+        const bool short_and_flat = n > zi::kMaxStepDesc && total / n <= kFlatAverage && is_flat(t, n_tensors, flat);
         const bool middling = n_long >= 2 && n_long >= n / 8 && total / n <= kListAverage;
         if (!short_and_flat && !middling && n <= zi::kMaxListDesc) return;
         kind = short_and_flat ? kFlat : kList;
         list.c = flat.c = args.c;
         list.d_norm = flat.d_norm = args.d_norm;
-    }
-
-    // Every tensor's five arrays begin the same number of elements (less than 2^32, its end included) behind the
-    // first tensor's, and all have a copy or none.  Sets the first tensor's addresses.
-    bool is_flat(const zi_tensor* t, int32_t n_tensors)
-    {
-        const zi_tensor* f = nullptr;
-        for (int32_t i = 0; i < n_tensors; ++i) {
-            if (t[i].numel <= 0) continue;
-            if (!f) f = &t[i];
-            const auto bytes = [](const void* x, const void* from) { return reinterpret_cast<uintptr_t>(x) - reinterpret_cast<uintptr_t>(from); };
-            const uintptr_t at = bytes(t[i].p, f->p);
-            if (at % 4 || at / 4 + (uintptr_t)t[i].numel > 0xFFFFFFFFull) return false;
-            if (bytes(t[i].m, f->m) != at || bytes(t[i].v, f->v) != at || bytes(t[i].g, f->g) != at / 2) return false;
-            if (!t[i].p_lp != !f->p_lp || (f->p_lp && bytes(t[i].p_lp, f->p_lp) != at / 2)) return false;
-        }
-        flat.p = (float*)f->p;
-        flat.m = (float*)f->m;
-        flat.v = (float*)f->v;
-        flat.g = (const uint16_t*)f->g;
-        flat.lp = (uint16_t*)f->p_lp;
-        return true;
     }
 
     int32_t max_desc() const { return kind == kFlat ? zi::FlatArgs::kMax : kind == kList ? zi::kMaxListDesc : zi::kMaxStepDesc; }
@@ -330,8 +338,7 @@ struct StepIssuer {
             return hipSuccess;
         }
         const hipError_t e = issue_held(false);
-        for (int32_t i = n; i < Args::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
-        for (int i = 0; i < Args::kGroups; ++i) a.group_start[i] = a.first_tile[i * Args::kGroup];
+        finish_starts(a, n);
         into = a;
         held_tiles = tiles;
         held_kind = kind;
@@ -444,6 +451,9 @@ struct CopyIssuer {
 // where a launch is full, a multiple of 512 elements into the segment's body.
 struct LinkIssuer {
     zi::LinkArgs args[2];          // the launch being assembled and the one held back
+    zi::LinkFlatArgs flat[2];
+    bool is_flat_list = false;     // which of them (expect())
+    int32_t n_flat = 0;
     int now = 0;
     bool held = false;
     int dt;
@@ -463,6 +473,23 @@ struct LinkIssuer {
         }
     }
 
+    // What the list will be, with addresses as the device sees them, before the first add().
+    void expect(const zi_tensor* t, int32_t n_tensors)
+    {
+        int64_t n = 0, total = 0;
+        for (int32_t i = 0; i < n_tensors; ++i) {
+            n += t[i].numel > 0;
+            total += t[i].numel;
+        }
+        is_flat_list = n > zi::kMaxLinkDesc && total / n <= StepIssuer::kFlatAverage && is_flat(t, n_tensors, flat[0].list);
+        if (!is_flat_list) return;
+        flat[0].list.c = args[0].c;
+        flat[0].list.d_norm = args[0].d_norm;
+        flat[0].h_flag = args[0].h_flag;
+        flat[0].n_tiles = 0;
+        flat[1] = flat[0];
+    }
+
     // As in StepIssuer, launches are held back by one and those between the first and the last may overlap: the
     // link stays busy while one launch's last tiles return and the next one's first requests are on their way.
     hipError_t issue_held(bool last)
@@ -471,17 +498,21 @@ struct LinkIssuer {
         const bool any_order = !last && launches > 0 && may_overlap(stream);
         ++launches;
         held = false;
-        return zi::launch_step_link(args[now ^ 1], dt, l2, any_order, stream);
+        return is_flat_list ? zi::launch_step_link_flat(flat[now ^ 1], dt, l2, any_order, stream)
+                            : zi::launch_step_link(args[now ^ 1], dt, l2, any_order, stream);
     }
 
     hipError_t close()       // the launch being assembled is complete
     {
-        if (args[now].n_desc == 0) return hipSuccess;
+        if (is_flat_list ? n_flat == 0 : args[now].n_desc == 0) return hipSuccess;
         const hipError_t e = issue_held(false);
+        if (is_flat_list) finish_starts(flat[now].list, n_flat);
         now ^= 1;
         held = true;
         args[now].n_desc = 0;
         args[now].n_tiles = 0;
+        flat[now].n_tiles = 0;
+        n_flat = 0;
         return e;
     }
 
@@ -493,6 +524,20 @@ struct LinkIssuer {
 
     hipError_t add(float* p, float* m, float* v, const uint16_t* g, uint16_t* p_lp, int64_t numel)
     {
+        if (is_flat_list && numel > 0) {
+            if (n_flat == zi::FlatArgs::kMax || flat[now].n_tiles >= zi::kLinkTilesPerLaunch)
+                if (const hipError_t e = close(); e != hipSuccess) return e;
+            zi::LinkFlatArgs& a = flat[now];
+            const int h = choose_head(p, m, v, g, p_lp);
+            const int64_t head = h < numel ? h : numel, nquad = (numel - head) / zi::kQuad;
+            const int64_t nt = (nquad + zi::kStepTileQuads - 1) / zi::kStepTileQuads;
+            a.list.t[n_flat] = {(uint32_t)(p + head - a.list.p), (uint32_t)nquad};
+            a.list.head[n_flat] = (uint8_t)head;
+            a.list.tail[n_flat] = (uint8_t)(numel - head - nquad * zi::kQuad);
+            a.list.first_tile[n_flat++] = a.n_tiles;
+            a.n_tiles += nt < 1 ? 1u : (uint32_t)nt;
+            return hipSuccess;
+        }
         while (numel > 0) {
             if (args[now].n_desc == zi::kMaxLinkDesc || args[now].n_tiles >= zi::kLinkTilesPerLaunch) {
                 const hipError_t e = close();

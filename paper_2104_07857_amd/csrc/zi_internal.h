@@ -212,6 +212,15 @@ struct LinkArgs {
 };
 static_assert(sizeof(LinkArgs) < 4096, "kernel arguments");
 
+// The same for more short tensors than kMaxLinkDesc at the same places of five flat buffers: 256 of them.  A launch of 48
+// tensors of a tile or two leaves half of the workgroups without work, and its one round trip over the link is paid per launch.
+struct LinkFlatArgs {
+    FlatArgs list;                  // addresses as the device sees them
+    uint32_t n_tiles;
+    uint32_t* h_flag;
+};
+static_assert(sizeof(LinkFlatArgs) < 4096, "kernel arguments");
+
 // Copies of 2-byte arrays between device and page-locked host memory by a kernel (link_copy_kernel): many segments in
 // one launch, in blocks of 2^14 elements that report to the host when they have arrived, or in pieces of 2^12 (one
 // round of loads for a wavefront) where nobody waits for a part.
@@ -282,6 +291,7 @@ hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2
 hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
+hipError_t launch_step_link_flat(const LinkFlatArgs& a, int dt, bool l2, bool any_order, hipStream_t s);
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
 hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s);
