@@ -111,6 +111,19 @@ def test_replays_of_a_captured_call_see_new_gradients():
         assert abs(nb.read()[0] - want) <= 1e-12 * want
 
 
+def test_workspace_and_result_in_page_locked_memory():
+    """The partials travel over the link then; the same bits."""
+    dt, n = zi.ZI_FP16, 70 * TILE + 5
+    d, nb = to_dev(_grads(n, dt, 21)), NormBuffers()
+    want = _norm([d], dt, nb)
+    out = torch.zeros(4, dtype=torch.float64, pin_memory=True)
+    ws = torch.full((zi.zi_norm_workspace_bytes(),), 0x3C, dtype=torch.uint8, pin_memory=True)
+    for _ in range(2):
+        zi.zi_grad_norm([(None, None, None, d, None, n)], dt, 2.0, out, ws)
+        torch.cuda.synchronize()
+        assert (float(out[0]), float(out[1])) == want[:2] and int(out.view(torch.int32)[4]) == 0
+
+
 @pytest.mark.parametrize("keep", [0, 1])
 @pytest.mark.parametrize("n", [TILE * 2 + 1, TILE * 600 + 11])
 def test_a_last_workgroup_that_does_not_wait_does_all_the_work(n, keep, tmp_path):

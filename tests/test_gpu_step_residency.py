@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2104_07857_amd as zi
 import zi_synth
-from gpu_util import compare_state, gen_numpy, to_dev, to_np, zi_cfg
+from gpu_util import NormBuffers, compare_state, gen_numpy, to_dev, to_np, zi_cfg
 
 pytestmark = pytest.mark.gpu
 TILE, SHORT, SHORT_LIST, LONG = 512, 3 << 11, 3 << 12, 1 << 18
@@ -22,6 +22,33 @@ def test_one_tensor_around_the_short_limit(n, dt):
     lp = np.zeros(n, np.uint16)
     oracle.adamw(hp, hm, hv, hg, lp, dt, oracle.config(step=10), 0.0, 0)
     compare_state((hp, hm, hv, lp), [to_np(dev[i]) for i in (0, 1, 2, 4)], dt)
+
+
+def test_one_short_tensor_replays_from_a_captured_graph():
+    dt, n = zi.ZI_BF16, 3000
+    host = gen_numpy(zi_synth.StateSpec(8, dt), n)
+    cfg = zi_cfg(zi_synth.workload("c4"))
+    sides = []
+    for _ in range(2):
+        bufs = [to_dev(a.copy()) for a in host] + [torch.zeros(n, dtype=torch.int16, device="cuda:0")]
+        sides.append((zi.make_tensors([tuple(bufs) + (n,)]), NormBuffers(), bufs))
+    (tl, nb, graphed), (tl_e, nb_e, eager) = sides
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        graph.capture_begin()
+        zi.zi_grad_norm(tl, dt, 1.0, nb.out, nb.ws, stream=stream)
+        zi.zi_adamw_step(tl, dt, cfg, nb.out, stream)
+        graph.capture_end()
+    for _ in range(4):
+        graph.replay()
+        zi.zi_grad_norm(tl_e, dt, 1.0, nb_e.out, nb_e.ws)
+        zi.zi_adamw_step(tl_e, dt, cfg, nb_e.out)
+        torch.cuda.synchronize()
+        for a, b in zip(graphed, eager):
+            assert torch.equal(a, b)
+            a[:3] += 0                               # eager work between the replays
+        assert nb.read() == nb_e.read()
 
 
 @pytest.mark.parametrize("count,each,shuffled", [(65, LONG // 64 * TILE, True), (65, LONG // 64 * TILE + 512, True),
