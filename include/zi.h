@@ -166,7 +166,8 @@ zi_status zi_grad_norm(const zi_tensor* t, int32_t n_tensors, zi_lp_dtype dt, fl
  * Limit: at most ZI_NOALLOC_MAX_PARTIALS non-empty tensors per call (ZI_ERR_UNSUPPORTED beyond,
  * nothing launched); within it any sizes are accepted.  The result is bit-identical to zi_grad_norm's.
  * All calls on one GPU share that GPU's array: two calls that overlap in time on the same GPU (different
- * streams or threads) race on it and give garbage; order them on one stream or with events.  Nothing in
+ * streams or threads) race on it and may give garbage or wait a second for each other; order them on one
+ * stream or with events.  Nothing in
  * the array needs clearing between calls: every partial the final pass reads was written by this call.
  * The device address of the array is looked up on the first call on each device (that first call must
  * not be under capture).  Asynchronous on hip_stream.
