@@ -169,6 +169,11 @@ extern "C" zi_status zi_adamw_step(const zi_tensor* t, int32_t n_tensors, zi_lp_
         ZI_HIP(zi::launch_step_short(one, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, (hipStream_t)hip_stream));
         return ZI_OK;
     }
+    zi::FlatFew few;
+    if (const uint32_t tiles = few_short_tensors(t, n_tensors, k, d_norm, few)) {
+        ZI_HIP(zi::launch_step_few(few, tiles, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, (hipStream_t)hip_stream));
+        return ZI_OK;
+    }
     StepIssuer issue(k, d_norm, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, (hipStream_t)hip_stream);
     issue.expect(t, n_tensors);
     for (int32_t i = 0; i < n_tensors; ++i)

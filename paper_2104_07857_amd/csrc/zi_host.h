@@ -182,7 +182,8 @@ inline bool one_short_tensor(const zi_tensor* t, int32_t n_tensors, const zi::St
 
 // Every tensor's five arrays begin the same number of elements (less than 2^32, its end included) behind the
 // first tensor's, and all have a copy or none.  Sets the first tensor's addresses.
-inline bool is_flat(const zi_tensor* t, int32_t n_tensors, zi::FlatArgs& flat)
+template <typename Flat>
+inline bool is_flat(const zi_tensor* t, int32_t n_tensors, Flat& flat)
 {
     const zi_tensor* f = nullptr;
     for (int32_t i = 0; i < n_tensors; ++i) {
@@ -208,6 +209,42 @@ inline void finish_starts(Args& a, int32_t n)
 {
     for (int32_t i = n; i < Args::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
     for (int i = 0; i < Args::kGroups; ++i) a.group_start[i] = a.first_tile[i * Args::kGroup];
+}
+
+// Makes a tensor the n-th of a flat list, from tile `first` of the launch; returns its tiles.
+template <typename Flat>
+inline uint32_t add_flat(Flat& a, int32_t n, uint32_t first, const float* p, int h, int64_t numel)
+{
+    const int64_t head = h < numel ? h : numel, nquad = (numel - head) / zi::kQuad;
+    const int64_t tiles = (nquad + zi::kStepTileQuads - 1) / zi::kStepTileQuads;
+    a.t[n] = {(uint32_t)(p + head - a.p), (uint32_t)nquad};
+    a.head[n] = (uint8_t)head;
+    a.tail[n] = (uint8_t)(numel - head - nquad * zi::kQuad);
+    a.first_tile[n] = first;
+    return tiles < 1 ? 1u : (uint32_t)tiles;
+}
+
+// A call on 2 to FlatFew::kMax tensors of kFewElems elements in all that are views at the same places of five flat buffers:
+// fills the launch's arguments and returns its tiles, 0 if it is another call.
+inline uint32_t few_short_tensors(const zi_tensor* t, int32_t n_tensors, const zi::StepConsts& c, const zi_norm_result* d_norm,
+                                  zi::FlatFew& a)
+{
+    int32_t n = 0;
+    int64_t total = 0;
+    for (int32_t i = 0; i < n_tensors && n <= zi::FlatFew::kMax && total <= zi::kFewElems; ++i) {
+        n += t[i].numel > 0;
+        total += t[i].numel < zi::kFewElems ? t[i].numel : zi::kFewElems + 1;
+    }
+    if (n < 2 || n > zi::FlatFew::kMax || total > zi::kFewElems || !is_flat(t, n_tensors, a)) return 0;
+    a.c = c;
+    a.d_norm = d_norm;
+    uint32_t tiles = 0;
+    n = 0;
+    for (int32_t i = 0; i < n_tensors; ++i)
+        if (t[i].numel > 0)
+            tiles += add_flat(a, n++, tiles, (const float*)t[i].p, choose_head(t[i].p, t[i].m, t[i].v, t[i].g, t[i].p_lp), t[i].numel);
+    finish_starts(a, n);
+    return tiles;
 }
 
 // Issues the fused step over a list of device-resident segments.
@@ -528,14 +565,7 @@ struct LinkIssuer {
             if (n_flat == zi::FlatArgs::kMax || flat[now].n_tiles >= zi::kLinkTilesPerLaunch)
                 if (const hipError_t e = close(); e != hipSuccess) return e;
             zi::LinkFlatArgs& a = flat[now];
-            const int h = choose_head(p, m, v, g, p_lp);
-            const int64_t head = h < numel ? h : numel, nquad = (numel - head) / zi::kQuad;
-            const int64_t nt = (nquad + zi::kStepTileQuads - 1) / zi::kStepTileQuads;
-            a.list.t[n_flat] = {(uint32_t)(p + head - a.list.p), (uint32_t)nquad};
-            a.list.head[n_flat] = (uint8_t)head;
-            a.list.tail[n_flat] = (uint8_t)(numel - head - nquad * zi::kQuad);
-            a.list.first_tile[n_flat++] = a.n_tiles;
-            a.n_tiles += nt < 1 ? 1u : (uint32_t)nt;
+            a.n_tiles += add_flat(a.list, n_flat++, a.n_tiles, p, choose_head(p, m, v, g, p_lp), numel);
             return hipSuccess;
         }
         while (numel > 0) {
@@ -626,6 +656,14 @@ struct NormIssuer {
         const int64_t nt = (body + zi::kNormTileElems - 1) / zi::kNormTileElems;
         return nt < 1 ? 1 : nt;              // the first tile also owns the unaligned ends
     }
+    template <typename Args>
+    static void finish_list(Args& a, int32_t n, uint32_t n_tiles)
+    {
+        a.first_tile[n] = n_tiles;
+        for (int32_t i = n + 1; i <= Args::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
+        for (int32_t i = 0; i < Args::kGroups; ++i)
+            a.group_start[i] = i * Args::kGroup < n ? a.first_tile[i * Args::kGroup] : 0xFFFFFFFFu;
+    }
     // final: the launch also makes the final sum.
     hipError_t flush_launch(bool final = false)
     {
@@ -648,13 +686,20 @@ struct NormIssuer {
         if (final && n_desc == 1 && used == 0) {
             e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, a.keep_tiles, blocks, a.mark_low, a.mark_high, a.patience, loss_scale,
                                      a.accumulate}, dt, keep, s);
-        } else {
-            a.first_tile[n_desc] = a.n_tiles;
-            for (int32_t i = n_desc + 1; i <= zi::NormArgs::kMax; ++i) a.first_tile[i] = 0xFFFFFFFFu;
-            for (int32_t i = 0; i < zi::NormArgs::kGroups; ++i) {
-                const int32_t d = i * zi::NormArgs::kGroup;
-                a.group_start[i] = d < n_desc ? a.first_tile[d] : 0xFFFFFFFFu;
+        } else if (final && keep && n_desc <= zi::NormFew::kMax && used == 0) {
+            zi::NormFew few;
+            for (int32_t i = 0; i < n_desc; ++i) {
+                few.where[i] = a.where[i];
+                few.first_tile[i] = a.first_tile[i];
             }
+            finish_list(few, n_desc, a.n_tiles);
+            few.n_tiles = a.n_tiles; few.keep_tiles = a.keep_tiles; few.n_groups = a.n_groups;
+            few.mark_low = a.mark_low; few.mark_high = a.mark_high; few.patience = a.patience;
+            few.loss_scale = a.loss_scale; few.partials = a.partials; few.out = a.out;
+            few.n_before = a.n_before; few.accumulate = a.accumulate;
+            e = zi::launch_norm_few(few, dt, s);
+        } else {
+            finish_list(a, n_desc, a.n_tiles);
             // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
             // one with the final sum are ordinary launches (the same order as in StepIssuer).
             const bool any_order = used > 0 && !final && may_overlap(s);

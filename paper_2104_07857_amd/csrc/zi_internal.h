@@ -177,8 +177,9 @@ struct FlatDesc {
     uint32_t nquad;
 };
 
-struct FlatArgs {
-    static constexpr int kGroup = 16, kGroups = 16, kMax = kGroup * kGroups;
+template <int GROUPS>
+struct FlatList {
+    static constexpr int kGroup = 16, kGroups = GROUPS, kMax = kGroup * kGroups;
     FlatDesc t[kMax];
     uint32_t first_tile[kMax];
     uint32_t group_start[kGroups];
@@ -189,7 +190,14 @@ struct FlatArgs {
     const zi_norm_result* d_norm;
     uint8_t head[kMax], tail[kMax];
 };
+struct FlatArgs : FlatList<16> {};
 static_assert(sizeof(FlatArgs) < 4096, "kernel arguments");
+// Up to 32 tensors with kFewElems elements or less in all, which take the host longer than the GPU: 568 bytes instead of
+// StepArgs' 2.5 KB, and no StepIssuer (StepOne says what that is worth).  Norm and step together, StepArgs and NormArgs / FlatFew and
+// NormFew, us: issue without the binding, 2 tensors 9.5 / 8.9, 16 9.8 / 9.3, 32 10.1 / 9.8; on the GPU 24 tensors of 1.0e4
+// elements 8.1 / 7.6, 12 of 8.0e4 9.8 / 9.6, 32 of 3.0e4 10.6 / 10.3.
+struct FlatFew : FlatList<2> {};
+constexpr int64_t kFewElems = (int64_t)1 << 20;
 
 // The step over state in page-locked host memory (adamw_link_kernel): a persistent grid of
 // single-wavefront workgroups that read and write the host arrays over the link themselves.
@@ -248,8 +256,9 @@ struct CopyArgs {
 // it took 224), which a workgroup looks up in groups as adamw_list_kernel does, in two round trips to the scalar cache where
 // halving takes eight.  Reduction alone, us: 288 tensors with 3.0e8 elements 94 -> 90, 300 of 1..20,000 8.7 -> 5.1 (two launches and
 // a final sum before), 1000 of 1..100,000 43 -> 29, 200 of 1..40,000 5.1 / 5.2.
-struct NormArgs {
-    static constexpr int kGroup = 16, kGroups = 20, kMax = kGroup * kGroups;
+template <int GROUPS>
+struct NormList {
+    static constexpr int kGroup = 16, kGroups = GROUPS, kMax = kGroup * kGroups;
     // Address of the tensor in the lower 48 bits (the GPU has no others); above, how many elements its length is
     // short of its tiles * kNormTileElems + kNormTileSlack.
     uint64_t where[kMax];
@@ -267,7 +276,9 @@ struct NormArgs {
     uint32_t n_before;
     int32_t accumulate;             // adds to what is in *out
 };
+struct NormArgs : NormList<20> {};
 static_assert(sizeof(NormArgs) < 4096, "kernel arguments");
+struct NormFew : NormList<2> {};        // short lists of up to 32 tensors, as FlatFew
 // Elements that a tensor's first tile takes beside its vectors: at most 7 in front of them and 7 behind.
 constexpr uint32_t kNormTileSlack = 2 * (kVec - 1);
 
@@ -287,6 +298,7 @@ static_assert(sizeof(NormOne) <= 112, "kernel arguments");
 // any_order: may run beside the launches in front of it on the stream (see StepIssuer for where that is safe).
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_short(const StepOne& a, int dt, bool l2, hipStream_t s);
+hipError_t launch_step_few(const FlatFew& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s);
@@ -295,6 +307,7 @@ hipError_t launch_step_link_flat(const LinkFlatArgs& a, int dt, bool l2, bool an
 // keep: read with ordinary loads instead of streaming ones (kNormKeepElems).
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
 hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s);
+hipError_t launch_norm_few(const NormFew& a, int dt, hipStream_t s);      // ordinary loads
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);
 

@@ -421,13 +421,16 @@ __device__ __forceinline__ Bodies bodies_of(const ListArgs& a, uint32_t d)
 }
 __device__ __forceinline__ int64_t head_of(const ListArgs& a, uint32_t d) { return a.t[d].head; }
 __device__ __forceinline__ int64_t tail_of(const ListArgs& a, uint32_t d) { return a.t[d].tail; }
-__device__ __forceinline__ Bodies bodies_of(const FlatArgs& a, uint32_t d)
+template <int GROUPS>
+__device__ __forceinline__ Bodies bodies_of(const FlatList<GROUPS>& a, uint32_t d)
 {
     const uint64_t at = a.t[d].body;
     return {a.p + at, a.m + at, a.v + at, a.g + at, a.lp ? a.lp + at : nullptr};
 }
-__device__ __forceinline__ int64_t head_of(const FlatArgs& a, uint32_t d) { return a.head[d]; }
-__device__ __forceinline__ int64_t tail_of(const FlatArgs& a, uint32_t d) { return a.tail[d]; }
+template <int GROUPS>
+__device__ __forceinline__ int64_t head_of(const FlatList<GROUPS>& a, uint32_t d) { return a.head[d]; }
+template <int GROUPS>
+__device__ __forceinline__ int64_t tail_of(const FlatList<GROUPS>& a, uint32_t d) { return a.tail[d]; }
 
 // The same for long lists: 64 tensors of any length to a launch (ListArgs), or 256 short ones of flat buffers
 // (FlatArgs), found by counting the starts of groups of tensors and then the starts inside one group.  A workgroup still lives for a few microseconds, so
@@ -531,6 +534,10 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, unsigned lds, 
     else               { if (l2) ZI_LAUNCH_LIST(ZI_FP16, true); else ZI_LAUNCH_LIST(ZI_FP16, false); }
 #undef ZI_LAUNCH_LIST
     return hipGetLastError();
+}
+hipError_t launch_step_few(const FlatFew& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s)
+{
+    return launch_list_of(a, n_tiles, kStepLds16, dt, l2, false, s);
 }
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
@@ -798,14 +805,15 @@ struct NormTensor {
     const ZI_GLOBAL uint16_t* g;
     uint32_t numel, first_tile, next_tile;
 };
-__device__ __forceinline__ NormTensor tensor_of_tile(const NormArgs& a, uint32_t tile)
+template <int GROUPS>
+__device__ __forceinline__ NormTensor tensor_of_tile(const NormList<GROUPS>& a, uint32_t tile)
 {
     uint32_t group = 0, first = 0;        // the first start is 0, so both counts are at least 1
 #pragma unroll
-    for (int i = 0; i < NormArgs::kGroups; ++i) count_start(tile, a.group_start[i], group, first);
-    uint32_t d = --group * NormArgs::kGroup;
+    for (int i = 0; i < NormList<GROUPS>::kGroups; ++i) count_start(tile, a.group_start[i], group, first);
+    uint32_t d = --group * NormList<GROUPS>::kGroup;
 #pragma unroll
-    for (int i = 0; i < NormArgs::kGroup; ++i) count_start(tile, a.first_tile[group * NormArgs::kGroup + i], d, first);
+    for (int i = 0; i < NormList<GROUPS>::kGroup; ++i) count_start(tile, a.first_tile[group * NormList<GROUPS>::kGroup + i], d, first);
     --d;
     const uint64_t where = a.where[d];
     const uint32_t next = a.first_tile[d + 1];
@@ -1032,6 +1040,14 @@ hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s)
     if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
     else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
 #undef ZI_LAUNCH_NORM
+    return hipGetLastError();
+}
+
+hipError_t launch_norm_few(const NormFew& a, int dt, hipStream_t s)
+{
+    const dim3 grid(a.n_groups), block(kNormKeepThreads);
+    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_partial_kernel<ZI_BF16, true, NormFew>), grid, block, 0, s, a);
+    else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16, true, NormFew>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
