@@ -195,9 +195,9 @@ static_assert(sizeof(FlatArgs) < 4096, "kernel arguments");
 // Up to 32 tensors with kFewElems elements or less in all, which take the host longer than the GPU: 568 bytes instead of
 // StepArgs' 2.5 KB, and no StepIssuer (StepOne says what that is worth).  Norm and step together, StepArgs and NormArgs / FlatFew and
 // NormFew, us: issue without the binding, 2 tensors 9.5 / 8.9, 16 9.8 / 9.3, 32 10.1 / 9.8; on the GPU 24 tensors of 1.0e4
-// elements 8.1 / 7.6, 12 of 8.0e4 9.8 / 9.6, 32 of 3.0e4 10.6 / 10.3.
+// elements 8.1 / 7.6, 12 of 8.0e4 9.8 / 9.6, 32 of 3.0e4 10.6 / 10.3, 24 with 1.6e6 13.0 / 12.6, 23 with 1.7e6 14.2 / 14.2, 24 of 1.0e5 17.0 / 17.2.
 struct FlatFew : FlatList<2> {};
-constexpr int64_t kFewElems = (int64_t)1 << 20;
+constexpr int64_t kFewElems = (int64_t)1 << 21;
 
 // The step over state in page-locked host memory (adamw_link_kernel): a persistent grid of
 // single-wavefront workgroups that read and write the host arrays over the link themselves.

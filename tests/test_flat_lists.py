@@ -28,12 +28,12 @@ def test_which_lists_are_one_launch(count):
 @pytest.mark.parametrize("dt", [zi.ZI_BF16, zi.ZI_FP16])
 @pytest.mark.parametrize("count,most", [(2, 0), (2, 1), (16, 0), (17, 0), (32, 0), (32, 1), (33, 0), (64, 0)])
 def test_every_tensor_as_by_itself(count, most, dt):
-    """Up to 32 tensors with 2^20 elements in all have arguments of their own; most: one element more."""
+    """Up to 32 tensors with 2^21 elements in all have arguments of their own; most: one element more."""
     rng = np.random.default_rng(count)
     sizes = [int(x) for x in rng.integers(1, 3000, count)]
     sizes[min(5, count - 2)], sizes[-1] = 1030 * 512 + 5, 1
     if count <= 32:
-        sizes[0] += (1 << 20) + most - sum(sizes)
+        sizes[0] += (1 << 21) + most - sum(sizes)
     starts = np.cumsum([7] + [n + int(x) for n, x in zip(sizes, rng.integers(0, 9, count))])[:-1].tolist()
     total = starts[-1] + sizes[-1] + 3
     gen = torch.Generator(device="cuda:0").manual_seed(count)
