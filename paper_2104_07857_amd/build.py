@@ -31,10 +31,15 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def has_python_headers() -> bool:
+    return os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h"))
+
+
 def needs_build() -> bool:
-    if not os.path.exists(LIB_PATH) or not os.path.exists(CALL_PATH):
+    built = [LIB_PATH, CALL_PATH] if has_python_headers() else [LIB_PATH]
+    if not all(os.path.exists(f) for f in built):
         return True
-    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(CALL_PATH))
+    t = min(os.path.getmtime(f) for f in built)
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + \
            [os.path.join(ROOT, "include", f) for f in ("zi.h", "zi_probe.h")]
     return any(os.path.getmtime(d) > t for d in deps)
@@ -46,8 +51,12 @@ HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-mavx2", "-mfma", "-mf16c", "-ffp-c
               "-Wall", "-Wextra", "-pthread"]
 
 
-def build_call() -> str:
-    """The Python side of the calls made once per step (csrc/zi_python.c)."""
+def build_call() -> str | None:
+    """The Python side of the calls made once per step (csrc/zi_python.c).  Without Python's headers there is none, and
+    binding.py takes every call through ctypes."""
+    if not has_python_headers():
+        sys.stderr.write("no Python.h: calls go through ctypes\n")
+        return None
     subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter",
                     "-Wno-missing-field-initializers", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
                     os.path.join(CSRC, "zi_python.c"), "-o", CALL_PATH], check=True)

@@ -684,8 +684,8 @@ struct NormIssuer {
         keep_left -= a.keep_tiles;
         a.n_before = final ? used : 0;
         if (final && n_desc == 1 && used == 0) {
-            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, a.keep_tiles, blocks, a.mark_low, a.mark_high, a.patience, loss_scale,
-                                     a.accumulate}, dt, keep, s);
+            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, a.keep_tiles, blocks, a.mark_low, a.mark_high,
+                                     a.patience, loss_scale, a.accumulate}, dt, keep, s);
         } else if (final && keep && n_desc <= zi::NormFew::kMax && used == 0) {
             zi::NormFew few;
             for (int32_t i = 0; i < n_desc; ++i) {

@@ -20,9 +20,9 @@ constexpr int64_t kStepTileElems = (int64_t)kStepTileQuads * kQuad;   // 512 ele
 constexpr int kMaxStepDesc = 32;     // tensors (or segments) per fused-step launch
 // Dynamic LDS requested (never touched) by the fused step caps its residency: single-wavefront workgroups per compute
 // unit.  On this 1:1 read/write stream few, short-lived wavefronts measured 4-8% faster than full occupancy, but how
-// few depends on the launch.  Up to kStepShortTiles or kListShortTiles tiles what counts is how few rounds of resident workgroups it takes; in
-// launches of more than kStepLongTiles bunching begins to cost, above all in adamw_list_kernel, whose wavefronts arrive at their
-// loads later.
+// few depends on the launch.  Up to kStepShortTiles or kListShortTiles tiles what counts is how few rounds of resident
+// workgroups it takes; in launches of more than kStepLongTiles bunching begins to cost, above all in adamw_list_kernel, whose
+// wavefronts arrive at their loads later.
 // Step alone in us, averages over six placements of the arrays (short ones: of a captured row of calls),
 // workgroups per compute unit:
 //                                             16      8      7      6
@@ -195,7 +195,8 @@ static_assert(sizeof(FlatArgs) < 4096, "kernel arguments");
 // Up to 32 tensors with kFewElems elements or less in all, which take the host longer than the GPU: 568 bytes instead of
 // StepArgs' 2.5 KB, and no StepIssuer (StepOne says what that is worth).  Norm and step together, StepArgs and NormArgs / FlatFew and
 // NormFew, us: issue without the binding, 2 tensors 9.5 / 8.9, 16 9.8 / 9.3, 32 10.1 / 9.8; on the GPU 24 tensors of 1.0e4
-// elements 8.1 / 7.6, 12 of 8.0e4 9.8 / 9.6, 32 of 3.0e4 10.6 / 10.3, 24 with 1.6e6 13.0 / 12.6, 23 with 1.7e6 14.2 / 14.2, 24 of 1.0e5 17.0 / 17.2.
+// elements 8.1 / 7.6, 12 of 8.0e4 9.8 / 9.6, 32 of 3.0e4 10.6 / 10.3, 24 with 1.6e6 13.0 / 12.6, 23 with 1.7e6 14.2 / 14.2,
+// 24 of 1.0e5 17.0 / 17.2.
 struct FlatFew : FlatList<2> {};
 constexpr int64_t kFewElems = (int64_t)1 << 21;
 

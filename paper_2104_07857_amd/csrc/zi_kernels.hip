@@ -433,8 +433,8 @@ template <int GROUPS>
 __device__ __forceinline__ int64_t tail_of(const FlatList<GROUPS>& a, uint32_t d) { return a.tail[d]; }
 
 // The same for long lists: 64 tensors of any length to a launch (ListArgs), or 256 short ones of flat buffers
-// (FlatArgs), found by counting the starts of groups of tensors and then the starts inside one group.  A workgroup still lives for a few microseconds, so
-// what is in front of its first load is kept to three round trips to the scalar cache (arguments; group starts
+// (FlatArgs; FlatFew: 32), found by counting the starts of groups of tensors and then the starts inside one group.  A
+// workgroup still lives for a few microseconds, so what is in front of its first load is kept to three round trips to the scalar cache (arguments; group starts
 // and norm result together; descriptor) and arithmetic that hides in them.  Measured, step alone in us, against
 // a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
 // 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,

@@ -4,9 +4,10 @@
  * without any binding.
  *
  * Only the usual forms are taken: a list made by make_tensors (or any ctypes array of zi_tensor with its length), a
- * zi_adamw_config, numbers that are Python's own int and float, addresses as int, None or an object with data_ptr(), a stream as
- * int, None or an object with cuda_stream.  For anything else, and for whatever raises on the way, a function here returns None and the caller goes the
- * general way, which accepts and refuses as it always has.  The GIL is released during the call as ctypes does it. */
+ * zi_adamw_config, numbers that are Python's own int and float, addresses as int, None or an object with data_ptr(), a
+ * stream as int, None or an object with cuda_stream.  For anything else, and for whatever raises on the way, a function
+ * here returns None and the caller goes the general way, which accepts and refuses as it always has.  The GIL is released
+ * during the call as ctypes does it. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
