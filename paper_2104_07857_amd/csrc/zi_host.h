@@ -149,6 +149,17 @@ inline bool may_overlap(hipStream_t stream)
     return false;
 }
 
+// Whether what is launched on the stream now may run again later, with the same arguments.  (The null stream cannot be
+// captured; of any other stream that the query refuses it is assumed.)
+inline bool is_captured(hipStream_t stream)
+{
+    if (!stream) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // A call on one tensor of up to kStepShortTiles tiles, as adamw_short_kernel takes it: false if it is another call.
 inline bool one_short_tensor(const zi_tensor* t, int32_t n_tensors, const zi::StepConsts& c, bool l2,
                              const zi_norm_result* d_norm, zi::StepOne& a)
@@ -621,7 +632,8 @@ inline uint64_t next_norm_number()
 
 // Issues the gradient reduction over a list of gradient arrays that the device can reach: partial-sum
 // launches of up to NormArgs::kMax tensors, the last of which also makes the final sum.  Whenever the workspace's partial slots
-// run out, a finalize pass folds them; after the first final sum the later ones add to the result already in d_out.
+// run out, and at the end of a captured call, a finalize pass folds them; after the first final sum the later ones add to the
+// result already in d_out.
 struct NormIssuer {
     zi::NormArgs a;
     int32_t n_desc = 0;
@@ -738,9 +750,13 @@ struct NormIssuer {
         }
         return hipSuccess;
     }
+    // Under capture nothing waits for partials by their marks: the marks are the same at every replay, and a workgroup that the
+    // last one has given up on leaves its partial with them for the next replay.  Both ways add in one order.
     hipError_t finish()
     {
-        return n_desc > 0 ? flush_launch(true) : flush_partials();
+        if (n_desc > 0 && !is_captured(s)) return flush_launch(true);
+        const hipError_t e = flush_launch();
+        return e != hipSuccess ? e : flush_partials();
     }
 };
 

@@ -923,9 +923,9 @@ __device__ __forceinline__ void put_norm_result(double sumsq, float loss_scale, 
 // the last one runs.  None of them waits for anything.  Should partials still be missing after `patience` looks (the device
 // is busy with other work, or a call that was not ordered behind this one overwrote them), the last workgroup goes over the
 // launch's tiles itself.
-// Marks tell this launch's partials from whatever the workspace held; they are taken away again behind the sum, since
-// a captured launch is replayed with the same ones.
-// The order of the sum does not depend on scheduling.
+// Marks tell this launch's partials from whatever the workspace held.  A launch that may run twice with the same ones, a captured
+// one, must not make the final sum (NormIssuer::finish): norm_finalize_kernel does it there.
+// The order of the sum is that kernel's, and does not depend on scheduling unless the last workgroup does all the work.
 template <int DT, bool KEEP, typename Args>
 __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const Args a)
 {
@@ -937,20 +937,28 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool last = a.out && blockIdx.x == a.n_groups - 1;
     uint32_t first = blockIdx.x, step = a.n_groups;
-    double before = 0.0;
-    if (last)
-        for (uint32_t i = threadIdx.x; i < a.n_before; i += THREADS) {
-            const NormPartial& p = (a.partials - a.n_before)[i];
-            before += partial_sum(p.low, p.high);
-        }
+    // (every kNormGroups-th of all partials, this launch's behind those before it, as norm_finalize_kernel has them)
+    double before[kRounds] = {};
+    if (last) {
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r)
+            for (uint32_t i = threadIdx.x + r * THREADS; i < a.n_before; i += kNormGroups) {
+                const NormPartial& p = (a.partials - a.n_before)[i];
+                before[r] += partial_sum(p.low, p.high);
+            }
+    }
+    bool whole = a.n_groups == 1 && a.n_before == 0;      // everything to be summed is in this workgroup
     for (;;) {
         double sum = sumsq_tiles<DT, THREADS, KEEP, Args>(a, first, step);
-        if (last && step == 1) sum += before;
+        if (whole) {
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) sum += before[r];
+        }
         sum = wave_sum(sum);
         if (lane == 0) s_sum[wave] = sum;
         if (threadIdx.x == 0) s_missing = 0;
         __syncthreads();
-        if (last && step == 1) {          // the launch's whole list is in this workgroup
+        if (last && whole) {
             if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_sum), a.loss_scale, a.accumulate, a.out);
             return;
         }
@@ -959,8 +967,8 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
 
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t i = threadIdx.x + r * THREADS;
-            double x = r == 0 ? before : 0.0;
+            const uint32_t i = (threadIdx.x + r * THREADS - a.n_before) % kNormGroups;
+            double x = before[r];
             if (i < a.n_groups) {
                 NormPartial* const at = a.partials + i;
                 uint64_t low = 0, high = 0;
@@ -972,8 +980,6 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
                 }
                 if (!there) s_missing = 1;
                 x += partial_sum(low, high);
-                __hip_atomic_store(&at->low, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&at->high, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             x = wave_sum(x);
             if (lane == 0) s_partial[r * kWaves + wave] = x;
@@ -986,12 +992,14 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
         __syncthreads();
         first = 0;
         step = 1;
+        whole = true;
     }
 }
 
 constexpr int kFinalThreads = kNormGroups;   // one partial each where one launch made them all
 
-// One workgroup adds partials in a fixed order and writes the result: where the workspace is full, and for empty lists.
+// One workgroup adds partials in a fixed order and writes the result: where the workspace is full, for captured calls and for
+// empty lists.
 __global__ __launch_bounds__(kFinalThreads) void norm_finalize_kernel(const NormPartial* __restrict__ partials,
                                                                       uint32_t count, float loss_scale,
                                                                       int accumulate, zi_norm_result* out)

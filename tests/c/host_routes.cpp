@@ -30,7 +30,9 @@ int current_device = 0;
 int n_launches = 0, n_copies = 0, n_faults = 0;
 int n_link_steps = 0;                                           // launches of the step over the link
 const char* last_partial_sum = "";                             // name of the partial-sum kernel launched last
+int n_partial_sums = 0, n_waiting = 0, n_final_sums = 0;        // launches of it, of those that make the final sum, of the kernel for that
 hipError_t capture_query = hipSuccess;
+hipStream_t captured = nullptr;
 char streams[64];
 int stream_device[64], n_streams = 1;                           // 0 is the null stream
 char events[1024];
@@ -102,7 +104,14 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
     ++n_launches;
     for (int i = 0; i < n_kernels; ++i) {
         if (kernels[i] != f) continue;
-        if (strstr(kernel_names[i], "sumsq_partial_kernel")) last_partial_sum = kernel_names[i];
+        if (strstr(kernel_names[i], "sumsq_partial_kernel")) {
+            last_partial_sum = kernel_names[i];
+            ++n_partial_sums;
+            n_waiting += strstr(last_partial_sum, "NormOne")   ? ((const zi::NormOne*)args[0])->out != nullptr
+                         : strstr(last_partial_sum, "NormFew") ? ((const zi::NormFew*)args[0])->out != nullptr
+                                                               : ((const zi::NormArgs*)args[0])->out != nullptr;
+        }
+        if (strstr(kernel_names[i], "norm_finalize_kernel")) ++n_final_sums;
         if (strstr(kernel_names[i], "adamw_link_kernel")) ++n_link_steps;
         if (strstr(kernel_names[i], "link_copy_kernel"))
             run_link_copy(*(const zi::CopyArgs*)args[0], device_of(s), strstr(kernel_names[i], "ILb1E") != nullptr);
@@ -163,9 +172,9 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = device_of(s); return hipSuccess; }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st)
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st)
 {
-    *st = hipStreamCaptureStatusNone;
+    *st = s && s == captured ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return capture_query;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)(events + n_events++); return hipSuccess; }
@@ -330,6 +339,37 @@ static int capture()
     return 0;
 }
 
+// A captured launch is replayed with the same marks, so a partial that came too late for one replay would pass for the next
+// one's: under capture no workgroup waits for partials, a kernel of its own makes the final sum.
+static int replays()
+{
+    char* out = (char*)on_device(64 * 1024 * 8, 0);
+    zi_norm_result* norm = (zi_norm_result*)(out + zi_norm_workspace_bytes(0, 0));
+    constexpr int kMost = 700;
+    const int64_t n = 40'000;
+    char* g = (char*)on_device((size_t)kMost * n * 2, 0);
+    hipStream_t stream;
+    CHECK(hipStreamCreateWithFlags(&stream, 0) == hipSuccess);
+    for (int32_t count : {1, 2, 32, 33, 320, 321, kMost})
+        for (int64_t numel : {(int64_t)7, n})
+            for (int noalloc = 0; noalloc < 2; ++noalloc)
+                for (int under = 0; under < 2; ++under) {
+                    std::vector<zi_tensor> list((size_t)count);
+                    for (int32_t i = 0; i < count; ++i) {
+                        list[(size_t)i].g = g + 2 * n * i;
+                        list[(size_t)i].numel = numel;
+                    }
+                    captured = under ? stream : nullptr;
+                    n_partial_sums = n_waiting = n_final_sums = 0;
+                    CHECK((noalloc ? zi_grad_norm_noalloc(list.data(), count, ZI_BF16, 1.0f, norm, stream)
+                                   : zi_grad_norm(list.data(), count, ZI_BF16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), stream)) == ZI_OK);
+                    CHECK(n_partial_sums == (count + 319) / 320);
+                    CHECK(n_waiting == (under ? 0 : 1) && n_final_sums == (under ? 1 : 0));
+                    captured = nullptr;
+                }
+    return 0;
+}
+
 // How the copies of the CPU placement go up: what one slot use takes, by kernels, except that of a use of one segment of
 // at most 64 blocks with more uses behind it.
 static int uploads()
@@ -448,7 +488,7 @@ static int spanning()
 
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");

@@ -124,29 +124,79 @@ def test_workspace_and_result_in_page_locked_memory():
         assert (float(out[0]), float(out[1])) == want[:2] and int(out.view(torch.int32)[4]) == 0
 
 
-@pytest.mark.parametrize("keep", [0, 1])
-@pytest.mark.parametrize("n", [TILE * 2 + 1, TILE * 600 + 11])
-def test_a_last_workgroup_that_does_not_wait_does_all_the_work(n, keep, tmp_path):
-    """With no patience at all the partials count as missing and the last workgroup goes over the whole list."""
+@pytest.fixture(scope="module")
+def launch(tmp_path_factory):
     rocm = "/opt/rocm/include"
     if shutil.which("g++") is None or not os.path.isdir(rocm):
         pytest.skip("no host compiler or no HIP headers")
-    so, libdir = str(tmp_path / "norm_launch.so"), os.path.dirname(zi.LIB_PATH)
+    so, libdir = str(tmp_path_factory.mktemp("launch") / "norm_launch.so"), os.path.dirname(zi.LIB_PATH)
     subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-isystem", rocm, "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(libdir, "csrc"), os.path.join(ROOT, "tests", "c", "norm_launch.cpp"), "-o", so,
                     "-L", libdir, "-lzi", "-Wl,-rpath," + libdir, "-Wl,--allow-shlib-undefined"], check=True)
     zi.lib()
-    launch = ctypes.CDLL(so).norm_launch
-    launch.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p]
-    dt = zi.ZI_FP16
-    g = _grads(n, dt, 8)
-    want, _ = oracle.grad_sumsq([g], dt)
-    d, nb = to_dev(g), NormBuffers()
-    for patience in (0, 1 << 20, 0):
-        progress(f"reduction of {n} elements, keep {keep}, patience {patience}")
-        nb.out.fill_(-1.0)
+    f = ctypes.CDLL(so).norm_launch
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_uint32,
+                  ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_int]
+    return f
+
+
+@pytest.mark.parametrize("each,pieces,form,keep,before,accumulate", [
+    (TILE * 2 + 1, 1, 0, 0, 0, 0), (TILE * 2 + 1, 1, 0, 1, 0, 0), (TILE * 600 + 11, 1, 0, 0, 0, 0), (TILE * 600 + 11, 1, 0, 1, 0, 0),
+    (TILE * 2 + 1, 1, 1, 0, 0, 0), (TILE * 600 + 11, 1, 1, 1, 0, 1),                      # NormOne
+    (TILE + 8, 5, 2, 1, 0, 0), (TILE * 30, 32, 2, 1, 0, 1),                               # NormFew
+    (264, 1, 0, 1, 1, 0), (TILE + 8, 200, 0, 0, 321, 0), (TILE * 2, 300, 0, 1, 1024, 1), (TILE * 2, 300, 0, 0, 15871, 1)])
+def test_a_last_workgroup_that_does_not_wait_does_all_the_work(launch, each, pieces, form, keep, before, accumulate):
+    """With no patience at all the partials count as missing and the last workgroup goes over the launch's whole list; what the
+    launches before left in the workspace, other gradients' partials among it, changes nothing.  Partials of earlier launches
+    and an earlier result are added either way."""
+    dt, n = zi.ZI_FP16, each * pieces
+    nb = NormBuffers()
+    older = np.random.default_rng(before).uniform(0.0, 1e3, before)
+    bits = older.view(np.uint64)
+    words = np.stack([bits << np.uint64(32) | np.uint64(3), bits >> np.uint64(32) << np.uint64(32) | np.uint64(5)], axis=1).copy()
+    ws = nb.ws.view(torch.int64)
+    ws[:2 * before].copy_(torch.from_numpy(words.view(np.int64).reshape(-1)))
+    results = []
+    for turn, patience in enumerate((0, 1 << 20, 0, 1 << 20)):
+        progress(f"reduction of {pieces} x {each} elements, form {form}, keep {keep}, {before} before, patience {patience}")
+        g = _grads(n, dt, 8 + min(turn, 2))                                               # the last two see the same gradients
+        want = oracle.grad_sumsq([g], dt)[0] + math.fsum(older) + (7.5 if accumulate else 0.0)
+        d = to_dev(g)
+        nb.out.fill_(7.5)
         torch.cuda.synchronize()
-        assert launch(d.data_ptr(), n, dt, keep, patience, nb.ws.data_ptr(), nb.out.data_ptr()) == 0
+        assert launch(d.data_ptr(), each, pieces, dt, form, keep, patience, nb.ws.data_ptr(), before, nb.out.data_ptr(), accumulate) == 0
         torch.cuda.synchronize()
         got = nb.read()
         assert got[2] == 0 and abs(got[0] - want) <= 1e-12 * want and abs(got[1] - math.sqrt(want) / 2) <= 1e-12 * got[1]
+        results.append(got)
+    assert results[0] != results[1] != results[2]
+
+
+@pytest.mark.parametrize("count", [1, 2, 33, 320, 321, 700])
+def test_captured_calls_give_the_bits_of_eager_ones(count):
+    """Under capture a kernel of its own makes the final sum; both add in one order, over one launch's partials or several's."""
+    rng = np.random.default_rng(count)
+    lengths = [int(x) for x in rng.integers(1, 3 * TILE, count)]
+    starts = np.cumsum([0] + lengths)[:-1].tolist()
+    n = sum(lengths)
+    d, nb, nb_e = to_dev(_grads(n, zi.ZI_BF16, 1)), NormBuffers(), NormBuffers()
+    tl = zi.make_tensors([(None, None, None, d[s:s + k], None, k) for s, k in zip(starts, lengths)])
+    out2 = torch.zeros(4, dtype=torch.float64, device="cuda:0")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    zi.zi_grad_norm_noalloc(tl, zi.ZI_BF16, 1.0, out2)                                     # (finds the array's address)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        zi.zi_grad_norm(tl, zi.ZI_BF16, 1.0, nb.out, nb.ws, stream=side)
+        zi.zi_grad_norm_noalloc(tl, zi.ZI_BF16, 1.0, out2, stream=side)
+        graph.capture_end()
+    for replay in range(4):
+        g = _grads(n, zi.ZI_BF16, 50 + replay)
+        d.copy_(to_dev(g))
+        torch.cuda.synchronize()
+        graph.replay()
+        zi.zi_grad_norm(tl, zi.ZI_BF16, 1.0, nb_e.out, nb_e.ws)
+        torch.cuda.synchronize()
+        want, _ = oracle.grad_sumsq([g[s:s + k].copy() for s, k in zip(starts, lengths)], zi.ZI_BF16)
+        assert abs(nb.read()[0] - want) <= 1e-12 * want
+        assert torch.equal(nb.out, nb_e.out) and torch.equal(out2, nb_e.out), replay
