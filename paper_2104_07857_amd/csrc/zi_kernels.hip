@@ -935,19 +935,27 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
     __shared__ double s_partial[kNormGroups / 64];
     __shared__ uint32_t s_missing;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool last = a.out && blockIdx.x == a.n_groups - 1;
-    uint32_t first = blockIdx.x, step = a.n_groups;
+    // (in one batch of argument loads, not one behind the other where each is first looked at)
+    ZI_GLOBAL zi_norm_result* out_ = (ZI_GLOBAL zi_norm_result*)(uintptr_t)a.out;
+    ZI_GLOBAL NormPartial* partials_ = (ZI_GLOBAL NormPartial*)(uintptr_t)a.partials;
+    uint32_t n_groups = a.n_groups, n_before = a.n_before;
+    asm volatile("" : "+s"(out_), "+s"(partials_), "+s"(n_groups), "+s"(n_before));
+    zi_norm_result* const out = (zi_norm_result*)out_;
+    NormPartial* const partials = (NormPartial*)partials_;
+    const bool last = out && blockIdx.x == n_groups - 1;
+    uint32_t first = blockIdx.x, step = n_groups;
     // (every kNormGroups-th of all partials, this launch's behind those before it, as norm_finalize_kernel has them)
     double before[kRounds] = {};
+    bool whole = false;                   // everything to be summed is in this workgroup
     if (last) {
+        whole = n_groups == 1 && n_before == 0;
 #pragma unroll
         for (int r = 0; r < kRounds; ++r)
-            for (uint32_t i = threadIdx.x + r * THREADS; i < a.n_before; i += kNormGroups) {
-                const NormPartial& p = (a.partials - a.n_before)[i];
+            for (uint32_t i = threadIdx.x + r * THREADS; i < n_before; i += kNormGroups) {
+                const NormPartial& p = (partials - n_before)[i];
                 before[r] += partial_sum(p.low, p.high);
             }
     }
-    bool whole = a.n_groups == 1 && a.n_before == 0;      // everything to be summed is in this workgroup
     for (;;) {
         double sum = sumsq_tiles<DT, THREADS, KEEP, Args>(a, first, step);
         if (whole) {
@@ -958,19 +966,19 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
         if (lane == 0) s_sum[wave] = sum;
         if (threadIdx.x == 0) s_missing = 0;
         __syncthreads();
-        if (last && whole) {
-            if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_sum), a.loss_scale, a.accumulate, a.out);
+        if (whole) {
+            if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_sum), a.loss_scale, a.accumulate, out);
             return;
         }
-        if (threadIdx.x == 0) put_partial(a.partials + blockIdx.x, sum_of_waves(s_sum), a.mark_low, a.mark_high);
+        if (threadIdx.x == 0) put_partial(partials + blockIdx.x, sum_of_waves(s_sum), a.mark_low, a.mark_high);
         if (!last) return;
 
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t i = (threadIdx.x + r * THREADS - a.n_before) % kNormGroups;
+            const uint32_t i = (threadIdx.x + r * THREADS - n_before) % kNormGroups;
             double x = before[r];
-            if (i < a.n_groups) {
-                NormPartial* const at = a.partials + i;
+            if (i < n_groups) {
+                NormPartial* const at = partials + i;
                 uint64_t low = 0, high = 0;
                 bool there = false;
                 for (uint32_t looks = 0; !there && looks < a.patience; ++looks) {
@@ -986,7 +994,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
         }
         __syncthreads();
         if (!s_missing) {
-            if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_partial), a.loss_scale, a.accumulate, a.out);
+            if (threadIdx.x == 0) put_norm_result(sum_of_waves(s_partial), a.loss_scale, a.accumulate, out);
             return;
         }
         __syncthreads();
