@@ -148,10 +148,10 @@ size_t zi_norm_workspace_bytes(int64_t total_numel, int32_t n_tensors);
  * need no initialisation and are garbage afterwards.  Asynchronous: returns
  * once the work is enqueued.  Two calls that share a workspace must be ordered
  * on one stream.
- * Of up to 512 MiB of gradients the first 176 MiB are read so that they stay in the GPU's memory-side
- * cache for the step that begins with them: norm and step together take 2 to 5% less, a
- * norm that no step follows up to 7% more, or 35 us if the cache is full of other data
- * that has just been written.
+ * Gradients of up to 176 MiB in all are read so that they stay in the GPU's memory-side
+ * cache for the step that reads them next: norm and step together take 2 to 7% less, a norm that no
+ * step follows up to 5% more; where a kernel has just filled that cache with other data, which has to
+ * leave first, norm and step take 2% more and the norm alone up to twice as long.
  */
 zi_status zi_grad_norm(const zi_tensor* t, int32_t n_tensors, zi_lp_dtype dt, float loss_scale,
                        zi_norm_result* d_out, void* d_workspace, size_t workspace_bytes, void* hip_stream);

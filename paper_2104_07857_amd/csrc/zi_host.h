@@ -642,8 +642,7 @@ struct NormIssuer {
     zi::NormPartial* partials;
     uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
     uint32_t used = 0;                   // partials written since the last finalize
-    bool keep = false;                   // see kNormKeepElems: all gradients, or the first tiles (of the launches to come)
-    uint32_t keep_left = 0;
+    bool keep = false;                   // see kNormKeepElems
     int launches = 0;                    // kernels so far
     int finalized = 0;
     int dt;
@@ -655,11 +654,6 @@ struct NormIssuer {
         : partials(partials_), dt(dt_), loss_scale(ls), d_out(out), s(st)
     {
         a.n_tiles = 0;
-    }
-    void keep_for_step(int64_t elems_of_call)
-    {
-        keep = elems_of_call <= zi::kNormKeepElems;
-        keep_left = keep || elems_of_call > zi::kNormKeepUpTo ? 0 : (uint32_t)(zi::kNormKeepElems / zi::kNormTileElems);
     }
     static int64_t tiles_for(const uint16_t* g, int64_t n)
     {
@@ -692,12 +686,10 @@ struct NormIssuer {
         a.loss_scale = loss_scale;
         a.accumulate = finalized;
         a.n_groups = blocks;
-        a.keep_tiles = keep_left < a.n_tiles ? keep_left : a.n_tiles;
-        keep_left -= a.keep_tiles;
         a.n_before = final ? used : 0;
         if (final && n_desc == 1 && used == 0) {
-            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, a.keep_tiles, blocks, a.mark_low, a.mark_high,
-                                     a.patience, loss_scale, a.accumulate}, dt, keep, s);
+            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, blocks, a.mark_low, a.mark_high, a.patience,
+                                     loss_scale, a.accumulate}, dt, keep, s);
         } else if (final && keep && n_desc <= zi::NormFew::kMax && used == 0) {
             zi::NormFew few;
             for (int32_t i = 0; i < n_desc; ++i) {
@@ -705,7 +697,7 @@ struct NormIssuer {
                 few.first_tile[i] = a.first_tile[i];
             }
             finish_list(few, n_desc, a.n_tiles);
-            few.n_tiles = a.n_tiles; few.keep_tiles = a.keep_tiles; few.n_groups = a.n_groups;
+            few.n_tiles = a.n_tiles; few.n_groups = a.n_groups;
             few.mark_low = a.mark_low; few.mark_high = a.mark_high; few.patience = a.patience;
             few.loss_scale = a.loss_scale; few.partials = a.partials; few.out = a.out;
             few.n_before = a.n_before; few.accumulate = a.accumulate;

@@ -68,19 +68,21 @@ constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 ele
 // a contiguous run of tiles per workgroup 12.2 / 94 / 378 / 101, half the loads in flight 13.0 / 92 / 376 / 100,
 // single-wavefront workgroups 12.7 / 92 / 373 / 105 at best.
 constexpr int kNormGroups = 512;
-// So many elements (176 of the 256 MiB of the memory-side cache), all of a call or the first of one of up to kNormKeepUpTo,
-// are read with ordinary loads, which leave them in the cache for the step that begins with them; streaming loads pass it by.
-// Norm and step in us, all streaming / this:
-//   elements                         3.4e7      6.7e7      9.2e7      1.3e8      2.0e8      2.6e8        3.0e8        1.3e9
-//   one call after the other         172 / 165  326 / 313  444 / 428  611 / 588  941 / 919  1228 / 1203  1420 / 1401  6148 / 6116
-//   a kernel has just written the gradients                447 / 431  612 / 597  948 / 924               1440 / 1419  6168 / 6128
-//   the cache is full of what a kernel has written elsewhere
-//                                                          449 / 457  614 / 623  946 / 955               1428 / 1440  6150 / 6170
-// What such a kernel wrote leaves the cache during the reduction then, at 35 us for all of it, which the step does not
-// quite give back.  The reduction alone, cold but clean, takes 2 to 3 us longer (9.2e7 elements 33.1 / 35.4, 288 tensors with 3.0e8
-// 91 / 94), on gradients just written it does not: beyond 2^28 elements that is more of its time than what the step gains of
-// its own.  7168 tiles instead of 5632 gain another 5 us and lose another 5.
-constexpr int64_t kNormKeepUpTo = (int64_t)1 << 28;
+// Calls of up to this many elements (176 of the 256 MiB of the memory-side cache) read the gradients with ordinary
+// loads, which leave them there for the step that reads them next; streaming loads pass the cache by.  In us, streaming / ordinary:
+//   elements                                      1.6e7        3.4e7        6.7e7        9.2e7
+//   norm and step, one call after the other       83.2 / 81.5  168 / 160    318 / 300    443 / 413
+//     a kernel has just written the gradients     84.2 / 80.3  168 / 160    318 / 303    437 / 417
+//     the cache is full of what a kernel has just written elsewhere
+//                                                 84.3 / 86.2  168 / 172    320 / 326    441 / 448
+//   norm alone, cold but clean                    10.6 / 10.7  16.1 / 16.0  24.7 / 25.7  31.9 / 33.4
+//     a kernel has just written the gradients     10.8 / 9.8   15.3 / 14.7  23.5 / 23.1  30.8 / 32.0
+//     the cache is full of what a kernel has just written elsewhere
+//                                                 10.5 / 16.3  15.8 / 28.6  24.4 / 50.9  31.8 / 69.0
+// What a kernel has written elsewhere leaves the cache during the reduction then, 38 us for all of it, of which the step gives
+// back most.  The first 176 MiB of longer calls, read last and so, would gain a step the same 24 us (1.0e8 elements 470 / 447, 2.6e8
+// 1219 / 1197), but with the cache full of other data both together lose 11 to 16 us (471 / 482, 1219 / 1235), and the reduction
+// alone takes 34.1 / 71.7 and 79.8 / 118 us: those calls stream as a whole.
 constexpr int64_t kNormKeepElems = (int64_t)11 << 23;
 // Gradients in host memory are bound by the link, which few requests in flight fill: GB/s by workgroups
 // 32: 55.9, 64: 57.5, 128: 57.4, 256: 56.4, 1024: 55.9.
@@ -265,7 +267,7 @@ struct NormList {
     uint64_t where[kMax];
     uint32_t first_tile[kMax + 1];  // behind the list: n_tiles, then 0xFFFFFFFF
     uint32_t group_start[kGroups];  // first_tile of every group's first
-    uint32_t n_tiles, keep_tiles;
+    uint32_t n_tiles;
     uint32_t n_groups;              // workgroups of the launch
     uint32_t mark_low, mark_high;   // neither is zero; no other launch of the process has the same two
     uint32_t patience;              // kNormPatience
@@ -288,7 +290,7 @@ struct NormOne {
     const uint16_t* g;
     NormPartial* partials;
     zi_norm_result* out;
-    uint32_t numel, n_tiles, keep_tiles, n_groups, mark_low, mark_high, patience;
+    uint32_t numel, n_tiles, n_groups, mark_low, mark_high, patience;
     float loss_scale;
     int32_t accumulate;
     static constexpr uint32_t n_before = 0;

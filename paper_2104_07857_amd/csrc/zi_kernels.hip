@@ -791,7 +791,7 @@ __device__ __forceinline__ double sum_of_waves(const double (&s)[NWAVES])
     return t;
 }
 
-// Tiles first, first + step, ... of all tensors of a list, counted from its end, each tile THREADS * UNROLL 16-byte vectors with all
+// Tiles first, first + step, ... of all tensors of a list in order, each tile THREADS * UNROLL 16-byte vectors with all
 // loads in flight before the first use (a vector past the end counts as zeros).  A tensor's first tile also takes the
 // elements in front of its first 16-byte aligned one and behind its last whole vector.  The tiles of a list are shared
 // out evenly, whatever its tensors' lengths: with workgroups of its own for every tensor a list of short ones left most
@@ -799,8 +799,7 @@ __device__ __forceinline__ double sum_of_waves(const double (&s)[NWAVES])
 // Squares are accumulated in double: exact products, and a finite gradient whose square would overflow fp32 still gives a
 // finite sum.  Infinities and NaN make the sum infinite or NaN and nothing else does (2^63 of the largest squares are
 // 1e96), so the sum itself says whether there was one.
-// KEEP: ordinary loads, which leave the gradients in the memory-side cache (kNormKeepElems); otherwise the list's first
-// keep_tiles tiles are read so, and last, so that they are there when the step begins with them.
+// KEEP: ordinary loads, which leave the gradients in the memory-side cache (kNormKeepElems).
 struct NormTensor {
     const ZI_GLOBAL uint16_t* g;
     uint32_t numel, first_tile, next_tile;
@@ -850,9 +849,8 @@ __device__ __forceinline__ double sumsq_tiles(const Args& a, uint32_t first, uin
     constexpr int UNROLL = kNormTileVecs / THREADS;
     double acc0 = 0.0, acc1 = 0.0;
     NormTensor T = {nullptr, 0, 0, 0};
-    for (uint32_t k = first; k < a.n_tiles; k += step) {
-        const uint32_t t = a.n_tiles - 1 - k;
-        if (t < T.first_tile || t >= T.next_tile) T = tensor_of_tile(a, t);
+    for (uint32_t t = first; t < a.n_tiles; t += step) {
+        if (t >= T.next_tile) T = tensor_of_tile(a, t);
         const uint32_t tile = t - T.first_tile;
         const uint32_t lead = (uint32_t)(-((uintptr_t)T.g / 2)) % kVec;
         const uint32_t head = lead < T.numel ? lead : T.numel;
@@ -864,13 +862,8 @@ __device__ __forceinline__ double sumsq_tiles(const Args& a, uint32_t first, uin
         const uintptr_t start = (uintptr_t)(g4 + at);
         const __amdgpu_buffer_rsrc_t here = raw_buffer(start, bytes);
         u32x4 g[UNROLL];
-        if (KEEP || t < a.keep_tiles) {
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) g[u] = load_in_tile<true>(here, threadIdx.x * 16, (uint32_t)u * THREADS * 16);
-        } else {
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) g[u] = load_in_tile<false>(here, threadIdx.x * 16, (uint32_t)u * THREADS * 16);
-        }
+        for (int u = 0; u < UNROLL; ++u) g[u] = load_in_tile<KEEP>(here, threadIdx.x * 16, (uint32_t)u * THREADS * 16);
         if (tile == 0) {
             const uint32_t lane = threadIdx.x, body_end = head + nvec * kVec;
             const bool front = lane < head, back = lane >= kVec && lane - kVec < T.numel - body_end;

@@ -17,8 +17,7 @@ from gpu_util import NormBuffers, progress, to_dev
 pytestmark = pytest.mark.gpu
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 TILE, GROUPS = 16384, 512
-KEEP = 11 << 23                       # elements up to which all gradients are read with ordinary loads
-KEEP_FIRST = 1 << 28                  # ... and up to which the first KEEP of them are
+KEEP = 11 << 23                       # elements up to which the gradients are read with ordinary loads
 
 
 def _grads(n, dt, seed):
@@ -77,7 +76,7 @@ def test_lists_around_the_lookup_s_limits(count, dt):
         assert _norm([e[s:s + n] for s, n in zip(starts, lengths)], dt, nb)[2] == flag
 
 
-@pytest.mark.parametrize("n", [KEEP, KEEP + 1, KEEP + TILE + 7, KEEP_FIRST, KEEP_FIRST + 1])
+@pytest.mark.parametrize("n", [KEEP, KEEP + 1, KEEP + TILE + 7, 1 << 28, (1 << 28) + 1])
 def test_both_ways_of_reading(n):
     g = to_dev(np.tile(_grads(1 << 16, zi.ZI_BF16, 3), n // (1 << 16) + 1))[:n]
     one, _ = oracle.grad_sumsq([g[:1 << 16].cpu().numpy().view(np.uint16)], zi.ZI_BF16)

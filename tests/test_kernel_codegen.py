@@ -21,6 +21,7 @@ from paper_2104_07857_amd import build as zb
 
 KERNEL = re.compile(r"^(_ZN2zi17adamw_wide_kernelILi([01])ELb([01])ELb([01])EEEvNS_8StepArgsE):", re.M)
 LIST_KERNEL = re.compile(r"^(_ZN2zi17adamw_list_kernelILi([01])ELb([01])ENS_8(List|Flat)ArgsEEEvT1_):", re.M)
+NORM_KERNEL = re.compile(r"^(_ZN2zi20sumsq_partial_kernelILi([01])ELb([01])ENS_(7NormOne|7NormFew|8NormArgs)EEEvT1_):", re.M)
 LINK_KERNEL = re.compile(r"^(_ZN2zi17adamw_link_kernelILi([01])ELb([01])EEEvNS_8LinkArgsE):", re.M)
 
 
@@ -77,6 +78,18 @@ def test_no_scratch_and_two_wavefronts_per_simd_fit(step_kernels, list_kernels, 
         assert directive(body, "private_segment_fixed_size") == 0, key
         assert directive(body, "next_free_vgpr") <= 256, key
         assert "scratch_" not in body and "buffer_" not in body, key
+
+
+def test_reduction_reads_all_gradients_one_way(assembly):
+    """Ordinary loads leave the gradients in the memory-side cache, and whatever a kernel has just written there has to leave
+    first; an instantiation with streaming loads has no others."""
+    kernels = _kernels(assembly, NORM_KERNEL)
+    assert len(kernels) == 10, sorted(kernels)     # {bf16, fp16} x ({streaming, ordinary} x {one tensor, list}, short list)
+    for key, body in kernels.items():
+        loads = [x for x in instructions(body) if x.startswith("buffer_load_dwordx4")]
+        assert len(loads) == (4 if key[1] == "1" else 8), (key, loads)
+        assert all(x.endswith(" nt") == (key[1] == "0") for x in loads), (key, loads)
+        assert directive(body, "private_segment_fixed_size") == 0, key
 
 
 def test_norm_result_is_read_with_one_scalar_load(step_kernels):
