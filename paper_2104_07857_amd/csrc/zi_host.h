@@ -495,8 +495,9 @@ struct CopyIssuer {
     }
 };
 
-// Issues the step over segments in page-locked host memory (adamw_link_kernel).  Long segments are cut
-// where a launch is full, a multiple of 512 elements into the segment's body.
+// Issues the step over segments in page-locked host memory (adamw_link_kernel, adamw_link_flat_kernel), kLinkTilesPerLaunch
+// tiles to a launch at most.  Long segments are cut where a launch is full, a multiple of 512 elements into the segment's
+// body; those of flat lists are not cut, and a list with one that is longer than a launch goes the other way.
 struct LinkIssuer {
     zi::LinkArgs args[2];          // the launch being assembled and the one held back
     zi::LinkFlatArgs flat[2];
@@ -524,12 +525,14 @@ struct LinkIssuer {
     // What the list will be, with addresses as the device sees them, before the first add().
     void expect(const zi_tensor* t, int32_t n_tensors)
     {
-        int64_t n = 0, total = 0;
+        int64_t n = 0, total = 0, longest = 0;
         for (int32_t i = 0; i < n_tensors; ++i) {
             n += t[i].numel > 0;
             total += t[i].numel;
+            if (t[i].numel > longest) longest = t[i].numel;
         }
-        is_flat_list = n > zi::kMaxLinkDesc && total / n <= StepIssuer::kFlatAverage && is_flat(t, n_tensors, flat[0].list);
+        is_flat_list = n > zi::kMaxLinkDesc && total / n <= StepIssuer::kFlatAverage && longest <= zi::kLinkTilesPerLaunch * zi::kStepTileElems &&
+                       is_flat(t, n_tensors, flat[0].list);
         if (!is_flat_list) return;
         flat[0].list.c = args[0].c;
         flat[0].list.d_norm = args[0].d_norm;
@@ -573,7 +576,8 @@ struct LinkIssuer {
     hipError_t add(float* p, float* m, float* v, const uint16_t* g, uint16_t* p_lp, int64_t numel)
     {
         if (is_flat_list && numel > 0) {
-            if (n_flat == zi::FlatArgs::kMax || flat[now].n_tiles >= zi::kLinkTilesPerLaunch)
+            const int64_t at_most = (numel + zi::kStepTileElems - 1) / zi::kStepTileElems;
+            if (n_flat == zi::FlatArgs::kMax || flat[now].n_tiles + at_most > zi::kLinkTilesPerLaunch)
                 if (const hipError_t e = close(); e != hipSuccess) return e;
             zi::LinkFlatArgs& a = flat[now];
             a.n_tiles += add_flat(a.list, n_flat++, a.n_tiles, p, choose_head(p, m, v, g, p_lp), numel);

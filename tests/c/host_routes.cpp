@@ -29,6 +29,9 @@ int n_kernels = 0;
 int current_device = 0;
 int n_launches = 0, n_copies = 0, n_faults = 0;
 int n_link_steps = 0;                                           // launches of the step over the link
+uint32_t most_link_tiles = 0;                                   // of one of them
+int64_t all_link_tiles = 0;
+int n_flat_link_steps = 0;                                      // of them over flat lists
 const char* last_partial_sum = "";                             // name of the partial-sum kernel launched last
 int n_partial_sums = 0, n_waiting = 0, n_final_sums = 0;        // launches of it, of those that make the final sum, of the kernel for that
 hipError_t capture_query = hipSuccess;
@@ -113,6 +116,12 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
         }
         if (strstr(kernel_names[i], "norm_finalize_kernel")) ++n_final_sums;
         if (strstr(kernel_names[i], "adamw_link_kernel")) ++n_link_steps;
+        if (strstr(kernel_names[i], "adamw_link_flat_kernel")) ++n_flat_link_steps;
+        if (strstr(kernel_names[i], "adamw_link_")) {
+            const uint32_t tiles = strstr(kernel_names[i], "_flat_") ? ((const zi::LinkFlatArgs*)args[0])->n_tiles : ((const zi::LinkArgs*)args[0])->n_tiles;
+            if (tiles > most_link_tiles) most_link_tiles = tiles;
+            all_link_tiles += tiles;
+        }
         if (strstr(kernel_names[i], "link_copy_kernel"))
             run_link_copy(*(const zi::CopyArgs*)args[0], device_of(s), strstr(kernel_names[i], "ILb1E") != nullptr);
     }
@@ -486,9 +495,46 @@ static int spanning()
     return 0;
 }
 
+// A launch over the link holds kLinkTilesPerLaunch tiles at most, also where a list that is short on average has long tensors.
+static int link_tiles()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 << 20, 3) == ZI_OK);
+    const zi_adamw_config c = config();
+    const int64_t limit = (int64_t)zi::kLinkTilesPerLaunch * zi::kStepTileElems;
+    const struct { int64_t length; int count; bool flat; } long_ones[] = {
+        {1000, 0, true}, {limit / 2, 3, true}, {limit - 512, 1, true}, {limit, 1, true}, {limit + 1, 1, false}, {limit + 576, 1, false},
+        {limit + limit / 2, 1, false}};
+    for (const auto& k : long_ones) {
+        std::vector<int64_t> lengths(1400, 700);
+        for (int i = 0; i < k.count; ++i) lengths[(size_t)(300 + 2 * i)] = k.length;
+        int64_t n = 0;
+        for (int64_t x : lengths) n += x;
+        void* a[5];
+        for (int w = 0; w < 5; ++w) (void)allocate(&a[w], (size_t)n * (w < 3 ? 4 : 2), w < 3 ? -1 : 0);
+        std::vector<zi_tensor> list;
+        int64_t at = 0, tiles = 0;
+        for (int64_t x : lengths) {
+            list.push_back({(float*)a[0] + at, (float*)a[1] + at, (float*)a[2] + at, (uint16_t*)a[3] + at, (uint16_t*)a[4] + at, x});
+            at += x;
+            tiles += (x + 511) / 512;
+        }
+        n_flat_link_steps = n_link_steps = 0;
+        most_link_tiles = 0;
+        all_link_tiles = 0;
+        CHECK(zi_adamw_step_streamed(e, list.data(), (int32_t)list.size(), ZI_BF16, &c, nullptr, nullptr) == ZI_OK);
+        CHECK(most_link_tiles <= zi::kLinkTilesPerLaunch);
+        CHECK(all_link_tiles <= tiles + 2 && all_link_tiles >= tiles - 1400);      // (a head of up to 63 elements may save a tile)
+        CHECK(k.flat ? n_flat_link_steps >= 6 && n_link_steps == 0 : n_flat_link_steps == 0 && n_link_steps > 6);
+        for (void* x : a) release(x);
+    }
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");
