@@ -1,7 +1,9 @@
-"""Builds libzi.so (HIP kernels + C ABI) for gfx950 with hipcc and _zi_call.so (argument marshalling) with gcc, in-tree."""
+"""Builds libzi.so (HIP kernels + C ABI) for gfx950 with hipcc and the module _zi_call (argument marshalling) with gcc, in-tree."""
 from __future__ import annotations
 
+import importlib.machinery
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -10,7 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libzi.so")
-CALL_PATH = os.path.join(HERE, "_zi_call.so")
+# (it uses more than the limited API, so its name has this interpreter's version in it)
+CALL_PATH = os.path.join(HERE, "_zi_call" + importlib.machinery.EXTENSION_SUFFIXES[0])
 SOURCES = ["zi_kernels.hip", "zi_api.hip", "zi_plan.hip", "zi_engine.hip", "zi_offload.hip", "zi_probe.hip"]
 
 # -ffp-contract=off: the only fused multiply-adds are the ones the kernels write as fma.
@@ -35,8 +38,12 @@ def has_python_headers() -> bool:
     return os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h"))
 
 
+def call_can_be_built() -> bool:
+    return has_python_headers() and shutil.which("gcc") is not None
+
+
 def needs_build() -> bool:
-    built = [LIB_PATH, CALL_PATH] if has_python_headers() else [LIB_PATH]
+    built = [LIB_PATH, CALL_PATH] if call_can_be_built() else [LIB_PATH]
     if not all(os.path.exists(f) for f in built):
         return True
     t = min(os.path.getmtime(f) for f in built)
@@ -52,14 +59,26 @@ HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-mavx2", "-mfma", "-mf16c", "-ffp-c
 
 
 def build_call() -> str | None:
-    """The Python side of the calls made once per step (csrc/zi_python.c).  Without Python's headers there is none, and
+    """The Python side of the calls made once per step (csrc/zi_python.c).  Where it cannot be built there is none, and
     binding.py takes every call through ctypes."""
-    if not has_python_headers():
-        sys.stderr.write("no Python.h: calls go through ctypes\n")
+    for old in (CALL_PATH, os.path.join(HERE, "_zi_call.so")):      # the second is any Python's to import
+        if os.path.exists(old):
+            os.remove(old)
+    if not call_can_be_built():
+        sys.stderr.write("no Python.h or no gcc: calls go through ctypes\n")
         return None
-    subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter",
-                    "-Wno-missing-field-initializers", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
-                    os.path.join(CSRC, "zi_python.c"), "-o", CALL_PATH], check=True)
+    try:
+        r = subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter",
+                            "-Wno-missing-field-initializers", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+                            os.path.join(CSRC, "zi_python.c"), "-o", CALL_PATH], capture_output=True, text=True)
+        failed, said = r.returncode != 0, r.stderr
+    except OSError as e:
+        failed, said = True, str(e)
+    if said.strip():
+        sys.stderr.write(said.rstrip() + "\n")
+    if failed:
+        sys.stderr.write("_zi_call was not built: calls go through ctypes\n")
+        return None
     return CALL_PATH
 
 

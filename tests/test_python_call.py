@@ -2,6 +2,9 @@
 and that it refuses what the general way refuses, with the same words (no GPU: every call here ends in the library's
 argument checks)."""
 import ctypes
+import importlib.machinery
+import os
+import subprocess
 import sys
 
 import numpy as np
@@ -10,14 +13,17 @@ import torch
 
 import paper_2104_07857_amd as zi
 from paper_2104_07857_amd import binding
+from paper_2104_07857_amd import build as zb
 
 OUT, WS = torch.zeros(4, dtype=torch.float64), torch.zeros(262144, dtype=torch.uint8)
 
 
 @pytest.fixture(scope="module")
 def calls():
+    if not zb.call_can_be_built():
+        pytest.skip("no Python.h or no gcc: every call goes through ctypes")
     binding.lib()
-    assert binding._call_step is not binding._not_taken, "_zi_call.so is not built"
+    assert binding._call_step is not binding._not_taken, zb.CALL_PATH + " is not built"
     return binding._call_norm, binding._call_norm_noalloc, binding._call_step
 
 
@@ -33,6 +39,36 @@ class _Stream:
 class _Raises:
     def data_ptr(self):
         raise RuntimeError("no")
+
+
+def test_module_is_named_for_this_interpreter(calls):
+    """Another Python finds neither this file nor one without a version in its name."""
+    from paper_2104_07857_amd import _zi_call
+    assert os.path.samefile(_zi_call.__file__, zb.CALL_PATH)
+    assert zb.CALL_PATH.endswith(importlib.machinery.EXTENSION_SUFFIXES[0]) and importlib.machinery.EXTENSION_SUFFIXES[0] != ".so"
+    assert not os.path.exists(os.path.join(zb.HERE, "_zi_call.so"))
+
+
+@pytest.mark.parametrize("why", ["no headers", "no compiler", "compiler fails", "compiler vanishes"])
+def test_build_goes_on_without_the_module(why, tmp_path, monkeypatch, capsys):
+    """Without the module every call goes through ctypes: one that cannot be built is reported, an older one goes away."""
+    here, old = tmp_path / ("_zi_call" + importlib.machinery.EXTENSION_SUFFIXES[0]), tmp_path / "_zi_call.so"
+    here.write_bytes(b"old")
+    old.write_bytes(b"old")
+    monkeypatch.setattr(zb, "HERE", str(tmp_path))
+    monkeypatch.setattr(zb, "CALL_PATH", str(here))
+
+    def run(*args, **kwargs):
+        assert why.startswith("compiler")
+        if why == "compiler vanishes":
+            raise FileNotFoundError("gcc")
+        return subprocess.CompletedProcess(args, 1, "", "no such luck")
+
+    monkeypatch.setattr(zb.subprocess, "run", run)
+    monkeypatch.setattr(zb, "has_python_headers", lambda: why != "no headers")
+    monkeypatch.setattr(zb.shutil, "which", lambda name: None if why == "no compiler" else "/usr/bin/" + name)
+    assert zb.build_call() is None
+    assert "ctypes" in capsys.readouterr().err and not here.exists() and not old.exists()
 
 
 def test_usual_forms_are_taken(calls):
