@@ -932,7 +932,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
     ZI_GLOBAL zi_norm_result* out_ = (ZI_GLOBAL zi_norm_result*)(uintptr_t)a.out;
     ZI_GLOBAL NormPartial* partials_ = (ZI_GLOBAL NormPartial*)(uintptr_t)a.partials;
     uint32_t n_groups = a.n_groups, n_before = a.n_before;
-    asm volatile("" : "+s"(out_), "+s"(partials_), "+s"(n_groups), "+s"(n_before));
+    if constexpr (!__is_same(Args, NormOne)) asm volatile("" : "+s"(out_), "+s"(partials_), "+s"(n_groups), "+s"(n_before));
     zi_norm_result* const out = (zi_norm_result*)out_;
     NormPartial* const partials = (NormPartial*)partials_;
     const bool last = out && blockIdx.x == n_groups - 1;
