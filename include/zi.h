@@ -403,10 +403,15 @@ zi_status zi_plan_chunks(const int64_t* numel, int32_t n_tensors, int64_t chunk_
  * the addresses and lengths of t[] are used).  One item per non-empty tensor: the number of leading
  * elements handled one by one before the 4-element lane vectors start (0..63, chosen so that as much
  * of the tensor's traffic as possible starts on 128-byte lines), its tiles of 512 elements, and the
- * launch it belongs to.  Tensors of 2^22 elements or more get a launch of their own (`alone`);
- * shorter ones share launches of up to 32 tensors.  Lists of more than 64 tensors share launches of 64,
- * long tensors too, or of 256 if they are short (327,680 elements on average at most) and all tensors are at the
- * same places of five flat buffers (one for each of p, m, v, g and p_lp).  Writes at most `cap` items and always the totals.
+ * launch it belongs to.  By what the list consists of (empty tensors do not count):
+ *   - more than 32 tensors of 327,680 elements on average at most, all at the same places of five flat
+ *     buffers (one for each of p, m, v, g and p_lp): launches of 256;
+ *   - any other list of more than 64 tensors, and shorter lists of 2^25 elements on average at most in
+ *     which two tensors or more, and one in eight, have 2^22 elements or more: launches of 64, long
+ *     tensors too;
+ *   - otherwise a tensor of 2^22 elements or more has a launch of its own, shorter ones share launches
+ *     of up to 32.
+ * `alone` follows from that and not from the length.  Writes at most `cap` items and always the totals.
  */
 typedef struct {
     int32_t tensor;        /* index into t[] */

@@ -22,7 +22,7 @@ constexpr int kMaxStepDesc = 32;     // tensors (or segments) per fused-step lau
 // unit.  On this 1:1 read/write stream few, short-lived wavefronts measured 4-8% faster than full occupancy, but how
 // few depends on the launch.  Up to kStepShortTiles or kListShortTiles tiles what counts is how few rounds of resident
 // workgroups it takes; in launches of more than kStepLongTiles bunching begins to cost, above all in adamw_list_kernel, whose
-// wavefronts arrive at their loads later.
+// wavefronts arrive at their loads later.  (The longest tensors by themselves: no difference beyond the placement's.)
 // Step alone in us, averages over six placements of the arrays (short ones: of a captured row of calls),
 // workgroups per compute unit:
 //                                             16      8      7      6
@@ -133,7 +133,8 @@ struct StepArgs {
 
 // One short tensor (adamw_short_kernel), in few bytes: a call on it takes the host longer than the GPU, and what the runtime takes
 // for a launch depends on the size of its arguments.  Issue of an empty kernel in us (the runtime runs in one of two modes for
-// the life of a process): up to 112 bytes 2.4 or 2.85, 120 and more 2.5 or 3.55, StepArgs' 3.3 KB 2.65 or 4.1.
+// the life of a process): up to 112 bytes 2.4 or 2.8, 120 to 1024 bytes 2.5 or 3.5 to 3.7, StepArgs' 2.5 KB 2.55 or 3.75, 3.6 KB and
+// more 2.55 or 3.8 to 4.1.
 struct StepOne {
     float* p_body;         // p + head
     float* m_body;
@@ -224,7 +225,7 @@ struct LinkArgs {
 static_assert(sizeof(LinkArgs) < 4096, "kernel arguments");
 
 // The same for more short tensors than kMaxLinkDesc at the same places of five flat buffers: 256 of them.  A launch of 48
-// tensors of a tile or two leaves half of the workgroups without work, and its one round trip over the link is paid per launch.
+// tensors of a tile or two leaves half of the workgroups without work, and its round trips over the link are paid per launch.
 struct LinkFlatArgs {
     FlatArgs list;                  // addresses as the device sees them
     uint32_t n_tiles;

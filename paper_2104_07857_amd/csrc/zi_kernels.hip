@@ -566,8 +566,10 @@ __device__ __forceinline__ uint32_t find_desc(const Desc* t, uint32_t d, uint32_
 
 // ------------------------------------------------- the step over state in page-locked host memory
 
-// Tile `tile` of a tensor in host memory, and with its first tile the elements outside the vector body.  Everything has
-// its loads in flight before the first use: a short tensor costs one round trip of the link, not three.
+// Tile `tile` of a tensor in host memory, and with its first tile the elements outside the vector body: head and tail together and
+// both quads together, not one behind the other.  The compiler still puts in waits of a round trip of the link each: for the
+// end elements' gradients before a first tile's quads are loaded, in the fp16 instantiations for the first quad's gradients
+// before the second quad's loads, and at the head of a wavefront's next tile for the stores of the last.
 template <int DT, bool L2, typename Desc>
 __device__ __forceinline__ void link_tile(const Desc& T, int64_t head, int64_t nquad, int64_t tail, uint32_t tile,
                                           float gscale, const StepConsts& c)
