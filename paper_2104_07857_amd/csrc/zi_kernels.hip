@@ -919,7 +919,7 @@ __device__ __forceinline__ void put_norm_result(double sumsq, float loss_scale, 
 // is busy with other work, or a call that was not ordered behind this one overwrote them), the last workgroup goes over the
 // launch's tiles itself.
 // Marks tell this launch's partials from whatever the workspace held.  A launch that may run twice with the same ones, a captured
-// one, must not make the final sum (NormIssuer::finish): norm_finalize_kernel does it there.
+// one, must not make the final sum over several workgroups (NormIssuer::finish): norm_finalize_kernel does it there.
 // The order of the sum is that kernel's, and does not depend on scheduling unless the last workgroup does all the work.
 template <int DT, bool KEEP, typename Args>
 __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const Args a)
@@ -1001,8 +1001,8 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
 
 constexpr int kFinalThreads = kNormGroups;   // one partial each where one launch made them all
 
-// One workgroup adds partials in a fixed order and writes the result: where the workspace is full, for captured calls and for
-// empty lists.
+// One workgroup adds partials in a fixed order and writes the result: where the workspace is full, for captured calls of more
+// than one workgroup and for empty lists.
 __global__ __launch_bounds__(kFinalThreads) void norm_finalize_kernel(const NormPartial* __restrict__ partials,
                                                                       uint32_t count, float loss_scale,
                                                                       int accumulate, zi_norm_result* out)

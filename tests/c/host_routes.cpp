@@ -349,7 +349,8 @@ static int capture()
 }
 
 // A captured launch is replayed with the same marks, so a partial that came too late for one replay would pass for the next
-// one's: under capture no workgroup waits for partials, a kernel of its own makes the final sum.
+// one's: under capture no workgroup waits for partials, a kernel of its own makes the final sum.  (A list of one tile is one
+// workgroup's, which has no others to wait for.)
 static int replays()
 {
     char* out = (char*)on_device(64 * 1024 * 8, 0);
@@ -373,7 +374,8 @@ static int replays()
                     CHECK((noalloc ? zi_grad_norm_noalloc(list.data(), count, ZI_BF16, 1.0f, norm, stream)
                                    : zi_grad_norm(list.data(), count, ZI_BF16, 1.0f, norm, out, zi_norm_workspace_bytes(0, 0), stream)) == ZI_OK);
                     CHECK(n_partial_sums == (count + 319) / 320);
-                    CHECK(n_waiting == (under ? 0 : 1) && n_final_sums == (under ? 1 : 0));
+                    const bool separate = under && !(count == 1 && numel == 7);
+                    CHECK(n_waiting == (separate ? 0 : 1) && n_final_sums == (separate ? 1 : 0));
                     captured = nullptr;
                 }
     return 0;
