@@ -165,8 +165,8 @@ extern "C" zi_status zi_adamw_step(const zi_tensor* t, int32_t n_tensors, zi_lp_
 
     const zi::StepConsts k = make_consts(*cfg);
     zi::StepOne one;
-    if (one_short_tensor(t, n_tensors, k, cfg->mode == ZI_MODE_ADAM_L2, d_norm, one)) {
-        ZI_HIP(zi::launch_step_short(one, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, (hipStream_t)hip_stream));
+    if (one_tensor(t, n_tensors, k, cfg->mode == ZI_MODE_ADAM_L2, d_norm, one)) {
+        ZI_HIP(zi::launch_step_one(one, (int)dt, cfg->mode == ZI_MODE_ADAM_L2, false, (hipStream_t)hip_stream));
         return ZI_OK;
     }
     zi::FlatFew few;

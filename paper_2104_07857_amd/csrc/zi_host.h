@@ -160,9 +160,9 @@ inline bool is_captured(hipStream_t stream)
     return true;
 }
 
-// A call on one tensor of up to kStepShortTiles tiles, as adamw_short_kernel takes it: false if it is another call.
-inline bool one_short_tensor(const zi_tensor* t, int32_t n_tensors, const zi::StepConsts& c, bool l2,
-                             const zi_norm_result* d_norm, zi::StepOne& a)
+// A call on one tensor, as launch_step_one takes it: false if it is another call, or one on more quads than StepOne counts.
+inline bool one_tensor(const zi_tensor* t, int32_t n_tensors, const zi::StepConsts& c, bool l2,
+                       const zi_norm_result* d_norm, zi::StepOne& a)
 {
     const zi_tensor* one = nullptr;
     for (int32_t i = 0; i < n_tensors; ++i) {
@@ -170,24 +170,17 @@ inline bool one_short_tensor(const zi_tensor* t, int32_t n_tensors, const zi::St
         if (one) return false;
         one = &t[i];
     }
-    if (!one || one->numel > zi::kStepShortTiles * zi::kStepTileElems) return false;
+    if (!one || one->numel > (int64_t)(zi::kFineMostTiles - 1) * zi::kStepTileElems) return false;
     const int64_t h = choose_head(one->p, one->m, one->v, one->g, one->p_lp), head = h < one->numel ? h : one->numel;
     a.p_body = (float*)one->p + head;
     a.m_body = (float*)one->m + head;
     a.v_body = (float*)one->v + head;
     a.g_body = (const uint16_t*)one->g + head;
     a.lp_body = one->p_lp ? (uint16_t*)one->p_lp + head : nullptr;
-    a.d_norm = d_norm;
-    a.inv_loss_scale = c.inv_loss_scale;
     a.nquad = (uint32_t)((one->numel - head) / zi::kQuad);
     a.head = (uint8_t)head;
     a.tail = (uint8_t)(one->numel - head - (int64_t)a.nquad * zi::kQuad);
-    a.scale_is_pow2 = (uint8_t)c.scale_is_pow2;
-    a.max_norm_is_pow2 = (uint8_t)c.max_norm_is_pow2;
-    a.beta1 = c.beta1; a.beta2 = c.beta2; a.omb1 = c.omb1; a.omb2 = c.omb2;
-    a.eps = c.eps; a.step_size = c.step_size; a.inv_sqrt_bc2 = c.inv_sqrt_bc2;
-    a.decay = l2 ? c.weight_decay : c.decay;
-    a.loss_scale = c.loss_scale; a.max_grad_norm = c.max_grad_norm; a.host_gscale = c.host_gscale;
+    set_scalars(a, c, l2, d_norm);
     return true;
 }
 

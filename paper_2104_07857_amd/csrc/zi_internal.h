@@ -18,35 +18,6 @@ constexpr int kStepUnroll = 2;       // quads per thread per tile
 constexpr int kStepTileQuads = kStepThreads * kStepUnroll;
 constexpr int64_t kStepTileElems = (int64_t)kStepTileQuads * kQuad;   // 512 elements per tile
 constexpr int kMaxStepDesc = 32;     // tensors (or segments) per fused-step launch
-// Dynamic LDS requested (never touched) by the fused step caps its residency: single-wavefront workgroups per compute
-// unit.  On this 1:1 read/write stream few, short-lived wavefronts measured 4-8% faster than full occupancy, but how
-// few depends on the launch.  Up to kStepShortTiles or kListShortTiles tiles what counts is how few rounds of resident
-// workgroups it takes; in launches of more than kStepLongTiles bunching begins to cost, above all in adamw_list_kernel, whose
-// wavefronts arrive at their loads later.  (The longest tensors by themselves: no difference beyond the placement's.)
-// Step alone in us, averages over six placements of the arrays (short ones: of a captured row of calls),
-// workgroups per compute unit:
-//                                             16      8      7      6
-//   one tensor       1.0e6                    4.4    4.8           6.1
-//                    2.1e6                   10.1   10.6          11.6
-//                    4.2e6                   20.3   20.6          21.6
-//                    8.4e6                   40.8   39.6          40.8
-//                    2.5e7                   113    112    112    113
-//                    3.0e8                          1313   1313   1331
-//                    1.3e9                          5847   5853   5905
-//                    (allocated one after another   5855   5800   5787)
-//   flat list        200 of 1..40,000        20.0   20.6          21.9
-//                    300 of 1.0e5                   145    147    154
-//                    1000 of 3.0e5                  1361   1363   1397
-//   other list       64 of 6e5 a launch             268    269    275
-//                    64 of 1.3e6                    587    583    591
-//                    64 of 2e6                      923    919    928
-//                    64 of 4.2e6                    1418   1400   1388
-//                    64 of 2e7                      6495   6415   6389
-//                    (without a copy, 16 against 8: 4.0e6 17.96 / 17.73, 6.2e6 26.7 / 26.2)
-constexpr uint32_t kStepShortTiles = 3u << 11;     // 3.1e6 elements, of one tensor
-constexpr uint32_t kListShortTiles = 3u << 12;     // 6.3e6 elements, of several
-constexpr uint32_t kStepLongTiles = 1u << 18;      // 1.3e8 elements
-constexpr unsigned kStepLds16 = 10 * 1024, kStepLds8 = 20 * 1024, kStepLds7 = 22 * 1024 + 512, kStepLds6 = 26 * 1024;
 // Workgroup ids are dealt round-robin to the 8 XCDs.  Tiles are renumbered so that, inside every run
 // of 8 * kStepXcdRun tiles, each XCD owns kStepXcdRun consecutive tiles (256 KiB of each fp32 array)
 // instead of every eighth one: measured +4% on top of the residency cap.
@@ -55,6 +26,56 @@ constexpr int kXcds = 8;
 #define ZI_STEP_XCD_RUN 128
 #endif
 constexpr int64_t kStepXcdRun = ZI_STEP_XCD_RUN;
+
+// Dynamic LDS requested (never touched) by the fused step caps its residency, in single-wavefront workgroups per compute unit:
+// on this 1:1 read/write stream few, short-lived wavefronts are faster than full occupancy.
+constexpr unsigned kStepLds20 = 8 * 1024, kStepLds16 = 10 * 1024, kStepLds14 = 11 * 1024, kStepLds12 = 13 * 1024, kStepLds7 = 22 * 1024 + 512;
+// Half a tile, one quad a lane (adamw_fine_kernel, adamw_fine_list_kernel): twice as many wavefronts with half as many loads
+// each, which live less than half as long, so that requests are spread more evenly over time and a launch's last round is shorter.
+// Which kernel a launch takes follows from its tiles.  Up to kFineShortTiles all of its fine workgroups are resident at once;
+// from there to kOneRoundTiles only those of whole tiles are; beyond, fine ones again.  One tensor's runs of kFineXcdRun
+// fine tiles go to one XCD each in launches of up to kFineRunTiles; longer ones, and lists, are dealt out as they come: then all
+// eight XCDs walk the same few MiB of every array, and it matters little how the arrays lie to each other.
+// Step alone in us, whole / fine tiles (range over one to four placements of the arrays each), one tensor:
+//   2.0e5 3.1 / 2.7   5.0e5 4.2 / 3.7   8.0e5 5.9 / 5.3   1.0e6 6.2 / 6.5   1.3e6 7.7 / 8.1   3.0e6 16.4 / 15.7   4.1e6 21.6 / 20.5
+//   8.4e6 40.1 / 38.5   2.5e7 112..114 / 109..111   6.0e7 269..272 / 258..261   1.0e8 442..459 / 427..431
+//   3.0e8 1312..1367 / 1282..1301   1.3e9 5759..6118 / 5529..5728
+//   (in runs 1.2e7 53.9..54.1, 2.5e7 110..112, 3.0e8 1342..1378, 1.3e9 5745..5918; in none 8.4e6 38.6..42, 1.2e7 54.0..54.9)
+// and lists: 60 tensors of up to 30,000 elements 8.7 / 8.1, 250 of 100,000 65.6 / 61, 300 of 200,000 147..153 / 141, 256 of 3e5
+// 342 / 336, a decoder's tensors at hidden size 1024, 6 layers 350 / 331, at 2048 1370..1395 / 1293..1304, 64 of 1.3e6 380 / 367,
+// 64 of 2e7 6104..6178 / 5623..5689.
+// Resident workgroups per compute unit (fine_lds): what counts is how many have loads in flight at a time.  Without a copy to write
+// they live shorter, and in front of their loads they wait for the norm result, if there is one, and in lists for the lookup.  us by
+// workgroups 11 / 12 / 13 / 14 / 16 / 20: one tensor of 3.0e8 1301 / 1284 / 1287 / 1288 / 1318 / 1338, without copies 1266 / 1236 / 1203 / 1185 /
+// 1197 / 1220, without norm and copies 1173 / 1173 / 1185 / 1194 / 1207 / 1216; a list of 3.0e8 1361 / 1325 / 1312 / 1305 / 1342 / 1366, without copies
+// 1415 / 1348 / 1301 / 1226 / 1213 / 1240, without norm and copies 1325 / 1282 / 1245 / 1204 / 1223 / 1257; 2.5e7 as a list 116 / 115 / 114 / 114 /
+// 113 / 115; flat lists of 4.0e6 23.6 / 23.1 / 22.9 / 22.6 / 21.9 / 21.7, of 3.0e7 149 / 145 / 145 / 141 / 141 / 139.
+constexpr int kFineTileQuads = kStepThreads;
+constexpr int64_t kFineXcdRun = 1024;
+constexpr uint32_t kFineShortTiles = 7u << 8;      // 9.2e5 elements
+constexpr uint32_t kOneRoundTiles = 1u << 12;      // 2.1e6 elements: 16 workgroups on every compute unit
+constexpr uint32_t kFineRunTiles = 1u << 15;       // 1.7e7 elements
+constexpr uint32_t kFineListTiles = 1u << 16;      // 3.4e7 elements
+constexpr uint32_t kFineMostTiles = 1u << 25;      // 1.7e10 elements: a launch has less than 2^32 lanes
+// Without copies, middling launches of lists stay with whole tiles.  Step alone in us, whole / fine, any lists: 1.3e7 55.1 / 55.4 and 54.2 / 53.8,
+// 2.5e7 103.6 / 107.6 and 104.0 / 104.3, 5.0e7 205.3 / 204.6 and 205.3 / 202.2, 7.6e7 308 / 304, 3.0e8 1262 / 1206; flat ones: 4.0e6 20.9 / 20.5,
+// 3.0e7 134 / 130, 7.7e7 315 / 321 and 314 / 318.
+constexpr uint32_t kBareListTiles = 1u << 15, kBareListMostTiles = 3u << 15;       // 1.7e7 to 5.0e7 elements; flat ones from kFineListTiles
+enum class Steps { kOne, kList, kFlat };
+inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies)
+{
+    if (kind == Steps::kList && !copies && n_tiles > kBareListTiles && n_tiles <= kBareListMostTiles) return false;
+    if (kind == Steps::kFlat && !copies && n_tiles > kFineListTiles) return false;
+    return n_tiles <= kFineShortTiles || (n_tiles > kOneRoundTiles && n_tiles < kFineMostTiles);
+}
+inline unsigned fine_lds(uint32_t n_tiles, Steps kind, bool copies, bool norm)
+{
+    const bool waits = norm && !copies;
+    if (kind == Steps::kOne) return n_tiles <= kFineRunTiles ? kStepLds16 : waits ? kStepLds14 : kStepLds12;
+    if (n_tiles <= kFineListTiles) return kind == Steps::kFlat ? kStepLds20 : kStepLds16;
+    return waits ? kStepLds16 : kStepLds14;
+}
+inline unsigned whole_tiles_lds(uint32_t n_tiles) { return n_tiles <= kOneRoundTiles ? kStepLds16 : kStepLds7; }
 
 // A tile of the reduction is 16,384 elements, one round of loads for a workgroup.  Gradients that are to stay in the
 // memory-side cache (kNormKeepElems) are read by 512 threads with four vectors each, longer lists by 256 with eight: in
@@ -131,7 +152,7 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
-// One short tensor (adamw_short_kernel), in few bytes: a call on it takes the host longer than the GPU, and what the runtime takes
+// One tensor (adamw_short_kernel, adamw_fine_kernel), in few bytes: a call on a short one takes the host longer than the GPU, and what the runtime takes
 // for a launch depends on the size of its arguments.  Issue of an empty kernel in us (the runtime runs in one of two modes for
 // the life of a process): up to 112 bytes 2.4 or 2.8, 120 to 1024 bytes 2.5 or 3.5 to 3.7, StepArgs' 2.5 KB 2.55 or 3.75, 3.6 KB and
 // more 2.55 or 3.8 to 4.1.
@@ -150,6 +171,17 @@ struct StepOne {
     float loss_scale, max_grad_norm, host_gscale;
 };
 static_assert(sizeof(StepOne) <= 112, "kernel arguments");
+inline void set_scalars(StepOne& a, const StepConsts& c, bool l2, const zi_norm_result* d_norm)
+{
+    a.d_norm = d_norm;
+    a.inv_loss_scale = c.inv_loss_scale;
+    a.scale_is_pow2 = (uint8_t)c.scale_is_pow2;
+    a.max_norm_is_pow2 = (uint8_t)c.max_norm_is_pow2;
+    a.beta1 = c.beta1; a.beta2 = c.beta2; a.omb1 = c.omb1; a.omb2 = c.omb2;
+    a.eps = c.eps; a.step_size = c.step_size; a.inv_sqrt_bc2 = c.inv_sqrt_bc2;
+    a.decay = l2 ? c.weight_decay : c.decay;
+    a.loss_scale = c.loss_scale; a.max_grad_norm = c.max_grad_norm; a.host_gscale = c.host_gscale;
+}
 
 // Launches over many tensors (adamw_list_kernel), which a workgroup looks up in groups.  A list whose tensors are
 // views at the same places of five flat buffers, as the partitions of a sharded optimizer are, needs one place per
@@ -301,7 +333,7 @@ static_assert(sizeof(NormOne) <= 112, "kernel arguments");
 // Launchers (zi_kernels.hip).  Each returns the hipError_t of the launch.
 // any_order: may run beside the launches in front of it on the stream (see StepIssuer for where that is safe).
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
-hipError_t launch_step_short(const StepOne& a, int dt, bool l2, hipStream_t s);
+hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_few(const FlatFew& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s);
 hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);
 hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s);

@@ -14,6 +14,8 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "zi_internal.h"
 
 namespace zi {
@@ -260,16 +262,17 @@ __device__ __forceinline__ u32x2 step_quad(f32x4& p, f32x4& m, f32x4& v, const u
 
 // XCD-aware renumbering.  Workgroup ids of the launch go round-robin to the XCDs, so the runs are
 // counted in launch-wide ids (a tensor that does not start on a run boundary keeps the XCD <->
-// contiguous-tiles correspondence); it is a bijection on every run of 8 * kStepXcdRun workgroups
+// contiguous-tiles correspondence); it is a bijection on every run of 8 * RUN workgroups
 // that lies inside one tensor, and the workgroups of incomplete runs keep their tiles.
+template <int64_t RUN = kStepXcdRun>
 __device__ __forceinline__ uint32_t tile_of_block(uint32_t block, uint32_t first_tile, uint32_t n_tiles)
 {
-    constexpr uint32_t run = kXcds * kStepXcdRun;
+    constexpr uint32_t run = kXcds * RUN;
     const uint32_t r = block % run;
     const uint32_t base = block - r;
     uint32_t nb = block;
     if (base >= first_tile && n_tiles >= run && base - first_tile <= n_tiles - run)
-        nb = base + (r % kXcds) * (uint32_t)kStepXcdRun + r / kXcds;
+        nb = base + (r % kXcds) * (uint32_t)RUN + r / kXcds;
     return nb - first_tile;
 }
 
@@ -328,6 +331,48 @@ __device__ __forceinline__ void step_tile(GlobalF4 __restrict__ p4, GlobalF4 __r
     }
 }
 
+// Half a tile, one quad a lane (kFineTileQuads), and with a tensor's first the elements outside the body.  Those are loaded in
+// front of the quads and updated behind them, so that a first tile makes one round trip to memory like any other.
+template <int DT, bool L2>
+__device__ __forceinline__ void step_fine_tile(GlobalF4 __restrict__ p4, GlobalF4 __restrict__ m4, GlobalF4 __restrict__ v4,
+                                               GlobalConstU2 __restrict__ g2, GlobalU2 __restrict__ lp2, uint32_t head,
+                                               uint32_t tail, uint32_t ti, uint32_t nquad, float gscale, const StepConsts& c)
+{
+    const uint32_t lane = threadIdx.x;
+    ZI_GLOBAL float *p1 = (ZI_GLOBAL float*)p4, *m1 = (ZI_GLOBAL float*)m4, *v1 = (ZI_GLOBAL float*)v4;
+    const ZI_GLOBAL uint16_t* g1 = (const ZI_GLOBAL uint16_t*)g2;
+    ZI_GLOBAL uint16_t* lp1 = (ZI_GLOBAL uint16_t*)lp2;
+    // element of the head or the tail by number (66 at most)
+    const auto outside = [=](uint32_t k) { return k < head ? (int64_t)k - head : (int64_t)nquad * kQuad + (k - head); };
+    const uint32_t n_outside = ti == 0 ? head + tail : 0;
+    const int64_t e = outside(lane);
+    float pe = 0.0f, me = 0.0f, ve = 0.0f;
+    uint32_t ge = 0;
+    if (n_outside > 0 && lane < n_outside) { ge = g1[e]; pe = p1[e]; me = m1[e]; ve = v1[e]; }
+
+    const uint64_t q0 = (uint64_t)ti * kFineTileQuads;
+    if (q0 + lane < nquad) {
+        const u32x2 g = load_stream_any(g2 + q0 + lane);
+        f32x4 p = load_stream_any(p4 + q0 + lane), m = load_stream_any(m4 + q0 + lane), v = load_stream_any(v4 + q0 + lane);
+        const u32x2 lp = step_quad<DT, L2>(p, m, v, g, gscale, c);
+        store_stream_any(p4 + q0 + lane, p);
+        store_stream_any(m4 + q0 + lane, m);
+        store_stream_any(v4 + q0 + lane, v);
+        if (lp2) store_stream_any(lp2 + q0 + lane, lp);
+    }
+    if (n_outside > 0) {
+        for (uint32_t k = lane; k < n_outside; k += kStepThreads) {
+            const int64_t i = outside(k);
+            if (k >= kStepThreads) { ge = g1[i]; pe = p1[i]; me = m1[i]; ve = v1[i]; }
+            adamw_element<L2>(pe, me, ve, widen16<DT>(ge), gscale, c);
+            p1[i] = pe;
+            m1[i] = me;
+            v1[i] = ve;
+            if (lp1) lp1[i] = (uint16_t)narrow16<DT>(pe);
+        }
+    }
+}
+
 // One workgroup = one tile of kStepTileElems elements of one tensor.  blockIdx.x counts tiles over
 // all tensors of the launch; first_tile locates the tensor.
 // SINGLE: the launch covers one tensor (every long tensor gets such a launch: a workgroup lives for a few
@@ -376,10 +421,9 @@ void adamw_wide_kernel(const StepArgs a)
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, a.c);
 }
 
-// Up to kStepShortTiles tiles of one tensor: the same from arguments that are quickly written (StepOne).
-template <int DT, bool L2>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
-void adamw_short_kernel(const StepOne a)
+// One tensor, from arguments that are quickly written (StepOne).  FINE: one quad a lane instead of two.
+template <int DT, bool L2, bool FINE>
+__device__ __forceinline__ void step_one(const StepOne& a)
 {
     const StepConsts c = {a.beta1, a.beta2, a.omb1, a.omb2, a.eps, a.step_size, a.inv_sqrt_bc2, L2 ? 0.0f : a.decay,
                           a.decay, a.loss_scale, a.max_grad_norm, a.host_gscale, a.scale_is_pow2, a.max_norm_is_pow2,
@@ -393,10 +437,25 @@ void adamw_short_kernel(const StepOne a)
     asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
     float gscale;
     if (!step_prologue(a.d_norm, c, gscale)) return;
-    const uint32_t tile = tile_of_block(blockIdx.x, 0, (nquad + kStepTileQuads - 1) / kStepTileQuads);
-    if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
-    step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
+    constexpr uint32_t tile_quads = FINE ? kFineTileQuads : kStepTileQuads;
+    const uint32_t n_tiles = nquad / tile_quads + (nquad % tile_quads ? 1 : 0);
+    const uint32_t tile = !FINE                                                           ? tile_of_block(blockIdx.x, 0, n_tiles)
+                          : n_tiles <= kFineRunTiles * (kStepTileQuads / kFineTileQuads) ? tile_of_block<kFineXcdRun>(blockIdx.x, 0, n_tiles)
+                                                                                          : blockIdx.x;
+    if constexpr (FINE) {
+        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, gscale, c);
+    } else {
+        if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
+        step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
+    }
 }
+template <int DT, bool L2>
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
+void adamw_short_kernel(const StepOne a) { step_one<DT, L2, false>(a); }
+// Bound: HBM, 28 bytes an element (26 without a copy); short ones: the latency of one round trip.  6.3 to 6.5 TB/s from 3e8 elements on, where
+// whole tiles reach 5.9 to 6.3, by the arrays' places (zi_internal.h, kFineTileQuads).
+template <int DT, bool L2>
+__global__ __launch_bounds__(kStepThreads) void adamw_fine_kernel(const StepOne a) { step_one<DT, L2, true>(a); }
 
 // n += block >= start; first = the start, if so.  Three scalar instructions; the compiler goes through a
 // vector register.
@@ -439,11 +498,11 @@ __device__ __forceinline__ int64_t tail_of(const FlatList<GROUPS>& a, uint32_t d
 // a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
 // 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,
 // 200 of 1..40,000 45.6 -> 35.3, as FlatArgs 25.3; with the norm result fetched after the descriptor 1478 instead of 1366.
-template <int DT, bool L2, typename Args>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
-void adamw_list_kernel(const Args a)
+template <int DT, bool L2, bool FINE, typename Args>
+__device__ __forceinline__ void step_list(const Args& a)
 {
-    const uint32_t block = blockIdx.x;
+    constexpr uint32_t kParts = FINE ? kStepTileQuads / kFineTileQuads : 1;     // workgroups to a tile
+    const uint32_t block = blockIdx.x / kParts;
     const zi_norm_result* d_norm = a.d_norm;
     StepConsts c = a.c;
     // (what the judgement below needs arrives with the first batch of arguments, not where it is used)
@@ -481,23 +540,115 @@ void adamw_list_kernel(const Args a)
     asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
     if (d_norm && raw[4]) return;
 
-    const uint32_t tile = tile_of_block(block, first, (nquad + kStepTileQuads - 1) / kStepTileQuads);
-    if (tile == 0) step_ends<DT, L2>(T, head_of(a, d), (int64_t)nquad * kQuad, tail_of(a, d), gscale, c);
-    step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
+    const uint32_t tile = FINE ? blockIdx.x - first * kParts
+                               : tile_of_block(block, first, (nquad + kStepTileQuads - 1) / kStepTileQuads);
+    if constexpr (FINE) {
+        uint32_t head = 0, tail = 0;
+        if (tile == 0) head = (uint32_t)head_of(a, d), tail = (uint32_t)tail_of(a, d);
+        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, gscale, c);
+    } else {
+        if (tile == 0) step_ends<DT, L2>(T, head_of(a, d), (int64_t)nquad * kQuad, tail_of(a, d), gscale, c);
+        step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
+    }
+}
+template <int DT, bool L2, typename Args>
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
+void adamw_list_kernel(const Args a) { step_list<DT, L2, false>(a); }
+// (a tile's halves are neighbouring workgroups, so the tables of starts count whole tiles for both kernels)
+template <int DT, bool L2, typename Args>
+__global__ __launch_bounds__(kStepThreads) void adamw_fine_list_kernel(const Args a) { step_list<DT, L2, true>(a); }
+
+hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hipStream_t s)
+{
+    const dim3 block(kStepThreads);
+    const uint32_t n_tiles = a.nquad / kStepTileQuads + (a.nquad % kStepTileQuads ? 1 : 0);
+    const uint32_t n_fine = a.nquad / kFineTileQuads + (a.nquad % kFineTileQuads ? 1 : 0);
+    const bool fine = fine_tiles(n_tiles, Steps::kOne, a.lp_body);
+    const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : n_tiles);
+    const unsigned lds = fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
+#define ZI_LAUNCH_ONE(DT, L2) do { \
+        if (!fine)          hipLaunchKernelGGL((adamw_short_kernel<DT, L2>), grid, block, lds, s, a); \
+        else if (any_order) hipExtLaunchKernelGGL((adamw_fine_kernel<DT, L2>), grid, block, lds, s, nullptr, nullptr, hipExtAnyOrderLaunch, a); \
+        else                hipLaunchKernelGGL((adamw_fine_kernel<DT, L2>), grid, block, lds, s, a); \
+    } while (0)
+    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_ONE(ZI_BF16, true); else ZI_LAUNCH_ONE(ZI_BF16, false); }
+    else               { if (l2) ZI_LAUNCH_ONE(ZI_FP16, true); else ZI_LAUNCH_ONE(ZI_FP16, false); }
+#undef ZI_LAUNCH_ONE
+    return hipGetLastError();
 }
 
-static unsigned step_lds(uint32_t n_tiles, uint32_t short_tiles, unsigned middling, unsigned longer)
+static bool has_copies(const ListArgs& a) { return a.t[0].lp_body; }
+template <int GROUPS>
+static bool has_copies(const FlatList<GROUPS>& a) { return a.lp; }
+
+template <typename Args>
+static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
-    return n_tiles <= short_tiles ? kStepLds16 : n_tiles <= kStepLongTiles ? middling : longer;
+    if (n_tiles == 0) return hipSuccess;
+    const Steps kind = std::is_same_v<Args, ListArgs> ? Steps::kList : Steps::kFlat;
+    const bool fine = fine_tiles(n_tiles, kind, has_copies(a));
+    const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
+    const unsigned lds = fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
+    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
+#define ZI_LAUNCH_LIST(DT, L2) do { \
+        if (fine) hipExtLaunchKernelGGL((adamw_fine_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
+        else      hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
+    } while (0)
+    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LIST(ZI_BF16, true); else ZI_LAUNCH_LIST(ZI_BF16, false); }
+    else               { if (l2) ZI_LAUNCH_LIST(ZI_FP16, true); else ZI_LAUNCH_LIST(ZI_FP16, false); }
+#undef ZI_LAUNCH_LIST
+    return hipGetLastError();
+}
+hipError_t launch_step_few(const FlatFew& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s)
+{
+    return launch_list_of(a, n_tiles, dt, l2, false, s);
+}
+hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
+{
+    return launch_list_of(a, n_tiles, dt, l2, any_order, s);
+}
+hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
+{
+    return launch_list_of(a, n_tiles, dt, l2, any_order, s);
+}
+
+// The same launch, whose tensors have less than 2^32 quads, as the kernels of fine tiles take it.
+static StepOne one_of(const StepArgs& a, bool l2)
+{
+    const StepDesc& d = a.t[0];
+    StepOne o;
+    o.p_body = d.p_body; o.m_body = d.m_body; o.v_body = d.v_body; o.g_body = d.g_body; o.lp_body = d.lp_body;
+    o.nquad = (uint32_t)d.nquad;
+    o.head = (uint8_t)d.head;
+    o.tail = (uint8_t)(d.numel - d.head - d.nquad * kQuad);
+    set_scalars(o, a.c, l2, a.d_norm);
+    return o;
+}
+static ListArgs list_of(const StepArgs& a)
+{
+    static_assert(kMaxStepDesc <= kMaxListDesc, "a launch stays one launch");
+    ListArgs l;
+    for (int i = 0; i < a.n_desc; ++i) {
+        const StepDesc& d = a.t[i];
+        l.t[i] = {d.p_body, d.m_body, d.v_body, d.g_body, d.lp_body, (uint32_t)d.nquad, (uint16_t)d.head,
+                  (uint16_t)(d.numel - d.head - d.nquad * kQuad)};
+    }
+    for (int i = 0; i < ListArgs::kMax; ++i) l.first_tile[i] = i < a.n_desc ? a.first_tile[i] : 0xFFFFFFFFu;
+    for (int i = 0; i < ListArgs::kGroups; ++i) l.group_start[i] = l.first_tile[i * ListArgs::kGroup];
+    l.c = a.c;
+    l.d_norm = a.d_norm;
+    return l;
 }
 
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
-    const dim3 grid(n_tiles), block(kStepThreads);
     const bool single = a.n_desc == 1;
+    if (fine_tiles(n_tiles, single ? Steps::kOne : Steps::kList, a.t[0].lp_body))
+        return single ? launch_step_one(one_of(a, l2), dt, l2, any_order, s) : launch_step_list(list_of(a), n_tiles, dt, l2, any_order, s);
+    const dim3 grid(n_tiles), block(kStepThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-    const unsigned lds = step_lds(n_tiles, single ? kStepShortTiles : kListShortTiles, kStepLds8, kStepLds7);
+    const unsigned lds = whole_tiles_lds(n_tiles);
 #define ZI_LAUNCH_STEP(DT, L2, SINGLE) \
     hipExtLaunchKernelGGL((adamw_wide_kernel<DT, L2, SINGLE>), grid, block, lds, s, nullptr, nullptr, flags, a)
     if (dt == ZI_BF16) {
@@ -509,43 +660,6 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
     }
 #undef ZI_LAUNCH_STEP
     return hipGetLastError();
-}
-
-hipError_t launch_step_short(const StepOne& a, int dt, bool l2, hipStream_t s)
-{
-    const uint32_t n_tiles = (a.nquad + kStepTileQuads - 1) / kStepTileQuads;
-    const dim3 grid(n_tiles < 1 ? 1 : n_tiles), block(kStepThreads);
-#define ZI_LAUNCH_SHORT(DT, L2) hipLaunchKernelGGL((adamw_short_kernel<DT, L2>), grid, block, kStepLds16, s, a)
-    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_SHORT(ZI_BF16, true); else ZI_LAUNCH_SHORT(ZI_BF16, false); }
-    else               { if (l2) ZI_LAUNCH_SHORT(ZI_FP16, true); else ZI_LAUNCH_SHORT(ZI_FP16, false); }
-#undef ZI_LAUNCH_SHORT
-    return hipGetLastError();
-}
-
-template <typename Args>
-static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, unsigned lds, int dt, bool l2, bool any_order, hipStream_t s)
-{
-    if (n_tiles == 0) return hipSuccess;
-    const dim3 grid(n_tiles), block(kStepThreads);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-#define ZI_LAUNCH_LIST(DT, L2) \
-    hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a)
-    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LIST(ZI_BF16, true); else ZI_LAUNCH_LIST(ZI_BF16, false); }
-    else               { if (l2) ZI_LAUNCH_LIST(ZI_FP16, true); else ZI_LAUNCH_LIST(ZI_FP16, false); }
-#undef ZI_LAUNCH_LIST
-    return hipGetLastError();
-}
-hipError_t launch_step_few(const FlatFew& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s)
-{
-    return launch_list_of(a, n_tiles, kStepLds16, dt, l2, false, s);
-}
-hipError_t launch_step_list(const ListArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
-{
-    return launch_list_of(a, n_tiles, step_lds(n_tiles, kListShortTiles, kStepLds7, kStepLds6), dt, l2, any_order, s);
-}
-hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
-{
-    return launch_list_of(a, n_tiles, step_lds(n_tiles, kListShortTiles, kStepLds8, kStepLds8), dt, l2, any_order, s);
 }
 
 // The descriptor that holds tile t of a launch, at or after entry d, by halving: a walk from entry to entry
