@@ -890,10 +890,33 @@ __device__ __forceinline__ void sumsq_vec(const u32x4 g, double& acc0, double& a
     sumsq_word<DT>(g.w, acc0, acc1);
 }
 
+// The sum over a wavefront's 64 lanes, in every lane: pairs 32 lanes apart first, then 16, 8, 4, 2 and 1.  Halves and quarters change places
+// by permlane swaps; inside a row of 16, whose lanes then repeat with the last distance, a rotation gives every lane its partner's value.
+// (Six dependent exchanges through LDS, as shuffles are, take 0.3 us, and a reduction makes two of these sums one after the other.)
+template <int ROW_ROTATION>
+__device__ __forceinline__ double rotated(double x)
+{
+    constexpr int kRowRor = 0x120;
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t low = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, kRowRor + ROW_ROTATION, 0xF, 0xF, true);
+    const uint32_t high = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), kRowRor + ROW_ROTATION, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, (uint64_t)high << 32 | low);
+}
 __device__ __forceinline__ double wave_sum(double x)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    const auto both = [](auto low, auto high) {
+        return __builtin_bit_cast(double, (uint64_t)high[0] << 32 | low[0]) + __builtin_bit_cast(double, (uint64_t)high[1] << 32 | low[1]);
+    };
+    uint64_t b = __builtin_bit_cast(uint64_t, x);
+    x = both(__builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false),
+             __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false));
+    b = __builtin_bit_cast(uint64_t, x);
+    x = both(__builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false),
+             __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false));
+    x += rotated<8>(x);
+    x += rotated<4>(x);
+    x += rotated<2>(x);
+    x += rotated<1>(x);
     return x;
 }
 
