@@ -59,7 +59,7 @@ extern "C" zi_status zi_grad_norm(const zi_tensor* t, int32_t n_tensors, zi_lp_d
     }
 
     NormIssuer issue((zi::NormPartial*)d_workspace, (int)dt, loss_scale, d_out, (hipStream_t)hip_stream);
-    issue.keep = total <= zi::kNormKeepElems;
+    issue.expect(total, n_tensors);
     for (int32_t i = 0; i < n_tensors; ++i) ZI_HIP(issue.add((const uint16_t*)t[i].g, t[i].numel));
     ZI_HIP(issue.finish());   // also writes zeros for an empty list
     return ZI_OK;
@@ -126,7 +126,7 @@ extern "C" zi_status zi_grad_norm_noalloc(const zi_tensor* t, int32_t n_tensors,
                     ZI_NOALLOC_MAX_PARTIALS);
 
     NormIssuer issue(partials, (int)dt, loss_scale, d_out, (hipStream_t)hip_stream);
-    issue.keep = total <= zi::kNormKeepElems;
+    issue.expect(total, n_tensors);
     for (int32_t i = 0; i < n_tensors; ++i) ZI_HIP(issue.add((const uint16_t*)t[i].g, t[i].numel));
     ZI_HIP(issue.finish());
     return ZI_OK;

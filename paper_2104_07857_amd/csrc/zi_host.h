@@ -640,6 +640,7 @@ struct NormIssuer {
     uint32_t groups = zi::kNormGroups;   // workgroups of a launch, at most
     uint32_t used = 0;                   // partials written since the last finalize
     bool keep = false;                   // see kNormKeepElems
+    int64_t tile = zi::kNormTileElems;   // elements of a tile: all launches' (see kNormShortElems)
     int launches = 0;                    // kernels so far
     int finalized = 0;
     int dt;
@@ -652,11 +653,17 @@ struct NormIssuer {
     {
         a.n_tiles = 0;
     }
-    static int64_t tiles_for(const uint16_t* g, int64_t n)
+    // What the list will be, before the first add(): gradients in device memory, `total` elements.
+    void expect(int64_t total, int64_t n_tensors)
+    {
+        keep = total <= zi::kNormKeepElems;
+        if (total > zi::kNormTileElems && total <= zi::kNormShortElems && n_tensors <= zi::NormArgs::kMax) tile = zi::kNormShortVecs * zi::kVec;
+    }
+    static int64_t tiles_for(const uint16_t* g, int64_t n, int64_t tile = zi::kNormTileElems)
     {
         const int64_t lead = (int64_t)(-(reinterpret_cast<uintptr_t>(g) / 2) % zi::kVec);
         const int64_t body = n > lead ? (n - lead) / zi::kVec * zi::kVec : 0;
-        const int64_t nt = (body + zi::kNormTileElems - 1) / zi::kNormTileElems;
+        const int64_t nt = (body + tile - 1) / tile;
         return nt < 1 ? 1 : nt;              // the first tile also owns the unaligned ends
     }
     template <typename Args>
@@ -684,9 +691,11 @@ struct NormIssuer {
         a.accumulate = finalized;
         a.n_groups = blocks;
         a.n_before = final ? used : 0;
+        const bool is_short = tile != zi::kNormTileElems;
         if (final && n_desc == 1 && used == 0) {
-            e = zi::launch_norm_one({g0, a.partials, a.out, n0, a.n_tiles, blocks, a.mark_low, a.mark_high, a.patience,
-                                     loss_scale, a.accumulate}, dt, keep, s);
+            const zi::NormOne one = {g0, a.partials, a.out, n0, a.n_tiles, blocks, a.mark_low, a.mark_high, a.patience,
+                                     loss_scale, a.accumulate};
+            e = is_short ? zi::launch_norm_short(one, dt, s) : zi::launch_norm_one(one, dt, keep, s);
         } else if (final && keep && n_desc <= zi::NormFew::kMax && used == 0) {
             zi::NormFew few;
             for (int32_t i = 0; i < n_desc; ++i) {
@@ -698,13 +707,13 @@ struct NormIssuer {
             few.mark_low = a.mark_low; few.mark_high = a.mark_high; few.patience = a.patience;
             few.loss_scale = a.loss_scale; few.partials = a.partials; few.out = a.out;
             few.n_before = a.n_before; few.accumulate = a.accumulate;
-            e = zi::launch_norm_few(few, dt, s);
+            e = is_short ? zi::launch_norm_short(few, dt, s) : zi::launch_norm_few(few, dt, s);
         } else {
             finish_list(a, n_desc, a.n_tiles);
             // Between two final sums the launches leave partials side by side and may overlap; the first of them and the
-            // one with the final sum are ordinary launches (the same order as in StepIssuer).
+            // one with the final sum are ordinary launches (the same order as in StepIssuer).  (A short list is one launch.)
             const bool any_order = used > 0 && !final && may_overlap(s);
-            e = zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
+            e = is_short ? zi::launch_norm_short(a, dt, s) : zi::launch_norm_partials(a, blocks, dt, keep, any_order, s);
         }
         ++launches;
         used = final ? 0 : used + blocks;
@@ -726,14 +735,14 @@ struct NormIssuer {
         for (; n > 0; g += zi::kNormMaxPiece, n -= zi::kNormMaxPiece) {
             if (n_desc == zi::NormArgs::kMax)
                 if (const hipError_t e = flush_launch(); e != hipSuccess) return e;
-            const int64_t m = n < zi::kNormMaxPiece ? n : zi::kNormMaxPiece, tiles = tiles_for(g, m);
+            const int64_t m = n < zi::kNormMaxPiece ? n : zi::kNormMaxPiece, tiles = tiles_for(g, m, tile);
             const uint64_t address = reinterpret_cast<uintptr_t>(g);
             if (address >> 48) return hipErrorInvalidValue;
             if (n_desc == 0) {
                 g0 = g;
                 n0 = (uint32_t)m;
             }
-            a.where[n_desc] = address | (uint64_t)(tiles * zi::kNormTileElems + zi::kNormTileSlack - m) << 48;
+            a.where[n_desc] = address | (uint64_t)(tiles * tile + zi::kNormTileSlack - m) << 48;
             a.first_tile[n_desc++] = a.n_tiles;
             a.n_tiles += (uint32_t)tiles;
         }

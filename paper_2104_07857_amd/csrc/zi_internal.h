@@ -83,6 +83,13 @@ inline unsigned whole_tiles_lds(uint32_t n_tiles) { return n_tiles <= kOneRoundT
 constexpr int kNormTileVecs = 2048;
 constexpr int kNormKeepThreads = 512, kNormStreamThreads = 256;
 constexpr int64_t kNormTileElems = (int64_t)kNormTileVecs * kVec;   // 16384 elements per workgroup iteration
+// Short lists, of more than one tile and up to kNormShortElems elements, in tiles of one vector a thread (short_sumsq_partial_kernel): four times as many
+// compute units have a share of the loads and of the conversions.  Tiles of 16,384 / 8192 / 4096 elements, 512 threads, us: 1.6e4 2.44 / 2.67 / 2.57,
+// 6.6e4 3.30 / 2.88 / 2.78, 3.0e5 3.08 / 3.50 / 2.92, 6.0e5 3.67 / 3.02 / 2.89, 1.0e6 3.59 / 3.38 / 3.36, 1.5e6 3.25 / 3.38 / 3.70, 2.1e6
+// 3.57 / 3.44 / 3.66, 4.2e6 4.41 / 4.37 / 4.59; 24 tensors with 1.2e5 4.25 / 4.11 / 3.94, 100 with 1.5e5 4.31 / 4.02 / 3.94, 32 with 9.4e5 3.91 / 3.78 /
+// 3.61, 200 with 4.0e6 5.70 / 5.75 / 6.64.  (256 threads 0.1 to 0.3 more, 128 up to 1.)
+constexpr int kNormShortVecs = 512;
+constexpr int64_t kNormShortElems = (int64_t)1 << 20;
 // Workgroups of a partial-sum launch (two per compute unit, 64 KiB of loads in flight in each).  Microseconds
 // for partials and final sum together on 2.5e7 / 3.0e8 / 1.3e9 elements and on a list of 288 tensors with 3.0e8:
 // 512: 12.0 / 91 / 372 / 99, 1024: 11.8 / 92 / 379 / 106, 2048: 11.8 / 92 / 376 / 105, 4096: 11.5 / 94 / 379 / 109;
@@ -296,7 +303,7 @@ template <int GROUPS>
 struct NormList {
     static constexpr int kGroup = 16, kGroups = GROUPS, kMax = kGroup * kGroups;
     // Address of the tensor in the lower 48 bits (the GPU has no others); above, how many elements its length is
-    // short of its tiles * kNormTileElems + kNormTileSlack.
+    // short of its tiles * the elements of a tile + kNormTileSlack.
     uint64_t where[kMax];
     uint32_t first_tile[kMax + 1];  // behind the list: n_tiles, then 0xFFFFFFFF
     uint32_t group_start[kGroups];  // first_tile of every group's first
@@ -344,6 +351,9 @@ hipError_t launch_step_link_flat(const LinkFlatArgs& a, int dt, bool l2, bool an
 hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bool keep, bool any_order, hipStream_t s);
 hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s);
 hipError_t launch_norm_few(const NormFew& a, int dt, hipStream_t s);      // ordinary loads
+hipError_t launch_norm_short(const NormOne& a, int dt, hipStream_t s);    // the same three in tiles of kNormShortVecs
+hipError_t launch_norm_short(const NormFew& a, int dt, hipStream_t s);
+hipError_t launch_norm_short(const NormArgs& a, int dt, hipStream_t s);
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s);
 

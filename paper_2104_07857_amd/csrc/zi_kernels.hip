@@ -943,7 +943,7 @@ struct NormTensor {
     const ZI_GLOBAL uint16_t* g;
     uint32_t numel, first_tile, next_tile;
 };
-template <int GROUPS>
+template <int VECS, int GROUPS>
 __device__ __forceinline__ NormTensor tensor_of_tile(const NormList<GROUPS>& a, uint32_t tile)
 {
     uint32_t group = 0, first = 0;        // the first start is 0, so both counts are at least 1
@@ -956,9 +956,10 @@ __device__ __forceinline__ NormTensor tensor_of_tile(const NormList<GROUPS>& a, 
     const uint64_t where = a.where[d];
     const uint32_t next = a.first_tile[d + 1];
     return {(const ZI_GLOBAL uint16_t*)(uintptr_t)(where << 16 >> 16),
-            (next - first) * (uint32_t)kNormTileElems + kNormTileSlack - (uint32_t)(where >> 48), first, next};
+            (next - first) * (uint32_t)(VECS * kVec) + kNormTileSlack - (uint32_t)(where >> 48), first, next};
 }
-__device__ __forceinline__ NormTensor tensor_of_tile(const NormOne& a, uint32_t) 
+template <int VECS>
+__device__ __forceinline__ NormTensor tensor_of_tile(const NormOne& a, uint32_t)
 {
     return {(const ZI_GLOBAL uint16_t*)(uintptr_t)a.g, a.numel, 0, 0xFFFFFFFFu};
 }
@@ -982,22 +983,22 @@ __device__ __forceinline__ u32x4 load_in_tile(__amdgpu_buffer_rsrc_t tile, uint3
     return __builtin_amdgcn_raw_buffer_load_b128(tile, (int)byte, (int)first, KEEP ? 0 : kStream);
 }
 
-template <int DT, int THREADS, bool KEEP, typename Args>
+template <int DT, int THREADS, int VECS, bool KEEP, typename Args>
 __device__ __forceinline__ double sumsq_tiles(const Args& a, uint32_t first, uint32_t step)
 {
-    constexpr int UNROLL = kNormTileVecs / THREADS;
+    constexpr int UNROLL = VECS / THREADS;
     double acc0 = 0.0, acc1 = 0.0;
     NormTensor T = {nullptr, 0, 0, 0};
     for (uint32_t t = first; t < a.n_tiles; t += step) {
-        if (t >= T.next_tile) T = tensor_of_tile(a, t);
+        if (t >= T.next_tile) T = tensor_of_tile<VECS>(a, t);
         const uint32_t tile = t - T.first_tile;
         const uint32_t lead = (uint32_t)(-((uintptr_t)T.g / 2)) % kVec;
         const uint32_t head = lead < T.numel ? lead : T.numel;
         const uint32_t nvec = (T.numel - head) / kVec;
         const ZI_GLOBAL u32x4* __restrict__ g4 = (const ZI_GLOBAL u32x4*)(T.g + head);
 
-        const uint32_t at = tile * kNormTileVecs, left = at < nvec ? nvec - at : 0;
-        const uint32_t bytes = (left < (uint32_t)kNormTileVecs ? left : (uint32_t)kNormTileVecs) * 16;
+        const uint32_t at = tile * VECS, left = at < nvec ? nvec - at : 0;
+        const uint32_t bytes = (left < (uint32_t)VECS ? left : (uint32_t)VECS) * 16;
         const uintptr_t start = (uintptr_t)(g4 + at);
         const __amdgpu_buffer_rsrc_t here = raw_buffer(start, bytes);
         u32x4 g[UNROLL];
@@ -1058,10 +1059,9 @@ __device__ __forceinline__ void put_norm_result(double sumsq, float loss_scale, 
 // Marks tell this launch's partials from whatever the workspace held.  A launch that may run twice with the same ones, a captured
 // one, must not make the final sum over several workgroups (NormIssuer::finish): norm_finalize_kernel does it there.
 // The order of the sum is that kernel's, and does not depend on scheduling unless the last workgroup does all the work.
-template <int DT, bool KEEP, typename Args>
-__global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const Args a)
+template <int DT, int THREADS, int VECS, bool KEEP, typename Args>
+__device__ __forceinline__ void reduce_list(const Args& a)
 {
-    constexpr int THREADS = KEEP ? kNormKeepThreads : kNormStreamThreads;
     constexpr int kWaves = THREADS / 64, kRounds = kNormGroups / THREADS;
     __shared__ double s_sum[kWaves];
     __shared__ double s_partial[kNormGroups / 64];
@@ -1089,7 +1089,7 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
             }
     }
     for (;;) {
-        double sum = sumsq_tiles<DT, THREADS, KEEP, Args>(a, first, step);
+        double sum = sumsq_tiles<DT, THREADS, VECS, KEEP, Args>(a, first, step);
         if (whole) {
 #pragma unroll
             for (int r = 0; r < kRounds; ++r) sum += before[r];
@@ -1134,6 +1134,18 @@ __global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void 
         step = 1;
         whole = true;
     }
+}
+
+template <int DT, bool KEEP, typename Args>
+__global__ __launch_bounds__(KEEP ? kNormKeepThreads : kNormStreamThreads) void sumsq_partial_kernel(const Args a)
+{
+    reduce_list<DT, KEEP ? kNormKeepThreads : kNormStreamThreads, kNormTileVecs, KEEP>(a);
+}
+
+template <int DT, typename Args>
+__global__ __launch_bounds__(kNormShortVecs) void short_sumsq_partial_kernel(const Args a)
+{
+    reduce_list<DT, kNormShortVecs, kNormShortVecs, true>(a);
 }
 
 constexpr int kFinalThreads = kNormGroups;   // one partial each where one launch made them all
@@ -1198,6 +1210,18 @@ hipError_t launch_norm_few(const NormFew& a, int dt, hipStream_t s)
     else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16, true, NormFew>), grid, block, 0, s, a);
     return hipGetLastError();
 }
+
+template <typename Args>
+static hipError_t launch_short_of(const Args& a, int dt, hipStream_t s)
+{
+    const dim3 grid(a.n_groups), block(kNormShortVecs);
+    if (dt == ZI_BF16) hipLaunchKernelGGL((short_sumsq_partial_kernel<ZI_BF16, Args>), grid, block, 0, s, a);
+    else               hipLaunchKernelGGL((short_sumsq_partial_kernel<ZI_FP16, Args>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+hipError_t launch_norm_short(const NormOne& a, int dt, hipStream_t s) { return launch_short_of(a, dt, s); }
+hipError_t launch_norm_short(const NormFew& a, int dt, hipStream_t s) { return launch_short_of(a, dt, s); }
+hipError_t launch_norm_short(const NormArgs& a, int dt, hipStream_t s) { return launch_short_of(a, dt, s); }
 
 hipError_t launch_norm_finalize(const NormPartial* partials, uint32_t count, float loss_scale, int accumulate,
                                 zi_norm_result* d_out, hipStream_t s)

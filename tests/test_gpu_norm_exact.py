@@ -25,8 +25,8 @@ def gradients(numels, dt, seed, offset):
 
 @pytest.mark.parametrize("dt", [zi.ZI_BF16, zi.ZI_FP16])
 @pytest.mark.parametrize("numels", [[1], [63], [64], [65], [513], [4095], [4096], [4097], [4104, 1], [16_384], [16_385], [70_001],
-                                    [1 << 20], [(1 << 21) + 3], [3_000_001], [8, 4096, 9, 1, 16_384, 77], [1000] * 32, [5000] * 33,
-                                    [20_000] * 100, [7] * 700])
+                                    [1 << 20], [(1 << 20) + 1], [1 << 19, (1 << 19) + 8], [(1 << 21) + 3], [3_000_001], [8, 4096, 9, 1, 16_384, 77], [1000] * 32, [5000] * 33,
+                                    [20_000] * 100, [3270] * 320, [3270] * 321, [7] * 700])
 def test_whole_numbers_sum_exactly(numels, dt):
     for offset in (0, 3):
         flat, tensors, total = gradients(numels, dt, len(numels) + numels[0], offset)
