@@ -61,6 +61,12 @@ constexpr uint32_t kFineMostTiles = 1u << 25;      // 1.7e10 elements: a launch 
 // 2.5e7 103.6 / 107.6 and 104.0 / 104.3, 5.0e7 205.3 / 204.6 and 205.3 / 202.2, 7.6e7 308 / 304, 3.0e8 1262 / 1206; flat ones: 4.0e6 20.9 / 20.5,
 // 3.0e7 134 / 130, 7.7e7 315 / 321 and 314 / 318.
 constexpr uint32_t kBareListTiles = 1u << 15, kBareListMostTiles = 3u << 15;       // 1.7e7 to 5.0e7 elements; flat ones from kFineListTiles
+// Quads that the first fine tile of a body at this address is short of, and the fine tiles of a body.
+__host__ __device__ inline uint32_t fine_shift(uintptr_t p_body) { return (uint32_t)(p_body / 16) % kFineTileQuads; }
+__host__ __device__ inline uint32_t fine_count(uint32_t nquad, uint32_t shift)
+{
+    return (uint32_t)(((uint64_t)nquad + shift + kFineTileQuads - 1) / kFineTileQuads);
+}
 enum class Steps { kOne, kList, kFlat };
 inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies)
 {

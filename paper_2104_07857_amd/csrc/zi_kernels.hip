@@ -333,10 +333,14 @@ __device__ __forceinline__ void step_tile(GlobalF4 __restrict__ p4, GlobalF4 __r
 
 // Half a tile, one quad a lane (kFineTileQuads), and with a tensor's first the elements outside the body.  Those are loaded in
 // front of the quads and updated behind them, so that a first tile makes one round trip to memory like any other.
+// A fine tile ends where p reaches a multiple of 1 KiB (fine_shift), so that neighbouring wavefronts, which are different
+// XCDs', do not share the 256 bytes that one channel has: views five elements into flat buffers, step alone in us, whole tiles / fine from the
+// body's start / so: 1.1e8 elements 498 / 503 / 478, 1.4e8 631 / 636 / 609, 2.4e8 1105 / 1112 / 1072, 3.2e8 1310 / 1376 / 1273.
+// more: the tile takes the quads behind its own too (the last of a list's tensor, where the shift makes one tile more).
 template <int DT, bool L2>
 __device__ __forceinline__ void step_fine_tile(GlobalF4 __restrict__ p4, GlobalF4 __restrict__ m4, GlobalF4 __restrict__ v4,
                                                GlobalConstU2 __restrict__ g2, GlobalU2 __restrict__ lp2, uint32_t head,
-                                               uint32_t tail, uint32_t ti, uint32_t nquad, float gscale, const StepConsts& c)
+                                               uint32_t tail, uint32_t ti, uint32_t nquad, bool more, float gscale, const StepConsts& c)
 {
     const uint32_t lane = threadIdx.x;
     ZI_GLOBAL float *p1 = (ZI_GLOBAL float*)p4, *m1 = (ZI_GLOBAL float*)m4, *v1 = (ZI_GLOBAL float*)v4;
@@ -350,16 +354,21 @@ __device__ __forceinline__ void step_fine_tile(GlobalF4 __restrict__ p4, GlobalF
     uint32_t ge = 0;
     if (n_outside > 0 && lane < n_outside) { ge = g1[e]; pe = p1[e]; me = m1[e]; ve = v1[e]; }
 
-    const uint64_t q0 = (uint64_t)ti * kFineTileQuads;
-    if (q0 + lane < nquad) {
-        const u32x2 g = load_stream_any(g2 + q0 + lane);
-        f32x4 p = load_stream_any(p4 + q0 + lane), m = load_stream_any(m4 + q0 + lane), v = load_stream_any(v4 + q0 + lane);
-        const u32x2 lp = step_quad<DT, L2>(p, m, v, g, gscale, c);
-        store_stream_any(p4 + q0 + lane, p);
-        store_stream_any(m4 + q0 + lane, m);
-        store_stream_any(v4 + q0 + lane, v);
-        if (lp2) store_stream_any(lp2 + q0 + lane, lp);
-    }
+    const uint32_t shift = fine_shift((uintptr_t)p4);
+    int64_t at = (int64_t)((uint64_t)ti * kFineTileQuads) - shift;      // this tile's first quad; the first one's may be in front of the body
+    do {
+        const uint32_t q = (uint32_t)at + lane;                         // (below 0: more than any nquad)
+        if (q < nquad) {
+            const u32x2 g = load_stream_any(g2 + at + lane);
+            f32x4 p = load_stream_any(p4 + at + lane), m = load_stream_any(m4 + at + lane), v = load_stream_any(v4 + at + lane);
+            const u32x2 lp = step_quad<DT, L2>(p, m, v, g, gscale, c);
+            store_stream_any(p4 + at + lane, p);
+            store_stream_any(m4 + at + lane, m);
+            store_stream_any(v4 + at + lane, v);
+            if (lp2) store_stream_any(lp2 + at + lane, lp);
+        }
+        at += kFineTileQuads;
+    } while (more && at < (int64_t)nquad);
     if (n_outside > 0) {
         for (uint32_t k = lane; k < n_outside; k += kStepThreads) {
             const int64_t i = outside(k);
@@ -437,13 +446,12 @@ __device__ __forceinline__ void step_one(const StepOne& a)
     asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
     float gscale;
     if (!step_prologue(a.d_norm, c, gscale)) return;
-    constexpr uint32_t tile_quads = FINE ? kFineTileQuads : kStepTileQuads;
-    const uint32_t n_tiles = nquad / tile_quads + (nquad % tile_quads ? 1 : 0);
+    const uint32_t n_tiles = FINE ? fine_count(nquad, fine_shift((uintptr_t)p4)) : (nquad + kStepTileQuads - 1) / kStepTileQuads;
     const uint32_t tile = !FINE                                                           ? tile_of_block(blockIdx.x, 0, n_tiles)
                           : n_tiles <= kFineRunTiles * (kStepTileQuads / kFineTileQuads) ? tile_of_block<kFineXcdRun>(blockIdx.x, 0, n_tiles)
                                                                                           : blockIdx.x;
     if constexpr (FINE) {
-        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, gscale, c);
+        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, false, gscale, c);
     } else {
         if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
         step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
@@ -545,7 +553,8 @@ __device__ __forceinline__ void step_list(const Args& a)
     if constexpr (FINE) {
         uint32_t head = 0, tail = 0;
         if (tile == 0) head = (uint32_t)head_of(a, d), tail = (uint32_t)tail_of(a, d);
-        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, gscale, c);
+        const bool last = tile + 1 == kParts * ((nquad + kStepTileQuads - 1) / kStepTileQuads);
+        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, last, gscale, c);
     } else {
         if (tile == 0) step_ends<DT, L2>(T, head_of(a, d), (int64_t)nquad * kQuad, tail_of(a, d), gscale, c);
         step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
@@ -562,7 +571,7 @@ hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hi
 {
     const dim3 block(kStepThreads);
     const uint32_t n_tiles = a.nquad / kStepTileQuads + (a.nquad % kStepTileQuads ? 1 : 0);
-    const uint32_t n_fine = a.nquad / kFineTileQuads + (a.nquad % kFineTileQuads ? 1 : 0);
+    const uint32_t n_fine = fine_count(a.nquad, fine_shift((uintptr_t)a.p_body));
     const bool fine = fine_tiles(n_tiles, Steps::kOne, a.lp_body);
     const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : n_tiles);
     const unsigned lds = fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
