@@ -14,6 +14,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "zi_internal.h"
@@ -572,7 +573,7 @@ hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hi
     const dim3 block(kStepThreads);
     const uint32_t n_tiles = a.nquad / kStepTileQuads + (a.nquad % kStepTileQuads ? 1 : 0);
     const uint32_t n_fine = fine_count(a.nquad, fine_shift((uintptr_t)a.p_body));
-    const bool fine = fine_tiles(n_tiles, Steps::kOne, a.lp_body);
+    const bool fine = fine_tiles(n_tiles, Steps::kOne, a.lp_body, 1);
     const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : n_tiles);
     const unsigned lds = fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
 #define ZI_LAUNCH_ONE(DT, L2) do { \
@@ -595,7 +596,8 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
 {
     if (n_tiles == 0) return hipSuccess;
     const Steps kind = std::is_same_v<Args, ListArgs> ? Steps::kList : Steps::kFlat;
-    const bool fine = fine_tiles(n_tiles, kind, has_copies(a));
+    const uint32_t n_tensors = (uint32_t)(std::lower_bound(a.first_tile, a.first_tile + Args::kMax, 0xFFFFFFFFu) - a.first_tile);
+    const bool fine = fine_tiles(n_tiles, kind, has_copies(a), n_tensors);
     const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
     const unsigned lds = fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
@@ -653,7 +655,7 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
 {
     if (n_tiles == 0) return hipSuccess;
     const bool single = a.n_desc == 1;
-    if (fine_tiles(n_tiles, single ? Steps::kOne : Steps::kList, a.t[0].lp_body))
+    if (fine_tiles(n_tiles, single ? Steps::kOne : Steps::kList, a.t[0].lp_body, (uint32_t)a.n_desc))
         return single ? launch_step_one(one_of(a, l2), dt, l2, any_order, s) : launch_step_list(list_of(a), n_tiles, dt, l2, any_order, s);
     const dim3 grid(n_tiles), block(kStepThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
