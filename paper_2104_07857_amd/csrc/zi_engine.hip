@@ -117,7 +117,8 @@ extern "C" zi_status zi_engine_create(zi_engine** out, int32_t device, size_t ch
     } while (0)
 
     ZI_HIP_E(hipMalloc((void**)&e->staging, (size_t)n_slots * kSlotArrays * e->array_bytes));
-    ZI_HIP_E(hipHostMalloc((void**)&e->h_norm, sizeof(zi_norm_result), hipHostMallocDefault));
+    ZI_HIP_E(hipHostMalloc((void**)&e->h_norm, sizeof(HostNorm), hipHostMallocDefault));
+    memset(e->h_norm, 0, sizeof(HostNorm));
     ZI_HIP_E(hipStreamCreateWithFlags(&e->s_h2d, hipStreamNonBlocking));
     ZI_HIP_E(hipStreamCreateWithFlags(&e->s_k, hipStreamNonBlocking));
     ZI_HIP_E(hipStreamCreateWithFlags(&e->s_d2h, hipStreamNonBlocking));
@@ -189,6 +190,7 @@ extern "C" zi_status zi_engine_set_option(zi_engine* e, int32_t option, int64_t 
         if (value != 0 && (value < 2 || value > kMaxHostSlots))
             return fail(ZI_ERR_INVALID_ARG, "host ring slots must be 0 or in 2..%d", kMaxHostSlots);
         ZI_HIP(hipSetDevice(e->device));
+        ZI_HIP(hipStreamSynchronize(e->s_d2h));      // the CPU placement's last fetch may still be about to end
         ring_release(e);
         if (value == 0) return ZI_OK;
         hipError_t he = hipHostMalloc((void**)&e->hring, (size_t)value * kSlotArrays * e->array_bytes, hipHostMallocDefault);

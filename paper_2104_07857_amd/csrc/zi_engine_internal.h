@@ -36,6 +36,23 @@ struct StateSrc {
     int64_t numel;
 };
 
+// One block of one segment for the host step's thread pool.
+struct CpuBlock {
+    float *p, *m, *v;
+    const uint16_t* g;
+    uint16_t* lp;
+    int64_t n;
+    const uint32_t* arrived;      // flag of the block's gradients (null: they are in host memory already)
+    uint16_t* lp_device;          // where the block of the copy goes (null: it is in its place)
+    bool lp_by_copy;              // ... by the runtime's copy, not by a kernel
+};
+
+// The norm result's landing place, and a flag that a kernel raises once it is there.
+struct HostNorm {
+    zi_norm_result result;
+    uint32_t arrived;
+};
+
 // Page-locked allocations seen during one call: an array that lies in one of them needs no further query,
 // and its device address follows from the allocation's.
 struct HostRanges {
@@ -95,7 +112,8 @@ struct zi_engine {
     hipEvent_t ev_h2d[8] = {}, ev_k[8] = {}, ev_d2h[8] = {};
     hipEvent_t ev_out_start[8] = {};   // the slot's device-to-host copies are about to start (its update is done)
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
-    zi_norm_result* h_norm = nullptr;  // pinned landing place of the norm result
+    zi_norm_result* h_norm = nullptr;  // pinned landing place of the norm result: HostNorm's
+    uint32_t norm_serial = 0;          // of the last result brought there by a kernel
 
     // Pinned ring for state that is not page-locked (ordinary memory, files): n_hslots slots shaped
     // like the HBM slots, filled and emptied by two small thread pools, each driven by one parked
@@ -129,6 +147,7 @@ struct zi_engine {
     std::vector<size_t> use_begin;
     std::vector<zi::host::Piece> pieces_in, pieces_out;
     std::vector<int32_t> host_idx;
+    std::vector<zi::host::CpuBlock> cpu_blocks;
     std::vector<uint32_t> cpu_done;    // per block of the host-CPU step: stepped in this use
 
     // options and figures
