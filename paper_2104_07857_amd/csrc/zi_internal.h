@@ -33,7 +33,8 @@ constexpr unsigned kStepLds20 = 8 * 1024, kStepLds16 = 10 * 1024, kStepLds14 = 1
 // Half a tile, one quad a lane (adamw_fine_kernel, adamw_fine_list_kernel): twice as many wavefronts with half as many loads
 // each, which live less than half as long, so that requests are spread more evenly over time and a launch's last round is shorter.
 // Which kernel a launch takes follows from its tiles.  Up to kFineShortTiles all of its fine workgroups are resident at once;
-// from there to kOneRoundTiles only those of whole tiles are; beyond, fine ones again.  One tensor's runs of kFineXcdRun
+// from there to kOneRoundTiles only those of whole tiles are (a tensor's up to kPacedTiles with all loads up front, else paced_quads()); beyond
+// those, fine ones again.  One tensor's runs of kFineXcdRun
 // fine tiles go to one XCD each in launches of up to kFineRunTiles; longer ones, and lists, are dealt out as they come: then all
 // eight XCDs walk the same few MiB of every array, and it matters little how the arrays lie to each other.
 // Step alone in us, whole / fine tiles (range over one to four placements of the arrays each), one tensor:
@@ -71,12 +72,30 @@ __host__ __device__ inline uint32_t fine_count(uint32_t nquad, uint32_t shift)
 // (norm included), 998 with 1.2e6 30.3 / 31.1, 108 with 4.5e5 6.1 / 6.2; but 118 with 6.0e5 7.2 / 6.4, 37 with 9.7e4 5.2 / 4.7.
 constexpr uint32_t kManyTensors = 64, kFewTiles = 9;
 enum class Steps { kOne, kList, kFlat };
-inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_tensors)
+inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_tensors)     // where paced_quads() says 0
 {
     if (n_tensors > kManyTensors && n_tiles < kFewTiles * n_tensors) return false;
     if (kind == Steps::kList && !copies && n_tiles > kBareListTiles && n_tiles <= kBareListMostTiles) return false;
     if (kind == Steps::kFlat && !copies && n_tiles > kFineListTiles) return false;
     return n_tiles <= kFineShortTiles || (n_tiles > kOneRoundTiles && n_tiles < kFineMostTiles);
+}
+// Launches whose workgroups are all resident at once (16 on a compute unit), at a measured pace (adamw_paced_kernel, adamw_paced_list_kernel): quads that
+// a lane takes, 0: not so.  Tensors of kPacedTiles and less are as fast with all loads up front, lists, whose lookups spread the loads anyway,
+// only where fine tiles fit; four quads stop paying where twice kOneRoundTiles end.  Lists have tables of whole tiles, which are two quads; with
+// 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.  Step alone in us, all loads up front (beyond
+// kOneRoundTiles fine tiles) / paced, one tensor: 1.2e6 7.6 / 7.4   1.3e6 7.6 / 7.5   1.4e6 8.1 / 7.7   1.6e6 9.5 / 8.4   1.8e6 10.5 / 9.1   2.1e6
+// 11.5 / 10.2, three quads 2.3e6 12.6 / 11.6   3.0e6 15.9 / 14.7, four 3.3e6 17.7 / 16.2   3.6e6 18.8 / 17.5   4.0e6 20.1 / 20.4, without copies 1.9e6
+// 10.4 / 9.2; lists of 12 tensors 1.0e6 8.8 / 8.0   1.3e6 9.5 / 8.4   2.0e6 12.8 / 11.5, of 60 1.0e6 9.1 / 8.3   2.0e6 13.3 / 12.5, of 200 8.0e5 8.7 / 8.9
+// 1.0e6 9.3 / 9.0   1.3e6 10.5 / 9.8   2.0e6 13.6 / 12.8, of 400 1.5e6 17.0 / 16.4.
+constexpr uint32_t kPacedTiles = 5u << 9;          // 1.3e6 elements
+constexpr uint32_t kMostPacedTiles = 7u << 10;     // 3.7e6 elements
+constexpr int kMostPaced = 4;
+inline int paced_quads(uint32_t n_tiles, Steps kind)
+{
+    if (kind != Steps::kOne) return n_tiles > kFineShortTiles && n_tiles <= kOneRoundTiles ? kStepUnroll : 0;
+    if (n_tiles <= kPacedTiles || n_tiles > kMostPacedTiles) return 0;
+    constexpr uint32_t per_quad = kOneRoundTiles / kStepUnroll;
+    return (int)((n_tiles + per_quad - 1) / per_quad);
 }
 inline unsigned fine_lds(uint32_t n_tiles, Steps kind, bool copies, bool norm)
 {

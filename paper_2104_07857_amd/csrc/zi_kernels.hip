@@ -332,8 +332,43 @@ __device__ __forceinline__ void step_tile(GlobalF4 __restrict__ p4, GlobalF4 __r
     }
 }
 
-// Half a tile, one quad a lane (kFineTileQuads), and with a tensor's first the elements outside the body.  Those are loaded in
-// front of the quads and updated behind them, so that a first tile makes one round trip to memory like any other.
+// The elements of a tensor outside its body, by one wavefront: loaded in front of its quads and updated behind them, so that a first tile makes
+// one round trip to memory like any other.
+template <int DT, bool L2>
+struct StepEnds {
+    ZI_GLOBAL float *p, *m, *v;
+    const ZI_GLOBAL uint16_t* g;
+    ZI_GLOBAL uint16_t* lp;
+    uint32_t head, count, nquad;
+    float pe = 0.0f, me = 0.0f, ve = 0.0f;
+    uint32_t ge = 0;
+
+    __device__ __forceinline__ StepEnds(GlobalF4 p4, GlobalF4 m4, GlobalF4 v4, GlobalConstU2 g2, GlobalU2 lp2, uint32_t head_, uint32_t tail,
+                                        uint32_t nquad_)
+        : p((ZI_GLOBAL float*)p4), m((ZI_GLOBAL float*)m4), v((ZI_GLOBAL float*)v4), g((const ZI_GLOBAL uint16_t*)g2),
+          lp((ZI_GLOBAL uint16_t*)lp2), head(head_), count(head_ + tail), nquad(nquad_)
+    {
+        if (count > 0 && threadIdx.x < count) load(at(threadIdx.x));
+    }
+    // element of the head or the tail by number (66 at most)
+    __device__ __forceinline__ int64_t at(uint32_t k) const { return k < head ? (int64_t)k - head : (int64_t)nquad * kQuad + (k - head); }
+    __device__ __forceinline__ void load(int64_t i) { ge = g[i]; pe = p[i]; me = m[i]; ve = v[i]; }
+    __device__ __forceinline__ void update(float gscale, const StepConsts& c)
+    {
+        if (count == 0) return;
+        for (uint32_t k = threadIdx.x; k < count; k += kStepThreads) {
+            const int64_t i = at(k);
+            if (k >= kStepThreads) load(i);
+            adamw_element<L2>(pe, me, ve, widen16<DT>(ge), gscale, c);
+            p[i] = pe;
+            m[i] = me;
+            v[i] = ve;
+            if (lp) lp[i] = (uint16_t)narrow16<DT>(pe);
+        }
+    }
+};
+
+// Half a tile, one quad a lane (kFineTileQuads), and with a tensor's first the elements outside the body.
 // A fine tile ends where p reaches a multiple of 1 KiB (fine_shift), so that neighbouring wavefronts, which are different
 // XCDs', do not share the 256 bytes that one channel has: views five elements into flat buffers, step alone in us, whole tiles / fine from the
 // body's start / so: 1.1e8 elements 498 / 503 / 478, 1.4e8 631 / 636 / 609, 2.4e8 1105 / 1112 / 1072, 3.2e8 1310 / 1376 / 1273.
@@ -344,17 +379,7 @@ __device__ __forceinline__ void step_fine_tile(GlobalF4 __restrict__ p4, GlobalF
                                                uint32_t tail, uint32_t ti, uint32_t nquad, bool more, float gscale, const StepConsts& c)
 {
     const uint32_t lane = threadIdx.x;
-    ZI_GLOBAL float *p1 = (ZI_GLOBAL float*)p4, *m1 = (ZI_GLOBAL float*)m4, *v1 = (ZI_GLOBAL float*)v4;
-    const ZI_GLOBAL uint16_t* g1 = (const ZI_GLOBAL uint16_t*)g2;
-    ZI_GLOBAL uint16_t* lp1 = (ZI_GLOBAL uint16_t*)lp2;
-    // element of the head or the tail by number (66 at most)
-    const auto outside = [=](uint32_t k) { return k < head ? (int64_t)k - head : (int64_t)nquad * kQuad + (k - head); };
-    const uint32_t n_outside = ti == 0 ? head + tail : 0;
-    const int64_t e = outside(lane);
-    float pe = 0.0f, me = 0.0f, ve = 0.0f;
-    uint32_t ge = 0;
-    if (n_outside > 0 && lane < n_outside) { ge = g1[e]; pe = p1[e]; me = m1[e]; ve = v1[e]; }
-
+    StepEnds<DT, L2> ends(p4, m4, v4, g2, lp2, ti == 0 ? head : 0, ti == 0 ? tail : 0, nquad);
     const uint32_t shift = fine_shift((uintptr_t)p4);
     int64_t at = (int64_t)((uint64_t)ti * kFineTileQuads) - shift;      // this tile's first quad; the first one's may be in front of the body
     do {
@@ -370,17 +395,52 @@ __device__ __forceinline__ void step_fine_tile(GlobalF4 __restrict__ p4, GlobalF
         }
         at += kFineTileQuads;
     } while (more && at < (int64_t)nquad);
-    if (n_outside > 0) {
-        for (uint32_t k = lane; k < n_outside; k += kStepThreads) {
-            const int64_t i = outside(k);
-            if (k >= kStepThreads) { ge = g1[i]; pe = p1[i]; me = m1[i]; ve = v1[i]; }
-            adamw_element<L2>(pe, me, ve, widen16<DT>(ge), gscale, c);
-            p1[i] = pe;
-            m1[i] = me;
-            v1[i] = ve;
-            if (lp1) lp1[i] = (uint16_t)narrow16<DT>(pe);
+    ends.update(gscale, c);
+}
+
+// Two quads a lane or, of one tensor, up to four, at a measured pace: a quad's loads are asked for when those before have arrived, and its stores
+// when those before are done.  Bound: HBM.  Where all workgroups of a launch are resident at once, all of them then read at the same time
+// and write at the same time, with a quarter to a half of the requests in the queues (paced_quads): 5.4 to 5.8 TB/s on 1.6e6 to 3.0e6 elements,
+// where all loads up front and fine tiles reach 4.7 to 5.3.
+template <int DT, bool L2, int QUADS>
+__device__ __forceinline__ void step_paced_tile(GlobalF4 __restrict__ p4, GlobalF4 __restrict__ m4, GlobalF4 __restrict__ v4,
+                                                GlobalConstU2 __restrict__ g2, GlobalU2 __restrict__ lp2, uint32_t head,
+                                                uint32_t tail, uint32_t ti, uint32_t nquad, float gscale, const StepConsts& c)
+{
+    StepEnds<DT, L2> ends(p4, m4, v4, g2, lp2, ti == 0 ? head : 0, ti == 0 ? tail : 0, nquad);
+    const uint32_t q0 = ti * (kStepThreads * QUADS) + threadIdx.x;
+    f32x4 p[QUADS], m[QUADS], v[QUADS];
+    u32x2 g[QUADS];
+#pragma unroll
+    for (int u = 0; u < QUADS; ++u) {
+        const uint32_t i = q0 + u * kStepThreads;
+        p[u] = m[u] = v[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        g[u] = u32x2{0, 0};
+        if (i < nquad) {
+            g[u] = load_stream_any(g2 + i);
+            p[u] = load_stream_any(p4 + i);
+            m[u] = load_stream_any(m4 + i);
+            v[u] = load_stream_any(v4 + i);
         }
+        asm volatile("" : "+v"(g[u]), "+v"(p[u]), "+v"(m[u]), "+v"(v[u]));      // (here: the compiler waits for them in front of this)
+        __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int u = 0; u < QUADS; ++u) {
+        constexpr int kNoMemoryAccessLeft = 0x0F70;       // vmcnt(0): loads and stores
+        if (u > 0) __builtin_amdgcn_s_waitcnt(kNoMemoryAccessLeft);
+        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t i = q0 + u * kStepThreads;
+        const u32x2 lp = step_quad<DT, L2>(p[u], m[u], v[u], g[u], gscale, c);
+        if (i < nquad) {
+            store_stream_any(p4 + i, p[u]);
+            store_stream_any(m4 + i, m[u]);
+            store_stream_any(v4 + i, v[u]);
+            if (lp2) store_stream_any(lp2 + i, lp);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    ends.update(gscale, c);
 }
 
 // One workgroup = one tile of kStepTileElems elements of one tensor.  blockIdx.x counts tiles over
@@ -431,8 +491,8 @@ void adamw_wide_kernel(const StepArgs a)
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, a.c);
 }
 
-// One tensor, from arguments that are quickly written (StepOne).  FINE: one quad a lane instead of two.
-template <int DT, bool L2, bool FINE>
+// One tensor, from arguments that are quickly written (StepOne).  FINE: one quad a lane instead of two.  PACED: so many, one after the other.
+template <int DT, bool L2, bool FINE, int PACED = 0>
 __device__ __forceinline__ void step_one(const StepOne& a)
 {
     const StepConsts c = {a.beta1, a.beta2, a.omb1, a.omb2, a.eps, a.step_size, a.inv_sqrt_bc2, L2 ? 0.0f : a.decay,
@@ -447,12 +507,15 @@ __device__ __forceinline__ void step_one(const StepOne& a)
     asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
     float gscale;
     if (!step_prologue(a.d_norm, c, gscale)) return;
-    const uint32_t n_tiles = FINE ? fine_count(nquad, fine_shift((uintptr_t)p4)) : (nquad + kStepTileQuads - 1) / kStepTileQuads;
+    constexpr uint32_t kTileQuads = PACED ? kStepThreads * PACED : kStepTileQuads;
+    const uint32_t n_tiles = FINE ? fine_count(nquad, fine_shift((uintptr_t)p4)) : (nquad + kTileQuads - 1) / kTileQuads;
     const uint32_t tile = !FINE                                                           ? tile_of_block(blockIdx.x, 0, n_tiles)
                           : n_tiles <= kFineRunTiles * (kStepTileQuads / kFineTileQuads) ? tile_of_block<kFineXcdRun>(blockIdx.x, 0, n_tiles)
                                                                                           : blockIdx.x;
     if constexpr (FINE) {
         step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, false, gscale, c);
+    } else if constexpr (PACED) {
+        step_paced_tile<DT, L2, PACED>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, gscale, c);
     } else {
         if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
         step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
@@ -465,6 +528,8 @@ void adamw_short_kernel(const StepOne a) { step_one<DT, L2, false>(a); }
 // whole tiles reach 5.9 to 6.3, by the arrays' places (zi_internal.h, kFineTileQuads).
 template <int DT, bool L2>
 __global__ __launch_bounds__(kStepThreads) void adamw_fine_kernel(const StepOne a) { step_one<DT, L2, true>(a); }
+template <int DT, bool L2, int QUADS>
+__global__ __launch_bounds__(kStepThreads) void adamw_paced_kernel(const StepOne a) { step_one<DT, L2, false, QUADS>(a); }
 
 // n += block >= start; first = the start, if so.  Three scalar instructions; the compiler goes through a
 // vector register.
@@ -507,7 +572,7 @@ __device__ __forceinline__ int64_t tail_of(const FlatList<GROUPS>& a, uint32_t d
 // a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
 // 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,
 // 200 of 1..40,000 45.6 -> 35.3, as FlatArgs 25.3; with the norm result fetched after the descriptor 1478 instead of 1366.
-template <int DT, bool L2, bool FINE, typename Args>
+template <int DT, bool L2, bool FINE, bool PACED, typename Args>
 __device__ __forceinline__ void step_list(const Args& a)
 {
     constexpr uint32_t kParts = FINE ? kStepTileQuads / kFineTileQuads : 1;     // workgroups to a tile
@@ -556,6 +621,10 @@ __device__ __forceinline__ void step_list(const Args& a)
         if (tile == 0) head = (uint32_t)head_of(a, d), tail = (uint32_t)tail_of(a, d);
         const bool last = tile + 1 == kParts * ((nquad + kStepTileQuads - 1) / kStepTileQuads);
         step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, last, gscale, c);
+    } else if constexpr (PACED) {
+        uint32_t head = 0, tail = 0;
+        if (tile == 0) head = (uint32_t)head_of(a, d), tail = (uint32_t)tail_of(a, d);
+        step_paced_tile<DT, L2, kStepUnroll>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, gscale, c);
     } else {
         if (tile == 0) step_ends<DT, L2>(T, head_of(a, d), (int64_t)nquad * kQuad, tail_of(a, d), gscale, c);
         step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
@@ -563,27 +632,37 @@ __device__ __forceinline__ void step_list(const Args& a)
 }
 template <int DT, bool L2, typename Args>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
-void adamw_list_kernel(const Args a) { step_list<DT, L2, false>(a); }
+void adamw_list_kernel(const Args a) { step_list<DT, L2, false, false>(a); }
 // (a tile's halves are neighbouring workgroups, so the tables of starts count whole tiles for both kernels)
 template <int DT, bool L2, typename Args>
-__global__ __launch_bounds__(kStepThreads) void adamw_fine_list_kernel(const Args a) { step_list<DT, L2, true>(a); }
+__global__ __launch_bounds__(kStepThreads) void adamw_fine_list_kernel(const Args a) { step_list<DT, L2, true, false>(a); }
+template <int DT, bool L2, typename Args>
+__global__ __launch_bounds__(kStepThreads) void adamw_paced_list_kernel(const Args a) { step_list<DT, L2, false, true>(a); }
 
 hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hipStream_t s)
 {
     const dim3 block(kStepThreads);
     const uint32_t n_tiles = a.nquad / kStepTileQuads + (a.nquad % kStepTileQuads ? 1 : 0);
     const uint32_t n_fine = fine_count(a.nquad, fine_shift((uintptr_t)a.p_body));
-    const bool fine = fine_tiles(n_tiles, Steps::kOne, a.lp_body, 1);
-    const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : n_tiles);
-    const unsigned lds = fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
+    const int paced = paced_quads(n_tiles, Steps::kOne);
+    const bool fine = !paced && fine_tiles(n_tiles, Steps::kOne, a.lp_body, 1);
+    const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : paced ? (a.nquad - 1) / (uint32_t)(paced * kStepThreads) + 1 : n_tiles);
+    const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
+    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
+#define ZI_LAUNCH_PACED(DT, L2, QUADS) \
+    hipExtLaunchKernelGGL((adamw_paced_kernel<DT, L2, QUADS>), grid, block, lds, s, nullptr, nullptr, flags, a)
 #define ZI_LAUNCH_ONE(DT, L2) do { \
-        if (!fine)          hipLaunchKernelGGL((adamw_short_kernel<DT, L2>), grid, block, lds, s, a); \
+        if (paced == 2)      ZI_LAUNCH_PACED(DT, L2, 2); \
+        else if (paced == 3) ZI_LAUNCH_PACED(DT, L2, 3); \
+        else if (paced)      ZI_LAUNCH_PACED(DT, L2, kMostPaced); \
+        else if (!fine)     hipLaunchKernelGGL((adamw_short_kernel<DT, L2>), grid, block, lds, s, a); \
         else if (any_order) hipExtLaunchKernelGGL((adamw_fine_kernel<DT, L2>), grid, block, lds, s, nullptr, nullptr, hipExtAnyOrderLaunch, a); \
         else                hipLaunchKernelGGL((adamw_fine_kernel<DT, L2>), grid, block, lds, s, a); \
     } while (0)
     if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_ONE(ZI_BF16, true); else ZI_LAUNCH_ONE(ZI_BF16, false); }
     else               { if (l2) ZI_LAUNCH_ONE(ZI_FP16, true); else ZI_LAUNCH_ONE(ZI_FP16, false); }
 #undef ZI_LAUNCH_ONE
+#undef ZI_LAUNCH_PACED
     return hipGetLastError();
 }
 
@@ -597,12 +676,14 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
     if (n_tiles == 0) return hipSuccess;
     const Steps kind = std::is_same_v<Args, ListArgs> ? Steps::kList : Steps::kFlat;
     const uint32_t n_tensors = (uint32_t)(std::lower_bound(a.first_tile, a.first_tile + Args::kMax, 0xFFFFFFFFu) - a.first_tile);
-    const bool fine = fine_tiles(n_tiles, kind, has_copies(a), n_tensors);
+    const bool paced = paced_quads(n_tiles, kind);
+    const bool fine = !paced && fine_tiles(n_tiles, kind, has_copies(a), n_tensors);
     const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
-    const unsigned lds = fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
+    const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
 #define ZI_LAUNCH_LIST(DT, L2) do { \
-        if (fine) hipExtLaunchKernelGGL((adamw_fine_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
+        if (paced) hipExtLaunchKernelGGL((adamw_paced_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
+        else if (fine) hipExtLaunchKernelGGL((adamw_fine_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
         else      hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
     } while (0)
     if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LIST(ZI_BF16, true); else ZI_LAUNCH_LIST(ZI_BF16, false); }
@@ -655,7 +736,8 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
 {
     if (n_tiles == 0) return hipSuccess;
     const bool single = a.n_desc == 1;
-    if (fine_tiles(n_tiles, single ? Steps::kOne : Steps::kList, a.t[0].lp_body, (uint32_t)a.n_desc))
+    const Steps kind = single ? Steps::kOne : Steps::kList;
+    if (paced_quads(n_tiles, kind) || fine_tiles(n_tiles, kind, a.t[0].lp_body, (uint32_t)a.n_desc))
         return single ? launch_step_one(one_of(a, l2), dt, l2, any_order, s) : launch_step_list(list_of(a), n_tiles, dt, l2, any_order, s);
     const dim3 grid(n_tiles), block(kStepThreads);
     const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
