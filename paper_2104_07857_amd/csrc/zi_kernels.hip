@@ -639,6 +639,29 @@ __global__ __launch_bounds__(kStepThreads) void adamw_fine_list_kernel(const Arg
 template <int DT, bool L2, typename Args>
 __global__ __launch_bounds__(kStepThreads) void adamw_paced_list_kernel(const Args a) { step_list<DT, L2, false, true>(a); }
 
+// One kernel with one structure of arguments, handed over where it is: the launch macros copy it several times on the way, and configure
+// a launch in a call of its own.  Issue of an empty kernel with 112 bytes 2.40 -> 2.24 us; a list of 467 short tensors, two launches of 4 KB, 17.3 -> 16.5.
+template <typename Args>
+static hipError_t launch(void (*kernel)(Args), dim3 grid, dim3 block, unsigned lds, hipStream_t s, const Args& a, bool any_order = false)
+{
+    void* args[] = {const_cast<Args*>(&a)};
+    if (any_order)
+        (void)hipExtLaunchKernel((const void*)kernel, grid, block, args, lds, s, nullptr, nullptr, hipExtAnyOrderLaunch);
+    else
+        (void)hipLaunchKernel((const void*)kernel, grid, block, args, lds, s);
+    return hipGetLastError();
+}
+
+// of(type, flag) for one of the two types of 2-byte elements and a flag.
+template <typename F>
+static auto instance(const F& of, int dt, bool flag)
+{
+    constexpr std::integral_constant<int, ZI_BF16> bf16;
+    constexpr std::integral_constant<int, ZI_FP16> fp16;
+    return dt == ZI_BF16 ? (flag ? of(bf16, std::true_type()) : of(bf16, std::false_type()))
+                         : (flag ? of(fp16, std::true_type()) : of(fp16, std::false_type()));
+}
+
 hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hipStream_t s)
 {
     const dim3 block(kStepThreads);
@@ -648,22 +671,16 @@ hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hi
     const bool fine = !paced && fine_tiles(n_tiles, Steps::kOne, a.lp_body, 1);
     const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : paced ? (a.nquad - 1) / (uint32_t)(paced * kStepThreads) + 1 : n_tiles);
     const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-#define ZI_LAUNCH_PACED(DT, L2, QUADS) \
-    hipExtLaunchKernelGGL((adamw_paced_kernel<DT, L2, QUADS>), grid, block, lds, s, nullptr, nullptr, flags, a)
-#define ZI_LAUNCH_ONE(DT, L2) do { \
-        if (paced == 2)      ZI_LAUNCH_PACED(DT, L2, 2); \
-        else if (paced == 3) ZI_LAUNCH_PACED(DT, L2, 3); \
-        else if (paced)      ZI_LAUNCH_PACED(DT, L2, kMostPaced); \
-        else if (!fine)     hipLaunchKernelGGL((adamw_short_kernel<DT, L2>), grid, block, lds, s, a); \
-        else if (any_order) hipExtLaunchKernelGGL((adamw_fine_kernel<DT, L2>), grid, block, lds, s, nullptr, nullptr, hipExtAnyOrderLaunch, a); \
-        else                hipLaunchKernelGGL((adamw_fine_kernel<DT, L2>), grid, block, lds, s, a); \
-    } while (0)
-    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_ONE(ZI_BF16, true); else ZI_LAUNCH_ONE(ZI_BF16, false); }
-    else               { if (l2) ZI_LAUNCH_ONE(ZI_FP16, true); else ZI_LAUNCH_ONE(ZI_FP16, false); }
-#undef ZI_LAUNCH_ONE
-#undef ZI_LAUNCH_PACED
-    return hipGetLastError();
+    const auto of = [=](auto dt_, auto l2_) {
+        constexpr int DT = decltype(dt_)::value;
+        constexpr bool L2 = decltype(l2_)::value;
+        return paced == 2 ? adamw_paced_kernel<DT, L2, 2>
+               : paced == 3 ? adamw_paced_kernel<DT, L2, 3>
+               : paced ? adamw_paced_kernel<DT, L2, kMostPaced>
+               : fine ? adamw_fine_kernel<DT, L2>
+                      : adamw_short_kernel<DT, L2>;
+    };
+    return launch(instance(of, dt, l2), grid, block, lds, s, a, any_order);
 }
 
 static bool has_copies(const ListArgs& a) { return a.t[0].lp_body; }
@@ -680,16 +697,12 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
     const bool fine = !paced && fine_tiles(n_tiles, kind, has_copies(a), n_tensors);
     const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
     const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-#define ZI_LAUNCH_LIST(DT, L2) do { \
-        if (paced) hipExtLaunchKernelGGL((adamw_paced_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
-        else if (fine) hipExtLaunchKernelGGL((adamw_fine_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
-        else      hipExtLaunchKernelGGL((adamw_list_kernel<DT, L2, Args>), grid, block, lds, s, nullptr, nullptr, flags, a); \
-    } while (0)
-    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LIST(ZI_BF16, true); else ZI_LAUNCH_LIST(ZI_BF16, false); }
-    else               { if (l2) ZI_LAUNCH_LIST(ZI_FP16, true); else ZI_LAUNCH_LIST(ZI_FP16, false); }
-#undef ZI_LAUNCH_LIST
-    return hipGetLastError();
+    const auto of = [=](auto dt_, auto l2_) {
+        constexpr int DT = decltype(dt_)::value;
+        constexpr bool L2 = decltype(l2_)::value;
+        return paced ? adamw_paced_list_kernel<DT, L2, Args> : fine ? adamw_fine_list_kernel<DT, L2, Args> : adamw_list_kernel<DT, L2, Args>;
+    };
+    return launch(instance(of, dt, l2), grid, block, lds, s, a, any_order);
 }
 hipError_t launch_step_few(const FlatFew& a, uint32_t n_tiles, int dt, bool l2, hipStream_t s)
 {
@@ -739,20 +752,12 @@ hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2
     const Steps kind = single ? Steps::kOne : Steps::kList;
     if (paced_quads(n_tiles, kind) || fine_tiles(n_tiles, kind, a.t[0].lp_body, (uint32_t)a.n_desc))
         return single ? launch_step_one(one_of(a, l2), dt, l2, any_order, s) : launch_step_list(list_of(a), n_tiles, dt, l2, any_order, s);
-    const dim3 grid(n_tiles), block(kStepThreads);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-    const unsigned lds = whole_tiles_lds(n_tiles);
-#define ZI_LAUNCH_STEP(DT, L2, SINGLE) \
-    hipExtLaunchKernelGGL((adamw_wide_kernel<DT, L2, SINGLE>), grid, block, lds, s, nullptr, nullptr, flags, a)
-    if (dt == ZI_BF16) {
-        if (l2) { if (single) ZI_LAUNCH_STEP(ZI_BF16, true, true); else ZI_LAUNCH_STEP(ZI_BF16, true, false); }
-        else    { if (single) ZI_LAUNCH_STEP(ZI_BF16, false, true); else ZI_LAUNCH_STEP(ZI_BF16, false, false); }
-    } else {
-        if (l2) { if (single) ZI_LAUNCH_STEP(ZI_FP16, true, true); else ZI_LAUNCH_STEP(ZI_FP16, true, false); }
-        else    { if (single) ZI_LAUNCH_STEP(ZI_FP16, false, true); else ZI_LAUNCH_STEP(ZI_FP16, false, false); }
-    }
-#undef ZI_LAUNCH_STEP
-    return hipGetLastError();
+    const auto of = [=](auto dt_, auto l2_) {
+        constexpr int DT = decltype(dt_)::value;
+        constexpr bool L2 = decltype(l2_)::value;
+        return single ? adamw_wide_kernel<DT, L2, true> : adamw_wide_kernel<DT, L2, false>;
+    };
+    return launch(instance(of, dt, l2), n_tiles, kStepThreads, whole_tiles_lds(n_tiles), s, a, any_order);
 }
 
 // The descriptor that holds tile t of a launch, at or after entry d, by halving: a walk from entry to entry
@@ -933,33 +938,23 @@ hipError_t launch_link_copy(const CopyArgs& a, hipStream_t s)
 {
     if (a.n_blocks == 0) return hipSuccess;
     const dim3 grid(a.n_blocks < (uint32_t)kCopyGroups ? a.n_blocks : (uint32_t)kCopyGroups), block(64);
-    if (a.flags) hipLaunchKernelGGL(link_copy_kernel<true>, grid, block, 0, s, a);
-    else         hipLaunchKernelGGL(link_copy_kernel<false>, grid, block, 0, s, a);
-    return hipGetLastError();
+    return launch(a.flags ? link_copy_kernel<true> : link_copy_kernel<false>, grid, block, 0, s, a);
 }
 
 hipError_t launch_step_link(const LinkArgs& a, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (a.n_tiles == 0) return hipSuccess;
     const dim3 grid(a.n_tiles < (uint32_t)kLinkGroups ? a.n_tiles : (uint32_t)kLinkGroups), block(kStepThreads);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-#define ZI_LAUNCH_LINK(DT, L2) hipExtLaunchKernelGGL((adamw_link_kernel<DT, L2>), grid, block, 0, s, nullptr, nullptr, flags, a)
-    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LINK(ZI_BF16, true); else ZI_LAUNCH_LINK(ZI_BF16, false); }
-    else               { if (l2) ZI_LAUNCH_LINK(ZI_FP16, true); else ZI_LAUNCH_LINK(ZI_FP16, false); }
-#undef ZI_LAUNCH_LINK
-    return hipGetLastError();
+    const auto of = [](auto dt_, auto l2_) { return adamw_link_kernel<decltype(dt_)::value, decltype(l2_)::value>; };
+    return launch(instance(of, dt, l2), grid, block, 0, s, a, any_order);
 }
 
 hipError_t launch_step_link_flat(const LinkFlatArgs& a, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (a.n_tiles == 0) return hipSuccess;
     const dim3 grid(a.n_tiles < (uint32_t)kLinkGroups ? a.n_tiles : (uint32_t)kLinkGroups), block(kStepThreads);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-#define ZI_LAUNCH_LINK(DT, L2) hipExtLaunchKernelGGL((adamw_link_flat_kernel<DT, L2>), grid, block, 0, s, nullptr, nullptr, flags, a)
-    if (dt == ZI_BF16) { if (l2) ZI_LAUNCH_LINK(ZI_BF16, true); else ZI_LAUNCH_LINK(ZI_BF16, false); }
-    else               { if (l2) ZI_LAUNCH_LINK(ZI_FP16, true); else ZI_LAUNCH_LINK(ZI_FP16, false); }
-#undef ZI_LAUNCH_LINK
-    return hipGetLastError();
+    const auto of = [](auto dt_, auto l2_) { return adamw_link_flat_kernel<decltype(dt_)::value, decltype(l2_)::value>; };
+    return launch(instance(of, dt, l2), grid, block, 0, s, a, any_order);
 }
 
 // ------------------------------------------------------- gradient sum of squares + overflow flag
@@ -1277,40 +1272,28 @@ hipError_t launch_norm_partials(const NormArgs& a, uint32_t n_blocks, int dt, bo
 {
     if (n_blocks == 0) return hipSuccess;
     const dim3 grid(n_blocks), block(keep ? kNormKeepThreads : kNormStreamThreads);
-    const uint32_t flags = any_order ? hipExtAnyOrderLaunch : 0;
-#define ZI_LAUNCH_NORM(DT, KEEP) \
-    hipExtLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP, NormArgs>), grid, block, 0, s, nullptr, nullptr, flags, a)
-    if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
-    else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
-#undef ZI_LAUNCH_NORM
-    return hipGetLastError();
+    const auto of = [](auto dt_, auto keep_) { return sumsq_partial_kernel<decltype(dt_)::value, decltype(keep_)::value, NormArgs>; };
+    return launch(instance(of, dt, keep), grid, block, 0, s, a, any_order);
 }
 
 hipError_t launch_norm_one(const NormOne& a, int dt, bool keep, hipStream_t s)
 {
     const dim3 grid(a.n_groups), block(keep ? kNormKeepThreads : kNormStreamThreads);
-#define ZI_LAUNCH_NORM(DT, KEEP) hipLaunchKernelGGL((sumsq_partial_kernel<DT, KEEP, NormOne>), grid, block, 0, s, a)
-    if (dt == ZI_BF16) { if (keep) ZI_LAUNCH_NORM(ZI_BF16, true); else ZI_LAUNCH_NORM(ZI_BF16, false); }
-    else               { if (keep) ZI_LAUNCH_NORM(ZI_FP16, true); else ZI_LAUNCH_NORM(ZI_FP16, false); }
-#undef ZI_LAUNCH_NORM
-    return hipGetLastError();
+    const auto of = [](auto dt_, auto keep_) { return sumsq_partial_kernel<decltype(dt_)::value, decltype(keep_)::value, NormOne>; };
+    return launch(instance(of, dt, keep), grid, block, 0, s, a);
 }
 
 hipError_t launch_norm_few(const NormFew& a, int dt, hipStream_t s)
 {
     const dim3 grid(a.n_groups), block(kNormKeepThreads);
-    if (dt == ZI_BF16) hipLaunchKernelGGL((sumsq_partial_kernel<ZI_BF16, true, NormFew>), grid, block, 0, s, a);
-    else               hipLaunchKernelGGL((sumsq_partial_kernel<ZI_FP16, true, NormFew>), grid, block, 0, s, a);
-    return hipGetLastError();
+    return launch(dt == ZI_BF16 ? sumsq_partial_kernel<ZI_BF16, true, NormFew> : sumsq_partial_kernel<ZI_FP16, true, NormFew>, grid, block, 0, s, a);
 }
 
 template <typename Args>
 static hipError_t launch_short_of(const Args& a, int dt, hipStream_t s)
 {
     const dim3 grid(a.n_groups), block(kNormShortVecs);
-    if (dt == ZI_BF16) hipLaunchKernelGGL((short_sumsq_partial_kernel<ZI_BF16, Args>), grid, block, 0, s, a);
-    else               hipLaunchKernelGGL((short_sumsq_partial_kernel<ZI_FP16, Args>), grid, block, 0, s, a);
-    return hipGetLastError();
+    return launch(dt == ZI_BF16 ? short_sumsq_partial_kernel<ZI_BF16, Args> : short_sumsq_partial_kernel<ZI_FP16, Args>, grid, block, 0, s, a);
 }
 hipError_t launch_norm_short(const NormOne& a, int dt, hipStream_t s) { return launch_short_of(a, dt, s); }
 hipError_t launch_norm_short(const NormFew& a, int dt, hipStream_t s) { return launch_short_of(a, dt, s); }
