@@ -80,15 +80,19 @@ inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_ten
     return n_tiles <= kFineShortTiles || (n_tiles > kOneRoundTiles && n_tiles < kFineMostTiles);
 }
 // Launches whose workgroups are all resident at once (16 on a compute unit), at a measured pace (adamw_paced_kernel, adamw_paced_list_kernel): quads that
-// a lane takes, 0: not so.  Tensors of kPacedTiles and less are as fast with all loads up front, lists, whose lookups spread the loads anyway,
-// only where fine tiles fit; four quads stop paying where twice kOneRoundTiles end.  Lists have tables of whole tiles, which are two quads; with
-// 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.  Step alone in us, all loads up front (beyond
-// kOneRoundTiles fine tiles) / paced, one tensor: 1.2e6 7.6 / 7.4   1.3e6 7.6 / 7.5   1.4e6 8.1 / 7.7   1.6e6 9.5 / 8.4   1.8e6 10.5 / 9.1   2.1e6
-// 11.5 / 10.2, three quads 2.3e6 12.6 / 11.6   3.0e6 15.9 / 14.7, four 3.3e6 17.7 / 16.2   3.6e6 18.8 / 17.5   4.0e6 20.1 / 20.4, without copies 1.9e6
-// 10.4 / 9.2; lists of 12 tensors 1.0e6 8.8 / 8.0   1.3e6 9.5 / 8.4   2.0e6 12.8 / 11.5, of 60 1.0e6 9.1 / 8.3   2.0e6 13.3 / 12.5, of 200 8.0e5 8.7 / 8.9
-// 1.0e6 9.3 / 9.0   1.3e6 10.5 / 9.8   2.0e6 13.6 / 12.8, of 400 1.5e6 17.0 / 16.4.
-constexpr uint32_t kPacedTiles = 5u << 9;          // 1.3e6 elements
+// a lane takes, 0: not so.  One tensor's that give no compute unit more than eight have all loads up front, lists, whose lookups spread the
+// loads anyway, only where fine tiles fit; four quads stop paying at 14 on a compute unit.  Lists have tables of whole tiles, which are two quads;
+// with 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.  Step alone in us, all loads up front
+// (beyond kOneRoundTiles fine tiles) / paced, one tensor: 1.0e6 6.6 / 7.0   1.05e6 6.3 / 7.7   1.05e6 + 424 6.8 / 6.2   1.2e6 7.5 / 6.9   1.4e6 8.0 / 7.4
+// 1.6e6 9.5 / 8.2   1.8e6 10.5 / 9.1   2.1e6 11.5 / 10.2, three quads 2.3e6 12.6 / 11.3   3.0e6 15.9 / 14.7, four 3.3e6 17.7 / 16.1   3.6e6 18.8 / 17.4
+// 4.0e6 20.1 / 20.4, without copies 1.8e6 10.1 / 8.5; lists of 12 tensors 9.5e5 8.4 / 7.4   1.3e6 9.5 / 8.4   2.0e6 12.8 / 11.5, of 60 9.5e5 8.9 / 7.9
+// 2.0e6 13.3 / 12.5, of 200 8.0e5 8.7 / 8.9   9.5e5 9.1 / 8.4   1.3e6 10.5 / 9.8   2.0e6 13.6 / 12.8, of 400 1.5e6 17.0 / 16.4.
+// Stores are paced too in launches of more than so many workgroups, loads only / both: one tensor 1.2e6 6.9 / 7.3   1.5e6 7.8 / 8.0   1.95e6 9.8 / 9.9
+// 2.0e6 10.9 / 10.5   2.1e6 10.8 / 10.3   2.3e6 11.3 / 11.5   2.8e6 13.6 / 13.8   3.1e6 15.8 / 15.2   3.5e6 17.1 / 17.3; 12 tensors 9.5e5 7.4 / 7.7   1.4e6
+// 9.3 / 9.2   1.7e6 10.3 / 10.0   2.0e6 12.0 / 11.5, four in arrays of their own 1.4e6 8.2 / 8.4   1.6e6 9.0 / 9.1   2.0e6 11.2 / 10.9.
+constexpr uint32_t kPacedTiles = 1u << 11;         // 1.0e6 elements
 constexpr uint32_t kMostPacedTiles = 7u << 10;     // 3.7e6 elements
+constexpr uint32_t kPacedStoresOne = 15u << 8, kPacedStoresList = 11u << 8;
 constexpr int kMostPaced = 4;
 inline int paced_quads(uint32_t n_tiles, Steps kind)
 {

@@ -398,14 +398,14 @@ __device__ __forceinline__ void step_fine_tile(GlobalF4 __restrict__ p4, GlobalF
     ends.update(gscale, c);
 }
 
-// Two quads a lane or, of one tensor, up to four, at a measured pace: a quad's loads are asked for when those before have arrived, and its stores
-// when those before are done.  Bound: HBM.  Where all workgroups of a launch are resident at once, all of them then read at the same time
-// and write at the same time, with a quarter to a half of the requests in the queues (paced_quads): 5.4 to 5.8 TB/s on 1.6e6 to 3.0e6 elements,
-// where all loads up front and fine tiles reach 4.7 to 5.3.
+// Two quads a lane or, of one tensor, up to four, at a measured pace: a quad's loads are asked for when those before have arrived and, where the
+// chip is nearly full (paced_stores), its stores when those before are done.  Bound: HBM.  Where all workgroups of a launch are resident
+// at once, all of them then read at the same time and write at the same time, with a quarter to a half of the requests in the queues
+// (paced_quads): 5.4 to 5.8 TB/s on 1.6e6 to 3.0e6 elements, where all loads up front and fine tiles reach 4.7 to 5.3.
 template <int DT, bool L2, int QUADS>
 __device__ __forceinline__ void step_paced_tile(GlobalF4 __restrict__ p4, GlobalF4 __restrict__ m4, GlobalF4 __restrict__ v4,
                                                 GlobalConstU2 __restrict__ g2, GlobalU2 __restrict__ lp2, uint32_t head,
-                                                uint32_t tail, uint32_t ti, uint32_t nquad, float gscale, const StepConsts& c)
+                                                uint32_t tail, uint32_t ti, uint32_t nquad, bool paced_stores, float gscale, const StepConsts& c)
 {
     StepEnds<DT, L2> ends(p4, m4, v4, g2, lp2, ti == 0 ? head : 0, ti == 0 ? tail : 0, nquad);
     const uint32_t q0 = ti * (kStepThreads * QUADS) + threadIdx.x;
@@ -428,7 +428,7 @@ __device__ __forceinline__ void step_paced_tile(GlobalF4 __restrict__ p4, Global
 #pragma unroll
     for (int u = 0; u < QUADS; ++u) {
         constexpr int kNoMemoryAccessLeft = 0x0F70;       // vmcnt(0): loads and stores
-        if (u > 0) __builtin_amdgcn_s_waitcnt(kNoMemoryAccessLeft);
+        if (u > 0 && paced_stores) __builtin_amdgcn_s_waitcnt(kNoMemoryAccessLeft);
         __builtin_amdgcn_sched_barrier(0);
         const uint32_t i = q0 + u * kStepThreads;
         const u32x2 lp = step_quad<DT, L2>(p[u], m[u], v[u], g[u], gscale, c);
@@ -515,7 +515,7 @@ __device__ __forceinline__ void step_one(const StepOne& a)
     if constexpr (FINE) {
         step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, false, gscale, c);
     } else if constexpr (PACED) {
-        step_paced_tile<DT, L2, PACED>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, gscale, c);
+        step_paced_tile<DT, L2, PACED>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, n_tiles > kPacedStoresOne, gscale, c);
     } else {
         if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
         step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
@@ -624,7 +624,7 @@ __device__ __forceinline__ void step_list(const Args& a)
     } else if constexpr (PACED) {
         uint32_t head = 0, tail = 0;
         if (tile == 0) head = (uint32_t)head_of(a, d), tail = (uint32_t)tail_of(a, d);
-        step_paced_tile<DT, L2, kStepUnroll>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, gscale, c);
+        step_paced_tile<DT, L2, kStepUnroll>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, gridDim.x > kPacedStoresList, gscale, c);
     } else {
         if (tile == 0) step_ends<DT, L2>(T, head_of(a, d), (int64_t)nquad * kQuad, tail_of(a, d), gscale, c);
         step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);

@@ -10,10 +10,10 @@ from gpu_util import NormBuffers, zi_cfg
 from test_gpu_fine_tiles import ONE_ROUND, SHORT, TILE, pieces, random_state, step_with_oracle
 
 pytestmark = pytest.mark.gpu
-PACED, MOST = 5 << 9, 7 << 10                                           # kPacedTiles, kMostPacedTiles
+PACED, STORES, MOST = 1 << 11, 15 << 8, 7 << 10                         # kPacedTiles, kPacedStoresOne, kMostPacedTiles
 
 
-@pytest.mark.parametrize("tiles", [PACED, ONE_ROUND, 3 << 11, MOST])
+@pytest.mark.parametrize("tiles", [PACED, STORES, ONE_ROUND, 3 << 11, MOST])
 @pytest.mark.parametrize("beyond,offset", [(0, 0), (1, 0), (4, 0), (259, 0), (66, 1)])
 def test_one_tensor_around_the_lines(tiles, beyond, offset):
     n = tiles * TILE + beyond
@@ -28,7 +28,7 @@ def test_arrays_that_start_anywhere():
 # Cuts around a few elements leave tensors without a body among the others.
 @pytest.mark.parametrize("copies", [True, False])
 @pytest.mark.parametrize("count", [2, 20, 50, 200])
-@pytest.mark.parametrize("tiles", [SHORT, 3000, ONE_ROUND - 60])
+@pytest.mark.parametrize("tiles", [SHORT, 2700, ONE_ROUND - 60])
 def test_lists_give_the_bits_of_short_launches(tiles, count, copies):
     n = tiles * TILE + 65
     state = random_state(n, n + count)
