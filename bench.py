@@ -30,7 +30,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 BYTES_PER_ELEM_STEP = 28       # read p, m, v (4 B each) + g (2 B); write p, m, v + 2-byte copy
 BYTES_PER_ELEM_NORM = 2
-TRAFFIC_FILE = os.path.join("profiles", "adamw_wide_kernel_c1_hbm_traffic.txt")
+TRAFFIC_FILE = os.path.join("profiles", "adamw_fine_kernel_c1_hbm_traffic.txt")
 
 
 def log(msg):
@@ -245,7 +245,7 @@ def resident(args, torch, zi, zs):
     norm_gbps = BYTES_PER_ELEM_NORM * n / (n_avg * 1e-3) / 1e9
     out = dict(
         n=n, sec_per_step=sec_per_step, parity=parity, cpu=cpu,
-        roofline=dict(bound="hbm", kernel="adamw_wide_kernel", achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
+        roofline=dict(bound="hbm", kernel="adamw_fine_kernel", achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
                       unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic,
                       traffic_source=traffic_source, bytes_per_launch=BYTES_PER_ELEM_STEP * n,
                       kernel_ms=round(k_avg, 4), kernel_ms_min=round(min(k_ms), 4),
@@ -350,7 +350,7 @@ def extra_c3(args, torch, zi, zs):
                    skipped_step_ms=round(skip_ms, 4)),
         run_b=dict(norm=norm, clip=min(1.0, w["max_grad_norm"] / (norm + 1e-6)), parity=rec,
                    params_per_s=n / sec, ms_per_step=sec * 1e3,
-                   roofline=dict(bound="hbm", kernel="adamw_wide_kernel (fp16)", achieved=round(ach, 1),
+                   roofline=dict(bound="hbm", kernel="adamw_fine_kernel (fp16)", achieved=round(ach, 1),
                                  peak=HBM_PEAK_GBS, unit="GB/s", frac=round(ach / HBM_PEAK_GBS, 4),
                                  kernel_ms=round(k_avg, 4), kernel_ms_min=round(min(k_ms), 4)),
                    norm_ms=round(n_avg, 4), norm_GBps=round(2 * n / (n_avg * 1e-3) / 1e9, 1)),

@@ -192,7 +192,7 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
-// One tensor (adamw_short_kernel, adamw_fine_kernel), in few bytes: a call on a short one takes the host longer than the GPU, and what the runtime takes
+// One tensor (adamw_short_kernel, adamw_fine_kernel, adamw_paced_kernel), in few bytes: a call on a short one takes the host longer than the GPU, and what the runtime takes
 // for a launch depends on the size of its arguments.  Issue of an empty kernel in us (the runtime runs in one of two modes for
 // the life of a process): up to 112 bytes 2.4 or 2.8, 120 to 1024 bytes 2.5 or 3.5 to 3.7, StepArgs' 2.5 KB 2.55 or 3.75, 3.6 KB and
 // more 2.55 or 3.8 to 4.1.
@@ -223,7 +223,7 @@ inline void set_scalars(StepOne& a, const StepConsts& c, bool l2, const zi_norm_
     a.loss_scale = c.loss_scale; a.max_grad_norm = c.max_grad_norm; a.host_gscale = c.host_gscale;
 }
 
-// Launches over many tensors (adamw_list_kernel), which a workgroup looks up in groups.  A list whose tensors are
+// Launches over many tensors (adamw_list_kernel, adamw_fine_list_kernel, adamw_paced_list_kernel), which a workgroup looks up in groups.  A list whose tensors are
 // views at the same places of five flat buffers, as the partitions of a sharded optimizer are, needs one place per
 // tensor (FlatArgs); any other list five addresses (ListArgs).
 struct ListDesc {
