@@ -53,6 +53,13 @@ constexpr unsigned kStepLds20 = 8 * 1024, kStepLds16 = 10 * 1024, kStepLds14 = 1
 // 113 / 115; flat lists of 4.0e6 23.6 / 23.1 / 22.9 / 22.6 / 21.9 / 21.7, of 3.0e7 149 / 145 / 145 / 141 / 141 / 139.
 constexpr int kFineTileQuads = kStepThreads;
 constexpr int64_t kFineXcdRun = 1024;
+// Lists whose tensors are arrays of their own go in runs all the same: allocators put such arrays of some MB at the same place of their
+// pages, and in plain order all wavefronts then meet on the same channels.  Of views of common buffers the
+// order hardly matters or plain is better.  Step alone in us, whole tiles / fine in plain order / in runs of 128 / 512 /
+// 1024, own arrays: 21 of 4.0e6 384 / 416 / 379 / 383 / 394, 60 of 4.0e6 1095 / 1151 / 1085 / 1096 / 1113, 30 of 8.0e6 1080 / 1136 / 1084 / 1072 / 1084, 60 of
+// 2.0e6 536 / 526 / 536 / 529 / 526, 40 of 3.3e6 600 / 585 / 603 / 594 / 586, 15 of 2.0e7 1346 / 1356 / 1361 / 1355 / 1349; views: 40 of 4.2e6 737 / 720 / 739 / 746 /
+// 743, 60 of 4.0e6 1078 / 1033 / 1070 / 1043 / 1038.
+constexpr int64_t kFineListRun = 512;
 constexpr uint32_t kFineShortTiles = 7u << 8;      // 9.2e5 elements
 constexpr uint32_t kOneRoundTiles = 1u << 12;      // 2.1e6 elements: 16 workgroups on every compute unit
 constexpr uint32_t kFineRunTiles = 1u << 15;       // 1.7e7 elements

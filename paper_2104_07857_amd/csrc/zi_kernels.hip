@@ -572,7 +572,7 @@ __device__ __forceinline__ int64_t tail_of(const FlatList<GROUPS>& a, uint32_t d
 // a launch for every tensor of 2^22 elements and shared ones for the rest (adamw_wide_kernel):
 // 72 tensors of 3.0e8 elements 1417 -> 1358 without clipping and 1366 with, 288 tensors of 3.0e8 1470 -> 1396,
 // 200 of 1..40,000 45.6 -> 35.3, as FlatArgs 25.3; with the norm result fetched after the descriptor 1478 instead of 1366.
-template <int DT, bool L2, bool FINE, bool PACED, typename Args>
+template <int DT, bool L2, bool FINE, bool PACED, typename Args, bool RUNS = false>
 __device__ __forceinline__ void step_list(const Args& a)
 {
     constexpr uint32_t kParts = FINE ? kStepTileQuads / kFineTileQuads : 1;     // workgroups to a tile
@@ -614,12 +614,14 @@ __device__ __forceinline__ void step_list(const Args& a)
     asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
     if (d_norm && raw[4]) return;
 
-    const uint32_t tile = FINE ? blockIdx.x - first * kParts
-                               : tile_of_block(block, first, (nquad + kStepTileQuads - 1) / kStepTileQuads);
+    const uint32_t n_tiles = kParts * ((nquad + kStepTileQuads - 1) / kStepTileQuads);
+    const uint32_t tile = !FINE  ? tile_of_block(block, first, n_tiles)
+                          : RUNS ? tile_of_block<kFineListRun>(blockIdx.x, first * kParts, n_tiles)
+                                 : blockIdx.x - first * kParts;
     if constexpr (FINE) {
         uint32_t head = 0, tail = 0;
         if (tile == 0) head = (uint32_t)head_of(a, d), tail = (uint32_t)tail_of(a, d);
-        const bool last = tile + 1 == kParts * ((nquad + kStepTileQuads - 1) / kStepTileQuads);
+        const bool last = tile + 1 == n_tiles;
         step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, head, tail, tile, nquad, last, gscale, c);
     } else if constexpr (PACED) {
         uint32_t head = 0, tail = 0;
@@ -634,8 +636,8 @@ template <int DT, bool L2, typename Args>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
 void adamw_list_kernel(const Args a) { step_list<DT, L2, false, false>(a); }
 // (a tile's halves are neighbouring workgroups, so the tables of starts count whole tiles for both kernels)
-template <int DT, bool L2, typename Args>
-__global__ __launch_bounds__(kStepThreads) void adamw_fine_list_kernel(const Args a) { step_list<DT, L2, true, false>(a); }
+template <int DT, bool L2, bool RUNS, typename Args>
+__global__ __launch_bounds__(kStepThreads) void adamw_fine_list_kernel(const Args a) { step_list<DT, L2, true, false, Args, RUNS>(a); }
 template <int DT, bool L2, typename Args>
 __global__ __launch_bounds__(kStepThreads) void adamw_paced_list_kernel(const Args a) { step_list<DT, L2, false, true>(a); }
 
@@ -684,6 +686,22 @@ hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hi
 }
 
 static bool has_copies(const ListArgs& a) { return a.t[0].lp_body; }
+// Whether the tensors are arrays of their own (kFineListRun), whose p, m and v lie between one another's, and not views of three common buffers.
+static bool has_own_arrays(const ListArgs& a, uint32_t n_tensors)
+{
+    uintptr_t lo[3], hi[3];
+    for (uint32_t i = 0; i < n_tensors; ++i) {
+        const uintptr_t at[3] = {(uintptr_t)a.t[i].p_body, (uintptr_t)a.t[i].m_body, (uintptr_t)a.t[i].v_body};
+        for (int w = 0; w < 3; ++w) {
+            lo[w] = i == 0 ? at[w] : std::min(lo[w], at[w]);
+            hi[w] = i == 0 ? at[w] : std::max(hi[w], at[w]);
+        }
+    }
+    const auto meet = [&](int x, int y) { return lo[x] < hi[y] && lo[y] < hi[x]; };
+    return n_tensors > 1 && (meet(0, 1) || meet(0, 2) || meet(1, 2));
+}
+template <int GROUPS>
+static bool has_own_arrays(const FlatList<GROUPS>&, uint32_t) { return false; }
 template <int GROUPS>
 static bool has_copies(const FlatList<GROUPS>& a) { return a.lp; }
 
@@ -695,12 +713,17 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
     const uint32_t n_tensors = (uint32_t)(std::lower_bound(a.first_tile, a.first_tile + Args::kMax, 0xFFFFFFFFu) - a.first_tile);
     const bool paced = paced_quads(n_tiles, kind);
     const bool fine = !paced && fine_tiles(n_tiles, kind, has_copies(a), n_tensors);
+    constexpr bool kMayRun = std::is_same_v<Args, ListArgs>;
+    const bool runs = kMayRun && fine && n_tiles >= kXcds * kFineListRun / (kStepTileQuads / kFineTileQuads) && has_own_arrays(a, n_tensors);
     const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
     const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
     const auto of = [=](auto dt_, auto l2_) {
         constexpr int DT = decltype(dt_)::value;
         constexpr bool L2 = decltype(l2_)::value;
-        return paced ? adamw_paced_list_kernel<DT, L2, Args> : fine ? adamw_fine_list_kernel<DT, L2, Args> : adamw_list_kernel<DT, L2, Args>;
+        return paced   ? adamw_paced_list_kernel<DT, L2, Args>
+               : !fine ? adamw_list_kernel<DT, L2, Args>
+               : runs  ? adamw_fine_list_kernel<DT, L2, kMayRun, Args>
+                       : adamw_fine_list_kernel<DT, L2, false, Args>;
     };
     return launch(instance(of, dt, l2), grid, block, lds, s, a, any_order);
 }

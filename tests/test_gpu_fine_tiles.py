@@ -111,3 +111,19 @@ def test_overflow_skips_fine_tiles(n, count):
     zi.zi_adamw_step(pieces(state, cuts), zi.ZI_BF16, zi_cfg(zi_synth.workload("c4")), nb.out)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(state, before))
+
+
+# Arrays of their own are dealt out in runs of XCDs: tensors with no run, one and several, at any place of the launch.
+@pytest.mark.parametrize("lengths", [[4_000_000, 1_100_001, 3_000_000], [5, 2_200_003, 70, 9_000_001, 1]])
+def test_arrays_of_their_own_give_the_bits_of_views(lengths):
+    n = sum(lengths)
+    state = random_state(n, n)
+    cuts = [0] + np.cumsum(lengths).tolist()
+    own = [tuple(x.clone() if torch.is_tensor(x) else x for x in t) for t in pieces(state, cuts)]
+    cfg = zi_cfg(zi_synth.workload("c1"))
+    zi.zi_adamw_step(own, zi.ZI_BF16, cfg)
+    for part in pieces(state, list(range(0, n, 800_000)) + [n]):
+        zi.zi_adamw_step([part], zi.ZI_BF16, cfg)
+    torch.cuda.synchronize()
+    for w, whole in enumerate(state):
+        assert torch.equal(torch.cat([t[w] for t in own]), whole), "p m v g lp".split()[w]
