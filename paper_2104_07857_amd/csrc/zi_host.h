@@ -270,8 +270,10 @@ struct StepIssuer {
     // 3.5, 60 of 3.0e4 13.1 -> 10.2, 48 of 2.6e5 69.4 -> 66.6; one launch either way, 24 of 1.0e5 13.0 / 13.4).  Four times as many to a launch
     // save 3 us each time, and twice as many entries in the lookup cost every workgroup some 4%.  Step alone, us, list /
     // flat: 200 tensors of 2e4 elements 35.3 / 25.3, 1000 of 1e5 512 / 480, 288 of 2.6e5 361 / 352, 288 of 1.0e6
-    // 1368 / 1427, 72 of 4.2e6 1363 / 1420: the line is drawn at an average of 5 * 2^16.
-    static constexpr int64_t kFlatAverage = 5 << 16;
+    // 1368 / 1427, 72 of 4.2e6 1363 / 1420: the line is drawn at an average of 5 * 2^16.  In fine tiles, with copies, the lookup costs less:
+    // 200 of 5e5 450 / 438, a decoder's 144 at hidden size 768 375 / 370, 288 of 1.0e6 1257 / 1257, without copies 90 of 9e5 332 / 335:
+    // lists that are several launches either way have the line at 2^20.
+    static constexpr int64_t kFlatAverage = 5 << 16, kFlatCopiesAverage = 1 << 20;
     // Shorter lists with several long tensors among few short ones, as a few layers of a decoder are, take `list` too: a launch
     // of its own for every long tensor pays a start and an end each time, which shows up to 2^25 elements on average, and beyond
     // that the longer lookup does.  Step alone, us, own launches / list: 2 tensors of 5e6 50.4 / 47.6, 8 of 5e6 198 / 180, 30 of 1e7
@@ -287,13 +289,16 @@ struct StepIssuer {
     void expect(const zi_tensor* t, int32_t n_tensors)
     {
         int64_t n = 0, n_long = 0, total = 0;
+        bool copies = false;
         for (int32_t i = 0; i < n_tensors; ++i) {
             n += t[i].numel > 0;
+            copies |= t[i].numel > 0 && t[i].p_lp;
             n_long += t[i].numel >= kSoloTiles * zi::kStepTileElems;
             total += t[i].numel;
         }
         if (n < 2) return;
-        const bool short_and_flat = n > zi::kMaxStepDesc && total / n <= kFlatAverage && is_flat(t, n_tensors, flat);
+        const bool short_and_flat = n > zi::kMaxStepDesc && total / n <= (copies && n > zi::kMaxListDesc ? kFlatCopiesAverage : kFlatAverage) &&
+                                    is_flat(t, n_tensors, flat);
         const bool middling = n_long >= 2 && n_long >= n / 8 && total / n <= kListAverage;
         if (!short_and_flat && !middling && n <= zi::kMaxListDesc) return;
         kind = short_and_flat ? kFlat : kList;

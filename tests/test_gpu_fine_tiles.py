@@ -127,3 +127,17 @@ def test_arrays_of_their_own_give_the_bits_of_views(lengths):
     torch.cuda.synchronize()
     for w, whole in enumerate(state):
         assert torch.equal(torch.cat([t[w] for t in own]), whole), "p m v g lp".split()[w]
+
+
+# More than 64 flat tensors of up to 2^20 elements on average go 256 to a launch.
+@pytest.mark.parametrize("lengths", [[400_000] * 64, [400_000] * 66, [5, 800_003] * 33])
+def test_shared_launches_give_the_bits_of_single_ones(lengths):
+    n = sum(lengths)
+    state = random_state(n, len(lengths))
+    whole = [x.clone() for x in state]
+    cfg = zi_cfg(zi_synth.workload("c1"))
+    zi.zi_adamw_step(pieces(state, [0] + np.cumsum(lengths).tolist()), zi.ZI_BF16, cfg)
+    for part in pieces(whole, list(range(0, n, 800_000)) + [n]):
+        zi.zi_adamw_step([part], zi.ZI_BF16, cfg)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(state, whole))
