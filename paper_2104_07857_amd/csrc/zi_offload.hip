@@ -259,20 +259,29 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     const std::vector<Segment>& segs = e->segs;
     const std::vector<size_t>& use_begin = e->use_begin;
 
+    // The flag and the sum of squares come to the host first: a skipped step touches, moves and waits for nothing else.
     zi::StepConsts k = make_consts(*cfg);
     float gscale = k.host_gscale;
+    if (d_norm) {
+        if (zi_status st = read_norm(e, d_norm, user)) return st;
+        if (e->h_norm->found_inf) return ZI_SKIPPED_OVERFLOW;
+        gscale = gradient_factor(e->h_norm->sumsq, k);
+    }
     // Gradient offloads on their way to host memory are complete before the CPUs read them, and gradients
-    // produced on the caller's stream before they are fetched.
+    // produced on the caller's stream before they are fetched (where the norm is here, that stream has been waited for).
     ZI_HIP(wait_for_offloads(e));
     e->offload_pending = false;
-    ZI_HIP(hipEventRecord(e->ev_in, user));
-    if (any_device) ZI_HIP(hipStreamWaitEvent(e->s_d2h, e->ev_in, 0));
+    if (!d_norm) {
+        ZI_HIP(hipEventRecord(e->ev_in, user));
+        if (any_device) ZI_HIP(hipStreamWaitEvent(e->s_d2h, e->ev_in, 0));
+    }
 
     const auto t0 = std::chrono::steady_clock::now();
-    // Around the uses, what the host waits for is the norm result and the last upload: with two stream waits in front, an event for the caller's
-    // stream and a wait for the fetches behind, and the norm read before anything was fetched, a call on 1000 elements took 118 us instead of 54,
-    // 5.0e4 118 / 81, 3.0e5 144 / 124, 1.5e6 305 / 271, 4.0e6 599 / 573, 1.7e7 1980..2000 / 1889..1953, 140 tensors with 1.4e6 530 / 452 (16 threads;
-    // jobs of few tasks without the whole pool are in that).
+    // Around the uses, the host waits for the norm result and for the last upload, and the engine's streams for nothing: with the runtime's copy of
+    // the result, stream waits behind an event for the caller's stream, an event in front of what follows on it, and a wait for the fetches, a
+    // call took, in us (16 threads, ordinary state; jobs of few tasks without the whole pool are in that), 1000 elements 110 / 34, 5.0e4 108 / 55,
+    // 3.0e5 140 / 102, 1.5e6 315 / 293, from 1.7e7 on no difference beyond that of two runs.  Fetching in front of the flag's way to
+    // the host made 1000 elements 57, and a skipped step 40 (one use) to 1290 (two uses of 2^24) where it takes 12.
     // Ring slot u mod n_h carries slot use u: its gradient half is filled by a kernel that reports every block
     // (link_copy_kernel), the CPUs step the use (reading that half, writing the copy half), and the copy half is
     // sent up by the same kind of kernel or by the runtime's copy (kUploadBlocks; arrays of another device).
@@ -316,14 +325,8 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
         for (int64_t u = 0; u < n_uses && u < ahead; ++u)
             if (zi_status st = fetch(u)) return st;
         // One thread waits for the gradients' producer, and for whoever still reads the copy, not all of them; from here on the caller's
-        // stream is no one's to wait for.  The flag and the sum of squares come to the host before anything of the caller's changes.
-        if (d_norm) {
-            if (zi_status st = read_norm(e, d_norm, user)) return st;
-            if (e->h_norm->found_inf) return ZI_SKIPPED_OVERFLOW;
-            gscale = gradient_factor(e->h_norm->sumsq, k);
-        } else {
-            ZI_HIP(hipEventSynchronize(e->ev_in));
-        }
+        // stream is no one's to wait for.
+        if (!d_norm) ZI_HIP(hipEventSynchronize(e->ev_in));
         for (int64_t u = 0; u < n_uses; ++u) {
             if (u + ahead < n_uses)
                 if (zi_status st = fetch(u + ahead)) return st;
@@ -372,10 +375,6 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     };
     const zi_status st = pipeline();
     if (st != ZI_OK) drain_streams(e);
-    if (st == ZI_SKIPPED_OVERFLOW) {
-        e->stats = zi_stream_stats{};
-        return st;
-    }
     e->stats.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return st;
     ZI_GUARD_END

@@ -28,6 +28,8 @@ const char* kernel_names[256];
 int n_kernels = 0;
 int current_device = 0;
 int n_launches = 0, n_copies = 0, n_faults = 0;
+uint64_t bytes_moved = 0;                                       // by the runtime's copies and link_copy_kernel
+int n_waits = 0;                                                // for events, by the host
 int n_link_steps = 0;                                           // launches of the step over the link
 uint32_t most_link_tiles = 0;                                   // of one of them
 int64_t all_link_tiles = 0;
@@ -75,6 +77,7 @@ void run_link_copy(const zi::CopyArgs& a, int device, bool report)
         const zi::CopySeg& s = a.t[i];
         if (!reachable(s.src, (size_t)s.elems * 2, device) || !reachable(s.dst, (size_t)s.elems * 2, device)) ++n_faults;
         memcpy(s.dst, s.src, (size_t)s.elems * 2);
+        bytes_moved += (size_t)s.elems * 2;
         for (int64_t k = 0; report && k * block < s.elems; ++k) __atomic_store_n(a.flags + s.flag + k, a.serial, __ATOMIC_RELEASE);
     }
 }
@@ -167,6 +170,7 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDevicept
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t)
 {
     ++n_copies;
+    bytes_moved += n;
     memcpy(dst, src, n);
     return hipSuccess;
 }
@@ -189,7 +193,7 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st)
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)(events + n_events++); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { ++n_waits; return hipSuccess; }
 }
 
 #define CHECK(cond)                                                                                     \
@@ -381,6 +385,55 @@ static int replays()
     return 0;
 }
 
+// A skipped step of the CPU placement moves the norm result and nothing else, wherever that and the gradients are, reports no
+// traffic, and does not wait for gradients that are still being offloaded.  The step after it is made as if there had been none.
+static int skipped()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    CHECK(zi_engine_set_option(e, ZI_OPT_HOST_RING_SLOTS, 6) == ZI_OK);
+    const zi_adamw_config c = config();
+    uint16_t* parts[2] = {(uint16_t*)on_device(4000, 0), (uint16_t*)on_device(4000, -1)};
+    for (int norm_on : {0, 1, -1})
+        for (int grads_on : {0, 1, -1})
+            for (int offloads = 0; offloads < 2; ++offloads)
+                for (int64_t n : {(int64_t)5, (int64_t)16384, (int64_t)9 * 16384 + 3}) {
+                    std::vector<float> state[4];
+                    for (int w = 0; w < 4; ++w) state[w].assign((size_t)n, 0.25f * (float)(w + 1));
+                    zi_tensor t{};
+                    t.p = state[0].data(); t.m = state[1].data(); t.v = state[2].data();
+                    t.g = on_device((size_t)n * 2, grads_on);
+                    t.p_lp = on_device((size_t)n * 2, 0);
+                    t.numel = n;
+                    zi_norm_result* norm = (zi_norm_result*)on_device(sizeof(zi_norm_result), norm_on);
+                    norm->found_inf = 1;
+                    if (offloads) CHECK(zi_grad_offload(e, parts[0], parts[1], 4000, nullptr) == ZI_OK);
+                    bytes_moved = 0;
+                    n_waits = 0;
+                    CHECK(zi_adamw_step_cpu(e, &t, 1, ZI_BF16, &c, norm, 3, nullptr) == ZI_SKIPPED_OVERFLOW);
+                    CHECK(bytes_moved == sizeof(zi_norm_result));
+                    CHECK(n_waits == 0);
+                    zi_stream_stats st{};
+                    CHECK(zi_engine_last_stats(e, &st) == ZI_OK);
+                    CHECK(st.bytes_d2h == 0 && st.bytes_h2d == 0 && st.n_copies == 0 && st.n_slot_uses == 0 && st.seconds == 0.0);
+                    for (int w = 0; w < 3; ++w)
+                        for (float x : state[w]) CHECK(x == 0.25f * (float)(w + 1));
+                    for (int64_t i = 0; i < n; ++i) CHECK(((uint16_t*)t.p_lp)[i] == 0);
+                    norm->found_inf = 0;
+                    CHECK(zi_adamw_step_cpu(e, &t, 1, ZI_BF16, &c, norm, 3, nullptr) == ZI_OK);
+                    CHECK(offloads == 0 || n_waits > 0);
+                    CHECK(zi_engine_last_stats(e, &st) == ZI_OK && st.bytes_d2h == (grads_on < 0 ? 0 : 2 * (uint64_t)n) && st.bytes_h2d == 2 * (uint64_t)n);
+                    for (float x : state[0]) CHECK(x < 0.25f && x == state[0][0]);
+                    for (int64_t i = 0; i < n; ++i) CHECK(((uint16_t*)t.p_lp)[i] == ((uint16_t*)t.p_lp)[0] && ((uint16_t*)t.p_lp)[i] != 0);
+                    release(const_cast<void*>(t.g));
+                    release(t.p_lp);
+                    release(norm);
+                }
+    CHECK(n_faults == 0);
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 // How the copies of the CPU placement go up: what one slot use takes, by kernels, except that of a use of one segment of
 // at most 64 blocks with more uses behind it.
 static int uploads()
@@ -536,7 +589,7 @@ static int link_tiles()
 
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"skipped", skipped}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");

@@ -1,5 +1,7 @@
 """The step on the host CPUs: what it does around the step itself (the norm result's way, a skipped step, calls that follow
 one another through the same ring)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -79,4 +81,56 @@ def test_a_captured_stream_is_refused():
         torch.cuda.synchronize()
         assert float(x.sum()) == 8.0
     finally:
+        zi.zi_engine_destroy(e)
+
+
+def with_infinity(n):
+    """A tensor of n zero gradients but for an infinity, host state that nobody has touched, and the norm result of it."""
+    g = torch.zeros(n, dtype=torch.int16, device="cuda:0")
+    g[n // 2] = 0x7F80
+    state = [torch.zeros(n) for _ in range(3)]
+    lp, nb = torch.zeros(n, dtype=torch.int16, device="cuda:0"), NormBuffers()
+    tensors = [(*state, g, lp, n)]
+    zi.zi_grad_norm(tensors, zi.ZI_BF16, 1.0, nb.out, nb.ws)
+    torch.cuda.synchronize()
+    return tensors, nb
+
+
+# Twelve uses of 8.4 MB may be fetched ahead: 100 MB, which take 1.7 ms over the link (57 GB/s).  A round trip takes some 0.05.
+def test_a_skipped_step_takes_a_round_trip():
+    e = zi.zi_engine_create(0, 16 << 20, 3)
+    zi.zi_engine_set_option(e, zi.ZI_OPT_HOST_RING_SLOTS, 14)
+    try:
+        tensors, nb = with_infinity(12 << 22)
+        took = []
+        for _ in range(6):
+            t0 = time.perf_counter()
+            assert zi.zi_adamw_step_cpu(e, tensors, zi.ZI_BF16, zi.make_config(**config()), nb.out, 4) == zi.ZI_SKIPPED_OVERFLOW
+            took.append(time.perf_counter() - t0)
+        assert min(took) < 0.7e-3, took
+        assert not any(x.any() for x in tensors[0][:3]) and not tensors[0][4].any()
+    finally:
+        zi.zi_engine_destroy(e)
+
+
+def test_a_skipped_step_does_not_wait_for_offloads():
+    e = engine()
+    producer, user = torch.cuda.Stream(), torch.cuda.Stream()
+    src, dst = torch.ones(1000, device="cuda:0"), torch.zeros(1000, pin_memory=True)
+    a = torch.zeros(8192, 8192, device="cuda:0")
+    b = a @ a
+    try:
+        tensors, nb = with_infinity(1000)
+        with torch.cuda.stream(producer):            # some 0.2 s of products in front of the offload
+            for _ in range(20):
+                torch.matmul(a, a, out=b)
+            busy = torch.cuda.Event()
+            busy.record()
+        zi.zi_grad_offload(e, src, dst, 4000, producer)
+        assert zi.zi_adamw_step_cpu(e, tensors, zi.ZI_BF16, zi.make_config(**config()), nb.out, 2, user) == zi.ZI_SKIPPED_OVERFLOW
+        assert not busy.query()
+        zi.zi_grad_offload_wait(e)
+        assert busy.query() and bool((dst == 1).all())
+    finally:
+        torch.cuda.synchronize()
         zi.zi_engine_destroy(e)
