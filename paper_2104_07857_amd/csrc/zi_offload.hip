@@ -141,8 +141,10 @@ bool wait_arrived(const CpuJob& job, const uint32_t* flag)
 
 // Brings the norm result to e->h_norm and waits for it, and with it for everything on the stream so far.  A kernel raises a flag behind
 // its 32 bytes (the runtime's copy and the wait for its signal took 13.5 us); what it may not touch, or on another device's
-// stream, the runtime copies.
-zi_status read_norm(zi_engine* e, const zi_norm_result* d_norm, hipStream_t user)
+// stream, the runtime copies.  The flag says that earlier kernels have ended, and what they wrote in this device's memory is
+// there for the kernels to come; written to page-locked memory or to another device it is certain to be there only once the stream has been synchronised,
+// and then the runtime's copy in front of that is the quicker one (skipped step 14 us, with the kernel 17).
+zi_status read_norm(zi_engine* e, const zi_norm_result* d_norm, hipStream_t user, bool flag_is_enough)
 {
     int owner = -1;
     hipDevice_t on = e->device;
@@ -150,7 +152,7 @@ zi_status read_norm(zi_engine* e, const zi_norm_result* d_norm, hipStream_t user
     if (user && hipStreamGetDevice(user, &on) != hipSuccess) on = -1;
     if (on < 0) (void)hipGetLastError();
     HostNorm* const host = reinterpret_cast<HostNorm*>(e->h_norm);
-    if (kind == 0 && owner == e->device && on == e->device) {
+    if (flag_is_enough && kind == 0 && owner == e->device && on == e->device) {
         const uint32_t serial = ++e->norm_serial;
         CopyIssuer out(user, &host->arrived, serial);
         ZI_HIP(out.add((const uint16_t*)d_norm, (uint16_t*)e->h_norm, sizeof(zi_norm_result) / 2, 0));
@@ -206,6 +208,7 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     // p, m, v: host memory of any kind (the CPUs work on them in place).  g, p_lp: device memory
     // (staged through the pinned ring, chunk by chunk) or host memory (used in place).
     bool any_device = false;
+    bool all_here = true;         // p, m, v in ordinary memory, g and p_lp on this device: see read_norm
     PointerChecker reach;
     e->src.resize((size_t)n_tensors);
     for (int32_t i = 0; i < n_tensors; ++i) {
@@ -221,10 +224,12 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
             if (k0 == -2) return fail(ZI_ERR_HIP, "no usable HIP device (pointer query failed)");
             if ((k0 != 1 && k0 != 2) || k1 != k0)
                 return fail(ZI_ERR_INVALID_ARG, "tensor %d: p, m, v must be host memory", i);
+            all_here = all_here && k0 == 2;
         }
         int owner = e->device;
         const int gk = memory_kind(S.g, &owner);
         if (gk < 0) return fail(ZI_ERR_INVALID_ARG, "tensor %d: g is neither device nor host memory", i);
+        all_here = all_here && (gk == 2 || (gk == 0 && owner == e->device));
         if (gk == 0) {
             if (zi_status st = reach.check(S.g, n * 2, i, "g")) return st;
             S.g_host = false;
@@ -234,6 +239,7 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
         if (S.p_lp) {
             const int lk = memory_kind(S.p_lp, &owner);
             if (lk < 0) return fail(ZI_ERR_INVALID_ARG, "tensor %d: p_lp is neither device nor host memory", i);
+            all_here = all_here && (lk == 2 || (lk == 0 && owner == e->device));
             if (lk == 0) {
                 if (zi_status st = reach.check(S.p_lp, n * 2, i, "p_lp")) return st;
                 S.lp_host = false;
@@ -263,7 +269,7 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     zi::StepConsts k = make_consts(*cfg);
     float gscale = k.host_gscale;
     if (d_norm) {
-        if (zi_status st = read_norm(e, d_norm, user)) return st;
+        if (zi_status st = read_norm(e, d_norm, user, all_here)) return st;
         if (e->h_norm->found_inf) return ZI_SKIPPED_OVERFLOW;
         gscale = gradient_factor(e->h_norm->sumsq, k);
     }
@@ -280,7 +286,7 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     // Around the uses, the host waits for the norm result and for the last upload, and the engine's streams for nothing: with the runtime's copy of
     // the result, stream waits behind an event for the caller's stream, an event in front of what follows on it, and a wait for the fetches, a
     // call took, in us (16 threads, ordinary state; jobs of few tasks without the whole pool are in that), 1000 elements 110 / 34, 5.0e4 108 / 55,
-    // 3.0e5 140 / 102, 1.5e6 315 / 293, from 1.7e7 on no difference beyond that of two runs.  Fetching in front of the flag's way to
+    // 3.0e5 140 / 102, 1.5e6 315 / 293 (page-locked state 115 / 36, 114 / 57, 141 / 101, 297 / 253), from 1.7e7 on no difference beyond that of two runs.  Fetching in front of the flag's way to
     // the host made 1000 elements 57, and a skipped step 40 (one use) to 1290 (two uses of 2^24) where it takes 12.
     // Ring slot u mod n_h carries slot use u: its gradient half is filled by a kernel that reports every block
     // (link_copy_kernel), the CPUs step the use (reading that half, writing the copy half), and the copy half is

@@ -29,6 +29,8 @@ int n_kernels = 0;
 int current_device = 0;
 int n_launches = 0, n_copies = 0, n_faults = 0;
 uint64_t bytes_moved = 0;                                       // by the runtime's copies and link_copy_kernel
+int n_syncs = 0;                                                // of the stream `watched`
+hipStream_t watched = nullptr;
 int n_waits = 0;                                                // for events, by the host
 int n_link_steps = 0;                                           // launches of the step over the link
 uint32_t most_link_tiles = 0;                                   // of one of them
@@ -181,7 +183,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned)
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { n_syncs += s == watched; return hipSuccess; }
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = device_of(s); return hipSuccess; }
@@ -434,6 +436,43 @@ static int skipped()
     return 0;
 }
 
+// What earlier work on the caller's stream has written to page-locked memory or on another device is certain to be there only
+// after the stream has been synchronised: a flag that a later kernel raises is not enough.
+static int earlier_work()
+{
+    zi_engine* e = nullptr;
+    CHECK(zi_engine_create(&e, 0, 64 * 1024, 3) == ZI_OK);
+    CHECK(zi_engine_set_option(e, ZI_OPT_HOST_RING_SLOTS, 4) == ZI_OK);
+    CHECK(hipStreamCreateWithFlags(&watched, 0) == hipSuccess);
+    const zi_adamw_config c = config();
+    const int64_t n = 20000;
+    zi_norm_result* norm = (zi_norm_result*)on_device(sizeof(zi_norm_result), 0);
+    std::vector<float> state[3];
+    for (auto& x : state) x.assign((size_t)n, 0.5f);
+    for (int other = 0; other < 5; ++other)                        // p, m, v, g, p_lp
+        for (int on : {-1, 1}) {
+            if (other < 3 && on == 1) continue;
+            zi_tensor t[2]{};
+            for (zi_tensor& x : t) {
+                x.p = state[0].data(); x.m = state[1].data(); x.v = state[2].data();
+                x.g = on_device((size_t)n * 2, 0); x.p_lp = on_device((size_t)n * 2, 0);
+                x.numel = n / 2;
+            }
+            t[1].p = state[0].data() + n / 2; t[1].m = state[1].data() + n / 2; t[1].v = state[2].data() + n / 2;
+            void* there = on_device((size_t)n * 4, on);
+            void** const array[5] = {(void**)&t[1].p, (void**)&t[1].m, (void**)&t[1].v, (void**)&t[1].g, (void**)&t[1].p_lp};
+            *array[other] = there;
+            n_syncs = 0;
+            CHECK(zi_adamw_step_cpu(e, t, 2, ZI_BF16, &c, norm, 2, watched) == ZI_OK);
+            CHECK(n_syncs > 0);
+            release(const_cast<void*>(t[0].g));
+            release(t[0].p_lp);
+        }
+    CHECK(n_faults == 0);
+    CHECK(zi_engine_destroy(e) == ZI_OK);
+    return 0;
+}
+
 // How the copies of the CPU placement go up: what one slot use takes, by kernels, except that of a use of one segment of
 // at most 64 blocks with more uses behind it.
 static int uploads()
@@ -589,7 +628,7 @@ static int link_tiles()
 
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"skipped", skipped}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"skipped", skipped}, {"earlier_work", earlier_work}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");
