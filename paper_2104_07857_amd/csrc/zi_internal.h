@@ -32,9 +32,8 @@ constexpr int64_t kStepXcdRun = ZI_STEP_XCD_RUN;
 constexpr unsigned kStepLds20 = 8 * 1024, kStepLds16 = 10 * 1024, kStepLds14 = 11 * 1024, kStepLds12 = 13 * 1024, kStepLds7 = 22 * 1024 + 512;
 // Half a tile, one quad a lane (adamw_fine_kernel, adamw_fine_list_kernel): twice as many wavefronts with half as many loads
 // each, which live less than half as long, so that requests are spread more evenly over time and a launch's last round is shorter.
-// Which kernel a launch takes follows from its tiles.  Up to kFineShortTiles all of its fine workgroups are resident at once;
-// from there to kOneRoundTiles only those of whole tiles are (a tensor's up to kPacedTiles with all loads up front, else paced_quads()); beyond
-// those, fine ones again.  One tensor's runs of kFineXcdRun
+// Which kernel a launch takes follows from its tiles: fine ones up to kFineShortTiles, where all of its workgroups are resident at once with
+// some places to spare; from there on paced_quads(), as long as those are; beyond, fine ones again.  One tensor's runs of kFineXcdRun
 // fine tiles go to one XCD each in launches of up to kFineRunTiles; longer ones, and lists, are dealt out as they come: then all
 // eight XCDs walk the same few MiB of every array, and it matters little how the arrays lie to each other.
 // Step alone in us, whole / fine tiles (range over one to four placements of the arrays each), one tensor:
@@ -87,26 +86,26 @@ inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_ten
     return n_tiles <= kFineShortTiles || (n_tiles > kOneRoundTiles && n_tiles < kFineMostTiles);
 }
 // Launches whose workgroups are all resident at once (16 on a compute unit), at a measured pace (adamw_paced_kernel, adamw_paced_list_kernel): quads that
-// a lane takes, 0: not so.  One tensor's that give no compute unit more than eight have all loads up front, lists, whose lookups spread the
-// loads anyway, only where fine tiles fit; four quads stop paying at 14 on a compute unit.  Lists have tables of whole tiles, which are two quads;
-// with 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.  Step alone in us, all loads up front
-// (beyond kOneRoundTiles fine tiles) / paced, one tensor: 1.0e6 6.6 / 7.0   1.05e6 6.3 / 7.7   1.05e6 + 424 6.8 / 6.2   1.2e6 7.5 / 6.9   1.4e6 8.0 / 7.4
+// a lane takes, 0: not so.  Four quads stop paying at 14 on a compute unit.  Lists have tables of whole tiles, which are two quads;
+// with 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.  Where the line to fine tiles lies, one tensor at
+// seven placements of the arrays, fine / two quads / whole tiles with all loads up front, with 48 sets of arrays in turn: 9.5e5 5.4..6.0 / 5.9..6.5 /
+// 6.2..6.7, 1.0e6 5.9..6.7 / 6.0..6.7 / 6.3..6.9, 2^20 6.5..6.9 / 6.0..6.2 / 6.1..6.3, 1.05e6 + 424 6.7..6.9 / 6.0..6.2 / 6.8; with one set 2^20 4.8..4.9 /
+// 4.5..5.2 / 4.6..5.5.  Step alone in us, all loads up front
+// (beyond kOneRoundTiles fine tiles) / paced, one tensor: 1.2e6 7.5 / 6.9   1.4e6 8.0 / 7.4
 // 1.6e6 9.5 / 8.2   1.8e6 10.5 / 9.1   2.1e6 11.5 / 10.2, three quads 2.3e6 12.6 / 11.3   3.0e6 15.9 / 14.7, four 3.3e6 17.7 / 16.1   3.6e6 18.8 / 17.4
 // 4.0e6 20.1 / 20.4, without copies 1.8e6 10.1 / 8.5; lists of 12 tensors 9.5e5 8.4 / 7.4   1.3e6 9.5 / 8.4   2.0e6 12.8 / 11.5, of 60 9.5e5 8.9 / 7.9
 // 2.0e6 13.3 / 12.5, of 200 8.0e5 8.7 / 8.9   9.5e5 9.1 / 8.4   1.3e6 10.5 / 9.8   2.0e6 13.6 / 12.8, of 400 1.5e6 17.0 / 16.4.
 // Stores are paced too in launches of more than so many workgroups, loads only / both: one tensor 1.2e6 6.9 / 7.3   1.5e6 7.8 / 8.0   1.95e6 9.8 / 9.9
 // 2.0e6 10.9 / 10.5   2.1e6 10.8 / 10.3   2.3e6 11.3 / 11.5   2.8e6 13.6 / 13.8   3.1e6 15.8 / 15.2   3.5e6 17.1 / 17.3; 12 tensors 9.5e5 7.4 / 7.7   1.4e6
 // 9.3 / 9.2   1.7e6 10.3 / 10.0   2.0e6 12.0 / 11.5, four in arrays of their own 1.4e6 8.2 / 8.4   1.6e6 9.0 / 9.1   2.0e6 11.2 / 10.9.
-constexpr uint32_t kPacedTiles = 1u << 11;         // 1.0e6 elements
 constexpr uint32_t kMostPacedTiles = 7u << 10;     // 3.7e6 elements
 constexpr uint32_t kPacedStoresOne = 15u << 8, kPacedStoresList = 11u << 8;
 constexpr int kMostPaced = 4;
 inline int paced_quads(uint32_t n_tiles, Steps kind)
 {
-    if (kind != Steps::kOne) return n_tiles > kFineShortTiles && n_tiles <= kOneRoundTiles ? kStepUnroll : 0;
-    if (n_tiles <= kPacedTiles || n_tiles > kMostPacedTiles) return 0;
+    if (n_tiles <= kFineShortTiles || n_tiles > (kind == Steps::kOne ? kMostPacedTiles : kOneRoundTiles)) return 0;
     constexpr uint32_t per_quad = kOneRoundTiles / kStepUnroll;
-    return (int)((n_tiles + per_quad - 1) / per_quad);
+    return n_tiles <= kOneRoundTiles ? kStepUnroll : (int)((n_tiles + per_quad - 1) / per_quad);
 }
 inline unsigned fine_lds(uint32_t n_tiles, Steps kind, bool copies, bool norm)
 {
@@ -199,7 +198,7 @@ struct StepArgs {
     uint32_t first_tile[kMaxStepDesc];
 };
 
-// One tensor (adamw_short_kernel, adamw_fine_kernel, adamw_paced_kernel), in few bytes: a call on a short one takes the host longer than the GPU, and what the runtime takes
+// One tensor (adamw_fine_kernel, adamw_paced_kernel), in few bytes: a call on a short one takes the host longer than the GPU, and what the runtime takes
 // for a launch depends on the size of its arguments.  Issue of an empty kernel in us (the runtime runs in one of two modes for
 // the life of a process): up to 112 bytes 2.4 or 2.8, 120 to 1024 bytes 2.5 or 3.5 to 3.7, StepArgs' 2.5 KB 2.55 or 3.75, 3.6 KB and
 // more 2.55 or 3.8 to 4.1.

@@ -491,8 +491,8 @@ void adamw_wide_kernel(const StepArgs a)
     step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, a.c);
 }
 
-// One tensor, from arguments that are quickly written (StepOne).  FINE: one quad a lane instead of two.  PACED: so many, one after the other.
-template <int DT, bool L2, bool FINE, int PACED = 0>
+// One tensor, from arguments that are quickly written (StepOne), in fine tiles or PACED quads a lane.
+template <int DT, bool L2, int PACED>
 __device__ __forceinline__ void step_one(const StepOne& a)
 {
     const StepConsts c = {a.beta1, a.beta2, a.omb1, a.omb2, a.eps, a.step_size, a.inv_sqrt_bc2, L2 ? 0.0f : a.decay,
@@ -507,29 +507,24 @@ __device__ __forceinline__ void step_one(const StepOne& a)
     asm volatile("" : "+s"(p4), "+s"(m4), "+s"(v4), "+s"(g2), "+s"(lp2), "+s"(nquad));
     float gscale;
     if (!step_prologue(a.d_norm, c, gscale)) return;
-    constexpr uint32_t kTileQuads = PACED ? kStepThreads * PACED : kStepTileQuads;
-    const uint32_t n_tiles = FINE ? fine_count(nquad, fine_shift((uintptr_t)p4)) : (nquad + kTileQuads - 1) / kTileQuads;
-    const uint32_t tile = !FINE                                                           ? tile_of_block(blockIdx.x, 0, n_tiles)
-                          : n_tiles <= kFineRunTiles * (kStepTileQuads / kFineTileQuads) ? tile_of_block<kFineXcdRun>(blockIdx.x, 0, n_tiles)
-                                                                                          : blockIdx.x;
-    if constexpr (FINE) {
-        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, false, gscale, c);
-    } else if constexpr (PACED) {
+    if constexpr (PACED) {
+        constexpr uint32_t kTileQuads = kStepThreads * PACED;
+        const uint32_t n_tiles = (nquad + kTileQuads - 1) / kTileQuads;
+        const uint32_t tile = tile_of_block(blockIdx.x, 0, n_tiles);
         step_paced_tile<DT, L2, PACED>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, n_tiles > kPacedStoresOne, gscale, c);
     } else {
-        if (tile == 0) step_ends<DT, L2>(a, a.head, (int64_t)nquad * kQuad, a.tail, gscale, c);
-        step_tile<DT, L2>(p4, m4, v4, g2, lp2, tile, nquad, gscale, c);
+        const uint32_t n_tiles = fine_count(nquad, fine_shift((uintptr_t)p4));
+        const uint32_t tile = n_tiles <= kFineRunTiles * (kStepTileQuads / kFineTileQuads) ? tile_of_block<kFineXcdRun>(blockIdx.x, 0, n_tiles)
+                                                                                           : blockIdx.x;
+        step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, false, gscale, c);
     }
 }
-template <int DT, bool L2>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
-void adamw_short_kernel(const StepOne a) { step_one<DT, L2, false>(a); }
 // Bound: HBM, 28 bytes an element (26 without a copy); short ones: the latency of one round trip.  6.3 to 6.5 TB/s from 3e8 elements on, where
 // whole tiles reach 5.9 to 6.3, by the arrays' places (zi_internal.h, kFineTileQuads).
 template <int DT, bool L2>
-__global__ __launch_bounds__(kStepThreads) void adamw_fine_kernel(const StepOne a) { step_one<DT, L2, true>(a); }
+__global__ __launch_bounds__(kStepThreads) void adamw_fine_kernel(const StepOne a) { step_one<DT, L2, 0>(a); }
 template <int DT, bool L2, int QUADS>
-__global__ __launch_bounds__(kStepThreads) void adamw_paced_kernel(const StepOne a) { step_one<DT, L2, false, QUADS>(a); }
+__global__ __launch_bounds__(kStepThreads) void adamw_paced_kernel(const StepOne a) { step_one<DT, L2, QUADS>(a); }
 
 // n += block >= start; first = the start, if so.  Three scalar instructions; the compiler goes through a
 // vector register.
@@ -670,17 +665,15 @@ hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hi
     const uint32_t n_tiles = a.nquad / kStepTileQuads + (a.nquad % kStepTileQuads ? 1 : 0);
     const uint32_t n_fine = fine_count(a.nquad, fine_shift((uintptr_t)a.p_body));
     const int paced = paced_quads(n_tiles, Steps::kOne);
-    const bool fine = !paced && fine_tiles(n_tiles, Steps::kOne, a.lp_body, 1);
-    const dim3 grid(n_tiles < 1 ? 1 : fine ? n_fine : paced ? (a.nquad - 1) / (uint32_t)(paced * kStepThreads) + 1 : n_tiles);
-    const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm) : whole_tiles_lds(n_tiles);
+    const dim3 grid(n_tiles < 1 ? 1 : paced ? (a.nquad - 1) / (uint32_t)(paced * kStepThreads) + 1 : n_fine);
+    const unsigned lds = paced ? kStepLds16 : fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm);
     const auto of = [=](auto dt_, auto l2_) {
         constexpr int DT = decltype(dt_)::value;
         constexpr bool L2 = decltype(l2_)::value;
-        return paced == 2 ? adamw_paced_kernel<DT, L2, 2>
-               : paced == 3 ? adamw_paced_kernel<DT, L2, 3>
-               : paced ? adamw_paced_kernel<DT, L2, kMostPaced>
-               : fine ? adamw_fine_kernel<DT, L2>
-                      : adamw_short_kernel<DT, L2>;
+        return paced == 2            ? adamw_paced_kernel<DT, L2, 2>
+               : paced == 3          ? adamw_paced_kernel<DT, L2, 3>
+               : paced == kMostPaced ? adamw_paced_kernel<DT, L2, kMostPaced>
+                                     : adamw_fine_kernel<DT, L2>;
     };
     return launch(instance(of, dt, l2), grid, block, lds, s, a, any_order);
 }

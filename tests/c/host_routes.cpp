@@ -36,6 +36,8 @@ int n_link_steps = 0;                                           // launches of t
 uint32_t most_link_tiles = 0;                                   // of one of them
 int64_t all_link_tiles = 0;
 int n_flat_link_steps = 0;                                      // of them over flat lists
+const char* last_kernel = "";                                  // name and workgroups of the launch before
+uint32_t last_groups = 0;
 const char* last_partial_sum = "";                             // name of the partial-sum kernel launched last
 int n_partial_sums = 0, n_waiting = 0, n_final_sums = 0;        // launches of it, of those that make the final sum, of the kernel for that
 hipError_t capture_query = hipSuccess;
@@ -107,11 +109,13 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
     *grid = configured.grid; *block = configured.block; *shared = configured.shared; *stream = configured.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s)
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t s)
 {
     ++n_launches;
     for (int i = 0; i < n_kernels; ++i) {
         if (kernels[i] != f) continue;
+        last_kernel = kernel_names[i];
+        last_groups = grid.x;
         if (strstr(kernel_names[i], "sumsq_partial_kernel")) {
             last_partial_sum = kernel_names[i];
             ++n_partial_sums;
@@ -626,9 +630,37 @@ static int link_tiles()
     return 0;
 }
 
+// What one tensor takes by its tiles of 512 elements, and that the workgroups of the launch cover it: fine tiles, two to four
+// quads a lane at a pace where all of them are resident at once, and fine tiles again.
+static int one_tensor_kernels()
+{
+    const zi_adamw_config c = config();
+    char* base = (char*)on_device(5 * ((size_t)16 << 20), 0);
+    const struct { int64_t tiles; const char* kernel; int quads; } rows[] = {
+        {1, "adamw_fine_kernel", 1}, {1792, "adamw_fine_kernel", 1}, {1793, "adamw_paced_kernel", 2}, {2047, "adamw_paced_kernel", 2},
+        {2048, "adamw_paced_kernel", 2}, {2049, "adamw_paced_kernel", 2}, {4096, "adamw_paced_kernel", 2}, {4097, "adamw_paced_kernel", 3},
+        {6144, "adamw_paced_kernel", 3}, {6145, "adamw_paced_kernel", 4}, {7168, "adamw_paced_kernel", 4}, {7169, "adamw_fine_kernel", 1}};
+    for (const auto& r : rows)
+        for (int64_t less : {0, 505}) {
+            zi_tensor t{};
+            t.p = base; t.m = base + ((size_t)16 << 20); t.v = base + ((size_t)32 << 20); t.g = base + ((size_t)48 << 20);
+            t.p_lp = base + ((size_t)64 << 20);
+            t.numel = r.tiles * 512 - less;
+            CHECK(zi_adamw_step(&t, 1, ZI_BF16, &c, nullptr, nullptr) == ZI_OK);
+            CHECK(strstr(last_kernel, r.kernel));
+            char quads[16];
+            snprintf(quads, sizeof quads, "Li%dEE", r.quads);
+            CHECK(r.quads == 1 || strstr(last_kernel, quads));
+            const int64_t per_group = 64 * 4 * r.quads;
+            const int64_t groups = (t.numel / 4 * 4 + per_group - 1) / per_group;
+            CHECK(last_groups == (groups ? groups : 1));
+        }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
-    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"skipped", skipped}, {"earlier_work", earlier_work}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
+    const struct { const char* name; int (*run)(); } all[] = {{"peer", peer}, {"sizes", sizes}, {"capture", capture}, {"replays", replays}, {"skipped", skipped}, {"earlier_work", earlier_work}, {"one_tensor_kernels", one_tensor_kernels}, {"uploads", uploads}, {"loads", loads}, {"offload", offload}, {"spanning", spanning}, {"link_tiles", link_tiles}};
     for (const auto& t : all)
         if (argc == 2 && !strcmp(argv[1], t.name)) return t.run();
     fprintf(stderr, "which check?\n");

@@ -26,7 +26,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["peer", "sizes", "capture", "replays", "skipped", "earlier_work", "uploads", "loads", "offload", "spanning", "link_tiles"])
+@pytest.mark.parametrize("check", ["peer", "sizes", "capture", "replays", "skipped", "earlier_work", "one_tensor_kernels", "uploads", "loads", "offload", "spanning", "link_tiles"])
 def test_route(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr[-2000:]

@@ -9,8 +9,7 @@ assembly hipcc emits for the library's own source (no GPU needed):
   * a full tile issues its eight non-temporal loads back to back, before the first wait on any of them;
   * every streaming access of the full-tile path is non-temporal;
 
-and the same for the kernel of one short tensor and for that of lists, whose norm result also has to travel beside the table
-of starts.  Of the kernels over the link and of the reduction only scratch, registers and the kind of loads are looked at.
+and the same for the kernel of lists, whose norm result also has to travel beside the table of starts.  Of the kernels over the link and of the reduction only scratch, registers and the kind of loads are looked at.
 """
 import os
 import re
@@ -22,7 +21,6 @@ import pytest
 from paper_2104_07857_amd import build as zb
 
 KERNEL = re.compile(r"^(_ZN2zi17adamw_wide_kernelILi([01])ELb([01])ELb([01])EEEvNS_8StepArgsE):", re.M)
-SHORT_KERNEL = re.compile(r"^(_ZN2zi18adamw_short_kernelILi([01])ELb([01])EEEvNS_7StepOneE):", re.M)
 LIST_KERNEL = re.compile(r"^(_ZN2zi17adamw_list_kernelILi([01])ELb([01])ENS_(8ListArgs|8FlatArgs|7FlatFew)EEEvT1_):", re.M)
 NORM_KERNEL = re.compile(r"^(_ZN2zi20sumsq_partial_kernelILi([01])ELb([01])ENS_(7NormOne|7NormFew|8NormArgs)EEEvT1_):", re.M)
 LINK_KERNEL = re.compile(r"^(_ZN2zi(?:17adamw_link|22adamw_link_flat)_kernelILi([01])ELb([01])EEEvNS_(8LinkArgs|12LinkFlatArgs)E):", re.M)
@@ -53,13 +51,6 @@ def step_kernels(assembly):
 
 
 @pytest.fixture(scope="module")
-def short_kernels(assembly):
-    kernels = _kernels(assembly, SHORT_KERNEL)
-    assert len(kernels) == 4, sorted(kernels)      # {bf16, fp16} x {AdamW, Adam+L2}
-    return kernels
-
-
-@pytest.fixture(scope="module")
 def list_kernels(assembly):
     kernels = _kernels(assembly, LIST_KERNEL)
     assert len(kernels) == 12, sorted(kernels)     # {bf16, fp16} x {AdamW, Adam+L2} x {any list, flat buffers, few of them}
@@ -81,10 +72,10 @@ def directive(body, name):
     return int(m.group(1))
 
 
-def test_no_scratch_and_four_wavefronts_per_simd_fit(step_kernels, short_kernels, list_kernels, assembly):
+def test_no_scratch_and_four_wavefronts_per_simd_fit(step_kernels, list_kernels, assembly):
     link = _kernels(assembly, LINK_KERNEL)
     assert len(link) == 8, sorted(link)            # {bf16, fp16} x {AdamW, Adam+L2} x {any list, flat buffers}
-    for key, body in [*step_kernels.items(), *short_kernels.items(), *list_kernels.items(), *link.items()]:
+    for key, body in [*step_kernels.items(), *list_kernels.items(), *link.items()]:
         assert directive(body, "private_segment_fixed_size") == 0, key
         assert directive(body, "next_free_vgpr") <= 128, key
         assert "scratch_" not in body and "buffer_" not in body, key
@@ -102,11 +93,11 @@ def test_reduction_reads_all_gradients_one_way(assembly):
         assert directive(body, "private_segment_fixed_size") == 0, key
 
 
-def test_norm_result_is_read_with_one_scalar_load(step_kernels, short_kernels):
+def test_norm_result_is_read_with_one_scalar_load(step_kernels):
     """Up to the prologue's fp64 arithmetic (the clip factor) the kernel has touched memory only through
     scalar loads: its arguments (base s[0:1]) and one 32-byte load of the whole norm result from another
     base; no vector memory instruction, and no field-by-field reads of the result."""
-    for key, body in [*step_kernels.items(), *((key + (1,), body) for key, body in short_kernels.items())]:
+    for key, body in step_kernels.items():
         ins = instructions(body)
         first_f64 = next(i for i, x in enumerate(ins) if x.startswith(("v_div_scale_f64", "v_sqrt_f64", "v_rsq_f64",
                                                                        "v_mul_f64", "v_add_f64")))
@@ -132,8 +123,8 @@ def test_long_lists_fetch_the_norm_result_beside_their_starts(list_kernels):
         assert starts, (key, head[result[0]:wait + 1])
 
 
-def test_full_tile_issues_all_loads_before_the_first_wait(step_kernels, short_kernels, list_kernels):
-    for key, body in [*step_kernels.items(), *short_kernels.items(), *list_kernels.items()]:
+def test_full_tile_issues_all_loads_before_the_first_wait(step_kernels, list_kernels):
+    for key, body in [*step_kernels.items(), *list_kernels.items()]:
         ins = instructions(body)
         # the full-tile block is the only place with non-temporal 16-byte loads at an immediate offset of one
         # wavefront row (the second quad of a lane)
