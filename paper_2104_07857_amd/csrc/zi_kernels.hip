@@ -710,13 +710,17 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
     const bool runs = kMayRun && fine && n_tiles >= kXcds * kFineListRun / (kStepTileQuads / kFineTileQuads) && has_own_arrays(a, n_tensors);
     const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
     const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
+    // (a launch over FlatFew is never one of whole tiles: too few tensors, too few tiles)
+    constexpr bool kMayBeWhole = !std::is_same_v<Args, FlatFew>;
+    static_assert(FlatFew::kMax <= kManyTensors && kFewElems / kStepTileElems + FlatFew::kMax <= kFineListTiles);
     const auto of = [=](auto dt_, auto l2_) {
         constexpr int DT = decltype(dt_)::value;
         constexpr bool L2 = decltype(l2_)::value;
-        return paced   ? adamw_paced_list_kernel<DT, L2, Args>
-               : !fine ? adamw_list_kernel<DT, L2, Args>
-               : runs  ? adamw_fine_list_kernel<DT, L2, kMayRun, Args>
-                       : adamw_fine_list_kernel<DT, L2, false, Args>;
+        if constexpr (kMayBeWhole)
+            if (!paced && !fine) return adamw_list_kernel<DT, L2, Args>;
+        return paced  ? adamw_paced_list_kernel<DT, L2, Args>
+               : runs ? adamw_fine_list_kernel<DT, L2, kMayRun, Args>
+                      : adamw_fine_list_kernel<DT, L2, false, Args>;
     };
     return launch(instance(of, dt, l2), grid, block, lds, s, a, any_order);
 }
