@@ -78,7 +78,7 @@ __host__ __device__ inline uint32_t fine_count(uint32_t nquad, uint32_t shift)
 // (norm included), 998 with 1.2e6 30.3 / 31.1, 108 with 4.5e5 6.1 / 6.2; but 118 with 6.0e5 7.2 / 6.4, 37 with 9.7e4 5.2 / 4.7.
 constexpr uint32_t kManyTensors = 64, kFewTiles = 9;
 enum class Steps { kOne, kList, kFlat };
-inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_tensors)     // where paced_quads() says 0
+inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_tensors)     // of lists, where paced_quads() says 0
 {
     if (n_tensors > kManyTensors && n_tiles < kFewTiles * n_tensors) return false;
     if (kind == Steps::kList && !copies && n_tiles > kBareListTiles && n_tiles <= kBareListMostTiles) return false;

@@ -443,30 +443,20 @@ __device__ __forceinline__ void step_paced_tile(GlobalF4 __restrict__ p4, Global
     ends.update(gscale, c);
 }
 
-// One workgroup = one tile of kStepTileElems elements of one tensor.  blockIdx.x counts tiles over
-// all tensors of the launch; first_tile locates the tensor.
-// SINGLE: the launch covers one tensor (every long tensor gets such a launch: a workgroup lives for a few
-// microseconds, so even a short search for its tensor costs bandwidth).  Otherwise the workgroup counts
-// the table entries <= its id: a few wide scalar loads and no dependent chain.
+// One tensor of kFineMostTiles tiles or more, whose fine tiles would be more lanes than a launch may have and whose quads may be more than
+// 32 bits count: one workgroup takes one tile of kStepTileElems elements.
 // (waves_per_eu: with the default target the scheduler saves registers by moving loads behind the first quad's arithmetic.
 // The upper bound is also what a SIMD may hold, and two a SIMD, with six a compute unit, leave a freed slot unusable while
 // its neighbours have none: lists of 72 tensors of 3.0e8 elements 1371 us with two, 1341 with three or four.)
-template <int DT, bool L2, bool SINGLE>
+template <int DT, bool L2>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
 void adamw_wide_kernel(const StepArgs a)
 {
-    const uint32_t block = blockIdx.x;
-    int d = 0;
-    if constexpr (!SINGLE) {
-        d = -1;                           // first_tile[0] is 0, so the count is at least 1
-#pragma unroll
-        for (int i = 0; i < kMaxStepDesc; ++i) d += block >= a.first_tile[i] ? 1 : 0;
-    }
-    const StepDesc& T = a.t[d];
+    const StepDesc& T = a.t[0];
 
     const int64_t nquad = T.nquad;
 
-    const uint32_t tile = tile_of_block(block, T.first_tile, T.n_tiles);
+    const uint32_t tile = tile_of_block(blockIdx.x, 0, T.n_tiles);
 
     GlobalF4 __restrict__ p4 = (GlobalF4)(uintptr_t)T.p_body;
     GlobalF4 __restrict__ m4 = (GlobalF4)(uintptr_t)T.m_body;
@@ -737,7 +727,7 @@ hipError_t launch_step_flat(const FlatArgs& a, uint32_t n_tiles, int dt, bool l2
     return launch_list_of(a, n_tiles, dt, l2, any_order, s);
 }
 
-// The same launch, whose tensors have less than 2^32 quads, as the kernels of fine tiles take it.
+// The same launch, whose tensors have less than 2^32 quads, as the kernels of one tensor and of lists take it.
 static StepOne one_of(const StepArgs& a, bool l2)
 {
     const StepDesc& d = a.t[0];
@@ -765,18 +755,14 @@ static ListArgs list_of(const StepArgs& a)
     return l;
 }
 
+// (Several tensors: the kernels over lists also where they take whole tiles.  With a kernel of their own behind StepArgs, which counted 32 starts, lists
+// without copies took 1 % longer, step alone in us, so / as lists: 24 of 8.0e5 78.5 / 77.3, 32 of 1.0e6 129.6 / 128.8, 20 of 2.0e6 161.0 / 160.4.)
 hipError_t launch_step_wide(const StepArgs& a, uint32_t n_tiles, int dt, bool l2, bool any_order, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
-    const bool single = a.n_desc == 1;
-    const Steps kind = single ? Steps::kOne : Steps::kList;
-    if (paced_quads(n_tiles, kind) || fine_tiles(n_tiles, kind, a.t[0].lp_body, (uint32_t)a.n_desc))
-        return single ? launch_step_one(one_of(a, l2), dt, l2, any_order, s) : launch_step_list(list_of(a), n_tiles, dt, l2, any_order, s);
-    const auto of = [=](auto dt_, auto l2_) {
-        constexpr int DT = decltype(dt_)::value;
-        constexpr bool L2 = decltype(l2_)::value;
-        return single ? adamw_wide_kernel<DT, L2, true> : adamw_wide_kernel<DT, L2, false>;
-    };
+    if (a.n_desc > 1) return launch_step_list(list_of(a), n_tiles, dt, l2, any_order, s);
+    if (n_tiles < kFineMostTiles) return launch_step_one(one_of(a, l2), dt, l2, any_order, s);
+    const auto of = [](auto dt_, auto l2_) { return adamw_wide_kernel<decltype(dt_)::value, decltype(l2_)::value>; };
     return launch(instance(of, dt, l2), n_tiles, kStepThreads, whole_tiles_lds(n_tiles), s, a, any_order);
 }
 

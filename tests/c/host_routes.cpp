@@ -655,6 +655,24 @@ static int one_tensor_kernels()
             const int64_t groups = (t.numel / 4 * 4 + per_group - 1) / per_group;
             CHECK(last_groups == (groups ? groups : 1));
         }
+    // The longest that fine tiles take and the shortest that they do not (in allocations that nobody touches), and whole tiles in a list.
+    const size_t at[5] = {(size_t)1 << 44, (size_t)2 << 44, (size_t)3 << 44, (size_t)4 << 44, (size_t)5 << 44};
+    for (size_t a : at) allocs[n_allocs++] = {(char*)a, (size_t)1 << 40, 0};
+    for (int64_t tiles : {(1 << 25) - 1, 1 << 25, (1 << 25) + 1}) {
+        zi_tensor t{};
+        t.p = (void*)at[0]; t.m = (void*)at[1]; t.v = (void*)at[2]; t.g = (void*)at[3]; t.p_lp = (void*)at[4];
+        t.numel = tiles * 512;
+        CHECK(zi_adamw_step(&t, 1, ZI_BF16, &c, nullptr, nullptr) == ZI_OK);
+        CHECK(strstr(last_kernel, tiles < 1 << 25 ? "adamw_fine_kernel" : "adamw_wide_kernel"));
+        CHECK(last_groups == (tiles < 1 << 25 ? 2 * tiles : tiles));
+    }
+    std::vector<zi_tensor> list(24);
+    for (size_t i = 0; i < list.size(); ++i) {
+        const size_t n = 1'000'000, from = i * n;
+        list[i] = {(float*)at[0] + from, (float*)at[1] + from, (float*)at[2] + from, (uint16_t*)at[3] + from, nullptr, (int64_t)n};
+    }
+    CHECK(zi_adamw_step(list.data(), 24, ZI_BF16, &c, nullptr, nullptr) == ZI_OK);
+    CHECK(strstr(last_kernel, "adamw_list_kernel") && last_groups == 24 * 1954);
     return 0;
 }
 

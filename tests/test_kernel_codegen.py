@@ -20,7 +20,7 @@ import pytest
 
 from paper_2104_07857_amd import build as zb
 
-KERNEL = re.compile(r"^(_ZN2zi17adamw_wide_kernelILi([01])ELb([01])ELb([01])EEEvNS_8StepArgsE):", re.M)
+KERNEL = re.compile(r"^(_ZN2zi17adamw_wide_kernelILi([01])ELb([01])EEEvNS_8StepArgsE):", re.M)
 LIST_KERNEL = re.compile(r"^(_ZN2zi17adamw_list_kernelILi([01])ELb([01])ENS_(8ListArgs|8FlatArgs|7FlatFew)EEEvT1_):", re.M)
 NORM_KERNEL = re.compile(r"^(_ZN2zi20sumsq_partial_kernelILi([01])ELb([01])ENS_(7NormOne|7NormFew|8NormArgs)EEEvT1_):", re.M)
 LINK_KERNEL = re.compile(r"^(_ZN2zi(?:17adamw_link|22adamw_link_flat)_kernelILi([01])ELb([01])EEEvNS_(8LinkArgs|12LinkFlatArgs)E):", re.M)
@@ -46,7 +46,7 @@ def _kernels(text, pattern):
 @pytest.fixture(scope="module")
 def step_kernels(assembly):
     kernels = {tuple(int(x) for x in key): body for key, body in _kernels(assembly, KERNEL).items()}
-    assert len(kernels) == 8, sorted(kernels)      # {bf16, fp16} x {AdamW, Adam+L2} x {one tensor, list}
+    assert len(kernels) == 4, sorted(kernels)      # {bf16, fp16} x {AdamW, Adam+L2}
     return kernels
 
 
@@ -104,8 +104,7 @@ def test_norm_result_is_read_with_one_scalar_load(step_kernels):
         head = ins[:first_f64]
         assert not [x for x in head if x.startswith(("global_", "flat_", "buffer_", "scratch_"))], key
         other = [x for x in head if x.startswith("s_load") and not re.search(r", s\[0:1\], ", x)]
-        # (a launch over a list also reads its tensor's descriptor through a computed base, before the result)
-        assert (len(other) == 1 or not key[2]) and other, (key, other)
+        assert len(other) == 1, (key, other)
         assert re.match(r"s_load_dwordx8 s\[\d+:\d+\], s\[\d+:\d+\], 0x0$", other[-1]), (key, other)
 
 
