@@ -10,10 +10,10 @@ from gpu_util import NormBuffers, zi_cfg
 from test_gpu_fine_tiles import ONE_ROUND, SHORT, TILE, pieces, random_state, step_with_oracle
 
 pytestmark = pytest.mark.gpu
-PACED, STORES, MOST = 1 << 11, 15 << 8, 7 << 10                         # kPacedTiles, kPacedStoresOne, kMostPacedTiles
+EIGHT, STORES, MOST = 1 << 11, 15 << 8, 7 << 10                         # workgroups on a compute unit, kPacedStoresOne, kMostPacedTiles
 
 
-@pytest.mark.parametrize("tiles", [PACED, STORES, ONE_ROUND, 3 << 11, MOST])
+@pytest.mark.parametrize("tiles", [SHORT, EIGHT, STORES, ONE_ROUND, 3 << 11, MOST])
 @pytest.mark.parametrize("beyond,offset", [(0, 0), (1, 0), (4, 0), (259, 0), (66, 1)])
 def test_one_tensor_around_the_lines(tiles, beyond, offset):
     n = tiles * TILE + beyond
