@@ -27,56 +27,43 @@ constexpr int kXcds = 8;
 #endif
 constexpr int64_t kStepXcdRun = ZI_STEP_XCD_RUN;
 
-// Dynamic LDS requested (never touched) by the fused step caps its residency, in single-wavefront workgroups per compute unit:
-// on this 1:1 read/write stream few, short-lived wavefronts are faster than full occupancy.
-constexpr unsigned kStepLds20 = 8 * 1024, kStepLds16 = 10 * 1024, kStepLds14 = 11 * 1024, kStepLds12 = 13 * 1024, kStepLds7 = 22 * 1024 + 512;
-// Half a tile, one quad a lane (adamw_fine_kernel, adamw_fine_list_kernel): twice as many wavefronts with half as many loads
-// each, which live less than half as long, so that requests are spread more evenly over time and a launch's last round is shorter.
-// Which kernel a launch takes follows from its tiles: fine ones up to kFineShortTiles, where all of its workgroups are resident at once with
-// some places to spare; from there on paced_quads(), as long as those are; beyond, fine ones again.  One tensor's runs of kFineXcdRun
-// fine tiles go to one XCD each in launches of up to kFineRunTiles; longer ones, and lists, are dealt out as they come: then all
-// eight XCDs walk the same few MiB of every array, and it matters little how the arrays lie to each other.
-// Step alone in us, whole / fine tiles (range over one to four placements of the arrays each), one tensor:
-//   2.0e5 3.1 / 2.7   5.0e5 4.2 / 3.7   8.0e5 5.9 / 5.3   1.0e6 6.2 / 6.5   1.3e6 7.7 / 8.1   3.0e6 16.4 / 15.7   4.1e6 21.6 / 20.5
-//   8.4e6 40.1 / 38.5   2.5e7 112..114 / 109..111   6.0e7 269..272 / 258..261   1.0e8 442..459 / 427..431
-//   3.0e8 1312..1367 / 1282..1301   1.3e9 5759..6118 / 5529..5728
-//   (in runs 1.2e7 53.9..54.1, 2.5e7 110..112, 3.0e8 1342..1378, 1.3e9 5745..5918; in none 8.4e6 38.6..42, 1.2e7 54.0..54.9)
-// and lists: 60 tensors of up to 30,000 elements 8.7 / 8.1, 250 of 100,000 65.6 / 61, 300 of 200,000 147..153 / 141, 256 of 3e5
-// 342 / 336, a decoder's tensors at hidden size 1024, 6 layers 350 / 331, at 2048 1370..1395 / 1293..1304, 64 of 1.3e6 380 / 367,
-// 64 of 2e7 6104..6178 / 5623..5689.
-// Resident workgroups per compute unit (fine_lds): what counts is how many have loads in flight at a time.  Without a copy to write
-// they live shorter, and in front of their loads they wait for the norm result, if there is one, and in lists for the lookup.  us by
-// workgroups 11 / 12 / 13 / 14 / 16 / 20: one tensor of 3.0e8 1301 / 1284 / 1287 / 1288 / 1318 / 1338, without copies 1266 / 1236 / 1203 / 1185 /
-// 1197 / 1220, without norm and copies 1173 / 1173 / 1185 / 1194 / 1207 / 1216; a list of 3.0e8 1361 / 1325 / 1312 / 1305 / 1342 / 1366, without copies
-// 1415 / 1348 / 1301 / 1226 / 1213 / 1240, without norm and copies 1325 / 1282 / 1245 / 1204 / 1223 / 1257; 2.5e7 as a list 116 / 115 / 114 / 114 /
-// 113 / 115; flat lists of 4.0e6 23.6 / 23.1 / 22.9 / 22.6 / 21.9 / 21.7, of 3.0e7 149 / 145 / 145 / 141 / 141 / 139.
+// Dynamic LDS requested (never touched) by the fused step caps its residency, in single-wavefront workgroups per compute unit: on this 1:1 read/write
+// stream few, short-lived wavefronts are faster than full occupancy.  LDS is handed out in units of 1280 bytes, 128 on a compute unit (found by
+// counting the workgroups that were resident at once; the runtime's occupancy query says one or two more).
+constexpr unsigned step_lds(int workgroups) { return (unsigned)(128 / workgroups) * 1280; }
+
+// Half a tile, one quad a lane (adamw_fine_kernel, adamw_fine_list_kernel): twice as many wavefronts with half as many loads each, which live less than
+// half as long, so that requests are spread more evenly over time and a launch's last round is shorter.  Step alone, whole / fine tiles, over several
+// placements of the arrays: one tensor of 3.0e8 elements 1312..1367 / 1282..1301 us, 64 of 2e7 6104..6178 / 5623..5689.
+// Which kernel a launch takes follows from its tiles: fine ones up to kFineShortTiles, where all of its workgroups are resident at once with some places
+// to spare (9.5e5 elements at a pace 5.9..6.5, fine 5.4..6.0); from there on paced_quads(), as long as those are (2^20 6.0..6.2 / 6.5..6.9); beyond, fine
+// ones again (4.0e6 20.4 / 20.1).
 constexpr int kFineTileQuads = kStepThreads;
-constexpr int64_t kFineXcdRun = 1024;
-// Lists whose tensors are arrays of their own go in runs all the same: allocators put such arrays of some MB at the same place of their
-// pages, and in plain order all wavefronts then meet on the same channels.  Of views of common buffers the
-// order hardly matters or plain is better.  Step alone in us, whole tiles / fine in plain order / in runs of 128 / 512 /
-// 1024, own arrays: 21 of 4.0e6 384 / 416 / 379 / 383 / 394, 60 of 4.0e6 1095 / 1151 / 1085 / 1096 / 1113, 30 of 8.0e6 1080 / 1136 / 1084 / 1072 / 1084, 60 of
-// 2.0e6 536 / 526 / 536 / 529 / 526, 40 of 3.3e6 600 / 585 / 603 / 594 / 586, 15 of 2.0e7 1346 / 1356 / 1361 / 1355 / 1349; views: 40 of 4.2e6 737 / 720 / 739 / 746 /
-// 743, 60 of 4.0e6 1078 / 1033 / 1070 / 1043 / 1038.
-constexpr int64_t kFineListRun = 512;
 constexpr uint32_t kFineShortTiles = 7u << 8;      // 9.2e5 elements
 constexpr uint32_t kOneRoundTiles = 1u << 12;      // 2.1e6 elements: 16 workgroups on every compute unit
-constexpr uint32_t kFineRunTiles = 1u << 15;       // 1.7e7 elements
-constexpr uint32_t kFineListTiles = 1u << 16;      // 3.4e7 elements
 constexpr uint32_t kFineMostTiles = 1u << 25;      // 1.7e10 elements: a launch has less than 2^32 lanes
-// Without copies, middling launches of lists stay with whole tiles.  Step alone in us, whole / fine, any lists: 1.3e7 55.1 / 55.4 and 54.2 / 53.8,
-// 2.5e7 103.6 / 107.6 and 104.0 / 104.3, 5.0e7 205.3 / 204.6 and 205.3 / 202.2, 7.6e7 308 / 304, 3.0e8 1262 / 1206; flat ones: 4.0e6 20.9 / 20.5,
-// 3.0e7 134 / 130, 7.7e7 315 / 321 and 314 / 318.
-constexpr uint32_t kBareListTiles = 1u << 15, kBareListMostTiles = 3u << 15;       // 1.7e7 to 5.0e7 elements; flat ones from kFineListTiles
+// One tensor's runs of kFineXcdRun fine tiles go to one XCD each in launches of up to kFineRunTiles; longer ones, and lists, are dealt out as they
+// come: then all eight XCDs walk the same few MiB of every array, and it matters little how the arrays lie to each other.  In runs / in none, 1.2e7
+// 53.9..54.1 / 54.0..54.9, 3.0e8 1342..1378 / 1282..1301.
+constexpr int64_t kFineXcdRun = 1024;
+constexpr uint32_t kFineRunTiles = 1u << 15;       // 1.7e7 elements
+// Lists whose tensors are arrays of their own go in runs all the same: allocators put such arrays of some MB at the same place of their
+// pages, and in plain order all wavefronts then meet on the same channels.  Of views of common buffers the order hardly matters or plain is
+// better.  Plain / in runs of 512, own arrays, 21 of 4.0e6 416 / 383, 60 of 4.0e6 1151 / 1096, 15 of 2.0e7 1356 / 1355; views, 60 of 4.0e6 1033 / 1043.
+constexpr int64_t kFineListRun = 512;
+// Without copies, middling launches of lists stay with whole tiles, and flat ones from kFineListTiles on.  Whole / fine, any lists: 1.3e7 55.1 / 55.4, 2.5e7
+// 103.6 / 107.6, 7.6e7 308 / 304; flat ones: 3.0e7 134 / 130, 7.7e7 315 / 321.
+constexpr uint32_t kBareListTiles = 1u << 15, kBareListMostTiles = 3u << 15;       // 1.7e7 to 5.0e7 elements
+constexpr uint32_t kFineListTiles = 1u << 16;      // 3.4e7 elements
+// And many tensors of few tiles each do, whose second halves are often empty: 203 tensors with 1.0e5 elements 13.1 / 13.7, 998 with 1.2e6 30.3 / 31.1; but
+// 118 with 6.0e5 7.2 / 6.4.
+constexpr uint32_t kManyTensors = 64, kFewTiles = 9;
 // Quads that the first fine tile of a body at this address is short of, and the fine tiles of a body.
 __host__ __device__ inline uint32_t fine_shift(uintptr_t p_body) { return (uint32_t)(p_body / 16) % kFineTileQuads; }
 __host__ __device__ inline uint32_t fine_count(uint32_t nquad, uint32_t shift)
 {
     return (uint32_t)(((uint64_t)nquad + shift + kFineTileQuads - 1) / kFineTileQuads);
 }
-// And many tensors of few tiles each do, whose second halves are often empty: 210 tensors with 1.9e5 elements 8.1 / 8.4, 203 with 1.0e5 13.1 / 13.7
-// (norm included), 998 with 1.2e6 30.3 / 31.1, 108 with 4.5e5 6.1 / 6.2; but 118 with 6.0e5 7.2 / 6.4, 37 with 9.7e4 5.2 / 4.7.
-constexpr uint32_t kManyTensors = 64, kFewTiles = 9;
 enum class Steps { kOne, kList, kFlat };
 inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_tensors)     // of lists, where paced_quads() says 0
 {
@@ -86,18 +73,11 @@ inline bool fine_tiles(uint32_t n_tiles, Steps kind, bool copies, uint32_t n_ten
     return n_tiles <= kFineShortTiles || (n_tiles > kOneRoundTiles && n_tiles < kFineMostTiles);
 }
 // Launches whose workgroups are all resident at once (16 on a compute unit), at a measured pace (adamw_paced_kernel, adamw_paced_list_kernel): quads that
-// a lane takes, 0: not so.  Four quads stop paying at 14 on a compute unit.  Lists have tables of whole tiles, which are two quads;
-// with 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.  Where the line to fine tiles lies, one tensor at
-// seven placements of the arrays, fine / two quads / whole tiles with all loads up front, with 48 sets of arrays in turn: 9.5e5 5.4..6.0 / 5.9..6.5 /
-// 6.2..6.7, 1.0e6 5.9..6.7 / 6.0..6.7 / 6.3..6.9, 2^20 6.5..6.9 / 6.0..6.2 / 6.1..6.3, 1.05e6 + 424 6.7..6.9 / 6.0..6.2 / 6.8; with one set 2^20 4.8..4.9 /
-// 4.5..5.2 / 4.6..5.5.  Step alone in us, all loads up front
-// (beyond kOneRoundTiles fine tiles) / paced, one tensor: 1.2e6 7.5 / 6.9   1.4e6 8.0 / 7.4
-// 1.6e6 9.5 / 8.2   1.8e6 10.5 / 9.1   2.1e6 11.5 / 10.2, three quads 2.3e6 12.6 / 11.3   3.0e6 15.9 / 14.7, four 3.3e6 17.7 / 16.1   3.6e6 18.8 / 17.4
-// 4.0e6 20.1 / 20.4, without copies 1.8e6 10.1 / 8.5; lists of 12 tensors 9.5e5 8.4 / 7.4   1.3e6 9.5 / 8.4   2.0e6 12.8 / 11.5, of 60 9.5e5 8.9 / 7.9
-// 2.0e6 13.3 / 12.5, of 200 8.0e5 8.7 / 8.9   9.5e5 9.1 / 8.4   1.3e6 10.5 / 9.8   2.0e6 13.6 / 12.8, of 400 1.5e6 17.0 / 16.4.
-// Stores are paced too in launches of more than so many workgroups, loads only / both: one tensor 1.2e6 6.9 / 7.3   1.5e6 7.8 / 8.0   1.95e6 9.8 / 9.9
-// 2.0e6 10.9 / 10.5   2.1e6 10.8 / 10.3   2.3e6 11.3 / 11.5   2.8e6 13.6 / 13.8   3.1e6 15.8 / 15.2   3.5e6 17.1 / 17.3; 12 tensors 9.5e5 7.4 / 7.7   1.4e6
-// 9.3 / 9.2   1.7e6 10.3 / 10.0   2.0e6 12.0 / 11.5, four in arrays of their own 1.4e6 8.2 / 8.4   1.6e6 9.0 / 9.1   2.0e6 11.2 / 10.9.
+// a lane takes, 0: not so.  Step alone, all loads up front / at a pace, two quads 1.8e6 10.5 / 9.1, three (fine tiles / at a pace) 3.0e6 15.9 / 14.7,
+// four 3.6e6 18.8 / 17.4; four stop paying at 14 on a compute unit.  Lists have tables of whole tiles, which are two quads: 12 tensors of 2.0e6 12.8 /
+// 11.5; with 20, 24 or 32 workgroups on a compute unit for longer ones they are no faster than fine tiles.
+// Stores are paced too in launches of more than so many workgroups: loads only / both, one tensor 1.95e6 9.8 / 9.9, 2.0e6 10.9 / 10.5; lists 1.4e6
+// 9.3 / 9.2, 2.0e6 12.0 / 11.5.
 constexpr uint32_t kMostPacedTiles = 7u << 10;     // 3.7e6 elements
 constexpr uint32_t kPacedStoresOne = 15u << 8, kPacedStoresList = 11u << 8;
 constexpr int kMostPaced = 4;
@@ -107,14 +87,19 @@ inline int paced_quads(uint32_t n_tiles, Steps kind)
     constexpr uint32_t per_quad = kOneRoundTiles / kStepUnroll;
     return n_tiles <= kOneRoundTiles ? kStepUnroll : (int)((n_tiles + per_quad - 1) / per_quad);
 }
+// Resident workgroups per compute unit: what counts is how many have loads in flight at a time.  Without a copy to write they live shorter, and
+// lists wait for the lookup in front of their loads.  us by 9 / 10 / 11 / 12 / 14 / 16 / 18 / 21: one tensor of 1.2e7 53.9 / 53.8 / 53.3 / 53.4 / 52.9 /
+// 53.3 / 54.1 / 54.5, of 3.0e8 1272 / 1254 / 1260 / 1272 / 1278 / 1300 / 1317 / 1339; 72 of 4.2e6 1286 / 1275 / 1270 / 1266 / 1272 / 1289 / 1302 / 1330; 200
+// flat ones of 2e4 22.5 / 21.7 / 21.3 / 21.2 / 20.7 / 20.1 / 19.9 / 20.0.
+constexpr unsigned kPacedLds = step_lds(16);
 inline unsigned fine_lds(uint32_t n_tiles, Steps kind, bool copies, bool norm)
 {
     const bool waits = norm && !copies;
-    if (kind == Steps::kOne) return n_tiles <= kFineRunTiles ? kStepLds16 : waits ? kStepLds14 : kStepLds12;
-    if (n_tiles <= kFineListTiles) return kind == Steps::kFlat ? kStepLds20 : kStepLds16;
-    return waits ? kStepLds16 : kStepLds14;
+    if (kind == Steps::kOne) return step_lds(n_tiles <= kFineRunTiles ? 16 : waits ? 14 : 11);
+    if (n_tiles <= kFineListTiles) return step_lds(kind == Steps::kFlat ? 18 : 16);
+    return step_lds(waits ? 16 : 14);
 }
-inline unsigned whole_tiles_lds(uint32_t n_tiles) { return n_tiles <= kOneRoundTiles ? kStepLds16 : kStepLds7; }
+inline unsigned whole_tiles_lds(uint32_t n_tiles) { return step_lds(n_tiles <= kOneRoundTiles ? 16 : 7); }
 
 // A tile of the reduction is 16,384 elements, one round of loads for a workgroup.  Gradients that are to stay in the
 // memory-side cache (kNormKeepElems) are read by 512 threads with four vectors each, longer lists by 256 with eight: in

@@ -656,7 +656,7 @@ hipError_t launch_step_one(const StepOne& a, int dt, bool l2, bool any_order, hi
     const uint32_t n_fine = fine_count(a.nquad, fine_shift((uintptr_t)a.p_body));
     const int paced = paced_quads(n_tiles, Steps::kOne);
     const dim3 grid(n_tiles < 1 ? 1 : paced ? (a.nquad - 1) / (uint32_t)(paced * kStepThreads) + 1 : n_fine);
-    const unsigned lds = paced ? kStepLds16 : fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm);
+    const unsigned lds = paced ? kPacedLds : fine_lds(n_tiles, Steps::kOne, a.lp_body, a.d_norm);
     const auto of = [=](auto dt_, auto l2_) {
         constexpr int DT = decltype(dt_)::value;
         constexpr bool L2 = decltype(l2_)::value;
@@ -699,7 +699,7 @@ static hipError_t launch_list_of(const Args& a, uint32_t n_tiles, int dt, bool l
     constexpr bool kMayRun = std::is_same_v<Args, ListArgs>;
     const bool runs = kMayRun && fine && n_tiles >= kXcds * kFineListRun / (kStepTileQuads / kFineTileQuads) && has_own_arrays(a, n_tensors);
     const dim3 grid(fine ? n_tiles * (kStepTileQuads / kFineTileQuads) : n_tiles), block(kStepThreads);
-    const unsigned lds = paced ? kStepLds16 : fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
+    const unsigned lds = paced ? kPacedLds : fine ? fine_lds(n_tiles, kind, has_copies(a), a.d_norm) : whole_tiles_lds(n_tiles);
     // (a launch over FlatFew is never one of whole tiles: too few tensors, too few tiles)
     constexpr bool kMayBeWhole = !std::is_same_v<Args, FlatFew>;
     static_assert(FlatFew::kMax <= kManyTensors && kFewElems / kStepTileElems + FlatFew::kMax <= kFineListTiles);
