@@ -173,13 +173,13 @@ struct StepDesc {
     uint32_t reserved;
 };
 
+// A launch as it is assembled: launch_step_wide hands it on in the form that its kernel takes.
 struct StepArgs {
     StepDesc t[kMaxStepDesc];
     int32_t n_desc;
     StepConsts c;
     const zi_norm_result* d_norm;   // device, may be null
-    // first_tile of every descriptor once more, packed, 0xFFFFFFFF beyond n_desc: a workgroup finds its
-    // tensor by counting the entries <= its id (a few wide scalar loads, no dependent chain).
+    // first_tile of every descriptor once more, packed, 0xFFFFFFFF beyond n_desc (see ListArgs)
     uint32_t first_tile[kMaxStepDesc];
 };
 

@@ -509,8 +509,8 @@ __device__ __forceinline__ void step_one(const StepOne& a)
         step_fine_tile<DT, L2>(p4, m4, v4, g2, lp2, a.head, a.tail, tile, nquad, false, gscale, c);
     }
 }
-// Bound: HBM, 28 bytes an element (26 without a copy); short ones: the latency of one round trip.  6.3 to 6.5 TB/s from 3e8 elements on, where
-// whole tiles reach 5.9 to 6.3, by the arrays' places (zi_internal.h, kFineTileQuads).
+// Bound: HBM, 28 bytes an element (26 without a copy); short ones: the latency of one round trip.  6.2 to 6.6 TB/s from 3e8 elements on, where
+// whole tiles reach 5.9 to 6.3, by the box and the arrays' places (zi_internal.h, kFineTileQuads).
 template <int DT, bool L2>
 __global__ __launch_bounds__(kStepThreads) void adamw_fine_kernel(const StepOne a) { step_one<DT, L2, 0>(a); }
 template <int DT, bool L2, int QUADS>
