@@ -283,11 +283,12 @@ extern "C" zi_status zi_adamw_step_cpu(zi_engine* e, const zi_tensor* t, int32_t
     }
 
     const auto t0 = std::chrono::steady_clock::now();
-    // Around the uses, the host waits for the norm result and for the last upload, and the engine's streams for nothing: with the runtime's copy of
+    // Around the uses, the host waits for the norm result and for the last upload, and the engine's streams for nothing.  With the runtime's copy of
     // the result, stream waits behind an event for the caller's stream, an event in front of what follows on it, and a wait for the fetches, a
-    // call took, in us (16 threads, ordinary state; jobs of few tasks without the whole pool are in that), 1000 elements 110 / 34, 5.0e4 108 / 55,
-    // 3.0e5 140 / 102, 1.5e6 315 / 293 (page-locked state 115 / 36, 114 / 57, 141 / 101, 297 / 253), from 1.7e7 on no difference beyond that of two runs.  Fetching in front of the flag's way to
-    // the host made 1000 elements 57, and a skipped step 40 (one use) to 1290 (two uses of 2^24) where it takes 12.
+    // call took (us, 16 threads, ordinary state; jobs of few tasks without the whole pool are in that) 1000 elements 110 / 34, 5.0e4 108 / 55,
+    // 3.0e5 140 / 102, 1.5e6 315 / 293; page-locked state 115 / 36, 114 / 57, 141 / 101, 297 / 253; from 1.7e7 on no difference beyond that of two
+    // runs.  Fetching in front of the flag's way to the host made 1000 elements 57, and a skipped step 40 (one use) to 1290 (two uses of 2^24)
+    // where it takes 12.
     // Ring slot u mod n_h carries slot use u: its gradient half is filled by a kernel that reports every block
     // (link_copy_kernel), the CPUs step the use (reading that half, writing the copy half), and the copy half is
     // sent up by the same kind of kernel or by the runtime's copy (kUploadBlocks; arrays of another device).
